@@ -50,7 +50,7 @@ typedef enum {
 
 typedef enum {
     HDT_BF16 = 0, /* bf16 tensors, fp32 accumulation, MFMA kernels                */
-    HDT_F32 = 1   /* fp32 tensors, plain fp32 arithmetic: the slow debugging path */
+    HDT_F32 = 1   /* fp32 tensors, plain fp32 arithmetic: the debugging path */
 } hdt_dtype_t;
 
 /* Level id of a pad position; anchors and tokens carry levels 0 .. HDT_MAX_LEVELS-1

@@ -470,6 +470,5 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_attn_bwd(cons
     if (dt == HDT_BF16)
         return hdt_launch_bwd_bf16(s, s_tr, q, k, v, o, lse, d_o, dq, dk, dv, heads, head_dim, scale, (float *)workspace, hs);
     return hdt_launch_bwd_f32(s, s_tr, (const float *)q, (const float *)k, (const float *)v, (const float *)o, lse,
-                              (const float *)d_o, (float *)dq, (float *)dk, (float *)dv, heads, head_dim, scale,
-                              (float *)workspace, hs);
+                              (const float *)d_o, (float *)dq, (float *)dk, (float *)dv, heads, head_dim, scale, hs);
 }

@@ -640,8 +640,7 @@ hdt_status_t hdt_cross_bwd_compact(const hdt_layout_t *l, const void *q, const v
     hdt_status_t status =
         bf16 ? hdt_launch_bwd_bf16(s, s_tr, q, kc, vc, o, lse, d_o, dq, dkc, dvc, heads, head_dim, scale, delta, st)
              : hdt_launch_bwd_f32(s, s_tr, (const float *)q, (const float *)kc, (const float *)vc, (const float *)o, lse,
-                                  (const float *)d_o, (float *)dq, (float *)dkc, (float *)dvc, heads, head_dim, scale, delta,
-                                  st);
+                                  (const float *)d_o, (float *)dq, (float *)dkc, (float *)dvc, heads, head_dim, scale, st);
     if (status != HDT_OK) return status;
     {
         const long long total = (long long)B * heads * n_enc * chunks;

@@ -202,8 +202,8 @@ hdt_status_t hdt_launch_fwd_bf16(const HdtSchedule &s, const void *q, const void
 hdt_status_t hdt_launch_fwd_f32(const HdtSchedule &s, const float *q, const float *k, const float *v, float *o,
                                 float *lse, int heads, int head_dim, float scale, hipStream_t st);
 // backward launchers: `s` schedules the dQ pass, `s_transposed` (the transposed mask's schedule; the same as `s` for
-// symmetric masks) the dK/dV pass.  `delta`: room for the rows' scalars, hdt_bwd_row_scalars_bytes(batch * heads * n_pos)
-// (two floats per row for the bf16 kernels: -D and -LSE / scale side by side; the fp32 kernels keep D in the first half).
+// symmetric masks) the dK/dV pass.  `ws_delta` (bf16): room for the rows' scalars, hdt_bwd_row_scalars_bytes(batch * heads
+// * n_pos), two floats per row: -D and -LSE / scale side by side.
 inline size_t hdt_bwd_row_scalars_bytes(size_t rows) { return (2 * rows * sizeof(float) + 255) & ~(size_t)255; }
 hdt_status_t hdt_launch_bwd_bf16(const HdtSchedule &s, const HdtSchedule &s_transposed, const void *q, const void *k, const void *v,
                                  const void *o, const float *lse, const void *d_o, void *dq, void *dk,
@@ -211,5 +211,4 @@ hdt_status_t hdt_launch_bwd_bf16(const HdtSchedule &s, const HdtSchedule &s_tran
                                  hipStream_t st);
 hdt_status_t hdt_launch_bwd_f32(const HdtSchedule &s, const HdtSchedule &s_transposed, const float *q, const float *k, const float *v,
                                 const float *o, const float *lse, const float *d_o, float *dq, float *dk,
-                                float *dv, int heads, int head_dim, float scale, float *ws_delta,
-                                hipStream_t st);
+                                float *dv, int heads, int head_dim, float scale, hipStream_t st);
