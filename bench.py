@@ -511,9 +511,8 @@ def main() -> int:
             fwd_us = tk.get(f"hdt_fwd_bf16_d{D}")
             if fwd_us and tk.get("hdt_cross_combine_fwd"):
                 fwd_us += tk["hdt_cross_combine_fwd"]
-            # the whole backward call: D pass and kernel, plus the copies of a compact layout or the sum of dQ's parts
-            bwd_parts = [tk.get(k) for k in (f"hdt_bwd_delta_d{D}", f"hdt_bwd_bf16_d{D}", "hdt_cross_gather", "hdt_cross_scatter",
-                                             "hdt_cross_sum_dq")]
+            # the whole backward call: D pass and kernel, plus the sum of dQ's parts
+            bwd_parts = [tk.get(k) for k in (f"hdt_bwd_delta_d{D}", f"hdt_bwd_bf16_d{D}", "hdt_cross_sum_dq")]
             bwd_us = sum(x for x in bwd_parts if x) if tk.get(f"hdt_bwd_bf16_d{D}") else None
             cross[name] = {"visible_positions": int(visible), "compact_rows": int(lay_c.info()["compact_rows"]), "kernels_us": tk,
                            "fwd_us": None if not fwd_us else round(fwd_us, 2),

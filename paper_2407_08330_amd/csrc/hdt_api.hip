@@ -284,7 +284,7 @@ static hdt_status_t destroy_layout(hdt_layout_t *layout, bool completed)
     if (layout->magic != HDT_LAYOUT_MAGIC) return hdt_fail(HDT_ERR_INVALID_ARG, "hdt_layout_destroy: not a layout");
     // the build and every attention call went through this handle: its streams cover the layouts it owns
     const HdtUsers users = completed ? HdtUsers() : hdt_users_at_release(hdt_layout_streams(layout));
-    hdt_layout_t *owned[3] = {layout->compact ? layout->compact->transposed : nullptr, layout->compact, layout->transposed};
+    hdt_layout_t *owned[2] = {layout->compact, layout->transposed};
     layout->compact = layout->transposed = nullptr;
     for (hdt_layout_t *t : owned) {
         if (!t) continue;
@@ -377,7 +377,8 @@ extern "C" __attribute__((visibility("default"))) size_t hdt_attn_bwd_workspace_
     if (!hdt_layout_ok(layout) || heads < 0) return 0;
     // two floats per (batch, head, position): D_i = sum_c dO_ic O_ic and LSE_i in the form the kernels start from
     size_t n = hdt_bwd_row_scalars_bytes((size_t)layout->s.batch * (size_t)heads * (size_t)layout->s.n_pos);
-    // a cross-attention layout with a compact pair: compact copies of K, V and of their gradients behind it
+    // a cross-attention layout with a compact schedule: room for compact copies of K, V and their gradients, which
+    // callers have been told to bring (the kernels work on the tensors themselves)
     if (layout->compact) n += hdt_cross_compact_workspace_bytes(layout, heads, head_dim, dt == HDT_BF16 ? 2 : 4);
     // a cross-attention layout with long key lists: the parts of dQ that the pieces of the lists produce
     if (dt == HDT_BF16 && (head_dim == 64 || head_dim == 128)) n += hdt_cross_dq_workspace_bytes(layout, heads, head_dim);
@@ -462,9 +463,9 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_attn_bwd(cons
         return hdt_fail(HDT_ERR_SHAPE, "hdt_attn_bwd: batch*heads*tiles exceeds the grid limit");
     hipStream_t hs = (hipStream_t)stream;
     hdt_layout_note_stream(layout, hs);
-    if (layout->compact)
-        return hdt_cross_bwd_compact(layout, q, k, v, o, lse, d_o, dq, dk, dv, heads, head_dim, dt == HDT_BF16, scale,
-                                     workspace, hs);
+    if (dt == HDT_BF16 && layout->compact)
+        return hdt_launch_bwd_bf16(s, layout->compact->s, q, k, v, o, lse, d_o, dq, dk, dv, heads, head_dim, scale,
+                                   (float *)workspace, hs);
     if (dt == HDT_BF16 && hdt_cross_pieces(layout, heads) > 1)
         return hdt_cross_bwd_split(layout, q, k, v, o, lse, d_o, dq, dk, dv, heads, head_dim, scale, workspace, hs);
     if (dt == HDT_BF16)

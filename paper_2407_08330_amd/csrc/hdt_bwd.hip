@@ -43,8 +43,10 @@ struct BwdCfg {
     // against 99 with two, whose allocation the compiler then leaves unconstrained).
     static constexpr int S_DQ = (D == 64) ? 3 : 2;
     static constexpr int S_DKV = 2;
-    template <typename G>
-    static constexpr int WAVES = (D == 64 && G::BM == 128) ? 3 : 2;
+    // The INDEXED form on 128 x 64 tiles gets one wave less: it would spill a few registers there, which the counted
+    // waits do not allow, and its few workgroups do not need the third (second) wave.
+    template <typename G, bool INDEXED>
+    static constexpr int WAVES = G::BM == 128 ? (D == 64 ? 3 : 2) - (INDEXED ? 1 : 0) : 2;
     // At head size 128 the dK/dV role would need 128 accumulator registers per lane on top of 64 operand
     // registers, which leaves one wave per SIMD.  It is split there into a dV role and a dK role (each
     // recomputes the scores), so that every role fits two waves per SIMD.
@@ -132,8 +134,9 @@ __device__ __forceinline__ void dq_role(char *smem, const HdtSchedule &s, const 
     // the B fragments are read back from there.  The ring may only take those stages over after a
     // barrier, so the prologue is issued in two pieces.
     constexpr uint32_t STG_Q = (uint32_t)(S - 1) * 2 * P::TILE, STG_DO = (uint32_t)(S - 2) * 2 * P::TILE;
-    stage_own_rows(pipe, q + own_base, I_own * BM, s.n_own, D, STG_Q);
-    stage_own_rows(pipe, d_o + own_base, I_own * BM, s.n_own, D, STG_DO);
+    const OwnRows<P> own = own_rows(pipe, I_own * BM, s.n_own);
+    stage_own_rows(pipe, q + own_base, own, STG_Q);
+    stage_own_rows(pipe, d_o + own_base, own, STG_DO);
     R::start(pipe, n);
     R::template prologue<0, S - 2>(pipe, n);
     if (S == 2 || n == 0) wait_vmcnt<0>();  // otherwise the prologue's first wait covered the staged rows
@@ -223,8 +226,8 @@ __device__ __forceinline__ void dq_role(char *smem, const HdtSchedule &s, const 
 }
 
 // ---------------------------------------------------------------------------------------- dK, dV
-// WHICH: 0 = dK and dV, 1 = dV only, 2 = dK only
-template <int D, typename G, int WHICH>
+// WHICH: 0 = dK and dV, 1 = dV only, 2 = dK only.  INDEXED: the rows are those own_index names (see HdtSchedule).
+template <int D, typename G, int WHICH, bool INDEXED>
 __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const __bf16 *__restrict__ q,
                                           const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
                                           const __bf16 *__restrict__ d_o, const float2 *__restrict__ row_scalars,
@@ -239,7 +242,11 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
 
     const int lane = threadIdx.x & 63;
     const int hf = lane >> 5;
-    const size_t base = (size_t)bh * s.n_pos * D, q_base = (size_t)bh * s.n_kv * D;  // rows are keys here
+    const size_t q_base = (size_t)bh * s.n_kv * D;  // rows are keys here
+    const size_t base = (size_t)bh * (INDEXED ? s.own_stride : s.n_pos) * D;
+    const int n_rows = INDEXED ? as_const(s.own_count)[b] : s.n_pos;
+    const int32_t *index = INDEXED ? s.own_index + (size_t)b * s.own_stride : nullptr;
+    if (INDEXED && I * BM >= n_rows) return;  // the whole workgroup: no visible position in this tile
     const float scale_log2 = scale * LOG2E;
 
     const size_t row = (size_t)b * s.tr + I;
@@ -268,8 +275,15 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
 
     // K and V rows of this wave: through the two highest ring stages, as Q and dO in the dQ pass
     constexpr uint32_t STG_K = (uint32_t)(S - 1) * 2 * P::TILE, STG_V = (uint32_t)(S - 2) * 2 * P::TILE;
-    stage_own_rows(pipe, k + base, I * BM, s.n_pos, D, STG_K);
-    if (DO_DK) stage_own_rows(pipe, v + base, I * BM, s.n_pos, D, STG_V);  // V only enters dP
+    const OwnRows<P> own = own_rows(pipe, I * BM, n_rows, index);
+    // where this wave's rows go: kept in LDS until the epilogue (registers are short, scalar ones included)
+    int *row_at = reinterpret_cast<int *>(smem + P::SMEM_BYTES) + wave * 32;
+    if (INDEXED && lane % P::CPR == 0) {
+#pragma unroll
+        for (int i = 0; i < 32 / P::RPI; i++) row_at[i * P::RPI + lane / P::CPR] = own.g[i];
+    }
+    stage_own_rows(pipe, k + base, own, STG_K);
+    if (DO_DK) stage_own_rows(pipe, v + base, own, STG_V);  // V only enters dP
     R::start(pipe, n);
     R::template prologue<0, S - 2>(pipe, n);
     if (S == 2 || n == 0) wait_vmcnt<0>();
@@ -372,13 +386,51 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
         const int wrow0 = I * BM + wave * 32;
         char *wl = smem + (n % S) * 2 * P::TILE + wave * 32 * ROWB;
         const int le = opaque(lane);
-        if (DO_DK) store_rows_via_lds<P, D>(wl, le, dkacc, scale, dk + base + (size_t)wrow0 * D, s.n_pos - wrow0);
-        if (DO_DV) store_rows_via_lds<P, D>(wl, le, dvacc, 1.f, dv + base + (size_t)wrow0 * D, s.n_pos - wrow0);
+        const size_t at = base + (INDEXED ? 0 : (size_t)wrow0 * D);
+        const int *to = INDEXED ? row_at : nullptr;
+        if (DO_DK) store_rows_via_lds<P, D>(wl, le, dkacc, scale, dk + at, n_rows - wrow0, to);
+        if (DO_DV) store_rows_via_lds<P, D>(wl, le, dvacc, 1.f, dv + at, n_rows - wrow0, to);
     }
 }
 
+// ---------------------------------------------------------------------------------------- zeros
+// dK, dV rows of the positions an INDEXED schedule does not cover: workgroup z writes kZeroChunks 16-byte chunks per
+// thread and tensor.  They ride in the same launch: with few positions visible the other workgroups leave most of the
+// chip idle and last about as long as writing the zeros takes.
+constexpr int kZeroChunks = 8;
 template <int D, typename G>
-__global__ __launch_bounds__(G::THREADS, BwdCfg<D>::template WAVES<G>) void k_bwd_bf16(
+struct ZeroRows {
+    static constexpr int ROWS = kZeroChunks * G::THREADS / (D / 8);  // rows of a tensor per workgroup
+};
+template <int D, typename G>
+__device__ __forceinline__ void zero_role(const HdtSchedule &s, __bf16 *__restrict__ dk, __bf16 *__restrict__ dv, unsigned z,
+                                          int heads)
+{
+    constexpr int CPR = D / 8, ROWS = ZeroRows<D, G>::ROWS;
+    const unsigned per = ((unsigned)s.own_stride + ROWS - 1u) / ROWS;
+    const int bh = z / per, b = bh / heads, p0 = (z % per) * ROWS;
+    const int32_t *rank = s.own_rank + (size_t)b * s.own_stride;
+    int r[kZeroChunks];
+#pragma unroll
+    for (int u = 0; u < kZeroChunks; u++) {
+        const int p = p0 + (u * G::THREADS + (int)threadIdx.x) / CPR;
+        r[u] = p < s.own_stride ? rank[p] : 0;
+    }
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int u = 0; u < kZeroChunks; u++) {
+        const size_t at = ((size_t)bh * s.own_stride + p0) * CPR + u * G::THREADS + threadIdx.x;
+        if (r[u] < 0) {
+            __builtin_nontemporal_store(zero, reinterpret_cast<u32x4 *>(dk) + at);
+            __builtin_nontemporal_store(zero, reinterpret_cast<u32x4 *>(dv) + at);
+        }
+    }
+}
+
+// INDEXED: s_tr covers visible positions only (HdtSchedule::own_index); the workgroups behind the grid of the roles
+// write the zeros of the rows it leaves out.
+template <int D, typename G, bool INDEXED>
+__global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)) void k_bwd_bf16(
     HdtSchedule s, HdtSchedule s_tr, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k,
     const __bf16 *__restrict__ v, const float *__restrict__ lse, const __bf16 *__restrict__ d_o,
     const float2 *__restrict__ row_scalars, __bf16 *__restrict__ dq, __bf16 *__restrict__ dk,
@@ -386,14 +438,22 @@ __global__ __launch_bounds__(G::THREADS, BwdCfg<D>::template WAVES<G>) void k_bw
 {
     using PQ = Pipe<D, BwdCfg<D>::S_DQ, false, G>;
     using PK = Pipe<D, BwdCfg<D>::S_DKV, true, G>;
-    constexpr int SMEM = PQ::SMEM_BYTES > PK::SMEM_BYTES ? PQ::SMEM_BYTES : PK::SMEM_BYTES;
+    constexpr int SMEM_K = PK::SMEM_BYTES + (INDEXED ? G::BM * 4 : 0);
+    constexpr int SMEM = PQ::SMEM_BYTES > SMEM_K ? PQ::SMEM_BYTES : SMEM_K;
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     // The roles tile different tensors (the same ones for self-attention): the workgroups of one tile follow each
     // other as far as both sides have that tile, the rest of the longer side comes behind them.
     constexpr unsigned R = BwdCfg<D>::SPLIT_KV ? 3u : 2u;  // roles per tile: dQ, then dK/dV or dV, dK
-    const unsigned w = logical_block(blockIdx.x, R * G::XCD_CHUNK);
     const unsigned nq = (unsigned)s.batch * heads * s.tr, nk = (unsigned)s_tr.batch * heads * s_tr.tr;
+    if (INDEXED) {
+        const unsigned roles = padded_grid(nq + (R - 1u) * nk, R * G::XCD_CHUNK);
+        if (blockIdx.x >= roles) {
+            zero_role<D, G>(s_tr, dk, dv, blockIdx.x - roles, heads);
+            return;
+        }
+    }
+    const unsigned w = logical_block(blockIdx.x, R * G::XCD_CHUNK);
     const unsigned common = nq < nk ? nq : nk;
     if (w >= nq + (R - 1u) * nk) return;  // padding of the grid
     unsigned role, lb;
@@ -414,15 +474,28 @@ __global__ __launch_bounds__(G::THREADS, BwdCfg<D>::template WAVES<G>) void k_bw
     } else {
         const int I = lb % s_tr.tr, bh = lb / s_tr.tr, b = bh / heads;
         if (!BwdCfg<D>::SPLIT_KV)
-            dkv_role<D, G, 0>(smem, s_tr, q, k, v, d_o, row_scalars, dk, dv, wave, I, bh, b, scale);
+            dkv_role<D, G, 0, INDEXED>(smem, s_tr, q, k, v, d_o, row_scalars, dk, dv, wave, I, bh, b, scale);
         else if (role == 1u)
-            dkv_role<D, G, 1>(smem, s_tr, q, k, v, d_o, row_scalars, dk, dv, wave, I, bh, b, scale);
+            dkv_role<D, G, 1, INDEXED>(smem, s_tr, q, k, v, d_o, row_scalars, dk, dv, wave, I, bh, b, scale);
         else
-            dkv_role<D, G, 2>(smem, s_tr, q, k, v, d_o, row_scalars, dk, dv, wave, I, bh, b, scale);
+            dkv_role<D, G, 2, INDEXED>(smem, s_tr, q, k, v, d_o, row_scalars, dk, dv, wave, I, bh, b, scale);
     }
 }
 
 }  // namespace
+
+template <int D, typename G, bool INDEXED>
+static void launch_roles(const HdtSchedule &s, const HdtSchedule &s_tr, const __bf16 *Q, const __bf16 *K, const __bf16 *V,
+                         const float *lse, const __bf16 *DO, const float2 *row_scalars, void *dq, void *dk, void *dv,
+                         int heads, float scale, hipStream_t st)
+{
+    const unsigned nq = (unsigned)s.batch * heads * s.tr, nk = (unsigned)s_tr.batch * heads * s_tr.tr;
+    constexpr unsigned roles = BwdCfg<D>::SPLIT_KV ? 3u : 2u, zr = ZeroRows<D, G>::ROWS;
+    const unsigned zeros = INDEXED ? (unsigned)s_tr.batch * heads * (((unsigned)s_tr.own_stride + zr - 1u) / zr) : 0u;
+    dim3 grid(padded_grid(nq + (roles - 1u) * nk, roles * G::XCD_CHUNK) + zeros), block(G::THREADS);
+    hipLaunchKernelGGL((k_bwd_bf16<D, G, INDEXED>), grid, block, 0, st, s, s_tr, Q, K, V, lse, DO, row_scalars, (__bf16 *)dq,
+                       (__bf16 *)dk, (__bf16 *)dv, heads, scale);
+}
 
 template <typename G>
 static void launch_bwd(const HdtSchedule &s, const HdtSchedule &s_tr, const __bf16 *Q, const __bf16 *K, const __bf16 *V,
@@ -443,15 +516,12 @@ static void launch_bwd(const HdtSchedule &s, const HdtSchedule &s_tr, const __bf
     }
     {
         HdtTimer t(head_dim == 64 ? "hdt_bwd_bf16_d64" : "hdt_bwd_bf16_d128", st);
-        const unsigned nq = (unsigned)s.batch * heads * s.tr, nk = (unsigned)s_tr.batch * heads * s_tr.tr;
-        const unsigned roles = head_dim == 128 ? 3u : 2u;  // BwdCfg<D>::SPLIT_KV
-        dim3 grid(padded_grid(nq + (roles - 1u) * nk, roles * G::XCD_CHUNK)), block(G::THREADS);
         if (head_dim == 64)
-            hipLaunchKernelGGL((k_bwd_bf16<64, G>), grid, block, 0, st, s, s_tr, Q, K, V, lse, DO, row_scalars,
-                               (__bf16 *)dq, (__bf16 *)dk, (__bf16 *)dv, heads, scale);
+            s_tr.own_index ? launch_roles<64, G, true>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st)
+                           : launch_roles<64, G, false>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st);
         else
-            hipLaunchKernelGGL((k_bwd_bf16<128, G>), grid, block, 0, st, s, s_tr, Q, K, V, lse, DO, row_scalars,
-                               (__bf16 *)dq, (__bf16 *)dk, (__bf16 *)dv, heads, scale);
+            s_tr.own_index ? launch_roles<128, G, true>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st)
+                           : launch_roles<128, G, false>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st);
     }
 }
 

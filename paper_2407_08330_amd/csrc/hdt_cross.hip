@@ -13,12 +13,12 @@
 // are marked empty, and a tile's range covers the ones in use.
 //
 // The dK/dV pass of the backward tiles the ENCODER rows, and with a few anchors visible nearly every 32-row
-// block of them holds one allowed row among 31 idle ones.  The build therefore reads the number of visible
-// positions back, and when they are at most a quarter of the encoder's positions it adds a second pair of
-// schedules in the index space of the visible positions (row = rank among them): hdt_attn_bwd then gathers
-// the visible rows of K and V into compact tensors (in its workspace), runs the ordinary backward kernels
-// on those, and scatters dK and dV back (zeros for the rows that are not visible).  The forward keeps
-// gathering straight from K and V.
+// block of them holds one allowed row among 31 idle ones.  The build therefore learns the number of visible
+// positions from the device, and when they are at most a quarter of the encoder's positions it adds a second
+// transposed schedule in the index space of the visible positions (row = rank among them): the dK/dV role of
+// hdt_attn_bwd then reads its K and V rows and writes its dK and dV rows through the list of visible positions,
+// and further workgroups of the same launch write the zeros of the rows that are not visible (512 x 8192, [SEC] and [SENT] visible: one
+// launch of 33 us where gathering compact copies, the roles and scattering the results took 5 + 21 + 24).
 //
 // With the regular tokens visible the opposite happens: a handful of decoder row tiles each walk a key list of
 // more than a hundred entries one after the other, on a few workgroups.  The list of a row tile is the same for
@@ -30,7 +30,6 @@
 // results live in the caller's workspace (hdt_attn_fwd_ws, hdt_attn_bwd).
 #include <string.h>
 
-#include <initializer_list>
 #include <new>
 #include <vector>
 
@@ -46,38 +45,76 @@ __device__ __forceinline__ bool visible(int level, uint32_t level_mask)
     return level >= 0 && level < 32 && ((level_mask >> level) & 1u);
 }
 
-// One workgroup per sample: the visible positions in document order (sel) and their number (count).
+// One workgroup per sample: the visible positions in document order (sel), every position's rank among them, and
+// their number (count).  A wave takes a contiguous share of the positions, kSelBatch groups of 64 in flight at a time:
+// it counts its visible positions, and once the shares in front of it are known hands out the ranks (8192 positions x 4
+// samples: 5.3 us; one chunk of 1024 positions after the other, three barriers each, took 9.2).  The last workgroup to
+// finish tells the host, which waits for this word, the largest count.
+constexpr int kSelBatch = 8;
 __global__ __launch_bounds__(kSelThreads) void k_cross_select(const int32_t *__restrict__ level, int n_enc,
                                                                uint32_t level_mask, int32_t *__restrict__ sel,
-                                                               int32_t *__restrict__ rank, int32_t *__restrict__ count)
+                                                               int32_t *__restrict__ rank, int32_t *__restrict__ count,
+                                                               HdtReport report)
 {
-    __shared__ int s_wave[kSelThreads / 64];
-    __shared__ int s_base;
+    constexpr int W = kSelThreads / 64;
+    __shared__ int s_wave[W];
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int32_t *lv = level + (size_t)b * n_enc;
-    int32_t *out = sel + (size_t)b * n_enc;
-    if (tid == 0) s_base = 0;
-    __syncthreads();
-    for (int i0 = 0; i0 < n_enc; i0 += kSelThreads) {
-        const int i = i0 + tid;
-        const bool vis = i < n_enc && visible(lv[i], level_mask);
-        const unsigned long long m = __ballot(vis);
-        if (lane == 0) s_wave[wave] = __popcll(m);
-        __syncthreads();
-        int before = s_base;
-        for (int w = 0; w < wave; w++) before += s_wave[w];
-        const int mine = before + __popcll(m & ((1ull << lane) - 1ull));
-        if (vis) out[mine] = i;
-        if (i < n_enc) rank[(size_t)b * n_enc + i] = vis ? mine : -1;
-        __syncthreads();
-        if (tid == 0) {
-            int tot = 0;
-            for (int w = 0; w < kSelThreads / 64; w++) tot += s_wave[w];
-            s_base += tot;
+    int32_t *out = sel + (size_t)b * n_enc, *rk = rank + (size_t)b * n_enc;
+    const int groups = (n_enc + 63) >> 6, share = (groups + W - 1) / W;
+    const int g0 = min(wave * share, groups), g1 = min(g0 + share, groups);
+    unsigned long long seen[kSelBatch];  // of the batch looked at last
+    auto look = [&](int gb) {
+        int l[kSelBatch];
+#pragma unroll
+        for (int u = 0; u < kSelBatch; u++) {
+            const int i = (gb + u) * 64 + lane;
+            l[u] = gb + u < g1 && i < n_enc ? lv[i] : -1;
         }
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kSelBatch; u++) seen[u] = __ballot(visible(l[u], level_mask));
+    };
+    int mine = 0;
+    for (int gb = g0; gb < g1; gb += kSelBatch) {
+        look(gb);
+#pragma unroll
+        for (int u = 0; u < kSelBatch; u++) mine += __popcll(seen[u]);
     }
-    if (tid == 0) count[b] = s_base;
+    if (lane == 0) s_wave[wave] = mine;
+    __syncthreads();
+    int at = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < W; w++) {
+        at += w < wave ? s_wave[w] : 0;
+        total += s_wave[w];
+    }
+    for (int gb = g0; gb < g1; gb += kSelBatch) {
+        if (share > kSelBatch) look(gb);  // otherwise the masks are still there
+#pragma unroll
+        for (int u = 0; u < kSelBatch; u++) {
+            const int i = (gb + u) * 64 + lane;
+            const bool vis = (seen[u] >> lane) & 1ull;
+            const int r = at + __popcll(seen[u] & ((1ull << lane) - 1ull));
+            if (vis) out[r] = i;
+            if (gb + u < g1 && i < n_enc) rk[i] = vis ? r : -1;
+            at += __popcll(seen[u]);
+        }
+    }
+    if (tid == 0) {
+        count[b] = total;
+        if (report.word) {
+            // the maximum first, and only when it is in place the arrival (returning atomics: each waits for the one before)
+            const int before = atomicMax(&report.counters[0], total);
+            asm volatile("" ::"v"(before));
+            if (atomicAdd(&report.counters[1], 1) == (int)gridDim.x - 1) {
+                const int most = __hip_atomic_load(&report.counters[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&report.counters[0], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&report.counters[1], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(report.word, ((unsigned long long)(report.ticket & 0xffffffu) << 40) | (uint32_t)most,
+                                   __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+        }
+    }
 }
 
 struct CrossArgs {
@@ -89,21 +126,24 @@ struct CrossArgs {
     int transposed;  // 0: rows = decoder positions, keys = visible encoder positions; 1: rows = encoder positions
                      // (allowed iff visible), keys = decoder positions
     int tr, e_max;   // row tiles per sample, list entries reserved per row tile
-    int compact;     // 0, or the rows per sample of the compact tensors: encoder positions are named by their rank
-                     // among the visible ones (keys of the forward schedule, rows of the transposed one)
+    int compact;     // transposed schedule: 0, or its rows per sample when they are the visible positions by rank
+    int entries;     // reserved entries: workgroups this schedule takes
     int32_t *q_range, *c_row, *c_cnt, *q_keys;
     uint32_t *q_sub;
     unsigned long long *bits_rm;
 };
 
-// One wave per reserved list entry (b, I, e): its keys, bitmaps and summary, or the "empty" marks.
-__global__ __launch_bounds__(64) void k_cross_entries(CrossArgs a)
+// One wave per reserved list entry (b, I, e): its keys, bitmaps and summary, or the "empty" marks.  Two schedules per
+// launch (a launch costs about what its entries do).
+__global__ __launch_bounds__(64) void k_cross_entries(CrossArgs a0, CrossArgs a1)
 {
     __shared__ uint32_t s_row[4], s_col[4];  // allowed rows / filled key slots of the entry, bit masks
     const int lane = threadIdx.x;
-    const int e = blockIdx.x % a.e_max, tile = blockIdx.x / a.e_max;  // tile = b * tr + I
+    const bool first = (int)blockIdx.x < a0.entries;
+    const CrossArgs &a = first ? a0 : a1;
+    const int64_t entry = first ? (int)blockIdx.x : (int)blockIdx.x - a0.entries;
+    const int e = (int)entry % a.e_max, tile = (int)entry / a.e_max;  // tile = b * tr + I
     const int b = tile / a.tr, I = tile % a.tr;
-    const int64_t entry = blockIdx.x;
     const int n_rows = a.transposed ? (a.compact ? a.compact : a.n_enc) : a.n_dec;
     const int n_keys = a.transposed ? a.n_dec : a.count[b];
     // rows of the tile
@@ -138,7 +178,7 @@ __global__ __launch_bounds__(64) void k_cross_entries(CrossArgs a)
         const bool ok = c < a.bn && idx < n_keys;
         // a slot past the last key holds ~f, f = the entry's first key: the row gathered in its place
         const int at = ok ? idx : e * a.bn;
-        const int key = (a.transposed || a.compact) ? at : a.sel[(size_t)b * a.n_enc + at];
+        const int key = a.transposed ? at : a.sel[(size_t)b * a.n_enc + at];
         if (c < a.bn) a.q_keys[entry * a.bn + c] = ok ? key : ~key;
         const unsigned long long m = __ballot(ok);
         if (lane == 0) {
@@ -178,60 +218,16 @@ __global__ __launch_bounds__(64) void k_cross_entries(CrossArgs a)
     }
 }
 
-// ---- compact copies for the backward: rows of [B][H][n][row_bytes] tensors, 16 bytes per thread ----------
-// dst[b][h][c] = src[b][h][sel[b][c]] for c < count[b], zeros for the other rows of the compact tensors
-// (they are operands of the kernels' contractions, masked but read); two tensors per launch.
-__global__ __launch_bounds__(256) void k_cross_gather(const int32_t *__restrict__ sel, const int32_t *__restrict__ count,
-                                                       int n_enc, int n_compact, int heads, int chunks,
-                                                       const u32x4 *__restrict__ src0, const u32x4 *__restrict__ src1,
-                                                       u32x4 *__restrict__ dst0, u32x4 *__restrict__ dst1, long long total)
-{
-    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (t >= total) return;
-    const int ch = (int)(t % chunks);
-    const long long row = t / chunks;  // (b * heads + h) * n_compact + c
-    const int c = (int)(row % n_compact);
-    const long long bh = row / n_compact;
-    const int b = (int)(bh / heads);
-    u32x4 x0 = {0u, 0u, 0u, 0u}, x1 = x0;
-    if (c < count[b]) {
-        const long long from = (bh * n_enc + sel[(size_t)b * n_enc + c]) * chunks + ch;
-        x0 = src0[from];
-        x1 = src1[from];
-    }
-    dst0[t] = x0;
-    dst1[t] = x1;
-}
-
-// dst[b][h][p] = src[b][h][rank[b][p]] for visible p, zeros otherwise; two tensors per launch
-__global__ __launch_bounds__(256) void k_cross_scatter(const int32_t *__restrict__ rank, int n_enc, int n_compact, int heads,
-                                                        int chunks, const u32x4 *__restrict__ src0,
-                                                        const u32x4 *__restrict__ src1, u32x4 *__restrict__ dst0,
-                                                        u32x4 *__restrict__ dst1, long long total)
-{
-    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (t >= total) return;
-    const int ch = (int)(t % chunks);
-    const long long row = t / chunks;  // (b * heads + h) * n_enc + p
-    const int pos = (int)(row % n_enc);
-    const long long bh = row / n_enc;
-    const int b = (int)(bh / heads);
-    const int r = rank[(size_t)b * n_enc + pos];
-    u32x4 x0 = {0u, 0u, 0u, 0u}, x1 = x0;
-    if (r >= 0) {
-        const long long from = (bh * n_compact + r) * chunks + ch;
-        x0 = src0[from];
-        x1 = src1[from];
-    }
-    __builtin_nontemporal_store(x0, &dst0[t]);
-    __builtin_nontemporal_store(x1, &dst1[t]);
-}
-
-// Entry ranges of the forward schedule with every key list cut into `pieces`: row tile p * tr + I of sample b gets
-// entries [p * chunk, (p + 1) * chunk) of the list of tile (b, I), chunk = ceil(entries / pieces).
+struct SplitRanges {
+    int32_t *out[3];
+};
+// Entry ranges of the forward schedule with every key list cut into 2, 4 and 8 pieces (blockIdx.y): row tile p * tr + I
+// of sample b gets entries [p * chunk, (p + 1) * chunk) of the list of tile (b, I), chunk = ceil(entries / pieces).
 __global__ __launch_bounds__(256) void k_cross_split_ranges(const int32_t *__restrict__ count, int batch, int tr, int bn,
-                                                             int e_max, int pieces, int32_t *__restrict__ out)
+                                                             int e_max, SplitRanges ranges)
 {
+    const int pieces = 2 << blockIdx.y;
+    int32_t *out = ranges.out[blockIdx.y];
     const int t = blockIdx.x * 256 + threadIdx.x;
     if (t >= batch * pieces * tr) return;
     const int b = t / (pieces * tr), r = t % (pieces * tr), p = r / tr, I = r % tr;
@@ -385,7 +381,6 @@ hdt_layout_t *new_layout(int batch, int n_rows, int n_kv, int bm, int bn)
     L->cross = 1;
     L->transposed = nullptr;
     L->compact = nullptr;
-    L->cross_sel = L->cross_count = L->cross_rank = nullptr;
     L->n_compact = 0;
     for (auto &r : L->cross_split_range) r = nullptr;
     L->cross_entries_max = 0;
@@ -460,7 +455,9 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_cross_l
     }
     L->transposed = T;
     L->cross_level_mask = T->cross_level_mask = level_mask;
-    hdt_layout_t *Lc = nullptr, *Tc = nullptr;  // the compact pair while it is being built
+    hdt_layout_t *Tc = nullptr;  // the compact schedule while it is being built
+    HdtReport report{};
+    bool reported = false;
     hdt_status_t status = HDT_OK;
     hipStream_t st = (hipStream_t)stream;
     L->streams.add(st);
@@ -492,83 +489,81 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_cross_l
         f = carve_cross((char *)L->arena, (char *)L->arena2, batch, n_enc, L->s.tr, ent_fwd, bm, bn, true);
         t = carve_cross((char *)T->arena, (char *)T->arena2, batch, n_enc, T->s.tr, ent_tr, bm, bn, false);
         if (!empty) {
+            // (a stream that is being captured runs nothing now: no report would come)
+            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+            reported = hipStreamIsCapturing(st, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone &&
+                       hdt_report_open(L->device, &report);
+            if (!reported) report = HdtReport{};
             {
                 HdtTimer tm("hdt_cross_select", st);
                 hipLaunchKernelGGL(k_cross_select, dim3((unsigned)batch), dim3(kSelThreads), 0, st, d_level_enc, n_enc,
-                                   level_mask, f.sel, f.rank, f.count);
+                                   level_mask, f.sel, f.rank, f.count, report);
             }
-            CrossArgs a{d_level_enc, f.sel, f.count, level_mask, n_enc, n_dec, bm, bn, 0, L->s.tr, e_fwd, 0,
+            CrossArgs a{d_level_enc, f.sel, f.count, level_mask, n_enc, n_dec, bm, bn, 0, L->s.tr, e_fwd, 0, (int)ent_fwd,
                         f.q_range, f.c_row, f.c_cnt, f.q_keys, f.q_sub, f.bits_rm};
-            {
-                HdtTimer tm("hdt_cross_entries", st);
-                hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)ent_fwd), dim3(64), 0, st, a);
-            }
-            CrossArgs at{d_level_enc, f.sel, f.count, level_mask, n_enc, n_dec, bm, bn, 1, T->s.tr, e_tr, 0,
+            CrossArgs at{d_level_enc, f.sel, f.count, level_mask, n_enc, n_dec, bm, bn, 1, T->s.tr, e_tr, 0, (int)ent_tr,
                          t.q_range, t.c_row, t.c_cnt, t.q_keys, t.q_sub, t.bits_rm};
             {
-                HdtTimer tm("hdt_cross_entries_transposed", st);
-                hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)ent_tr), dim3(64), 0, st, at);
+                HdtTimer tm("hdt_cross_entries", st);
+                if (ent_fwd + ent_tr < (1LL << 25)) {
+                    hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)(ent_fwd + ent_tr)), dim3(64), 0, st, a, at);
+                } else {  // a grid holds less than 2^32 threads
+                    hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)ent_fwd), dim3(64), 0, st, a, a);
+                    hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)ent_tr), dim3(64), 0, st, at, at);
+                }
             }
             CROSS_TRY(hipGetLastError());
-            L->cross_sel = f.sel;
-            L->cross_rank = f.rank;
-            L->cross_count = f.count;
-            // How many positions are visible?  (The one read-back of the build: it waits for the select kernel.)
-            std::vector<int32_t> h_count((size_t)batch, 0);
-            CROSS_TRY(hipMemcpyAsync(h_count.data(), f.count, sizeof(int32_t) * batch, hipMemcpyDeviceToHost, st));
-            CROSS_TRY(hipStreamSynchronize(st));
+            // How many positions are visible?  The select kernel reports the largest count while the entries are being
+            // written; without a report it is read back the slow way.
             int c_max = 0;
-            for (int32_t c : h_count) c_max = c > c_max ? c : c_max;
+            unsigned long long word = 0;
+            if (reported && hdt_report_wait(report, &word)) {
+                c_max = (int)(uint32_t)(word & 0xffffffffu);
+            } else {
+                std::vector<int32_t> h_count((size_t)batch, 0);
+                CROSS_TRY(hipMemcpyAsync(h_count.data(), f.count, sizeof(int32_t) * batch, hipMemcpyDeviceToHost, st));
+                CROSS_TRY(hipStreamSynchronize(st));
+                for (int32_t c : h_count) c_max = c > c_max ? c : c_max;
+            }
             L->cross_entries_max = (c_max + bn - 1) / bn;
             if (L->cross_entries_max >= 16) {  // lists worth cutting: the entry ranges for 2, 4 and 8 pieces
-                for (int k = 0; k < 3; k++) {
-                    const int pieces = 2 << k, total = batch * pieces * L->s.tr;
-                    hipLaunchKernelGGL(k_cross_split_ranges, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, f.count,
-                                       batch, L->s.tr, bn, e_fwd, pieces, f.split_range[k]);
-                    L->cross_split_range[k] = f.split_range[k];
-                }
+                SplitRanges ranges;
+                for (int k = 0; k < 3; k++) L->cross_split_range[k] = ranges.out[k] = f.split_range[k];
+                const int total = batch * 8 * L->s.tr;
+                hipLaunchKernelGGL(k_cross_split_ranges, dim3((unsigned)((total + 255) / 256), 3), dim3(256), 0, st, f.count,
+                                   batch, L->s.tr, bn, e_fwd, ranges);
                 CROSS_TRY(hipGetLastError());
             }
             if (c_max > 0 && (int64_t)c_max * 4 <= n_enc) {
-                // the compact pair: decoder rows x ranks, and ranks x decoder rows
+                // the compact transposed schedule: ranks x decoder rows
                 const int n_c = (c_max + 31) / 32 * 32;
-                Lc = new_layout(batch, n_dec, n_c, bm, bn);
-                Tc = Lc ? new_layout(batch, n_c, n_dec, bm, bn) : nullptr;
-                if (!Lc || !Tc) {
+                Tc = new_layout(batch, n_c, n_dec, bm, bn);
+                if (!Tc) {
                     status = hdt_fail(HDT_ERR_OOM, "hdt_build_cross_layout: host allocation failed");
                     goto fail;
                 }
-                Lc->transposed = Tc;
-                Lc->cross_level_mask = Tc->cross_level_mask = level_mask;
-                const int e_fc = (n_c + bn - 1) / bn;
-                const int64_t ent_fc = (int64_t)batch * Lc->s.tr * e_fc, ent_tc = (int64_t)batch * Tc->s.tr * e_tr;
-                CrossBuffers fc = carve_cross(nullptr, nullptr, batch, n_enc, Lc->s.tr, ent_fc, bm, bn, false);
+                Tc->cross_level_mask = level_mask;
+                const int64_t ent_tc = (int64_t)batch * Tc->s.tr * e_tr;
                 CrossBuffers tc = carve_cross(nullptr, nullptr, batch, n_enc, Tc->s.tr, ent_tc, bm, bn, false);
-                CROSS_TRY(hdt_pool_alloc(&Lc->arena, fc.bytes1 + 256, &Lc->arena_bytes, st));
-                CROSS_TRY(hdt_pool_alloc(&Lc->arena2, fc.bytes2 + 256, &Lc->arena2_bytes, st));
                 CROSS_TRY(hdt_pool_alloc(&Tc->arena, tc.bytes1 + 256, &Tc->arena_bytes, st));
                 CROSS_TRY(hdt_pool_alloc(&Tc->arena2, tc.bytes2 + 256, &Tc->arena2_bytes, st));
-                fc = carve_cross((char *)Lc->arena, (char *)Lc->arena2, batch, n_enc, Lc->s.tr, ent_fc, bm, bn, false);
                 tc = carve_cross((char *)Tc->arena, (char *)Tc->arena2, batch, n_enc, Tc->s.tr, ent_tc, bm, bn, false);
-                CrossArgs ac{d_level_enc, f.sel, f.count, level_mask, n_enc, n_dec, bm, bn, 0, Lc->s.tr, e_fc, n_c,
-                             fc.q_range, fc.c_row, fc.c_cnt, fc.q_keys, fc.q_sub, fc.bits_rm};
-                {
-                    HdtTimer tm("hdt_cross_entries_compact", st);
-                    hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)ent_fc), dim3(64), 0, st, ac);
-                }
-                CrossArgs atc{d_level_enc, f.sel, f.count, level_mask, n_enc, n_dec, bm, bn, 1, Tc->s.tr, e_tr, n_c,
+                CrossArgs atc{d_level_enc, f.sel, f.count, level_mask, n_enc, n_dec, bm, bn, 1, Tc->s.tr, e_tr, n_c, (int)ent_tc,
                               tc.q_range, tc.c_row, tc.c_cnt, tc.q_keys, tc.q_sub, tc.bits_rm};
                 {
-                    HdtTimer tm("hdt_cross_entries_compact_transposed", st);
-                    hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)ent_tc), dim3(64), 0, st, atc);
+                    HdtTimer tm("hdt_cross_entries_compact", st);
+                    hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)ent_tc), dim3(64), 0, st, atc, atc);
                 }
                 CROSS_TRY(hipGetLastError());
-                adopt(Lc, fc, ent_fc);
                 adopt(Tc, tc, ent_tc);
-                L->compact = Lc;
+                Tc->s.own_index = f.sel;
+                Tc->s.own_count = f.count;
+                Tc->s.own_rank = f.rank;
+                Tc->s.own_stride = n_enc;
+                L->compact = Tc;
                 L->n_compact = n_c;
-                L->device_bytes += Lc->device_bytes + Tc->device_bytes;
-                Lc = Tc = nullptr;  // owned by L from here on
+                L->device_bytes += Tc->device_bytes;
+                Tc = nullptr;  // owned by L from here on
             }
         }
         struct {
@@ -585,11 +580,10 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_cross_l
         return HDT_OK;
     }
 fail:
-    for (hdt_layout_t *x : {Tc, Lc}) {
-        if (!x) continue;
-        hdt_layout_release(x, build_only);
-        x->magic = 0;
-        delete x;
+    if (Tc) {
+        hdt_layout_release(Tc, build_only);
+        Tc->magic = 0;
+        delete Tc;
     }
     hdt_layout_release(T, build_only);
     T->magic = 0;
@@ -602,54 +596,17 @@ fail:
 #undef CROSS_TRY
 }
 
-// ---- backward through the compact pair ------------------------------------------------------------------
 static size_t compact_tensor_bytes(const hdt_layout_t *l, int heads, int head_dim, int elem_bytes)
 {
     const size_t n = (size_t)l->s.batch * (size_t)heads * (size_t)l->n_compact * (size_t)head_dim * (size_t)elem_bytes;
     return (n + 255) & ~(size_t)255;
 }
 
+// Room for copies of the visible rows of K, V, dK and dV: what hdt_attn_bwd_workspace_bytes has always asked for a layout
+// with a compact schedule, and the size the limit of hdt_attn_bwd_no_alloc is counted in.
 size_t hdt_cross_compact_workspace_bytes(const hdt_layout_t *l, int heads, int head_dim, int elem_bytes)
 {
     return l->compact ? 4 * compact_tensor_bytes(l, heads, head_dim, elem_bytes) : 0;
-}
-
-// Workspace: D of the decoder rows (as for every backward), then the compact K, V, dK, dV.  The visible rows of K
-// and V are gathered, the ordinary backward runs on the compact pair of schedules (dQ is written in place: its rows
-// are the decoder's), and dK, dV are scattered to the encoder's rows, zeros where a row is not visible.
-hdt_status_t hdt_cross_bwd_compact(const hdt_layout_t *l, const void *q, const void *k, const void *v, const void *o,
-                                   const float *lse, const void *d_o, void *dq, void *dk, void *dv, int heads,
-                                   int head_dim, bool bf16, float scale, void *workspace, hipStream_t st)
-{
-    const hdt_layout_t *lc = l->compact;
-    const HdtSchedule &s = lc->s, &s_tr = lc->transposed->s;
-    const int elem = bf16 ? 2 : 4, n_enc = l->s.n_kv, n_c = l->n_compact, B = l->s.batch;
-    const size_t d_bytes = hdt_bwd_row_scalars_bytes((size_t)B * heads * (size_t)l->s.n_pos);
-    const size_t t_bytes = compact_tensor_bytes(l, heads, head_dim, elem);
-    char *w = static_cast<char *>(workspace);
-    float *delta = reinterpret_cast<float *>(w);
-    void *kc = w + d_bytes, *vc = w + d_bytes + t_bytes, *dkc = w + d_bytes + 2 * t_bytes, *dvc = w + d_bytes + 3 * t_bytes;
-    const int chunks = head_dim * elem / 16;
-    {
-        const long long total = (long long)B * heads * n_c * chunks;
-        HdtTimer tm("hdt_cross_gather", st);
-        hipLaunchKernelGGL(k_cross_gather, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, l->cross_sel, l->cross_count,
-                           n_enc, n_c, heads, chunks, (const u32x4 *)k, (const u32x4 *)v, (u32x4 *)kc, (u32x4 *)vc, total);
-    }
-    HDT_HIP_TRY(hipGetLastError());
-    hdt_status_t status =
-        bf16 ? hdt_launch_bwd_bf16(s, s_tr, q, kc, vc, o, lse, d_o, dq, dkc, dvc, heads, head_dim, scale, delta, st)
-             : hdt_launch_bwd_f32(s, s_tr, (const float *)q, (const float *)kc, (const float *)vc, (const float *)o, lse,
-                                  (const float *)d_o, (float *)dq, (float *)dkc, (float *)dvc, heads, head_dim, scale, st);
-    if (status != HDT_OK) return status;
-    {
-        const long long total = (long long)B * heads * n_enc * chunks;
-        HdtTimer tm("hdt_cross_scatter", st);
-        hipLaunchKernelGGL(k_cross_scatter, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, l->cross_rank, n_enc, n_c,
-                           heads, chunks, (const u32x4 *)dkc, (const u32x4 *)dvc, (u32x4 *)dk, (u32x4 *)dv, total);
-    }
-    HDT_HIP_TRY(hipGetLastError());
-    return HDT_OK;
 }
 
 // ---- key lists cut into pieces ---------------------------------------------------------------------------

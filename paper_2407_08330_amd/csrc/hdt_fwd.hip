@@ -156,7 +156,7 @@ __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
     constexpr uint32_t Q_STAGE = (uint32_t)(S - 1) * 2 * P::TILE;
     bf16x8 qf[KSTEPS];
     if (n > 0) {
-        stage_own_rows(pipe, q + own_base, I_own * BM, s.n_own, D, Q_STAGE);
+        stage_own_rows(pipe, q + own_base, own_rows(pipe, I_own * BM, s.n_own), Q_STAGE);
         R::start(pipe, n);
         R::template prologue<0, S - 1>(pipe, n);  // its first wait covers the Q rows
 #pragma unroll

@@ -47,6 +47,12 @@ struct HdtSchedule {
     // [batch][n_pos] >= 0 iff the row is a real position (may attend to anything), or NULL = every row is:
     // the level ids of a self-attention layout, the ranks of a cross-attention layout's encoder rows
     const int32_t *row_flag;
+    // A schedule over the visible positions of a cross-attention layout (hdt_cross.hip; dK/dV pass only): row r of
+    // sample b stands for row own_index[b * own_stride + r] of row-side tensors with own_stride rows per sample, r <
+    // own_count[b] (the tiles behind hold nothing), and the rows with own_rank < 0 are the ones no tile writes (zeros).
+    // NULL: rows are rows.
+    const int32_t *own_index, *own_count, *own_rank;
+    int32_t own_stride;
 };
 
 // whether row r of list entry t may attend to the key in slot c (plain indexing of bits_rm)
@@ -88,15 +94,10 @@ struct hdt_layout {
     // directed masks (edges without up/down symmetry): the schedule of the transposed mask (rows = keys,
     // list entries = the queries attending to them), owned by this layout; NULL for symmetric masks
     hdt_layout *transposed;
-    // Cross-attention layouts with few visible positions (hdt_cross.hip): a second pair of schedules in the index
-    // space of the visible positions (a position's row = its rank among them), on which the backward runs with
-    // compact copies of K and V.  `compact` schedules the dQ pass (keys = ranks), compact->transposed the
-    // dK/dV pass (rows = ranks); all owned by this layout.  NULL: no such pair.
+    // Cross-attention layouts with few visible positions (hdt_cross.hip): the schedule of the dK/dV pass in the index
+    // space of the visible positions (row = rank among them), owned by this layout.  NULL: there is none.
     hdt_layout *compact;
-    const int32_t *cross_sel;    // [batch][n_kv] visible positions in document order (device)
-    const int32_t *cross_count;  // [batch] their number (device)
-    const int32_t *cross_rank;   // [batch][n_kv] rank among the visible positions, -1 = not visible (device)
-    int32_t n_compact;           // rows per (sample, head) of the compact tensors
+    int32_t n_compact;           // rows per sample of the compact schedule
     // Long key lists cut into 2, 4 or 8 pieces (hdt_cross.hip): the entry ranges of the row tiles of every piece,
     // [batch][pieces * tr][2] each (device, in this layout's first arena); NULL if the lists are short
     const int32_t *cross_split_range[3];
@@ -182,11 +183,17 @@ hdt_status_t hdt_cross_bwd_split(const hdt_layout_t *l, const void *q, const voi
                                  const float *lse, const void *d_o, void *dq, void *dk, void *dv, int heads,
                                  int head_dim, float scale, void *workspace, hipStream_t st);
 
-// --- backward of a cross-attention layout with a compact pair (hdt_cross.hip) ---
 size_t hdt_cross_compact_workspace_bytes(const hdt_layout_t *l, int heads, int head_dim, int elem_bytes);
-hdt_status_t hdt_cross_bwd_compact(const hdt_layout_t *l, const void *q, const void *k, const void *v, const void *o,
-                                   const float *lse, const void *d_o, void *dq, void *dk, void *dv, int heads,
-                                   int head_dim, bool bf16, float scale, void *workspace, hipStream_t st);
+
+// --- the device's report to a waiting host: one 64-bit word of pinned host memory per build in flight, and a slot of
+// device counters that is zero between builds (hdt_layout.hip) ---
+struct HdtReport {
+    unsigned long long *word;  // [63:40] ticket of the build, [39] error, [31:0] value
+    int32_t *counters;         // 64 device words, zero; the kernel leaves them zero
+    uint32_t ticket, ticket_before;
+};
+bool hdt_report_open(int device, HdtReport *r);                       // false: no memory for it
+bool hdt_report_wait(const HdtReport &r, unsigned long long *word);   // false: nothing came within the time limit
 
 // --- per-kernel timing (hdt_api.hip) ---
 struct HdtTimer {  // brackets one kernel launch with events when timing is enabled

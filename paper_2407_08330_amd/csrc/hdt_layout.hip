@@ -1611,6 +1611,18 @@ hipError_t hdt_pool_alloc(void **out, size_t bytes, size_t *got, hipStream_t nex
     return pool_alloc(out, bytes, got, next_user);
 }
 
+bool hdt_report_open(int device, HdtReport *r)
+{
+    r->word = report_slot(&r->ticket, &r->ticket_before);
+    r->counters = r->word ? counter_slot(device, r->ticket) : nullptr;
+    return r->counters != nullptr;
+}
+
+bool hdt_report_wait(const HdtReport &r, unsigned long long *word)
+{
+    return wait_for_report(r.word, r.ticket, r.ticket_before, word);
+}
+
 void hdt_layout_release(hdt_layout_t *L, const HdtUsers &users)
 {
     pool_free(L->arena, L->arena_bytes, L->device, users);
@@ -1835,7 +1847,6 @@ static hdt_status_t build_one(const int32_t *d_level, const int32_t *d_parent, i
     L->cross_level_mask = 0;
     L->transposed = nullptr;
     L->compact = nullptr;
-    L->cross_sel = L->cross_count = L->cross_rank = nullptr;
     L->n_compact = 0;
     L->device_bytes = 0;
     L->device = 0;

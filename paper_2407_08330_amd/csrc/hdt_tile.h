@@ -265,19 +265,34 @@ struct Ring {
     }
 };
 
-// A wave's own 32 rows of a [n_pos][D] tensor (rows row0 + 32*wave .. +31, clamped to n_pos-1),
-// loaded straight into LDS as rows 32*wave .. of a swizzled tile at byte offset lds_off: full rows per
+// A wave's own 32 rows of a [n_pos][D] tensor (rows row0 + 32*wave .. +31, clamped to n_pos-1; with an index, the rows
+// it names), loaded straight into LDS as rows 32*wave .. of a swizzled tile at byte offset lds_off: full rows per
 // 8 or 16 lanes, so every 128-byte line is fetched once.  The MFMA B fragments of those rows are
 // then read back with read_row().  Issues 32/RPI vector-memory instructions.
 template <typename P>
-__device__ __forceinline__ void stage_own_rows(const P &p, const __bf16 *t, int row0, int n_pos, int D, uint32_t lds_off)
+struct OwnRows {
+    int g[32 / P::RPI];  // the row this lane loads 16 bytes of, per instruction
+};
+template <typename P>
+__device__ __forceinline__ OwnRows<P> own_rows(const P &p, int row0, int n_pos, const int32_t *index = nullptr)
+{
+    OwnRows<P> o;
+    const int lr = p.lane / P::CPR;
+#pragma unroll
+    for (int i = 0; i < 32 / P::RPI; i++) {
+        const int g = min(row0 + p.wave * 32 + i * P::RPI + lr, n_pos - 1);
+        o.g[i] = index ? index[g] : g;
+    }
+    return o;
+}
+template <typename P>
+__device__ __forceinline__ void stage_own_rows(const P &p, const __bf16 *t, const OwnRows<P> &rows, uint32_t lds_off)
 {
     const int lr = p.lane / P::CPR, c = p.lane % P::CPR;
 #pragma unroll
     for (int i = 0; i < 32 / P::RPI; i++) {
         const int r = p.wave * 32 + i * P::RPI + lr;
-        const int g = min(row0 + r, n_pos - 1);
-        dma16(t, (uint32_t)g * P::ROWB + (uint32_t)((c ^ swz<P::CPR>(r)) * 16),
+        dma16(t, (uint32_t)rows.g[i] * P::ROWB + (uint32_t)((c ^ swz<P::CPR>(r)) * 16),
               p.smem_addr + lds_off + (uint32_t)((p.wave * 32 + i * P::RPI) * P::ROWB));
     }
 }
@@ -293,10 +308,11 @@ __device__ __forceinline__ int opaque(int x)
 
 // Epilogue: a wave's 32 x D accumulator block, held transposed in C fragments (lane (row l%32, hf)
 // holds columns 32j + 4hf + 8g + 0..3), is scaled, rounded to bf16, transposed through a wave-private
-// LDS area of 32*ROWB bytes and written to global memory as full rows (16 bytes per lane).
+// LDS area of 32*ROWB bytes and written to global memory as full rows (16 bytes per lane): row r of the block to row r
+// of dst, or with an index (in LDS) to row index[r].
 template <typename P, int D>
 __device__ __forceinline__ void store_rows_via_lds(char *wave_lds, int lane, const f32x16 (&acc)[D / 32], float mult,
-                                                   __bf16 *dst, int rows_valid)
+                                                   __bf16 *dst, int rows_valid, const int *index = nullptr)
 {
     const int r = lane & 31, hf = lane >> 5;
 #pragma unroll
@@ -315,7 +331,10 @@ __device__ __forceinline__ void store_rows_via_lds(char *wave_lds, int lane, con
         const int row = i * P::RPI + lr;
         const u32x4 v = *reinterpret_cast<const u32x4 *>(wave_lds + row * P::ROWB + ((c ^ (row & 7)) << 4));
         // streaming store: results are not read again by this launch and should not displace its inputs in L2
-        if (row < rows_valid) __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst + (size_t)row * D + c * 8));
+        if (row < rows_valid) {
+            const int at = index ? index[row] : row;
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst + (size_t)at * D + c * 8));
+        }
     }
 }
 

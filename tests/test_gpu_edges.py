@@ -5,8 +5,9 @@ import pytest
 
 from paper_2407_08330_amd import inputs
 from test_gpu_bwd import run_bwd_case
+from test_gpu_cross import _compare_schedule, run_cross_case
 from test_gpu_fwd import run_fwd_case
-from gpu_common import say
+from gpu_common import say, to_dev_i32
 
 pytestmark = pytest.mark.gpu
 
@@ -29,3 +30,29 @@ def test_fp32_rows_lists_and_tile_shapes(oracle, tile, D, windowed):
     run_fwd_case(oracle, level, parent, 3, D, "f32", 31, tile=tile, windowed=windowed)
     run_bwd_case(oracle, level, parent, 3, D, "f32", 32, tile=tile, windowed=windowed)
     run_bwd_case(oracle, level, parent, 1, D, "f32", 33, tile=tile, windowed=windowed, edges=6)
+
+
+@pytest.mark.parametrize("tile,D", [((128, 64), 64), ((64, 32), 128)])
+def test_cross_few_visible_positions_at_tile_edges(oracle, tile, D):
+    # the dK/dV pass works on the visible positions by rank: their number at and around the edges of a wave's 32 rows and
+    # of the row tiles, one sample with two, and an encoder length that no zero-writing workgroup divides
+    n_enc = 1217
+    counts = (2, 32, 33, 127, 128, 129, 304)
+    level = np.full((len(counts), n_enc), 3, np.int32)
+    rng = np.random.default_rng(5)
+    for b, c in enumerate(counts):
+        level[b, rng.choice(n_enc, c, replace=False)] = 1
+    say(f"[cross edges] {counts} of {n_enc} positions visible, tile {tile} d={D}")
+    run_cross_case(oracle, level, 100, 2, 2, D, "bf16", 41, tile=tile, poison_invisible=True)
+
+
+def test_cross_select_on_long_encoders(oracle):
+    # more than 8 groups of 64 positions per wave of the selecting workgroup, a ragged last group
+    import paper_2407_08330_amd as hdt
+    level = np.random.default_rng(6).integers(-1, 4, size=(3, 20011)).astype(np.int32)
+    lay = hdt.hdt_build_cross_layout(to_dev_i32(level), 70, 4, tile_m=128, tile_n=64)
+    assert lay.info()["compact_rows"] > 0
+    for b in range(level.shape[0]):
+        f_ref, t_ref = oracle.cross_schedule(level[b], 70, 4, 128, 64)
+        _compare_schedule(lay, f_ref, b, "forward")
+        _compare_schedule(lay.transposed(), t_ref, b, "transposed")
