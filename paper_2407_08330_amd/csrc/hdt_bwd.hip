@@ -434,7 +434,7 @@ __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)
     HdtSchedule s, HdtSchedule s_tr, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k,
     const __bf16 *__restrict__ v, const float *__restrict__ lse, const __bf16 *__restrict__ d_o,
     const float2 *__restrict__ row_scalars, __bf16 *__restrict__ dq, __bf16 *__restrict__ dk,
-    __bf16 *__restrict__ dv, int heads, float scale)
+    __bf16 *__restrict__ dv, int heads, float scale, unsigned chunk)
 {
     using PQ = Pipe<D, BwdCfg<D>::S_DQ, false, G>;
     using PK = Pipe<D, BwdCfg<D>::S_DKV, true, G>;
@@ -447,13 +447,13 @@ __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)
     constexpr unsigned R = BwdCfg<D>::SPLIT_KV ? 3u : 2u;  // roles per tile: dQ, then dK/dV or dV, dK
     const unsigned nq = (unsigned)s.batch * heads * s.tr, nk = (unsigned)s_tr.batch * heads * s_tr.tr;
     if (INDEXED) {
-        const unsigned roles = padded_grid(nq + (R - 1u) * nk, R * G::XCD_CHUNK);
+        const unsigned roles = padded_grid(nq + (R - 1u) * nk, chunk);
         if (blockIdx.x >= roles) {
             zero_role<D, G>(s_tr, dk, dv, blockIdx.x - roles, heads);
             return;
         }
     }
-    const unsigned w = logical_block(blockIdx.x, R * G::XCD_CHUNK);
+    const unsigned w = logical_block(blockIdx.x, chunk);
     const unsigned common = nq < nk ? nq : nk;
     if (w >= nq + (R - 1u) * nk) return;  // padding of the grid
     unsigned role, lb;
@@ -492,9 +492,10 @@ static void launch_roles(const HdtSchedule &s, const HdtSchedule &s_tr, const __
     const unsigned nq = (unsigned)s.batch * heads * s.tr, nk = (unsigned)s_tr.batch * heads * s_tr.tr;
     constexpr unsigned roles = BwdCfg<D>::SPLIT_KV ? 3u : 2u, zr = ZeroRows<D, G>::ROWS;
     const unsigned zeros = INDEXED ? (unsigned)s_tr.batch * heads * (((unsigned)s_tr.own_stride + zr - 1u) / zr) : 0u;
-    dim3 grid(padded_grid(nq + (roles - 1u) * nk, roles * G::XCD_CHUNK) + zeros), block(G::THREADS);
+    const unsigned items = nq + (roles - 1u) * nk, chunk = xcd_chunk(items, roles * G::XCD_CHUNK, roles);
+    dim3 grid(padded_grid(items, chunk) + zeros), block(G::THREADS);
     hipLaunchKernelGGL((k_bwd_bf16<D, G, INDEXED>), grid, block, 0, st, s, s_tr, Q, K, V, lse, DO, row_scalars, (__bf16 *)dq,
-                       (__bf16 *)dk, (__bf16 *)dv, heads, scale);
+                       (__bf16 *)dk, (__bf16 *)dv, heads, scale, chunk);
 }
 
 template <typename G>

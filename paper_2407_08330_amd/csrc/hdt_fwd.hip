@@ -115,7 +115,7 @@ __device__ __forceinline__ void fwd_step(const char *sK, const char *sV, const R
 template <int D, typename G>
 __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
     HdtSchedule s, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
-    __bf16 *__restrict__ o, float *__restrict__ lse, int heads, float scale_log2)
+    __bf16 *__restrict__ o, float *__restrict__ lse, int heads, float scale_log2, unsigned chunk)
 {
     using P = Pipe<D, FwdCfg<D>::S, false, G>;
     using R = Ring<P>;
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int qn = lane & 31, hf = lane >> 5;
-    const unsigned lb = logical_block(blockIdx.x, G::XCD_CHUNK);
+    const unsigned lb = logical_block(blockIdx.x, chunk);
     if (lb >= (unsigned)s.batch * heads * s.tr) return;  // padding of the grid
     const int I = lb % s.tr, bh = lb / s.tr, b = bh / heads;
     const int I_own = I % s.tr_own;  // the rows this tile works on (several tiles share them when key lists are cut)
@@ -216,13 +216,14 @@ template <typename G>
 static void launch_fwd(const HdtSchedule &s, const void *q, const void *k, const void *v, void *o, float *lse,
                        int heads, int head_dim, float scale_log2, hipStream_t st)
 {
-    dim3 grid(padded_grid((unsigned)((size_t)s.batch * heads * s.tr), G::XCD_CHUNK)), block(G::THREADS);
+    const unsigned items = (unsigned)((size_t)s.batch * heads * s.tr), chunk = xcd_chunk(items, G::XCD_CHUNK, 1u);
+    dim3 grid(padded_grid(items, chunk)), block(G::THREADS);
     if (head_dim == 64)
         hipLaunchKernelGGL((k_fwd_bf16<64, G>), grid, block, 0, st, s, (const __bf16 *)q, (const __bf16 *)k,
-                           (const __bf16 *)v, (__bf16 *)o, lse, heads, scale_log2);
+                           (const __bf16 *)v, (__bf16 *)o, lse, heads, scale_log2, chunk);
     else
         hipLaunchKernelGGL((k_fwd_bf16<128, G>), grid, block, 0, st, s, (const __bf16 *)q, (const __bf16 *)k,
-                           (const __bf16 *)v, (__bf16 *)o, lse, heads, scale_log2);
+                           (const __bf16 *)v, (__bf16 *)o, lse, heads, scale_log2, chunk);
 }
 
 hdt_status_t hdt_launch_fwd_bf16(const HdtSchedule &s, const void *q, const void *k, const void *v, void *o,

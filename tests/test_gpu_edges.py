@@ -56,3 +56,14 @@ def test_cross_select_on_long_encoders(oracle):
         f_ref, t_ref = oracle.cross_schedule(level[b], 70, 4, 128, 64)
         _compare_schedule(lay, f_ref, b, "forward")
         _compare_schedule(lay.transposed(), t_ref, b, "transposed")
+
+
+@pytest.mark.parametrize("heads", [1, 8, 9, 257, 514])
+def test_every_row_tile_is_worked_on_whatever_their_number(oracle, heads):
+    # the grid is cut into 8 equal shares per round: numbers of row tiles (1 and 2 per head) below, at and above them
+    docs = [inputs.document_from_sections([[20, 40]], 70)]
+    level, parent = _padded(docs, 70)
+    for tile in ((128, 64), (64, 32)):
+        say(f"[grid edges] {heads} heads, tile {tile}")
+        run_fwd_case(oracle, level, parent, heads, 64, "bf16", 51, tile=tile)
+        run_bwd_case(oracle, level, parent, heads, 128 if heads < 10 else 64, "bf16", 52, tile=tile)
