@@ -12,56 +12,92 @@
 // token in its sentence), so the encoding of a position is the sum of L rows of a small table that stays in
 // L2: the add is then bound by reading and writing x once, not by 2*L*d_model sine evaluations per position.
 // Indices beyond the table are evaluated directly.
+#include <limits.h>
 #include <math.h>
+
+#include <algorithm>
 
 #include "hdt_internal.h"
 
 namespace {
 
 constexpr int kOrdThreads = 1024, kOrdWaves = kOrdThreads / 64;
+constexpr int kMaxShares = 64;  // workgroups per sample
+constexpr int kBack = 8;        // groups of 64 positions a wave has in flight while it looks at earlier positions
+
+// Both kernels below give a workgroup a contiguous share of a sample's positions, which it takes 1024 at a time; what it
+// has to know about the positions in front of its share it finds by reading them, all waves together.  That reads up
+// to `shares` / 2 times the sample's ids (a few hundred KB, out of L2), and takes less time than carrying the state from
+// chunk to chunk in one workgroup per sample, whose chunks follow one another (8192 positions x 4 samples: parents
+// 31 -> 6.7 us, ordinals 20.8 -> 8.2; 32768 positions, 1 sample: 126 -> 11 and 78 -> 18).
+__host__ inline int hpe_shares(int n) { return std::min((n + kOrdThreads - 1) / kOrdThreads, kMaxShares); }
+__device__ __forceinline__ int2 my_share(int n, int shares)  // [first, last) of workgroup blockIdx.x = b * shares + k
+{
+    const int chunks = (n + kOrdThreads - 1) / kOrdThreads, per = (chunks + shares - 1) / shares;
+    const int first = min((int)(blockIdx.x % shares) * per, chunks);
+    return make_int2(first * kOrdThreads, min(min(first + per, chunks) * kOrdThreads, n));
+}
 
 // ---- parents of a document laid out with its anchors in front (pre-order) ---------------------------
-// parent[i] = the nearest earlier position whose level is level[i] - 1 (none: -1).  One workgroup per
-// sample walks the positions in chunks of 1024 and keeps, per level, the last position seen so far:
-// inside a wave by ballots, across the waves of a chunk and across chunks through LDS.
-__global__ __launch_bounds__(kOrdThreads) void k_parents_from_levels(const int32_t *__restrict__ level, int n,
+// parent[i] = the nearest earlier position whose level is level[i] - 1 (none: -1).  Inside a wave by ballots, across
+// the waves of a chunk and in front of it through LDS (the last position of every level).  The positions in front of a
+// share are read backwards until every level that somebody still misses has been seen.
+__global__ __launch_bounds__(kOrdThreads) void k_parents_from_levels(const int32_t *__restrict__ level, int n, int shares,
                                                                       int32_t *__restrict__ parent)
 {
     __shared__ int s_last[kOrdWaves][32];  // last position of each level in each wave of the chunk (-1: none)
-    __shared__ int s_carry[32];            // last position of each level in the chunks before
-    const int b = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const size_t o = (size_t)b * n;
+    __shared__ int s_carry[32];            // last position of each level in front of the chunk
+    __shared__ unsigned s_missing;         // levels that positions of the chunk look for and the share has not seen
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const size_t o = (size_t)(blockIdx.x / shares) * n;
+    const int2 share = my_share(n, shares);
+    unsigned searched = 0u;  // levels looked for in front of the share
     if (tid < 32) s_carry[tid] = -1;
+    if (tid == 0) s_missing = 0u;
     __syncthreads();
-    for (int c0 = 0; c0 < n; c0 += kOrdThreads) {
+    for (int c0 = share.x; c0 < share.y; c0 += kOrdThreads) {
         const int i = c0 + tid;
-        int lv = i < n ? level[o + i] : -1;
+        int lv = i < share.y ? level[o + i] : -1;
         if (lv < 0 || lv >= 32) lv = -1;
-        // the last lane of every level in this wave, kept by lane = level
-        int mine = -1;
-        for (int l = 0; l < 32; l++) {
-            const unsigned long long m = __ballot(lv == l);
-            if (lane == l && m) mine = c0 + wave * 64 + 63 - __builtin_clzll(m);
+        // level by level of those in this wave: its last position (kept by lane = level), and for the positions one
+        // level down the nearest earlier one
+        int mine = -1, par = -1;
+        unsigned long long todo = __ballot(lv >= 0);
+        while (todo) {
+            const int t = __builtin_amdgcn_readlane(lv, __ffsll((long long)todo) - 1);
+            const unsigned long long m = __ballot(lv == t), before = m & ((1ull << lane) - 1ull);
+            if (lane == t) mine = c0 + wave * 64 + 63 - __builtin_clzll(m);
+            if (lv == t + 1 && before) par = c0 + wave * 64 + 63 - __builtin_clzll(before);
+            todo &= ~m;
         }
         if (lane < 32) s_last[wave][lane] = mine;
-        // the nearest earlier lane of this wave with level lv - 1
-        int par = -1;
-        unsigned long long todo = __ballot(lv > 0);
-        while (todo) {
-            const int leader = __ffsll((long long)todo) - 1;
-            const int t = __builtin_amdgcn_readlane(lv, leader) - 1;
-            const unsigned long long m = __ballot(lv == t);
-            const bool me = lv - 1 == t && lv > 0;
-            const unsigned long long before = m & ((1ull << lane) - 1ull);
-            if (me && before) par = c0 + wave * 64 + 63 - __builtin_clzll(before);
-            todo &= ~__ballot(me);
-        }
         __syncthreads();
-        if (lv > 0 && par < 0) {  // not in this wave: earlier waves of the chunk, then earlier chunks
+        if (lv > 0)  // not in this wave: earlier waves of the chunk, then earlier chunks of the share
             for (int w = wave - 1; w >= 0 && par < 0; w--) par = s_last[w][lv - 1];
-            if (par < 0) par = s_carry[lv - 1];
+        const bool miss = lv > 0 && par < 0;
+        if (miss && s_carry[lv - 1] < 0) atomicOr(&s_missing, 1u << (lv - 1));
+        __syncthreads();
+        unsigned missing = s_missing & ~searched;
+        searched |= missing;
+        for (int end = share.x; missing && end > 0; end -= kBack * kOrdThreads) {
+            int l[kBack];
+#pragma unroll
+            for (int u = 0; u < kBack; u++) {
+                const int j = end - (u + 1) * kOrdThreads + tid;
+                l[u] = j >= 0 ? level[o + j] : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < kBack; u++) {
+                const int j = end - (u + 1) * kOrdThreads + tid;
+                if (l[u] >= 0 && l[u] < 32 && ((missing >> l[u]) & 1u) && s_carry[l[u]] < j) atomicMax(&s_carry[l[u]], j);
+            }
+            __syncthreads();
+            for (int t = 0; t < 32; t++)
+                if (s_carry[t] >= 0) missing &= ~(1u << t);
+            __syncthreads();  // everybody has looked before the next round writes
         }
-        if (i < n) parent[o + i] = par;
+        if (miss) par = s_carry[lv - 1];
+        if (i < share.y) parent[o + i] = par;
         __syncthreads();
         if (tid < 32) {
             for (int w = kOrdWaves - 1; w >= 0; w--)
@@ -70,136 +106,122 @@ __global__ __launch_bounds__(kOrdThreads) void k_parents_from_levels(const int32
                     break;
                 }
         }
+        if (tid == 0) s_missing = 0u;
         __syncthreads();
     }
 }
 
 // ---- ordinal of every position among its siblings (same parent), in document order ---------------
-// One workgroup per sample walks the positions in chunks of 1024 * kOrdV (a thread takes kOrdV consecutive
-// positions).  Inside a chunk, consecutive positions with the same parent form a run (the tokens of a sentence,
-// for one): a position's ordinal is
-//   1 + (siblings in earlier chunks: a per-parent counter in global memory)
-//     + (siblings in earlier runs of this chunk: a sum over the earlier run heads, shared by kOrdSplit lanes)
+// Consecutive positions with the same parent form a run (the tokens of a sentence, for one); a run ends at the latest
+// with the 64 positions a wave holds.  A position's ordinal is
+//   1 + (siblings in front of the chunk: a counter per parent in LDS, filled from the positions in front of the share
+//        and then chunk by chunk)
+//     + (siblings in earlier runs of the chunk: a sum over the earlier runs, shared by kOrdSplit lanes)
 //     + (its offset inside its run).
-// Roots (parent -1) count as children of one virtual parent.  Pads and positions past n form runs of
-// their own (group -1), which only serve to end the runs before them.
-constexpr int kOrdV = 4, kOrdChunk = kOrdThreads * kOrdV, kOrdSplit = 16;
+// Roots (parent -1) count as children of one virtual parent, n.  Pads and positions past the share are a group of their
+// own (-1), which only serves to end the runs before them.  The counters cover a window of the parents at a time: one
+// window up to kOrdWindow positions, as many LDS words as that takes; beyond, the windows in which parents of the share lie.
+constexpr int kOrdSplit = 16, kOrdWindow = 33 * 1024;
+
+__device__ __forceinline__ int ord_group(int level, int parent, int n)
+{
+    return level < 0 ? -1 : ((parent >= 0 && parent < n) ? parent : n);
+}
+// whether this lane's position starts a run, and the run's length (1 .. 64)
+__device__ __forceinline__ bool run_head(int grp, int lane, int *len)
+{
+    const int before = __shfl_up(grp, 1);
+    const bool head = lane == 0 || before != grp;
+    const unsigned long long heads = __ballot(head), rest = lane == 63 ? 0ull : heads >> (lane + 1);
+    *len = rest ? __ffsll((long long)rest) : 64 - lane;
+    return head;
+}
 
 __global__ __launch_bounds__(kOrdThreads) void k_sibling_ordinals(const int32_t *__restrict__ level,
-                                                                   const int32_t *__restrict__ parent, int n,
-                                                                   int32_t *cnt,  // [B][n + 1] scratch
-                                                                   int32_t *ord)  // [B][n]
+                                                                   const int32_t *__restrict__ parent, int n, int shares,
+                                                                   int32_t *__restrict__ ord)  // [B][n]
 {
-    // per run head of the chunk: its group, its first position in the chunk; per position of the chunk that
-    // starts a run: siblings before that run (s_run_base)
-    __shared__ int s_head_parent[kOrdChunk], s_head_start[kOrdChunk], s_run_base[kOrdChunk];
-    __shared__ int s_last_grp[kOrdThreads];
-    __shared__ int s_wave_max[kOrdWaves], s_wave_heads[kOrdWaves];
-    const int b = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const size_t o = (size_t)b * n;
-    int32_t *my_cnt = cnt + (size_t)b * (n + 1);
-    for (int i = tid; i <= n; i += kOrdThreads) my_cnt[i] = 0;
+    extern __shared__ int s_count[];  // children seen so far of the parents w0 .. w0 + window - 1
+    __shared__ int s_run_grp[kOrdThreads], s_run_len[kOrdThreads], s_run_base[kOrdThreads];
+    __shared__ int s_wave_runs[kOrdWaves];
+    __shared__ int s_lo, s_hi;  // the groups of the share
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const size_t o = (size_t)(blockIdx.x / shares) * n;
+    const int2 share = my_share(n, shares);
+    if (share.x >= share.y) return;
+    const int window = min(n + 1, kOrdWindow);
+    if (tid == 0) {
+        s_lo = INT_MAX;
+        s_hi = -1;
+    }
     __syncthreads();
-    for (int c0 = 0; c0 < n; c0 += kOrdChunk) {
-        const int idx0 = tid * kOrdV;  // this thread's first position inside the chunk
-        int grp[kOrdV];                // the parent (n for roots), -1 for pads and positions past n
-#pragma unroll
-        for (int u = 0; u < kOrdV; u++) {
-            const int i = c0 + idx0 + u;
-            grp[u] = -1;
-            if (i < n && level[o + i] >= 0) {
-                const int p = parent[o + i];
-                grp[u] = (p >= 0 && p < n) ? p : n;
-            }
-        }
-        s_last_grp[tid] = grp[kOrdV - 1];
-        __syncthreads();
-        // run heads; the last head at or before every position: a running maximum over the threads
-        int before = tid == 0 ? -2 : s_last_grp[tid - 1];
-        bool head[kOrdV];
-        int n_mine = 0, last_head = -1;
-#pragma unroll
-        for (int u = 0; u < kOrdV; u++) {
-            head[u] = grp[u] != before;
-            before = grp[u];
-            if (head[u]) {
-                n_mine++;
-                last_head = idx0 + u;
-            }
-        }
-        int run_max = last_head, heads_incl = n_mine;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int y = __shfl_up(run_max, d), z = __shfl_up(heads_incl, d);
-            if (lane >= d) {
-                run_max = max(run_max, y);
-                heads_incl += z;
-            }
-        }
-        if (lane == 63) {
-            s_wave_max[wave] = run_max;
-            s_wave_heads[wave] = heads_incl;
-        }
-        __syncthreads();
-        int start_in = __shfl_up(run_max, 1);  // last head before this thread's positions
-        if (lane == 0) start_in = -1;
-        int my_head = heads_incl - n_mine, n_heads = 0;
-        for (int w = 0; w < kOrdWaves; w++) {
-            if (w < wave) {
-                start_in = max(start_in, s_wave_max[w]);
-                my_head += s_wave_heads[w];
-            }
-            n_heads += s_wave_heads[w];
-        }
-        int start[kOrdV];
-        {
-            int cur = start_in, h = my_head;
-#pragma unroll
-            for (int u = 0; u < kOrdV; u++) {
-                if (head[u]) {
-                    cur = idx0 + u;
-                    s_head_parent[h] = grp[u];
-                    s_head_start[h] = cur;
-                    h++;
-                }
-                start[u] = cur;
+    if (n + 1 > kOrdWindow) {
+        for (int i = share.x + tid; i < share.y; i += kOrdThreads) {
+            const int g = ord_group(level[o + i], parent[o + i], n);
+            if (g >= 0) {
+                atomicMin(&s_lo, g);
+                atomicMax(&s_hi, g);
             }
         }
         __syncthreads();
-        // siblings in earlier runs of this chunk: kOrdSplit lanes share the scan over the earlier heads of one head
-        for (int h = tid / kOrdSplit; h < n_heads; h += kOrdThreads / kOrdSplit) {
-            const int g = s_head_parent[h];
-            if (g < 0) continue;
-            int k = 0;
-            for (int e = tid % kOrdSplit; e < h; e += kOrdSplit)
-                if (s_head_parent[e] == g) k += s_head_start[e + 1] - s_head_start[e];
+    }
+    for (int w0 = 0; w0 <= n; w0 += window) {
+        if (n + 1 > kOrdWindow && (s_hi < w0 || s_lo >= w0 + window)) continue;
+        for (int t = tid; t < window; t += kOrdThreads) s_count[t] = 0;
+        __syncthreads();
+        for (int j0 = 0; j0 < share.x; j0 += kBack * kOrdThreads) {
+            int g[kBack];
 #pragma unroll
-            for (int d = 1; d < kOrdSplit; d <<= 1) k += __shfl_xor(k, d);
-            if (tid % kOrdSplit == 0) {
-                // siblings in earlier chunks (the counter last changed before the barrier that ended the previous chunk)
-                const int base = __hip_atomic_load(&my_cnt[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                s_run_base[s_head_start[h]] = base + k;
+            for (int u = 0; u < kBack; u++) {
+                const int j = j0 + u * kOrdThreads + tid;
+                g[u] = -1;
+                if (j < share.x) g[u] = ord_group(level[o + j], parent[o + j], n);
+            }
+#pragma unroll
+            for (int u = 0; u < kBack; u++) {
+                int len;
+                const bool head = run_head(g[u], lane, &len);
+                if (head && g[u] >= w0 && g[u] < w0 + window) atomicAdd(&s_count[g[u] - w0], len);
             }
         }
-        __syncthreads();
+        for (int c0 = share.x; c0 < share.y; c0 += kOrdThreads) {
+            const int i = c0 + tid;
+            const int grp = i < share.y ? ord_group(level[o + i], parent[o + i], n) : -1;
+            int len;
+            const bool head = run_head(grp, lane, &len);
+            const unsigned long long heads = __ballot(head);
+            if (lane == 0) s_wave_runs[wave] = __popcll(heads);
+            __syncthreads();
+            int first = 0, runs = 0;  // runs in front of this wave's, runs of the chunk
 #pragma unroll
-        for (int u = 0; u < kOrdV; u++)
-            if (grp[u] >= 0) ord[o + c0 + idx0 + u] = 1 + s_run_base[start[u]] + (idx0 + u - start[u]);
-        // add this chunk's runs to the counters; the returned value makes the thread wait for the atomic
-        {
-            int h = my_head;
-#pragma unroll
-            for (int u = 0; u < kOrdV; u++) {
-                if (!head[u]) continue;
-                if (grp[u] >= 0) {
-                    const int end = h + 1 < n_heads ? s_head_start[h + 1] : kOrdChunk;
-                    const int old = atomicAdd(&my_cnt[grp[u]], end - (idx0 + u));
-                    asm volatile("" ::"v"(old));
-                }
-                h++;
+            for (int w = 0; w < kOrdWaves; w++) {
+                first += w < wave ? s_wave_runs[w] : 0;
+                runs += s_wave_runs[w];
             }
+            const int run = first + __popcll(heads & ((2ull << lane) - 1ull)) - 1;  // this lane's
+            if (head) {
+                s_run_grp[run] = grp;
+                s_run_len[run] = len;
+            }
+            __syncthreads();
+            for (int r = tid / kOrdSplit; r < runs; r += kOrdThreads / kOrdSplit) {
+                const int g = s_run_grp[r];
+                if (g < w0 || g >= w0 + window) continue;  // a pad's, or of another window
+                int k = 0;
+                for (int e = tid % kOrdSplit; e < r; e += kOrdSplit)
+                    if (s_run_grp[e] == g) k += s_run_len[e];
+#pragma unroll
+                for (int d = 1; d < kOrdSplit; d <<= 1) k += __shfl_xor(k, d);
+                if (tid % kOrdSplit == 0) s_run_base[r] = s_count[g - w0] + k;
+            }
+            __syncthreads();
+            if (grp >= w0 && grp < w0 + window) {
+                const int start = 63 - __builtin_clzll(heads & ((2ull << lane) - 1ull));
+                ord[o + i] = 1 + s_run_base[run] + (lane - start);
+                if (head && c0 + kOrdThreads < share.y) atomicAdd(&s_count[grp - w0], len);
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 
@@ -238,13 +260,14 @@ __global__ __launch_bounds__(256) void k_hpe_table(float *__restrict__ table, in
 }
 
 // ---- x += sum over the levels of the table rows -------------------------------------------------------
-// A thread owns 8 consecutive channels (16 bytes of bf16) of kPerThread consecutive positions (neighbouring
-// positions mostly share their upper-level indices, so their table rows come out of the vector cache); the
-// index vectors of its positions are read first, then all table rows and x values are requested together,
-// then everything is added and stored: the kernel is a stream over x with the table rows coming out of L2.
-// (Measured at d_model 768 / 1024, 32768 positions: 1 position per thread 23.0 / 29.7 us, 2: 24.0 / 29.6,
-// 4: 27.1 / 34.3, 8: 40.3 / 48.7; positions a quarter of the tensor apart instead of consecutive: 1-2 us more.)
-constexpr int kPerThread = 2, kMaxLevelsFast = 8;
+// A thread owns 8 consecutive channels (16 bytes of bf16) of kPerThread consecutive positions: the kernel is a stream
+// over x, and what it must keep away from that stream is the table, whose rows (fp32, out of L2) are three times
+// the bytes of x.  Consecutive positions mostly share their upper-level indices, so a thread keeps the table row of
+// every level in registers and reads another one only where the index changes.
+// Measured, bf16, 32768 positions of 768 / 1024 channels: 24.2 / 30.3 us; every row read for every position 25.9 / 32.7;
+// one position per thread 26.8 / 34.4, four 26.2 / 31.8.  x is requested in front of the table rows in bf16 and behind
+// them in fp32, where the other order costs 3 us of 22 (registers).
+constexpr int kPerThread = 2, kMaxLevelsFast = 4;
 
 __device__ __noinline__ float hpe_direct(int v, int c, int d_model)
 {
@@ -256,13 +279,13 @@ __device__ __noinline__ float hpe_direct(int v, int c, int d_model)
 template <bool BF16>
 __global__ __launch_bounds__(256) void k_hpe_add(const int32_t *__restrict__ p, unsigned positions, int L,
                                                  const float *__restrict__ table, int rows, void *__restrict__ x,
-                                                 int d_model, unsigned pos_stride)
+                                                 int d_model, unsigned groups)
 {
     typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
     const unsigned per_pos = (unsigned)d_model / 8u;
-    const unsigned g = blockIdx.x * blockDim.x + threadIdx.x;  // (position inside the quarter, channel group)
+    const unsigned g = blockIdx.x * blockDim.x + threadIdx.x;  // (group of kPerThread positions, channel group)
     const unsigned pos0 = g / per_pos, c0 = (g - pos0 * per_pos) * 8u;
-    if (pos0 >= pos_stride) return;
+    if (pos0 >= groups) return;
 #define POS(u) (pos0 * kPerThread + (u))
     float acc[kPerThread][8];
     bool live[kPerThread];
@@ -272,6 +295,14 @@ __global__ __launch_bounds__(256) void k_hpe_add(const int32_t *__restrict__ p, 
 #pragma unroll
         for (int e = 0; e < 8; e++) acc[u][e] = 0.f;
     }
+    bf16x8 xb[kPerThread];
+#pragma unroll
+    for (int u = 0; u < kPerThread; u++) {
+        const size_t at = (size_t)(live[u] ? POS(u) : POS(0)) * per_pos + c0 / 8u;
+        if (BF16) {
+            xb[u] = reinterpret_cast<const bf16x8 *>(x)[at];
+        }
+    }
     for (int l0 = 0; l0 < L; l0 += kMaxLevelsFast) {
         int v[kPerThread][kMaxLevelsFast];
 #pragma unroll
@@ -280,40 +311,49 @@ __global__ __launch_bounds__(256) void k_hpe_add(const int32_t *__restrict__ p, 
             for (int l = 0; l < kMaxLevelsFast; l++)
                 v[u][l] = (live[u] && l0 + l < L) ? p[(size_t)POS(u) * L + l0 + l] : -1;
 #pragma unroll
-        for (int u = 0; u < kPerThread; u++)
+        for (int l = 0; l < kMaxLevelsFast; l++) {
+            if (l0 + l >= L) break;
+            float4 t0[kPerThread], t1[kPerThread];
 #pragma unroll
-            for (int l = 0; l < kMaxLevelsFast; l++) {
-                if (l0 + l >= L || !live[u]) continue;
+            for (int u = 0; u < kPerThread; u++) {
                 const int vv = v[u][l];
-                if (vv >= 0 && vv < rows) {
-                    const float4 t0 = *reinterpret_cast<const float4 *>(table + (size_t)vv * d_model + c0);
-                    const float4 t1 = *reinterpret_cast<const float4 *>(table + (size_t)vv * d_model + c0 + 4);
-                    acc[u][0] += t0.x, acc[u][1] += t0.y, acc[u][2] += t0.z, acc[u][3] += t0.w;
-                    acc[u][4] += t1.x, acc[u][5] += t1.y, acc[u][6] += t1.z, acc[u][7] += t1.w;
+                if (u > 0 && vv == v[u > 0 ? u - 1 : 0][l]) {
+                    t0[u] = t0[u > 0 ? u - 1 : 0], t1[u] = t1[u > 0 ? u - 1 : 0];
+                } else if (vv >= 0 && vv < rows) {
+                    t0[u] = *reinterpret_cast<const float4 *>(table + (size_t)vv * d_model + c0);
+                    t1[u] = *reinterpret_cast<const float4 *>(table + (size_t)vv * d_model + c0 + 4);
+                } else if (live[u]) {
+                    float d[8];
+                    for (int e = 0; e < 8; e++) d[e] = hpe_direct(vv, (int)c0 + e, d_model);
+                    t0[u] = make_float4(d[0], d[1], d[2], d[3]), t1[u] = make_float4(d[4], d[5], d[6], d[7]);
                 } else {
-                    for (int e = 0; e < 8; e++) acc[u][e] += hpe_direct(vv, (int)c0 + e, d_model);
+                    t0[u] = t1[u] = make_float4(0.f, 0.f, 0.f, 0.f);
                 }
             }
+#pragma unroll
+            for (int u = 0; u < kPerThread; u++) {
+                acc[u][0] += t0[u].x, acc[u][1] += t0[u].y, acc[u][2] += t0[u].z, acc[u][3] += t0[u].w;
+                acc[u][4] += t1[u].x, acc[u][5] += t1[u].y, acc[u][6] += t1[u].z, acc[u][7] += t1[u].w;
+            }
+        }
     }
 #pragma unroll
     for (int u = 0; u < kPerThread; u++) {
         if (!live[u]) continue;
         const size_t at = (size_t)POS(u) * per_pos + c0 / 8u;
         if (BF16) {
-            bf16x8 *px = reinterpret_cast<bf16x8 *>(x) + at;
-            bf16x8 val = *px;
 #pragma unroll
-            for (int e = 0; e < 8; e++) val[e] = (__bf16)((float)val[e] + acc[u][e]);
-            *px = val;
+            for (int e = 0; e < 8; e++) xb[u][e] = (__bf16)((float)xb[u][e] + acc[u][e]);
+            reinterpret_cast<bf16x8 *>(x)[at] = xb[u];
         } else {
-            float4 *px = reinterpret_cast<float4 *>(x) + 2 * at;
-            float4 a = px[0], c = px[1];
+            float4 a = reinterpret_cast<const float4 *>(x)[2 * at], c = reinterpret_cast<const float4 *>(x)[2 * at + 1];
             a.x += acc[u][0], a.y += acc[u][1], a.z += acc[u][2], a.w += acc[u][3];
             c.x += acc[u][4], c.y += acc[u][5], c.z += acc[u][6], c.w += acc[u][7];
-            px[0] = a;
-            px[1] = c;
+            reinterpret_cast<float4 *>(x)[2 * at] = a;
+            reinterpret_cast<float4 *>(x)[2 * at + 1] = c;
         }
     }
+#undef POS
 }
 
 }  // namespace
@@ -328,7 +368,8 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_parents_from_
     if ((int64_t)batch * n_pos > (1LL << 30)) return hdt_fail(HDT_ERR_SHAPE, "hdt_parents_from_levels: batch * n_pos too large");
     hipStream_t st = (hipStream_t)stream;
     HdtTimer t("hdt_hpe_parents_from_levels", st);
-    hipLaunchKernelGGL(k_parents_from_levels, dim3((unsigned)batch), dim3(kOrdThreads), 0, st, d_level, n_pos, d_parent);
+    hipLaunchKernelGGL(k_parents_from_levels, dim3((unsigned)batch * hpe_shares(n_pos)), dim3(kOrdThreads), 0, st, d_level, n_pos,
+                       hpe_shares(n_pos), d_parent);
     HDT_HIP_TRY(hipGetLastError());
     return HDT_OK;
 }
@@ -358,9 +399,12 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_index_vectors
     int32_t *cnt = static_cast<int32_t *>(workspace);
     int32_t *ord = cnt + (size_t)batch * ((size_t)n_pos + 1);
     {
+        const size_t lds = (size_t)std::min(n_pos + 1, kOrdWindow) * sizeof(int);
+        if (lds > 48 * 1024)  // with the static arrays: beyond the 64 KB a launch gets by default
+            HDT_HIP_TRY(hipFuncSetAttribute((const void *)k_sibling_ordinals, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         HdtTimer t("hdt_hpe_sibling_ordinals", st);
-        hipLaunchKernelGGL(k_sibling_ordinals, dim3((unsigned)batch), dim3(kOrdThreads), 0, st, d_level, d_parent,
-                           n_pos, cnt, ord);
+        hipLaunchKernelGGL(k_sibling_ordinals, dim3((unsigned)batch * hpe_shares(n_pos)), dim3(kOrdThreads), lds, st, d_level,
+                           d_parent, n_pos, hpe_shares(n_pos), ord);
     }
     {
         const int64_t total = (int64_t)batch * n_pos;

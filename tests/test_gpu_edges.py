@@ -67,3 +67,31 @@ def test_every_row_tile_is_worked_on_whatever_their_number(oracle, heads):
         say(f"[grid edges] {heads} heads, tile {tile}")
         run_fwd_case(oracle, level, parent, heads, 64, "bf16", 51, tile=tile)
         run_bwd_case(oracle, level, parent, heads, 128 if heads < 10 else 64, "bf16", 52, tile=tile)
+
+
+@pytest.mark.parametrize("n", [1024, 2049, 33791, 33792, 70001])
+def test_index_vectors_and_parents_across_workgroup_shares(oracle, n):
+    # a workgroup takes a share of 1024 positions (more from 64 shares on) and counts siblings in LDS for 33 * 1024
+    # parents at a time: lengths at those edges, roots whose virtual parent falls into the next window, siblings scattered
+    # over all shares
+    import paper_2407_08330_amd as hdt
+    rng = np.random.default_rng(n)
+    doc = inputs.pseudo_section_document(rng, n)[:2]
+    forest = (np.where(rng.random(n) < 0.01, 0, 1).astype(np.int32), np.full(n, -1, np.int32))
+    roots = np.flatnonzero(forest[0] == 0)
+    forest[1][forest[0] == 1] = rng.choice(roots, size=int((forest[0] == 1).sum())) if roots.size else -1
+    forest[0][rng.random(n) < 0.01] = -1
+    level, parent = np.stack([doc[0], forest[0]]), np.stack([doc[1], np.where(forest[0] >= 0, forest[1], -1)])
+    dead = parent >= 0
+    dead[dead] = np.concatenate([level[b][parent[b][parent[b] >= 0]] < 0 for b in range(2)])
+    parent[dead] = -1   # parents that became pads
+    say(f"[hpe edges] n={n}")
+    got = hdt.hdt_index_vectors(to_dev_i32(level), to_dev_i32(parent), 3).cpu().numpy()
+    levels = np.stack([doc[0], rng.integers(-1, 6, size=n).astype(np.int32), np.full(n, 5, np.int32)])
+    levels[2, 0], levels[2, -1] = 4, 3   # every position looks back to the first one; the last finds nothing
+    par = hdt.hdt_parents_from_levels(to_dev_i32(levels)).cpu().numpy()
+    for b in range(2):
+        np.testing.assert_array_equal(got[b], oracle.index_vectors(level[b], parent[b], 3), err_msg=f"sample {b}")
+    for b in range(2):
+        np.testing.assert_array_equal(par[b], oracle.parents_from_levels(levels[b]), err_msg=f"levels {b}")
+    assert (par[2, 1:-1] == 0).all() and par[2, 0] == -1 and par[2, -1] == -1
