@@ -62,15 +62,18 @@ constexpr int kChunk = kThreads;              // positions per workgroup of the 
 // atomic gives a workgroup its slice and tells the last one that it is the last.
 enum { CNT_ERR = 0, CNT_CAND = 2 };
 
-// reserves `count` entries; returns the first one; *final_total >= 0 iff this was the last workgroup
-__device__ __forceinline__ int reserve_entries(int32_t *counters, int count, int *final_total)
+// reserves `count` entries; what comes back is looked at with reserved_first and is_last (apart, so that a caller can do
+// other work while the atomic is in flight)
+__device__ __forceinline__ unsigned long long reserve_entries(int32_t *counters, int count)
 {
-    unsigned long long *word = reinterpret_cast<unsigned long long *>(counters + CNT_CAND);
-    const unsigned long long old = atomicAdd(word, (1ull << 40) + (unsigned long long)count);
-    const int base = (int)(old & 0xffffffffffull);
-    *final_total = (int)(old >> 40) == (int)gridDim.x - 1 ? base + count : -1;
-    return base;
+    // (a lane's own address, as far as the compiler can tell: for a uniform one it adds the lanes up first and hands the
+    // result round with readfirstlane, which waits for it on the spot)
+    int word = CNT_CAND;
+    asm volatile("" : "+v"(word));
+    return atomicAdd(reinterpret_cast<unsigned long long *>(counters + word), (1ull << 40) + (unsigned long long)count);
 }
+__device__ __forceinline__ int reserved_first(unsigned long long old) { return (int)(old & 0xffffffffffull); }
+__device__ __forceinline__ bool is_last(unsigned long long old) { return (int)(old >> 40) == (int)gridDim.x - 1; }
 
 // What the candidate kernel reports to the host through pinned host memory: one 64-bit word
 // [63:40] ticket of the build, [39] hierarchy error, [31:0] list entries needed.
@@ -85,6 +88,20 @@ __device__ __forceinline__ int wave_sum(int x)
 {
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d);
+    return x;
+}
+
+// inclusive sum over the lanes of a wave
+__device__ __forceinline__ int wave_scan(int x)
+{
+#define SCAN_STEP(ctrl, rows) x += __builtin_amdgcn_update_dpp(0, x, ctrl, rows, 0xf, false)
+    SCAN_STEP(0x111, 0xf);  // row_shr:1, 2, 4, 8: inside the rows of 16 lanes
+    SCAN_STEP(0x112, 0xf);
+    SCAN_STEP(0x114, 0xf);
+    SCAN_STEP(0x118, 0xf);
+    SCAN_STEP(0x142, 0xa);  // row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3
+    SCAN_STEP(0x143, 0xc);
+#undef SCAN_STEP
     return x;
 }
 
@@ -342,11 +359,11 @@ __global__ __launch_bounds__(kThreads) void k_candidates(CandArgs a)
         // this workgroup's slice of the list arrays; the last workgroup to get here knows the final count
         // and tells the host, which is waiting for exactly this word, while the lists and the bitmaps are
         // still being written (no device-scope fence: it would write back the whole L2 of this XCD)
-        int final_total;
-        s_base = reserve_entries(a.counters, total, &final_total);
-        if (final_total >= 0) {
+        const unsigned long long old = reserve_entries(a.counters, total);
+        s_base = reserved_first(old);
+        if (is_last(old)) {
             const int err = __hip_atomic_load(&a.counters[CNT_ERR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(a.report, report_word(a.ticket, err, (uint32_t)final_total), __ATOMIC_RELEASE,
+            __hip_atomic_store(a.report, report_word(a.ticket, err, (uint32_t)(reserved_first(old) + total)), __ATOMIC_RELEASE,
                                __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
@@ -482,16 +499,24 @@ __device__ __forceinline__ EntryPart entry_columns(int64_t c, int k0, int lane, 
     const int kj = slot ? ek[k] : -1, kr = slot ? ep[k] : -1;  // -1: no key
     const int v_up = (edges & HDT_EDGE_UP) ? kj : -1, v_sib = (edges & HDT_EDGE_SIBLING) ? kr : -1;
     uint32_t col[4] = {0u, 0u, 0u, 0u};
+    // (the table in registers, an entry per lane: out of LDS every step of the loop would wait for its two reads)
+    auto look_up = [&](int v, uint32_t r0, uint32_t r1, uint32_t r2, uint32_t r3) {
+        const bool hit = v_up == v || v_sib == v;  // v >= 0
+        if (__ballot(hit) == 0ull) return;
+        col[0] |= hit ? r0 : 0u;
+        col[1] |= hit ? r1 : 0u;
+        col[2] |= hit ? r2 : 0u;
+        col[3] |= hit ? r3 : 0u;
+    };
+    const int tv = lane < tab.n ? tab.v[lane] : -1;
+    const uint4 tr = lane < tab.n ? tab.rows[lane] : make_uint4(0u, 0u, 0u, 0u);
+    for (int t = 0; t < min(tab.n, 64); t++)
+        look_up(__builtin_amdgcn_readlane(tv, t), __builtin_amdgcn_readlane(tr.x, t), __builtin_amdgcn_readlane(tr.y, t),
+                __builtin_amdgcn_readlane(tr.z, t), __builtin_amdgcn_readlane(tr.w, t));
 #pragma unroll 1
-    for (int t = 0; t < tab.n; t++) {
-        const int v = tab.v[t];  // >= 0
-        const bool hit = v_up == v || v_sib == v;
-        if (__ballot(hit) == 0ull) continue;
+    for (int t = 64; t < tab.n; t++) {
         const uint4 r = tab.rows[t];
-        col[0] |= hit ? r.x : 0u;
-        col[1] |= hit ? r.y : 0u;
-        col[2] |= hit ? r.z : 0u;
-        col[3] |= hit ? r.w : 0u;
+        look_up(tab.v[t], r.x, r.y, r.z, r.w);
     }
     // the key itself; the key's parent (the key is that row's child).  A key or a key's parent inside the
     // tile's range is a real position, hence a valid row.
@@ -503,7 +528,7 @@ __device__ __forceinline__ EntryPart entry_columns(int64_t c, int k0, int lane, 
         if (has_down && (r_down >> 5) == w) col[w] |= 1u << (r_down & 31);
     }
     EntryPart part;
-    part.cnt = wave_sum(__popc(col[0]) + __popc(col[1]) + __popc(col[2]) + __popc(col[3]));
+    part.cnt = __builtin_amdgcn_readlane(wave_scan(__popc(col[0]) + __popc(col[1]) + __popc(col[2]) + __popc(col[3])), 63);
     part.any = part.all = 0;
     const int cblk = k >> 5, cc = k & 31, e = ((cc >> 3) << 2) | (cc & 3), hf = (cc >> 2) & 1;
     uint32_t *rm32 = reinterpret_cast<uint32_t *>(bits_rm + (size_t)c * nsub * 16);
@@ -553,144 +578,193 @@ __device__ __forceinline__ void raise_error(int32_t *counters)
 constexpr int kBatch = 8;
 constexpr int kLdsKeys = 2048;  // key lists up to this length stay in LDS between the packing and the bitmaps
 
-// ---- key lists: ONE kernel from level/parent to the finished entries, a workgroup per query tile ----
-// Key j is needed by the tile iff it is one of the tile's rows, the parent of one (bitmap over the
-// positions, in LDS), a child of one (its parent is a row of the tile) or a sibling of one (its parent
-// is the parent of a row) - each kind only if its edges are enabled.  All four tests are exact, for any
-// forest.  The workgroup scans level[] and
-// parent[] of the whole sample once (two coalesced streams, nothing waits on a chain of dependent
-// loads), keeps the needed positions as a bitmap, and packs them in KEY ORDER - by level, ties in
-// document order, i.e. the order of kperm restricted to the needed keys - with a counting sort over the
-// needed keys only: every wave counts the levels in its contiguous share, the counts are turned into
-// first indices (level major, then wave), and after the workgroup has reserved its entries each wave
-// hands out indices in document order.  The global key order is therefore not an input of this kernel.
-// The workgroup then evaluates its own entries by key columns (entry_columns: lane masks, pair counts,
-// summaries), one wave per 64 key slots.  It also validates its own rows.
-// A list of up to kLdsKeys keys is packed into LDS while the reservation (a returning device-scope atomic,
-// about 2 us) is in flight, copied to global memory from there, and evaluated from there; a longer list is
-// packed straight into global memory once the reservation is back and read again from there.
-// The workgroup has 1024 threads.  Tiles of up to 64 rows go to key_lists_pair below, two to a workgroup; where its
-// bitmaps do not fit the LDS (documents beyond 64 K positions) they come here with 512 threads: they make twice
-// the workgroups, and two of 512 threads share a compute unit where one of 1024 fills it (measured at 8192
-// positions x 4 samples, 64-row tiles: 24 us against 28).
-template <int kListThreads>
+// ---- key lists: ONE kernel from level/parent to the finished entries -------------------------------------
+// A workgroup makes the lists of T neighbouring query tiles (T = 2: tiles of up to 64 rows, which share one scan of
+// the sample's ids; T = 1: tiles of up to 128 rows, and documents whose bitmaps do not fit the LDS twice).
+// Key j is needed by a tile iff it is one of the tile's rows, the parent of one, a child of one (its parent is a row of the
+// tile) or a sibling of one (its parent is the parent of a row) - each kind only if its edges are enabled.  Two
+// bitmaps over the positions, in LDS, say so exactly for any forest: `keys`, the positions that are needed by themselves
+// (rows, and parents of rows), and `pars`, those whose children are (the same two kinds).  The workgroup scans level[] and
+// parent[] of the whole sample once (two coalesced streams, nothing waits on a chain of dependent loads): for 64
+// positions the first kind is a word of `keys` as it stands, the second one look-up per lane; the result replaces that
+// word.  The needed keys are then packed in KEY ORDER - by level, ties in document order, i.e. the order of kperm
+// restricted to the needed keys - in two steps: into LDS in document order (a prefix sum over the bitmap), and from there
+// by a counting sort over the levels of the needed keys alone, 64 of them per wave.  The global key order is therefore
+// not an input of this kernel.
+// What bounds it is the chain of these phases in one workgroup (a compute unit has one or two) and, in the scan, the
+// instructions per position.  The groups of 64 positions go round the waves: the keys a tile needs lie close together, and
+// with a contiguous share of the document per wave one or two waves had all of the packing to do.  Event-bracketed, with
+// level counts taken in the scan, bitmap tests of every kind per position and contiguous shares before: 8192 positions x 4
+// samples, 64 x 32 tiles: 19.6 -> 13.5 us; 128 x 64: 17.6 -> 12.5; 32768 positions, 64 x 32: 43.2 -> 21.0.
+// Then the workgroup evaluates its own entries by key columns (entry_columns: lane masks, pair counts, summaries), one
+// wave per 64 key slots, the entries of both tiles in one sequence.  It also validates its own rows.
+// The lists are in LDS by the time the reservation of their entries (a returning device-scope atomic, about 2 us) is
+// back.  Lists beyond kLdsKeys keys in all are packed straight into global memory instead, with a contiguous share of
+// the document per wave, and read again from there.
+// 1024 threads; 512 for T = 1 with tiles of up to 64 rows, which make twice the workgroups (two of 512 threads share a
+// compute unit where one of 1024 fills it).
+__host__ __device__ inline int list_words(int n) { return (((n + 31) >> 5) + 4) & ~3; }  // of `pars`, per tile: a zero word behind
+__host__ inline size_t list_lds(int n, int tiles)
+{
+    return (size_t)tiles * ((size_t)list_words(n) + 2 * (size_t)((n + 63) >> 6)) * sizeof(uint32_t);
+}
+
+template <int kListThreads, int T>
 __global__ __launch_bounds__(kListThreads) void k_key_lists(KeyListArgs a)
 {
-    constexpr int kListWaves = kListThreads / 64;
-    extern __shared__ uint32_t s_dyn[];  // [ceil(n/32)] parents of the tile's rows, then [2 * groups] needed positions
-    __shared__ int2 s_row[128];          // (position, parent) of the tile's rows; position -2: no such row
-    __shared__ int s_lcnt[kListWaves][kBuckets];  // needed keys per (wave, level), then their first index
-    __shared__ int s_cnt[2][kListWaves];  // partial results of an entry's two waves (tile_n > 64), by parity of the round
-    __shared__ uint32_t s_any[2][kListWaves], s_all[2][kListWaves];
-    __shared__ int s_base, s_total, s_wtotal[kListWaves];
+    constexpr int W = kListThreads / 64, RT = 128 / T;
+    constexpr int kItemGroups = kLdsKeys / 64 + T, kRounds = (kItemGroups + W - 1) / W;  // groups of 64 packed keys
+    static_assert(W <= kItemGroups, "the level counts of the waves share the array of the item groups");
+    // pars: word w of tile h at [w * T + h]; after the scan its place holds the number of needed keys in front of every
+    // group of 64 positions (16 bits, group g of tile h at [g * T + h]).  keys: the same order, so that the words of all
+    // tiles for 64 positions are 8 T consecutive bytes.
+    extern __shared__ __attribute__((aligned(16))) uint32_t s_dyn[];
+    __shared__ int2 s_row[128];          // (position, parent) of the rows: tile h at [h * RT, h * RT + RT); position -2: no such row
+    __shared__ int s_lcnt[kItemGroups][kBuckets];  // keys per (group of 64 packed keys, level)
+    __shared__ int s_cnt[2][W];          // partial results of an entry's two waves (tile_n > 64), by parity of the round
+    __shared__ uint32_t s_any[2][W], s_all[2][W];
+    __shared__ int s_base, s_wtotal[T][W], s_total[T];
     __shared__ __attribute__((aligned(16))) int s_keys[kLdsKeys], s_kpar[kLdsKeys];
-    __shared__ int s_tab_v[128], s_ntab;  // distinct parents of the tile's rows, and the rows of each
-    __shared__ int s_first;               // first real row of the tile (a position), INT_MAX if it has none
+    __shared__ int s_tab_v[128], s_ntab[T];  // distinct parents of a tile's rows, and the rows of each
     __shared__ uint4 s_tab_rows[128];
-    const int b = blockIdx.x / a.tr, I = blockIdx.x - b * a.tr, n = a.n;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    __shared__ int s_first[T];               // first real row of a tile (a position), INT_MAX if it has none
+    const int per_sample = (a.tr + T - 1) / T;
+    const int b = blockIdx.x / per_sample, I0 = (blockIdx.x - b * per_sample) * T, n = a.n;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int bm = a.bm, bn = a.bn;
     const int32_t *level = a.level + (size_t)b * n, *parent = a.parent + (size_t)b * n;
-    const int pw = (n + 31) >> 5, ng = (n + 63) >> 6;
-    uint32_t *s_par = s_dyn, *s_need = s_dyn + pw;
-    // kBatch groups of 64 positions at a time: all their loads are issued before the first is used, and those
-    // of the first batch before anything else
-    const int gpw = (ng + kListWaves - 1) / kListWaves;
-    const int g0 = min(wave * gpw, ng), g1 = min(g0 + gpw, ng);
+    const int pw = list_words(n), ng = (n + 63) >> 6;
+    uint32_t *s_pars = s_dyn, *s_need = s_dyn + T * pw;
+    uint16_t *s_before = reinterpret_cast<uint16_t *>(s_dyn);
+    struct Words { uint32_t w[2 * T]; };  // of 64 positions: [half * T + h]
+    auto words = [&](int g) { return reinterpret_cast<Words *>(s_need) + g; };
+    int row0[T];
+#pragma unroll
+    for (int h = 0; h < T; h++) row0[h] = (I0 + h) * bm;
+    const bool e_up = a.edges & HDT_EDGE_UP, e_sib = a.edges & HDT_EDGE_SIBLING, e_down = a.edges & HDT_EDGE_DOWN;
+    // kBatch groups of 64 positions per wave at a time: all their loads are issued before the first is used, and those
+    // of the next batch before this one is looked at
+    const int rounds = (ng + W - 1) / W;  // group u * W + wave is this wave's u-th
     int klv[kBatch], kp[kBatch];
-    auto load_batch = [&](int gb) {
+    auto load_batch = [&](int u0, int (&l)[kBatch], int (&p)[kBatch]) {
 #pragma unroll
         for (int u = 0; u < kBatch; u++) {
-            const int j = (gb + u) * 64 + lane;
-            const bool ok = gb + u < g1 && j < n;
-            klv[u] = ok ? level[j] : -1;
-            kp[u] = ok ? parent[j] : -1;
+            const int j = ((u0 + u) * W + wave) * 64 + lane;
+            const bool ok = j < n;
+            l[u] = ok ? level[j] : -1;
+            p[u] = ok ? parent[j] : -1;
         }
     };
-    load_batch(g0);
-    for (int w = tid; w < pw; w += kListThreads) s_par[w] = 0;
-    if (tid == 0) s_first = INT_MAX;
+    // the rows' ids first: they are looked at first
+    int my_level = -1, my_parent = -1;
+    const int my_tile = tid / RT, my_row = (I0 + my_tile) * bm + tid % RT;  // of the first 128 threads
+    const bool have_row = tid < 128 && tid % RT < bm && I0 + my_tile < a.tr && my_row < n;
+    if (have_row) {
+        my_level = level[my_row];
+        my_parent = parent[my_row];
+    }
+    load_batch(0, klv, kp);
+    for (int w = tid; w < T * (pw + 2 * ng); w += kListThreads) s_dyn[w] = 0u;
+    if (tid < T) s_first[tid] = INT_MAX;
     lds_barrier();
-    const int row0 = I * bm;
     bool check_parent = false;
-    int my_parent = 0;
     if (tid < 128) {
-        int2 me = make_int2(-2, -2);
-        if (tid < bm && row0 + tid < n) {
-            const int i = row0 + tid;
-            const int l = level[i], p = parent[i];
-            a.level_copy[(size_t)b * n + i] = l;
-            a.parent_copy[(size_t)b * n + i] = p;
-            if (l < -1 || l >= HDT_MAX_LEVELS || p < -1 || p >= n || p == i || (l < 0 && p != -1))
-                raise_error(a.counters);
-            else if (l >= 0) {
-                me = make_int2(i, p);
-                atomicMin(&s_first, i);
-                if (p >= 0) {
-                    atomicOr(&s_par[p >> 5], 1u << (p & 31));
-                    check_parent = true;
-                    my_parent = p;
-                }
-            }
+        const int p = my_parent;
+        if (have_row && (my_level < -1 || my_level >= HDT_MAX_LEVELS || p < -1 || p >= n || p == my_row || (my_level < 0 && p != -1))) {
+            raise_error(a.counters);
+            my_level = -1;
         }
-        s_row[tid] = me;
+        const bool real = have_row && my_level >= 0;
+        s_row[tid] = real ? make_int2(my_row, p) : make_int2(-2, -2);
+        // this wave's rows: two words of the bitmaps
+        const unsigned long long rows = __ballot(real);
+        if (lane < 2 && rows) {
+            const uint32_t word = (uint32_t)(rows >> (32 * lane));
+            const int at = (((my_row - lane) >> 5) + lane) * T + my_tile;
+            if (word) atomicOr(&s_need[at], word);
+            if (word && e_down) atomicOr(&s_pars[at], word);
+            if (lane == 0) atomicMin(&s_first[my_tile], my_row + __ffsll((long long)rows) - 1);
+        }
+        if (real && p >= 0) {
+            if (e_sib) atomicOr(&s_pars[(p >> 5) * T + my_tile], 1u << (p & 31));
+            if (e_up) atomicOr(&s_need[(p >> 5) * T + my_tile], 1u << (p & 31));
+            check_parent = true;
+        }
     }
     const int parent_level = check_parent ? level[my_parent] : 0;  // looked at once the scan is under way
     lds_barrier();
-    // A key is a real position, and so is the parent of one (or the build fails on the hierarchy): for both, being
-    // a row of the tile is a matter of the range alone.  The two bitmap lookups are issued for every position,
-    // needed or not, so that the loads of a whole batch are in flight together.
-    auto in_tile = [&](int x) { return (unsigned)(x - row0) < (unsigned)bm; };
-    const bool e_up = a.edges & HDT_EDGE_UP, e_sib = a.edges & HDT_EDGE_SIBLING, e_down = a.edges & HDT_EDGE_DOWN;
-    int lcount = 0;  // lane k: needed keys of level k in this wave's share
-    int wtotal = 0;  // needed keys in this wave's share
-    for (int gb = g0; gb < g1; gb += kBatch) {
-        if (gb != g0) load_batch(gb);
-        bool need[kBatch];
+    const bool one_batch = rounds <= kBatch;
+    Words need{};  // lane u: the needed positions of the last batch's group u
+    int wtotal[T];  // needed keys in this lane's groups
 #pragma unroll
-        for (int u = 0; u < kBatch; u++) {  // groups past the share were loaded as pads
-            const int j = (gb + u) * 64 + lane, pj = kp[u];
-            const bool real = klv[u] >= 0 && j < n, has_parent = pj >= 0 && pj < n;
-            const int jc = real ? j : 0, pc = has_parent ? pj : 0;
-            const uint32_t wj = s_par[jc >> 5], wp = s_par[pc >> 5];
-            const bool by_self = in_tile(j) | (e_up & (bool)((wj >> (jc & 31)) & 1u));
-            const bool by_parent = has_parent & ((e_down & in_tile(pj)) | (e_sib & (bool)((wp >> (pc & 31)) & 1u)));
-            need[u] = real & (by_self | by_parent);
-        }
+    for (int h = 0; h < T; h++) wtotal[h] = 0;
+    for (int u0 = 0; u0 < rounds; u0 += kBatch) {
+        int nlv[kBatch], np[kBatch];
+        const bool more = u0 + kBatch < rounds;
+        if (more) load_batch(u0 + kBatch, nlv, np);
+        const int mine = (u0 + lane) * W + wave;  // the group lane u < kBatch puts together
+        const bool have = lane < kBatch && mine < ng;
+        Words par_words[kBatch];  // of the position's parent (T words); no parent, or one that is none: the zero word
 #pragma unroll
         for (int u = 0; u < kBatch; u++) {
-            if (gb + u >= g1) break;
-            const unsigned long long m = __ballot(need[u]);
-            if (lane == 0) {
-                s_need[2 * (gb + u)] = (uint32_t)m;
-                s_need[2 * (gb + u) + 1] = (uint32_t)(m >> 32);
+            const unsigned pc = min((unsigned)kp[u], (unsigned)pw * 32u - 1u);
+#pragma unroll
+            for (int h = 0; h < T; h++) par_words[u].w[h] = s_pars[(pc >> 5) * T + h];
+        }
+        if (have) need = *words(mine);
+#pragma unroll
+        for (int u = 0; u < kBatch; u++) {
+#pragma unroll
+            for (int h = 0; h < T; h++) {
+                const unsigned long long by_parent = __ballot((par_words[u].w[h] >> (kp[u] & 31)) & 1u);
+                if (lane == u) {
+                    need.w[h] |= (uint32_t)by_parent;
+                    need.w[T + h] |= (uint32_t)(by_parent >> 32);
+                }
             }
-            wtotal += __popcll(m);
-            if (m != 0ull) lcount += wave_bucket_count(need[u], a.no_sort ? 0 : bucket_of(klv[u]));
+        }
+        if (have) {
+            *words(mine) = need;
+#pragma unroll
+            for (int h = 0; h < T; h++) wtotal[h] += __popc(need.w[h]) + __popc(need.w[T + h]);
+        }
+        if (more) {
+#pragma unroll
+            for (int u = 0; u < kBatch; u++) klv[u] = nlv[u], kp[u] = np[u];
         }
     }
-    const bool one_batch = g1 - g0 <= kBatch;  // the registers still hold the wave's whole share
-    if (lane < kBuckets) s_lcnt[wave][lane] = lcount;
-    if (lane == 0) s_wtotal[wave] = wtotal;
+#pragma unroll
+    for (int h = 0; h < T; h++) {
+        const int t = __builtin_amdgcn_readlane(wave_scan(wtotal[h]), 63);
+        if (lane == 0) s_wtotal[h][wave] = t;
+    }
     if (check_parent && parent_level < 0) raise_error(a.counters);  // a parent must be a real position
+    // (all loads have landed by now; said here, or the compiler waits for them, and with them for the reservation, where
+    // the registers are used)
+#pragma unroll
+    for (int u = 0; u < kBatch; u++) asm volatile("" : "+v"(klv[u]), "+v"(kp[u]));
     lds_barrier();
-    // This tile's slice of the per-entry arrays: reserved by wave 1 as soon as the length of the list is known,
-    // used once the list has been packed.  The last workgroup to reserve knows the final count and tells the
+    // These tiles' slice of the per-entry arrays: reserved by wave 1 as soon as the length of the lists is known,
+    // used once the lists have been packed.  The last workgroup to reserve knows the final count and tells the
     // host, which is waiting for exactly this word, while the lists and the bitmaps are still being written (no
     // device-scope fence: it would write back the whole L2 of this XCD).
-    int reserved = 0, final_total = -1;
+    unsigned long long reserved;  // (of thread 64; no value elsewhere, so that nothing waits for it before it is looked at)
     if (wave == 1) {
-        const int total = wave_sum(lane < kListWaves ? s_wtotal[lane] : 0);
-        if (lane == 0) {
-            s_total = total;
-            reserved = reserve_entries(a.counters, (total + bn - 1) / bn, &final_total);
+        int entries = 0;
+#pragma unroll
+        for (int h = 0; h < T; h++) {
+            const int t = __builtin_amdgcn_readlane(wave_scan(lane < W ? s_wtotal[h][lane] : 0), 63);
+            entries += (t + bn - 1) / bn;
+            if (lane == 0) s_total[h] = t;
         }
+        if (lane == 0) reserved = reserve_entries(a.counters, entries);
     }
-    if (wave == 2) {  // meanwhile: the table of the rows' parents (see entry_columns)
-        const int2 ra = s_row[lane], rb = s_row[64 + lane];
+    if (wave >= 2 && wave < 2 + T) {  // the table of the rows' parents (see entry_columns)
+        const int h = wave - 2;
+        const int2 ra = s_row[h * RT + lane], rb = T == 1 ? s_row[64 + lane] : make_int2(-2, -2);
         const int pa = ra.x >= 0 ? ra.y : -1, pb = rb.x >= 0 ? rb.y : -1;
         unsigned long long rem_a = __ballot(pa >= 0), rem_b = __ballot(pb >= 0);
-        int nt = 0;
+        int nt = h * RT;
         while (rem_a | rem_b) {
             const int v = rem_a ? __builtin_amdgcn_readlane(pa, __ffsll((long long)rem_a) - 1)
                                 : __builtin_amdgcn_readlane(pb, __ffsll((long long)rem_b) - 1);
@@ -703,470 +777,247 @@ __global__ __launch_bounds__(kListThreads) void k_key_lists(KeyListArgs a)
             rem_b &= ~mb;
             nt++;
         }
-        if (lane == 0) s_ntab = nt;
+        if (lane == 0) s_ntab[h] = nt - h * RT;
     }
-    if (wave == 0) {  // first index of every (level, wave): level major, then wave
-        int t = 0;
-        if (lane < kBuckets) {
-#pragma unroll
-            for (int w = 0; w < kListWaves; w++) t += s_lcnt[w][lane];
-        }
-        int incl = t;  // inclusive scan of the level totals over lanes
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int y = __shfl_up(incl, d);
-            if (lane >= d) incl += y;
-        }
-        int run = incl - t;
-        if (lane < kBuckets) {
-#pragma unroll
-            for (int w = 0; w < kListWaves; w++) {
-                const int c = s_lcnt[w][lane];
-                s_lcnt[w][lane] = run;
-                run += c;
-            }
+    if (wave >= 4 && wave < 4 + T) {  // the needed keys of a tile in front of every group of 64 positions
+        const int h = wave - 4;
+        int first = 0;
+        for (int g0 = 0; g0 < ng; g0 += 64) {
+            const int g = g0 + lane;
+            const int c = g < ng ? __popc(words(g)->w[h]) + __popc(words(g)->w[T + h]) : 0, incl = wave_scan(c);
+            // (lists of more than kLdsKeys keys do not use these: that the counts wrap does not matter)
+            if (g < ng) s_before[g * T + h] = (uint16_t)(first + incl - c);
+            first += __builtin_amdgcn_readlane(incl, 63);
         }
     }
     lds_barrier();
-    const int total = s_total, n_ent = (total + bn - 1) / bn;
-    const bool in_lds = n_ent * bn <= kLdsKeys;
-    // Slots behind the last key name no key: they hold ~f, f = the tile's first real row (a list with a key has
-    // one), which is the row the attention kernels gather for such a slot.
-    const int no_key = ~s_first;
-    // hands out the indices of this wave's needed keys, in document order inside every level
-    int mybase = lane < kBuckets ? s_lcnt[wave][lane] : 0;  // lane k: next index of level k in this wave
-    auto pack = [&](bool to_lds, int32_t *keys, int32_t *kpars, int key_fit) {
-        for (int gb = g0; gb < g1; gb += kBatch) {
-            if (!one_batch) load_batch(gb);
+    int total[T], n_ent[T], koff[T], n_all = 0;  // lengths of the lists, and where they begin in s_keys
 #pragma unroll
-            for (int u = 0; u < kBatch; u++) {
-                if (gb + u >= g1) break;
-                const int g = gb + u;
-                const unsigned long long m = (unsigned long long)s_need[2 * g] | ((unsigned long long)s_need[2 * g + 1] << 32);
-                if (m == 0ull) continue;
-                const bool need = (m >> lane) & 1ull;
-                const int bucket = a.no_sort ? 0 : bucket_of(klv[u]);
-                int t = 0;
-                unsigned long long remaining = m;
-                while (remaining) {
-                    const int leader = __ffsll((long long)remaining) - 1;
-                    const int bk = __builtin_amdgcn_readlane(bucket, leader);
-                    const bool is_bk = need && bucket == bk;
-                    const unsigned long long mm = __ballot(is_bk);
-                    const int first = __builtin_amdgcn_readlane(mybase, bk);
-                    if (is_bk) t = first + __popcll(mm & lanemask_lt());
-                    if (lane == bk) mybase += __popcll(mm);
-                    remaining &= ~mm;
-                }
-                if (need) {
-                    if (to_lds) {
-                        s_keys[t] = g * 64 + lane;
-                        s_kpar[t] = kp[u];
-                    } else if (t < key_fit) {
-                        keys[t] = g * 64 + lane;
-                        kpars[t] = kp[u];
+    for (int h = 0; h < T; h++) {
+        total[h] = __builtin_amdgcn_readfirstlane(s_total[h]);
+        n_ent[h] = (total[h] + bn - 1) / bn;
+        koff[h] = n_all * bn;
+        n_all += n_ent[h];
+    }
+    const bool in_lds = n_all * bn <= kLdsKeys;
+    auto bucket = [&](int l) { return a.no_sort ? 0 : bucket_of(l); };
+    if (in_lds) {  // while the reservation is in flight
+        // document order: key and level in one word (positions take 19 bits), the parents beside it
+        auto put = [&](uint32_t lo, uint32_t hi, int first, int g, int l, int p) {
+            const unsigned long long m = (unsigned long long)lo | ((unsigned long long)hi << 32);
+            if ((m >> lane) & 1ull) {
+                const int t = first + __popcll(m & lanemask_lt());
+                s_keys[t] = (bucket(l) << 24) | (g * 64 + lane);
+                s_kpar[t] = p;
+            }
+        };
+        if (one_batch) {
+            const int mine = min(lane * W + wave, ng - 1);
+#pragma unroll
+            for (int h = 0; h < T; h++) {
+                const int first = (h ? total[0] : 0) + s_before[mine * T + h];
+                const unsigned long long some = __ballot(lane < kBatch && (need.w[h] | need.w[T + h]) != 0u);
+#pragma unroll
+                for (int u = 0; u < kBatch; u++)
+                    if ((some >> u) & 1ull)
+                        put(__builtin_amdgcn_readlane(need.w[h], u), __builtin_amdgcn_readlane(need.w[T + h], u),
+                            __builtin_amdgcn_readlane(first, u), u * W + wave, klv[u], kp[u]);
+            }
+        } else {
+            for (int u0 = 0; u0 < rounds; u0 += 64) {  // lane l looks at this wave's group u0 + l
+                const int mine = (u0 + lane) * W + wave;
+#pragma unroll
+                for (int h = 0; h < T; h++) {
+                    const bool have = mine < ng;
+                    const uint32_t lo = have ? words(mine)->w[h] : 0u, hi = have ? words(mine)->w[T + h] : 0u;
+                    const int first = (h ? total[0] : 0) + (have ? s_before[mine * T + h] : 0);
+                    unsigned long long todo = __ballot((lo | hi) != 0u);
+                    while (todo) {
+                        const int x = __ffsll((long long)todo) - 1, g = (u0 + x) * W + wave, j = min(g * 64 + lane, n - 1);
+                        todo &= todo - 1ull;
+                        put(__builtin_amdgcn_readlane(lo, x), __builtin_amdgcn_readlane(hi, x), __builtin_amdgcn_readlane(first, x), g,
+                            level[j], parent[j]);
                     }
                 }
             }
         }
-    };
-    if (in_lds) {  // while the reservation is in flight
-        for (int t = total + tid; t < n_ent * bn; t += kListThreads) {  // tail of the last entry
-            s_keys[t] = no_key;
-            s_kpar[t] = -1;
+        lds_barrier();
+        // key order: a wave takes groups of 64 of them (of one tile each) into registers and counts their levels; from
+        // the counts of all groups it knows the first index of every level in its own
+        int igroups[T], i0[T];
+#pragma unroll
+        for (int h = 0; h < T; h++) {
+            igroups[h] = (total[h] + 63) >> 6;
+            i0[h] = h ? igroups[0] : 0;
         }
-        pack(true, nullptr, nullptr, 0);
+        const int n_groups = igroups[0] + (T > 1 ? igroups[T - 1] : 0);
+        int key[kRounds], par[kRounds];
+        auto tile_of = [&](int k) { return T > 1 && k >= igroups[0] ? T - 1 : 0; };
+#pragma unroll
+        for (int x = 0; x < kRounds; x++) {
+            const int k = x * W + wave;
+            if (k >= n_groups) break;
+            const int h = tile_of(k), t = (k - i0[h]) * 64 + lane, at = (h ? total[0] : 0) + t;
+            key[x] = t < total[h] ? s_keys[at] : -1;
+            par[x] = t < total[h] ? s_kpar[at] : -1;
+            const int mine = wave_bucket_count(key[x] >= 0, key[x] >> 24);
+            if (lane < kBuckets) s_lcnt[k][lane] = mine;
+        }
+        lds_barrier();
+        // Slots behind the last key name no key: they hold ~f, f = the tile's first real row (a list with a key has
+        // one), which is the row the attention kernels gather for such a slot.
+#pragma unroll
+        for (int h = 0; h < T; h++)
+            for (int t = total[h] + tid; t < n_ent[h] * bn; t += kListThreads) {
+                s_keys[koff[h] + t] = ~s_first[h];
+                s_kpar[koff[h] + t] = -1;
+            }
+#pragma unroll
+        for (int x = 0; x < kRounds; x++) {
+            const int k = x * W + wave;
+            if (k >= n_groups) break;
+            const int h = tile_of(k);
+            int all = 0, before = 0;  // lane l: keys of level l, and those in front of this group
+            if (lane < kBuckets)
+                for (int e = i0[h]; e < i0[h] + igroups[h]; e++) {
+                    const int c = s_lcnt[e][lane];
+                    all += c;
+                    before += e < k ? c : 0;
+                }
+            const int first_of_level = koff[h] + wave_scan(all) - all + before;
+            const bool in = key[x] >= 0;
+            const int bk_mine = key[x] >> 24;
+            int t = 0;
+            unsigned long long remaining = __ballot(in);
+            while (remaining) {
+                const int bk = __builtin_amdgcn_readlane(bk_mine, __ffsll((long long)remaining) - 1);
+                const unsigned long long m = __ballot(in && bk_mine == bk);
+                if (in && bk_mine == bk) t = __builtin_amdgcn_readlane(first_of_level, bk) + __popcll(m & lanemask_lt());
+                remaining &= ~m;
+            }
+            if (in) {
+                s_keys[t] = key[x] & 0xffffff;
+                s_kpar[t] = par[x];
+            }
+        }
     }
     if (tid == 64) {
-        s_base = reserved;
-        if (final_total >= 0) {
+        s_base = reserved_first(reserved);
+        if (is_last(reserved)) {
             const int err = __hip_atomic_load(&a.counters[CNT_ERR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (a.self_reset) {  // nobody touches the counters after the last reservation: clear them for the next build
                 __hip_atomic_store(&a.counters[CNT_ERR], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(reinterpret_cast<unsigned long long *>(a.counters + CNT_CAND), 0ull, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             }
-            const unsigned long long word = report_word(a.ticket, err, (uint32_t)final_total);
+            const unsigned long long word = report_word(a.ticket, err, (uint32_t)(s_base + n_all));
             *a.report_dev = word;
             __hip_atomic_store(a.report, word, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
     lds_barrier();
-    const int64_t base = s_base;
-    const size_t row = (size_t)b * a.tr + I;
-    // entries past the capacity are not written, and the tile's range ends where they would begin: whoever walks
+    if (have_row) {  // (not earlier: a store takes 2-3 us to be acknowledged, and a wait for a later load waits for it)
+        a.level_copy[(size_t)b * n + my_row] = my_level;
+        a.parent_copy[(size_t)b * n + my_row] = my_parent;
+    }
+    // Entries past the capacity are not written, and a tile's range ends where they would begin: whoever walks
     // the lists stays inside the arrays (the host learns of the shortfall from the report and repeats the build
     // with larger arrays, or tells the caller of a deferred build to)
-    const int64_t room = a.capacity - base;
-    const int n_fit = room <= 0 ? 0 : (room < n_ent ? (int)room : n_ent);
-    if (tid == 0) {
-        const int32_t first = (int32_t)(room <= 0 ? a.capacity : base);
-        a.q_range[2 * row] = first;
-        a.q_range[2 * row + 1] = first + n_fit;
-    }
-    const int key_fit = n_fit * bn;
-    for (int e = tid; e < n_fit; e += kListThreads) a.c_row[base + e] = (int32_t)row;
-    int32_t *keys = a.q_keys + (size_t)base * bn, *kpars = a.q_kpar + (size_t)base * bn;
-    if (in_lds) {
-        for (int t = tid; t < key_fit; t += kListThreads) {
-            keys[t] = s_keys[t];
-            if (t < total) kpars[t] = s_kpar[t];
-        }
-    } else {
-        for (int t = total + tid; t < key_fit; t += kListThreads) keys[t] = no_key;
-        pack(false, keys, kpars, key_fit);
-        // The keys were written to global memory by other waves of this workgroup; the barrier orders those
-        // stores before the loads below at workgroup scope, which is all that is needed on one compute unit
-        // (the loads also bypass the vector cache).
-        __syncthreads();
-    }
-    // The entries of this tile out of LDS, one wave per 64 key slots; a list that did not fit is brought back
-    // one round of entries at a time.
-    const int wpe = (bn + 63) >> 6, per_round = kListWaves / wpe;  // waves per entry, entries per round
-    const int quad = wave / wpe, k0 = (wave - quad * wpe) * 64;
-    ParentTable tab;
-    tab.n = s_ntab;
-    tab.v = s_tab_v;
-    tab.rows = s_tab_rows;
-    int par = 0;
-    for (int e0 = 0; e0 < n_fit; e0 += per_round, par ^= 1) {
-        const int e = e0 + quad;
-        int kb = e * bn;  // the entry's first key in s_keys, s_kpar
-        if (!in_lds) {
-            lds_barrier();  // the previous round's keys have been read
-            for (int t = tid; t < per_round * bn; t += kListThreads) {
-                const int gi = e0 * bn + t;
-                int kk = -1, kq = -1;
-                if (gi < key_fit) kk = __hip_atomic_load(&keys[gi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (kk >= 0 && kk < n) kq = __hip_atomic_load(&kpars[gi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                s_keys[t] = (kk >= 0 && kk < n) ? kk : -1;
-                s_kpar[t] = kq;
-            }
-            lds_barrier();
-            kb = quad * bn;
-        }
-        const bool active = e < n_fit;
-        EntryPart part;
-        part.cnt = 0;
-        part.any = part.all = 0;
-        if (active) part = entry_columns(base + e, k0, lane, tab, s_keys + kb, s_kpar + kb, row0, bm, bn, a.edges, a.bits_rm);
-        if (wpe == 1) {
-            if (active && lane == 0) {
-                a.c_cnt[base + e] = part.cnt;
-                a.q_sub[base + e] = part.any | (part.all << 16);
-            }
-            continue;
-        }
-        // two waves per entry: the slots of this parity were last read two rounds ago, in front of the previous
-        // round's barrier
-        if (lane == 0) {
-            s_cnt[par][wave] = part.cnt;
-            s_any[par][wave] = part.any;
-            s_all[par][wave] = part.all;
-        }
-        lds_barrier();
-        if (active && k0 == 0 && lane == 0) {
-            a.c_cnt[base + e] = s_cnt[par][wave] + s_cnt[par][wave + 1];
-            a.q_sub[base + e] = (s_any[par][wave] | s_any[par][wave + 1]) | ((s_all[par][wave] | s_all[par][wave + 1]) << 16);
-        }
-    }
-}
-
-// ---- key lists of TWO neighbouring query tiles of up to 64 rows per workgroup -------------------------
-// Tiles of 64 rows make twice the query tiles, and every query tile's workgroup scans the ids of the whole
-// sample; here the tiles 2P and 2P + 1 share one workgroup of 1024 threads and one scan, which tests every
-// position against both tiles (two bitmaps of the rows' parents, two lists of needed keys); the two lists are
-// then packed, reserved (one atomic for both: the entries of tile 2P, then those of tile 2P + 1) and evaluated
-// as in key_lists, the waves working on the entries of both tiles side by side.  Same results, array by array
-// (measured at 8192 positions x 4 samples, 64 x 32 tiles: 20 us against 24; 32768 positions: 43 against 48).
-constexpr int kPairThreads = 1024, kPairWaves = kPairThreads / 64;
-
-__global__ __launch_bounds__(kPairThreads) void k_key_lists_pair(KeyListArgs a)
-{
-    constexpr int W = kPairWaves;
-    extern __shared__ uint32_t s_dyn[];  // 2 x [ceil(n/32)] parents of each tile's rows, then 2 x [2 * groups] needed positions
-    __shared__ int2 s_row[128];          // (position, parent) of the rows: tile h at [64h, 64h + 64); position -2: no such row
-    __shared__ int s_lcnt[2][W][kBuckets];
-    __shared__ int s_cnt[2][W];
-    __shared__ uint32_t s_any[2][W], s_all[2][W];
-    __shared__ int s_base[2], s_total[2], s_wtotal[2][W];
-    __shared__ __attribute__((aligned(16))) int s_keys[kLdsKeys], s_kpar[kLdsKeys];
-    __shared__ int s_tab_v[2][64], s_ntab[2];
-    __shared__ uint4 s_tab_rows[2][64];
-    __shared__ int s_first[2];
-    const int pairs = (a.tr + 1) >> 1;
-    const int b = blockIdx.x / pairs, P = blockIdx.x - b * pairs, n = a.n;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int bm = a.bm, bn = a.bn;  // bm <= 64
-    const int32_t *level = a.level + (size_t)b * n, *parent = a.parent + (size_t)b * n;
-    const int pw = (n + 31) >> 5, ng = (n + 63) >> 6;
-    uint32_t *s_par0 = s_dyn, *s_par1 = s_dyn + pw, *s_need0 = s_dyn + 2 * pw, *s_need1 = s_dyn + 2 * pw + 2 * ng;
-    const int I0 = 2 * P, I1 = 2 * P + 1;
-    const bool have1 = I1 < a.tr;  // the last pair of an odd number of tiles has one tile only
-    const int row0_0 = I0 * bm, row0_1 = I1 * bm;
-    const int bm1 = have1 ? bm : 0;
-    const int gpw = (ng + W - 1) / W;
-    const int g0 = min(wave * gpw, ng), g1 = min(g0 + gpw, ng);
-    int klv[kBatch], kp[kBatch];
-    auto load_batch = [&](int gb) {
+    int64_t base[T];
+    int n_fit[T], key_fit[T];
+    int32_t *keys[T], *kpars[T];
 #pragma unroll
-        for (int u = 0; u < kBatch; u++) {
-            const int j = (gb + u) * 64 + lane;
-            const bool ok = gb + u < g1 && j < n;
-            klv[u] = ok ? level[j] : -1;
-            kp[u] = ok ? parent[j] : -1;
-        }
-    };
-    load_batch(g0);
-    for (int w = tid; w < 2 * pw; w += kPairThreads) s_dyn[w] = 0;
-    if (tid < 2) s_first[tid] = INT_MAX;
-    lds_barrier();
-    bool check_parent = false;
-    int my_parent = 0;
-    if (tid < 128) {
-        const int h = tid >> 6, r = tid & 63;
-        const int i = (h ? row0_1 : row0_0) + r;
-        int2 me = make_int2(-2, -2);
-        if (r < (h ? bm1 : bm) && i < n) {
-            const int l = level[i], p = parent[i];
-            a.level_copy[(size_t)b * n + i] = l;
-            a.parent_copy[(size_t)b * n + i] = p;
-            if (l < -1 || l >= HDT_MAX_LEVELS || p < -1 || p >= n || p == i || (l < 0 && p != -1))
-                raise_error(a.counters);
-            else if (l >= 0) {
-                me = make_int2(i, p);
-                atomicMin(&s_first[h], i);
-                if (p >= 0) {
-                    atomicOr(&(h ? s_par1 : s_par0)[p >> 5], 1u << (p & 31));
-                    check_parent = true;
-                    my_parent = p;
-                }
-            }
-        }
-        s_row[tid] = me;
-    }
-    const int parent_level = check_parent ? level[my_parent] : 0;
-    lds_barrier();
-    const bool e_up = a.edges & HDT_EDGE_UP, e_sib = a.edges & HDT_EDGE_SIBLING, e_down = a.edges & HDT_EDGE_DOWN;
-    int lcount0 = 0, lcount1 = 0, wtotal0 = 0, wtotal1 = 0;
-    for (int gb = g0; gb < g1; gb += kBatch) {
-        if (gb != g0) load_batch(gb);
-        bool need0[kBatch], need1[kBatch];
-#pragma unroll
-        for (int u = 0; u < kBatch; u++) {
-            const int j = (gb + u) * 64 + lane, pj = kp[u];
-            const bool real = klv[u] >= 0 && j < n, has_parent = pj >= 0 && pj < n;
-            const int jc = real ? j : 0, pc = has_parent ? pj : 0;
-            const uint32_t wj0 = s_par0[jc >> 5], wp0 = s_par0[pc >> 5], wj1 = s_par1[jc >> 5], wp1 = s_par1[pc >> 5];
-            const bool j_in0 = (unsigned)(j - row0_0) < (unsigned)bm, j_in1 = (unsigned)(j - row0_1) < (unsigned)bm1;
-            const bool p_in0 = (unsigned)(pj - row0_0) < (unsigned)bm, p_in1 = (unsigned)(pj - row0_1) < (unsigned)bm1;
-            const bool self0 = j_in0 | (e_up & (bool)((wj0 >> (jc & 31)) & 1u));
-            const bool self1 = j_in1 | (e_up & (bool)((wj1 >> (jc & 31)) & 1u));
-            const bool par0 = has_parent & ((e_down & p_in0) | (e_sib & (bool)((wp0 >> (pc & 31)) & 1u)));
-            const bool par1 = has_parent & ((e_down & p_in1) | (e_sib & (bool)((wp1 >> (pc & 31)) & 1u)));
-            need0[u] = real & (self0 | par0);
-            need1[u] = real & (self1 | par1);
-        }
-#pragma unroll
-        for (int u = 0; u < kBatch; u++) {
-            if (gb + u >= g1) break;
-            const unsigned long long m0 = __ballot(need0[u]), m1 = __ballot(need1[u]);
-            if (lane == 0) {
-                s_need0[2 * (gb + u)] = (uint32_t)m0;
-                s_need0[2 * (gb + u) + 1] = (uint32_t)(m0 >> 32);
-                s_need1[2 * (gb + u)] = (uint32_t)m1;
-                s_need1[2 * (gb + u) + 1] = (uint32_t)(m1 >> 32);
-            }
-            wtotal0 += __popcll(m0);
-            wtotal1 += __popcll(m1);
-            const int bucket = a.no_sort ? 0 : bucket_of(klv[u]);
-            if (m0 != 0ull) lcount0 += wave_bucket_count(need0[u], bucket);
-            if (m1 != 0ull) lcount1 += wave_bucket_count(need1[u], bucket);
-        }
-    }
-    const bool one_batch = g1 - g0 <= kBatch;
-    if (lane < kBuckets) {
-        s_lcnt[0][wave][lane] = lcount0;
-        s_lcnt[1][wave][lane] = lcount1;
-    }
-    if (lane == 0) {
-        s_wtotal[0][wave] = wtotal0;
-        s_wtotal[1][wave] = wtotal1;
-    }
-    if (check_parent && parent_level < 0) raise_error(a.counters);
-    lds_barrier();
-    int reserved = 0, final_total = -1;
-    if (wave == 1) {  // one reservation for both tiles
-        const int t0 = wave_sum(lane < W ? s_wtotal[0][lane] : 0), t1 = wave_sum(lane < W ? s_wtotal[1][lane] : 0);
-        if (lane == 0) {
-            s_total[0] = t0;
-            s_total[1] = t1;
-            reserved = reserve_entries(a.counters, (t0 + bn - 1) / bn + (t1 + bn - 1) / bn, &final_total);
-        }
-    }
-    if (wave == 2 || wave == 3) {  // the tables of the rows' parents, one per tile (64 rows each)
-        const int h = wave - 2;
-        const int2 ra = s_row[64 * h + lane];
-        const int pa = ra.x >= 0 ? ra.y : -1;
-        unsigned long long rem = __ballot(pa >= 0);
-        int nt = 0;
-        while (rem) {
-            const int v = __builtin_amdgcn_readlane(pa, __ffsll((long long)rem) - 1);
-            const unsigned long long ma = __ballot(pa == v);
-            if (lane == 0) {
-                s_tab_v[h][nt] = v;
-                s_tab_rows[h][nt] = make_uint4((uint32_t)ma, (uint32_t)(ma >> 32), 0u, 0u);
-            }
-            rem &= ~ma;
-            nt++;
-        }
-        if (lane == 0) s_ntab[h] = nt;
-    }
-    if (wave == 0 || wave == 4) {  // first index of every (level, wave) of a tile: level major, then wave
-        const int h = wave >> 2;
-        int t = 0;
-        if (lane < kBuckets) {
-#pragma unroll
-            for (int w = 0; w < W; w++) t += s_lcnt[h][w][lane];
-        }
-        int incl = t;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int y = __shfl_up(incl, d);
-            if (lane >= d) incl += y;
-        }
-        int run = incl - t;
-        if (lane < kBuckets) {
-#pragma unroll
-            for (int w = 0; w < W; w++) {
-                const int c = s_lcnt[h][w][lane];
-                s_lcnt[h][w][lane] = run;
-                run += c;
-            }
-        }
-    }
-    lds_barrier();
-    const int total0 = s_total[0], total1 = s_total[1];
-    const int n_ent0 = (total0 + bn - 1) / bn, n_ent1 = (total1 + bn - 1) / bn;
-    const int koff1 = n_ent0 * bn;  // tile 1's list behind tile 0's in s_keys
-    const bool in_lds = (n_ent0 + n_ent1) * bn <= kLdsKeys;
-    const int no_key0 = ~s_first[0], no_key1 = ~s_first[1];
-    // hands out the indices of this wave's needed keys of tile h, in document order inside every level
-    auto pack = [&](int h, bool to_lds, int32_t *keys, int32_t *kpars, int key_fit) {
-        int mybase = lane < kBuckets ? s_lcnt[h][wave][lane] : 0;
-        const uint32_t *s_need = h ? s_need1 : s_need0;
-        const int koff = h ? koff1 : 0;
-        for (int gb = g0; gb < g1; gb += kBatch) {
-            if (!one_batch) load_batch(gb);
-#pragma unroll
-            for (int u = 0; u < kBatch; u++) {
-                if (gb + u >= g1) break;
-                const int g = gb + u;
-                const unsigned long long m = (unsigned long long)s_need[2 * g] | ((unsigned long long)s_need[2 * g + 1] << 32);
-                if (m == 0ull) continue;
-                const bool need = (m >> lane) & 1ull;
-                const int bucket = a.no_sort ? 0 : bucket_of(klv[u]);
-                int t = 0;
-                unsigned long long remaining = m;
-                while (remaining) {
-                    const int leader = __ffsll((long long)remaining) - 1;
-                    const int bk = __builtin_amdgcn_readlane(bucket, leader);
-                    const bool is_bk = need && bucket == bk;
-                    const unsigned long long mm = __ballot(is_bk);
-                    const int first = __builtin_amdgcn_readlane(mybase, bk);
-                    if (is_bk) t = first + __popcll(mm & lanemask_lt());
-                    if (lane == bk) mybase += __popcll(mm);
-                    remaining &= ~mm;
-                }
-                if (need) {
-                    if (to_lds) {
-                        s_keys[koff + t] = g * 64 + lane;
-                        s_kpar[koff + t] = kp[u];
-                    } else if (t < key_fit) {
-                        keys[t] = g * 64 + lane;
-                        kpars[t] = kp[u];
-                    }
-                }
-            }
-        }
-    };
-    if (in_lds) {  // while the reservation is in flight
-        for (int t = total0 + tid; t < n_ent0 * bn; t += kPairThreads) {
-            s_keys[t] = no_key0;
-            s_kpar[t] = -1;
-        }
-        for (int t = total1 + tid; t < n_ent1 * bn; t += kPairThreads) {
-            s_keys[koff1 + t] = no_key1;
-            s_kpar[koff1 + t] = -1;
-        }
-        pack(0, true, nullptr, nullptr, 0);
-        pack(1, true, nullptr, nullptr, 0);
-    }
-    if (tid == 64) {
-        s_base[0] = reserved;
-        s_base[1] = reserved + n_ent0;
-        if (final_total >= 0) {
-            const int err = __hip_atomic_load(&a.counters[CNT_ERR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (a.self_reset) {
-                __hip_atomic_store(&a.counters[CNT_ERR], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(reinterpret_cast<unsigned long long *>(a.counters + CNT_CAND), 0ull, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            }
-            const unsigned long long word = report_word(a.ticket, err, (uint32_t)final_total);
-            *a.report_dev = word;
-            __hip_atomic_store(a.report, word, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-        }
-    }
-    lds_barrier();
-    // per tile: its slice of the arrays, as far as it fits (see key_lists)
-    int64_t base[2];
-    int n_fit[2], key_fit[2];
-    int32_t *keys[2], *kpars[2];
-    for (int h = 0; h < 2; h++) {
-        base[h] = s_base[h];
-        const int n_ent = h ? n_ent1 : n_ent0;
+    for (int h = 0; h < T; h++) {
+        base[h] = (int64_t)s_base + (h ? n_ent[0] : 0);
         const int64_t room = a.capacity - base[h];
-        n_fit[h] = room <= 0 ? 0 : (room < n_ent ? (int)room : n_ent);
+        n_fit[h] = room <= 0 ? 0 : (room < n_ent[h] ? (int)room : n_ent[h]);
         key_fit[h] = n_fit[h] * bn;
         keys[h] = a.q_keys + (size_t)(room <= 0 ? 0 : base[h]) * bn;
         kpars[h] = a.q_kpar + (size_t)(room <= 0 ? 0 : base[h]) * bn;
-        const size_t row = (size_t)b * a.tr + (h ? I1 : I0);
-        if (h == 1 && !have1) break;
-        if (tid == 0) {
+        if (I0 + h < a.tr && tid == 0) {
+            const size_t row = (size_t)b * a.tr + I0 + h;
             const int32_t first = (int32_t)(room <= 0 ? a.capacity : base[h]);
             a.q_range[2 * row] = first;
             a.q_range[2 * row + 1] = first + n_fit[h];
         }
-        for (int e = tid; e < n_fit[h]; e += kPairThreads) a.c_row[base[h] + e] = (int32_t)row;
+        for (int e = tid; e < n_fit[h]; e += kListThreads) a.c_row[base[h] + e] = (int32_t)((size_t)b * a.tr + I0 + h);
+        if (in_lds)
+            for (int t = tid; t < key_fit[h]; t += kListThreads) keys[h][t] = s_keys[koff[h] + t];
     }
-    if (!have1) n_fit[1] = key_fit[1] = 0;
-    if (in_lds) {
-        for (int t = tid; t < key_fit[0]; t += kPairThreads) {
-            keys[0][t] = s_keys[t];
-            if (t < total0) kpars[0][t] = s_kpar[t];
+    if (!in_lds) {
+        const int gpw = (ng + W - 1) / W, g0 = min(wave * gpw, ng), g1 = min(g0 + gpw, ng);  // this wave's share
+#pragma unroll
+        for (int h = 0; h < T; h++) {
+            for (int t = total[h] + tid; t < key_fit[h]; t += kListThreads) keys[h][t] = ~s_first[h];
+            // levels of the needed keys of the share, kBatch groups in flight
+            auto each = [&](auto work) {
+                for (int gb = g0; gb < g1; gb += kBatch) {
+                    int l[kBatch], p[kBatch];
+#pragma unroll
+                    for (int u = 0; u < kBatch; u++) {
+                        const int j = (gb + u) * 64 + lane;
+                        const bool ok = gb + u < g1 && j < n;
+                        l[u] = ok ? level[j] : -1;
+                        p[u] = ok ? parent[j] : -1;
+                    }
+#pragma unroll
+                    for (int u = 0; u < kBatch; u++) {
+                        const int g = gb + u;
+                        if (g >= g1) break;
+                        const unsigned long long need = (unsigned long long)words(g)->w[h] | ((unsigned long long)words(g)->w[T + h] << 32);
+                        if (need != 0ull) work(g, need, bucket(l[u]), p[u]);
+                    }
+                }
+            };
+            int mine = 0;  // lane k: needed keys of level k in the share
+            each([&](int, unsigned long long m, int bk, int) { mine += wave_bucket_count((m >> lane) & 1ull, bk); });
+            if (lane < kBuckets) s_lcnt[wave][lane] = mine;
+            lds_barrier();
+            int all = 0, before = 0;
+            if (lane < kBuckets) {
+#pragma unroll
+                for (int w = 0; w < W; w++) {
+                    all += s_lcnt[w][lane];
+                    before += w < wave ? s_lcnt[w][lane] : 0;
+                }
+            }
+            int next = wave_scan(all) - all + before;  // lane k: next index of level k in this wave
+            each([&](int g, unsigned long long m, int bk_mine, int p) {
+                const bool need = (m >> lane) & 1ull;
+                int t = 0;
+                unsigned long long remaining = m;
+                while (remaining) {
+                    const int bk = __builtin_amdgcn_readlane(bk_mine, __ffsll((long long)remaining) - 1);
+                    const bool is_bk = need && bk_mine == bk;
+                    const unsigned long long mm = __ballot(is_bk);
+                    const int first = __builtin_amdgcn_readlane(next, bk);
+                    if (is_bk) t = first + __popcll(mm & lanemask_lt());
+                    if (lane == bk) next += __popcll(mm);
+                    remaining &= ~mm;
+                }
+                if (need && t < key_fit[h]) {
+                    keys[h][t] = g * 64 + lane;
+                    kpars[h][t] = p;
+                }
+            });
+            // The keys were written to global memory by other waves of this workgroup; the barrier orders those
+            // stores before the loads below at workgroup scope, which is all that is needed on one compute unit
+            // (the loads also bypass the vector cache).
+            __syncthreads();
         }
-        for (int t = tid; t < key_fit[1]; t += kPairThreads) {
-            keys[1][t] = s_keys[koff1 + t];
-            if (t < total1) kpars[1][t] = s_kpar[koff1 + t];
-        }
-    } else {
-        for (int t = total0 + tid; t < key_fit[0]; t += kPairThreads) keys[0][t] = no_key0;
-        for (int t = total1 + tid; t < key_fit[1]; t += kPairThreads) keys[1][t] = no_key1;
-        pack(0, false, keys[0], kpars[0], key_fit[0]);
-        pack(1, false, keys[1], kpars[1], key_fit[1]);
-        __syncthreads();  // the keys were written by other waves of this workgroup (see key_lists)
     }
-    // The entries of both tiles, one wave per 64 key slots.  Lists kept in LDS: the waves take the entries of both
-    // tiles in one sequence; lists that did not fit are brought back tile by tile, a round of entries at a time.
-    const int wpe = (bn + 63) >> 6, per_round = W / wpe;
+    // The entries, one wave per 64 key slots.  Lists kept in LDS: the waves take the entries of all tiles in one
+    // sequence; lists that did not fit are brought back tile by tile, as many entries at a time as fit.
+    const int wpe = (bn + 63) >> 6, per_round = W / wpe;  // waves per entry, entries per round
     const int quad = wave / wpe, k0 = (wave - quad * wpe) * 64;
-    ParentTable tab[2];
-    for (int h = 0; h < 2; h++) {
+    ParentTable tab[T];
+#pragma unroll
+    for (int h = 0; h < T; h++) {
         tab[h].n = s_ntab[h];
-        tab[h].v = s_tab_v[h];
-        tab[h].rows = s_tab_rows[h];
+        tab[h].v = s_tab_v + h * RT;
+        tab[h].rows = s_tab_rows + h * RT;
     }
-    int par = 0;
+    int parity = 0;
     auto finish = [&](bool active, int64_t c, const EntryPart &part) {  // pair count and summary of entry c
         if (wpe == 1) {
             if (active && lane == 0) {
@@ -1175,54 +1026,61 @@ __global__ __launch_bounds__(kPairThreads) void k_key_lists_pair(KeyListArgs a)
             }
             return;
         }
+        // two waves per entry: the slots of this parity were last read two rounds ago, in front of the previous
+        // round's barrier
         if (lane == 0) {
-            s_cnt[par][wave] = part.cnt;
-            s_any[par][wave] = part.any;
-            s_all[par][wave] = part.all;
+            s_cnt[parity][wave] = part.cnt;
+            s_any[parity][wave] = part.any;
+            s_all[parity][wave] = part.all;
         }
         lds_barrier();
         if (active && k0 == 0 && lane == 0) {
-            a.c_cnt[c] = s_cnt[par][wave] + s_cnt[par][wave + 1];
-            a.q_sub[c] = (s_any[par][wave] | s_any[par][wave + 1]) | ((s_all[par][wave] | s_all[par][wave + 1]) << 16);
+            a.c_cnt[c] = s_cnt[parity][wave] + s_cnt[parity][wave + 1];
+            a.q_sub[c] = (s_any[parity][wave] | s_any[parity][wave + 1]) | ((s_all[parity][wave] | s_all[parity][wave + 1]) << 16);
         }
-        par ^= 1;
+        parity ^= 1;
     };
     if (in_lds) {
-        const int n_all = n_fit[0] + n_fit[1];
-        for (int x0 = 0; x0 < n_all; x0 += per_round) {
+        const int fit0 = n_fit[0], fits = fit0 + (T > 1 ? n_fit[T - 1] : 0);
+        for (int x0 = 0; x0 < fits; x0 += per_round) {
             const int x = x0 + quad;
-            const bool active = x < n_all;
-            const int h = (active && x >= n_fit[0]) ? 1 : 0, e = x - (h ? n_fit[0] : 0);
+            const bool active = x < fits;
+            const int h = T > 1 && active && x >= fit0 ? T - 1 : 0, e = x - (h ? fit0 : 0);
             EntryPart part;
             part.cnt = 0;
             part.any = part.all = 0;
             if (active)
-                part = entry_columns(base[h] + e, k0, lane, tab[h], s_keys + (h ? koff1 : 0) + e * bn,
-                                     s_kpar + (h ? koff1 : 0) + e * bn, h ? row0_1 : row0_0, bm, bn, a.edges, a.bits_rm);
+                part = entry_columns(base[h] + e, k0, lane, tab[h], s_keys + koff[h] + e * bn, s_kpar + koff[h] + e * bn, row0[h],
+                                     bm, bn, a.edges, a.bits_rm);
             finish(active, base[h] + e, part);
         }
-    } else {
-        for (int h = 0; h < 2; h++) {
-            for (int e0 = 0; e0 < n_fit[h]; e0 += per_round) {
-                const int e = e0 + quad;
-                lds_barrier();  // the previous round's keys have been read
-                for (int t = tid; t < per_round * bn; t += kPairThreads) {
-                    const int gi = e0 * bn + t;
-                    int kk = -1, kq = -1;
-                    if (gi < key_fit[h]) kk = __hip_atomic_load(&keys[h][gi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (kk >= 0 && kk < n) kq = __hip_atomic_load(&kpars[h][gi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    s_keys[t] = (kk >= 0 && kk < n) ? kk : -1;
-                    s_kpar[t] = kq;
-                }
-                lds_barrier();
-                const bool active = e < n_fit[h];
+        return;
+    }
+#pragma unroll
+    for (int h = 0; h < T; h++) {
+        const int at_once = kLdsKeys / bn;
+        for (int e0 = 0; e0 < n_fit[h]; e0 += at_once) {
+            const int entries = min(at_once, n_fit[h] - e0);
+            lds_barrier();  // the previous entries' keys have been read
+            for (int t = tid; t < entries * bn; t += kListThreads) {
+                const int gi = e0 * bn + t;
+                const int kk = __hip_atomic_load(&keys[h][gi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                int kq = -1;
+                if (kk >= 0 && kk < n) kq = __hip_atomic_load(&kpars[h][gi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                s_keys[t] = (kk >= 0 && kk < n) ? kk : -1;
+                s_kpar[t] = kq;
+            }
+            lds_barrier();
+            for (int x0 = 0; x0 < entries; x0 += per_round) {
+                const int x = x0 + quad;
+                const bool active = x < entries;
                 EntryPart part;
                 part.cnt = 0;
                 part.any = part.all = 0;
                 if (active)
-                    part = entry_columns(base[h] + e, k0, lane, tab[h], s_keys + quad * bn, s_kpar + quad * bn, h ? row0_1 : row0_0,
-                                         bm, bn, a.edges, a.bits_rm);
-                finish(active, base[h] + e, part);
+                    part = entry_columns(base[h] + e0 + x, k0, lane, tab[h], s_keys + x * bn, s_kpar + x * bn, row0[h], bm, bn,
+                                         a.edges, a.bits_rm);
+                finish(active, base[h] + e0 + x, part);
             }
         }
     }
@@ -1980,21 +1838,21 @@ static hdt_status_t build_one(const int32_t *d_level, const int32_t *d_parent, i
                                q.c_cnt, p.level_copy, p.parent_copy, q.q_sub, q.bits_rm,
                                slot_counters ? slot_counters : p.counters, report, p.report_copy, ticket,
                                slot_counters != nullptr};
-                const size_t lds = ((size_t)(n + 31) / 32 + (size_t)2 * ((n + 63) / 64)) * sizeof(uint32_t);
                 const bool small_wg = bm <= 64;
                 // tiles of up to 64 rows: two per workgroup, as long as the two sets of bitmaps fit the LDS beside the
                 // kernel's static arrays (documents of up to 64 K positions)
-                const bool pair = small_wg && 2 * lds <= 32 * 1024;
-                if (!pair && lds > 32 * 1024)  // with the kernel's static arrays: beyond the 64 KB a launch gets by default
-                    BUILD_TRY(hipFuncSetAttribute(small_wg ? (const void *)k_key_lists<512> : (const void *)k_key_lists<1024>,
+                const bool pair = small_wg && list_lds(n, 2) <= 33 * 1024;
+                const size_t lds = list_lds(n, pair ? 2 : 1);
+                if (lds > 33 * 1024)  // with the kernel's static arrays: beyond the 64 KB a launch gets by default
+                    BUILD_TRY(hipFuncSetAttribute(small_wg ? (const void *)k_key_lists<512, 1> : (const void *)k_key_lists<1024, 1>,
                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
                 HdtTimer t("hdt_layout_key_lists", st);
                 if (pair)
-                    hipLaunchKernelGGL(k_key_lists_pair, dim3((unsigned)B * ((tr + 1) / 2)), dim3(kPairThreads), 2 * lds, st, ka);
+                    hipLaunchKernelGGL((k_key_lists<1024, 2>), dim3((unsigned)B * ((tr + 1) / 2)), dim3(1024), lds, st, ka);
                 else if (small_wg)
-                    hipLaunchKernelGGL(k_key_lists<512>, dim3((unsigned)B * tr), dim3(512), lds, st, ka);
+                    hipLaunchKernelGGL((k_key_lists<512, 1>), dim3((unsigned)B * tr), dim3(512), lds, st, ka);
                 else
-                    hipLaunchKernelGGL(k_key_lists<1024>, dim3((unsigned)B * tr), dim3(1024), lds, st, ka);
+                    hipLaunchKernelGGL((k_key_lists<1024, 1>), dim3((unsigned)B * tr), dim3(1024), lds, st, ka);
             }
             if (windowed) {
                 const unsigned grid = (unsigned)(cap < 2048 ? (cap > 0 ? cap : 1) : 2048);

@@ -7,7 +7,7 @@ from paper_2407_08330_amd import inputs
 from test_gpu_bwd import run_bwd_case
 from test_gpu_cross import _compare_schedule, run_cross_case
 from test_gpu_fwd import run_fwd_case
-from gpu_common import say, to_dev_i32
+from gpu_common import compare_layout, say, to_dev_i32
 
 pytestmark = pytest.mark.gpu
 
@@ -95,3 +95,41 @@ def test_index_vectors_and_parents_across_workgroup_shares(oracle, n):
     for b in range(2):
         np.testing.assert_array_equal(par[b], oracle.parents_from_levels(levels[b]), err_msg=f"levels {b}")
     assert (par[2, 1:-1] == 0).all() and par[2, 0] == -1 and par[2, -1] == -1
+
+
+def _shuffled(level, parent, rng):
+    n = level.shape[0]
+    perm = rng.permutation(n)
+    lv, pr = np.empty(n, np.int32), np.empty(n, np.int32)
+    lv[perm] = level
+    pr[perm] = np.where(parent >= 0, perm[np.maximum(parent, 0)], -1)
+    return lv, pr
+
+
+@pytest.mark.parametrize("bm,bn,n_keys", [(128, 64, 2048), (128, 64, 2049), (64, 32, 1024), (64, 32, 1025), (96, 96, 2016), (96, 96, 2017)])
+def test_key_lists_at_the_length_that_fits_lds(oracle, bm, bn, n_keys):
+    # a root and its children: every row sees every key, and a workgroup's lists (two of them on 64-row tiles) hold
+    # exactly as many keys as stay in LDS, or one more
+    import paper_2407_08330_amd as hdt
+    level = np.ones((2, n_keys), np.int32)
+    level[:, 0] = 0
+    parent = np.zeros((2, n_keys), np.int32)
+    parent[:, 0] = -1
+    level[1], parent[1] = _shuffled(level[1], parent[1], np.random.default_rng(n_keys))
+    lay = hdt.hdt_build_layout(to_dev_i32(level), to_dev_i32(parent), tile_m=bm, tile_n=bn)
+    compare_layout(oracle, lay, level, parent, bm, bn)
+
+
+@pytest.mark.parametrize("bm,bn", [(128, 64), (64, 32)])
+@pytest.mark.parametrize("n", [8191, 8192, 8193, 8257])
+@pytest.mark.parametrize("edges", [7, 6, 1])
+def test_key_lists_around_a_wave_batch_of_positions(oracle, bm, bn, n, edges):
+    # up to 8 groups of 64 positions per wave stay in registers (8192 positions); one more group, a ragged one; document
+    # order and shuffled positions; directed masks (the two bitmaps of a tile differ)
+    import paper_2407_08330_amd as hdt
+    rng = np.random.default_rng(n)
+    doc = inputs.pseudo_section_document(rng, n)[:2]
+    pair = [doc, _shuffled(*doc, rng)]
+    level, parent = np.stack([d[0] for d in pair]), np.stack([d[1] for d in pair])
+    lay = hdt.hdt_build_layout(to_dev_i32(level), to_dev_i32(parent), tile_m=bm, tile_n=bn, edges=edges)
+    compare_layout(oracle, lay, level, parent, bm, bn, edges=edges)
