@@ -241,7 +241,7 @@ hdt_status_t hdt_layout_export(const hdt_layout_t *layout, int32_t sample, int32
                                int64_t tile_capacity);
 
 /* Destroys the layout.  NULL is accepted, and the call does not wait: attention calls that use the layout may
- * still be queued or running.  Its device buffers go to a cache (at most 16 buffers / 1 GiB per process) that
+ * still be queued or running.  Its device buffers go to a cache (at most 16 buffers / 1 GiB per process; the oldest make room) that
  * later hdt_build_layout calls draw from; a build that takes them orders itself behind everything enqueued so far
  * on the streams this layout was built and used on (an event per other stream, nothing for its own stream, no
  * host wait).  The streams of those calls must still exist then, or the build waits for the device instead. */

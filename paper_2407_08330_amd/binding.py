@@ -12,6 +12,7 @@ import numpy as np
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libhdt.so")
 _lib = None
+_DTYPES = {}  # torch dtype -> hdt_dtype_t, filled with the library
 
 HDT_BF16, HDT_F32 = 0, 1
 HDT_EDGE_UP, HDT_EDGE_SIBLING, HDT_EDGE_DOWN, HDT_EDGE_ALL = 1, 2, 4, 7
@@ -59,7 +60,8 @@ def load_library():
         raise FileNotFoundError(f"{_LIB_PATH} not built; run __graft_entry__.build() first")
     # PyTorch-ROCm ships its own HIP runtime.  Import it first so that libhdt binds to that same
     # copy: two HIP runtimes in one process do not see each other's device state.
-    import torch  # noqa: F401
+    import torch
+    _DTYPES.update({torch.bfloat16: HDT_BF16, torch.float32: HDT_F32})
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i32, i64, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
     lib.hdt_build_layout.argtypes = [vp, vp, i32, i32, ctypes.POINTER(_Opts), vp, ctypes.POINTER(vp)]
@@ -128,15 +130,17 @@ def _check(status: int):
         raise HdtError(status, lib.hdt_status_string(status).decode(), lib.hdt_last_error().decode())
 
 
-def _stream_ptr(stream) -> Optional[int]:
+# Calls of small layers are bound by what happens on the host, so the helpers below stay close to the metal: addresses
+# go to ctypes as plain integers (the argument types turn them into pointers), the current stream as torch's raw handle.
+def _stream_ptr(stream) -> int:
     if stream is None:
         import torch
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _scratch(nbytes: int, device, stream):
@@ -275,19 +279,18 @@ def hdt_build_cross_layout(level_enc, n_dec: int, level_mask: int, tile_m: int =
 
 
 def _dtype_code(t):
-    import torch
-    if t.dtype == torch.bfloat16:
-        return HDT_BF16
-    if t.dtype == torch.float32:
-        return HDT_F32
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    load_library()
+    code = _DTYPES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 def _check_tensors(ts, shape=None):
     for t in ts:
         if not (t.is_cuda and t.is_contiguous()):
             raise ValueError("tensors must be contiguous device tensors")
-        if shape is not None and tuple(t.shape) != tuple(shape):
+        if shape is not None and t.shape != shape:
             raise ValueError(f"tensor shape {tuple(t.shape)} != {tuple(shape)}")
 
 

@@ -1259,19 +1259,24 @@ hipError_t pool_alloc(void **out, size_t bytes, size_t *got, hipStream_t next_us
     return hipMalloc(out, bytes);
 }
 
+// The block goes to the cache; where it has no room, the blocks that have been there longest make some (the sizes a
+// program has stopped using: kept, they would send every later build to hipMalloc and hipFree, which waits for the device).
 void pool_free(void *ptr, size_t bytes, int device, const HdtUsers &users)
 {
     if (!ptr) return;
-    {
+    std::vector<CachedBlock> out;
+    if (bytes <= kPoolMaxBytes) {
         std::lock_guard<std::mutex> lk(g_pool_mutex);
-        size_t held = 0;
+        size_t held = bytes, drop = 0;
         for (auto &b : g_pool) held += b.bytes;
-        if (g_pool.size() < kPoolMaxBlocks && held + bytes <= kPoolMaxBytes) {
-            g_pool.push_back({ptr, bytes, device, users});
-            return;
-        }
+        while (drop < g_pool.size() && (held > kPoolMaxBytes || g_pool.size() - drop >= kPoolMaxBlocks)) held -= g_pool[drop++].bytes;
+        for (size_t i = 0; i < drop; i++) out.push_back(std::move(g_pool[i]));
+        g_pool.erase(g_pool.begin(), g_pool.begin() + (ptrdiff_t)drop);
+        g_pool.push_back({ptr, bytes, device, users});
+        ptr = nullptr;
     }
-    (void)hipFree(ptr);  // waits for the device
+    for (auto &b : out) (void)hipFree(b.ptr);  // waits for the device
+    if (ptr) (void)hipFree(ptr);
 }
 
 // carve buffers (each rounded up to 256 bytes) out of an arena

@@ -133,3 +133,28 @@ def test_key_lists_around_a_wave_batch_of_positions(oracle, bm, bn, n, edges):
     level, parent = np.stack([d[0] for d in pair]), np.stack([d[1] for d in pair])
     lay = hdt.hdt_build_layout(to_dev_i32(level), to_dev_i32(parent), tile_m=bm, tile_n=bn, edges=edges)
     compare_layout(oracle, lay, level, parent, bm, bn, edges=edges)
+
+
+def test_buffer_cache_makes_room_for_the_sizes_in_use(oracle):
+    # more sizes than the cache of destroyed layouts' buffers holds (16 blocks); the size built from then on stays cached: its
+    # builds neither take nor give back device memory
+    import torch
+    import paper_2407_08330_amd as hdt
+    wl = inputs.make_workload(1)
+    for n in range(1024, 1024 + 20 * 4096, 4096):
+        level = np.full((1, n), 1, np.int32)
+        level[0, 0], parent = 0, np.zeros((1, n), np.int32)
+        parent[0, 0] = -1
+        hdt.hdt_build_layout(to_dev_i32(level), to_dev_i32(parent), tile_m=32, tile_n=32).destroy()
+    ids = to_dev_i32(wl.level), to_dev_i32(wl.parent)
+    hdt.hdt_build_layout(*ids).destroy()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    for _ in range(5):
+        lay = hdt.hdt_build_layout(*ids)
+        assert torch.cuda.mem_get_info()[0] == free
+        lay.destroy()
+        assert torch.cuda.mem_get_info()[0] == free
+    lay = hdt.hdt_build_layout(*ids)
+    compare_layout(oracle, lay, wl.level, wl.parent, 128, 64)
+    hdt.hdt_release_cached_memory()
