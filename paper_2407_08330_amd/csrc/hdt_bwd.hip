@@ -23,9 +23,9 @@
 //                  symmetry) the layout holds a second schedule, built from the same ids with the
 //                  parent and child kinds exchanged.
 // Both roles recompute the scores, which costs two extra contractions but keeps dQ out of HBM as fp32
-// partial sums.  At head size 128 the dK/dV role is split once more, into a dV role and a dK role (three
-// workgroups per tile): together they would need more registers than two waves per SIMD leave.  The two workgroups of a tile are neighbours in the launch order and run on the same XCD
-// at the same time.  That is what the pairing is for: the dQ role reads the tile's Q, dO rows and gathers
+// partial sums.  Where a call of head size 128 does not fill the chip, the dK/dV role is split once more, into a dV role
+// and a dK role (three workgroups per tile, see launch_roles).  The workgroups of a tile are neighbours in the launch
+// order and run on the same XCD at the same time.  That is what the pairing is for: the dQ role reads the tile's Q, dO rows and gathers
 // K, V rows of the neighbourhood, the dK/dV role reads the tile's K, V rows and gathers Q, dO rows of the
 // same neighbourhood, so each role finds in the XCD's L2 what the other (or a neighbouring pair) has just
 // fetched, and Q, K, V, dO come from HBM once per backward pass instead of once per role (measured: the
@@ -47,10 +47,6 @@ struct BwdCfg {
     // waits do not allow, and its few workgroups do not need the third (second) wave.
     template <typename G, bool INDEXED>
     static constexpr int WAVES = G::BM == 128 ? (D == 64 ? 3 : 2) - (INDEXED ? 1 : 0) : 2;
-    // At head size 128 the dK/dV role would need 128 accumulator registers per lane on top of 64 operand
-    // registers, which leaves one wave per SIMD.  It is split there into a dV role and a dK role (each
-    // recomputes the scores), so that every role fits two waves per SIMD.
-    static constexpr bool SPLIT_KV = D == 128;
 };
 
 // ---------------------------------------------------------------------------------------- D
@@ -234,7 +230,11 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
                                           __bf16 *__restrict__ dk, __bf16 *__restrict__ dv, int wave, int I, int bh,
                                           int b, float scale)
 {
-    using P = Pipe<D, BwdCfg<D>::S_DKV, true, G>;
+    // Head size 128 and both results: 128 accumulator and 64 operand registers leave 64 of the 256 a wave gets at two per
+    // SIMD.  What can be computed anew per entry or sub-block from the lane number is (LEAN): held in registers throughout
+    // the loop, as the compiler would have it, 30 to 56 registers did not fit.
+    constexpr bool LEAN = D == 128 && WHICH == 0;
+    using P = Pipe<D, BwdCfg<D>::S_DKV, true, G, LEAN>;
     using R = Ring<P>;
     constexpr int BM = G::BM, BN = G::BN, KB = G::KB;
     constexpr int ROWB = P::ROWB, KSTEPS = P::KSTEPS, DBLK = P::DBLK, S = P::S;
@@ -329,6 +329,9 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
         for (int kb = 0; kb < KB; kb++) {  // 32 query slots
             const int sb = wave * KB + kb;
             if (!((sub >> sb) & 1u)) continue;
+            const int ol = LEAN ? opaque(lane) : lane;
+            const RowLane rl = row_lane<P::CPR>(ol);
+            const TrLane tl = tr_lane<P::CPR>(ol);
             // element gq * 4 + e of a lane belongs to the query in slot kb * 32 + hf * 4 + gq * 8 + e
             f32x16 sacc, dpacc;
 #pragma unroll
@@ -427,9 +430,9 @@ __device__ __forceinline__ void zero_role(const HdtSchedule &s, __bf16 *__restri
     }
 }
 
-// INDEXED: s_tr covers visible positions only (HdtSchedule::own_index); the workgroups behind the grid of the roles
+// SPLIT: a dV and a dK role instead of one for both.  INDEXED: s_tr covers visible positions only (HdtSchedule::own_index); the workgroups behind the grid of the roles
 // write the zeros of the rows it leaves out.
-template <int D, typename G, bool INDEXED>
+template <int D, typename G, bool INDEXED, bool SPLIT>
 __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)) void k_bwd_bf16(
     HdtSchedule s, HdtSchedule s_tr, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k,
     const __bf16 *__restrict__ v, const float *__restrict__ lse, const __bf16 *__restrict__ d_o,
@@ -444,7 +447,7 @@ __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     // The roles tile different tensors (the same ones for self-attention): the workgroups of one tile follow each
     // other as far as both sides have that tile, the rest of the longer side comes behind them.
-    constexpr unsigned R = BwdCfg<D>::SPLIT_KV ? 3u : 2u;  // roles per tile: dQ, then dK/dV or dV, dK
+    constexpr unsigned R = SPLIT ? 3u : 2u;  // roles per tile: dQ, then dK/dV or dV, dK
     const unsigned nq = (unsigned)s.batch * heads * s.tr, nk = (unsigned)s_tr.batch * heads * s_tr.tr;
     if (INDEXED) {
         const unsigned roles = padded_grid(nq + (R - 1u) * nk, chunk);
@@ -473,7 +476,7 @@ __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)
         dq_role<D, G>(smem, s, q, k, v, lse, d_o, row_scalars, dq, wave, I, bh, b, scale);
     } else {
         const int I = lb % s_tr.tr, bh = lb / s_tr.tr, b = bh / heads;
-        if (!BwdCfg<D>::SPLIT_KV)
+        if (!SPLIT)
             dkv_role<D, G, 0, INDEXED>(smem, s_tr, q, k, v, d_o, row_scalars, dk, dv, wave, I, bh, b, scale);
         else if (role == 1u)
             dkv_role<D, G, 1, INDEXED>(smem, s_tr, q, k, v, d_o, row_scalars, dk, dv, wave, I, bh, b, scale);
@@ -484,18 +487,35 @@ __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)
 
 }  // namespace
 
+template <int D, typename G, bool INDEXED, bool SPLIT>
+static void launch_kernel(const HdtSchedule &s, const HdtSchedule &s_tr, const __bf16 *Q, const __bf16 *K, const __bf16 *V,
+                          const float *lse, const __bf16 *DO, const float2 *row_scalars, void *dq, void *dk, void *dv,
+                          int heads, float scale, hipStream_t st)
+{
+    const unsigned nq = (unsigned)s.batch * heads * s.tr, nk = (unsigned)s_tr.batch * heads * s_tr.tr;
+    constexpr unsigned roles = SPLIT ? 3u : 2u, zr = ZeroRows<D, G>::ROWS;
+    const unsigned zeros = INDEXED ? (unsigned)s_tr.batch * heads * (((unsigned)s_tr.own_stride + zr - 1u) / zr) : 0u;
+    const unsigned items = nq + (roles - 1u) * nk, chunk = xcd_chunk(items, roles * G::XCD_CHUNK, roles);
+    dim3 grid(padded_grid(items, chunk) + zeros), block(G::THREADS);
+    hipLaunchKernelGGL((k_bwd_bf16<D, G, INDEXED, SPLIT>), grid, block, 0, st, s, s_tr, Q, K, V, lse, DO, row_scalars,
+                       (__bf16 *)dq, (__bf16 *)dk, (__bf16 *)dv, heads, scale, chunk);
+}
+
+// At head size 128 one role for dK and dV is less work than two (the scores are computed twice instead of three times,
+// and the rows gathered), two are the shorter chain.  Two as long as their workgroups, two waves per SIMD, are all on the
+// chip at the same time; measured, one role / two: 32768 positions x 16 heads 230 / 261 us (64 x 32 tiles) and 264 / 307
+// (128 x 64); 3000 x 16 (2 samples x 8 heads) 33.4 / 33.2 and 37.1 / 37.0; 1000 x 4 heads 16.9 / 14.3.
 template <int D, typename G, bool INDEXED>
 static void launch_roles(const HdtSchedule &s, const HdtSchedule &s_tr, const __bf16 *Q, const __bf16 *K, const __bf16 *V,
                          const float *lse, const __bf16 *DO, const float2 *row_scalars, void *dq, void *dk, void *dv,
                          int heads, float scale, hipStream_t st)
 {
-    const unsigned nq = (unsigned)s.batch * heads * s.tr, nk = (unsigned)s_tr.batch * heads * s_tr.tr;
-    constexpr unsigned roles = BwdCfg<D>::SPLIT_KV ? 3u : 2u, zr = ZeroRows<D, G>::ROWS;
-    const unsigned zeros = INDEXED ? (unsigned)s_tr.batch * heads * (((unsigned)s_tr.own_stride + zr - 1u) / zr) : 0u;
-    const unsigned items = nq + (roles - 1u) * nk, chunk = xcd_chunk(items, roles * G::XCD_CHUNK, roles);
-    dim3 grid(padded_grid(items, chunk) + zeros), block(G::THREADS);
-    hipLaunchKernelGGL((k_bwd_bf16<D, G, INDEXED>), grid, block, 0, st, s, s_tr, Q, K, V, lse, DO, row_scalars, (__bf16 *)dq,
-                       (__bf16 *)dk, (__bf16 *)dv, heads, scale, chunk);
+    constexpr unsigned kResident = 256u * 8u / G::NW;  // workgroups on the chip at two waves per SIMD
+    const size_t nq = (size_t)s.batch * heads * s.tr, nk = (size_t)s_tr.batch * heads * s_tr.tr;
+    if (D == 128 && nq + 2 * nk <= kResident)
+        launch_kernel<D, G, INDEXED, D == 128>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st);
+    else
+        launch_kernel<D, G, INDEXED, false>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st);
 }
 
 template <typename G>

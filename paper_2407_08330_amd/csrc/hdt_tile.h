@@ -128,12 +128,22 @@ __device__ __forceinline__ void wg_barrier()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// A value the compiler cannot see through: what is derived from it is computed after this point.  Used on
+// the lane index in front of an epilogue, whose per-lane addresses would otherwise be hoisted above the
+// tile loop and held in registers throughout it.
+__device__ __forceinline__ int opaque(int x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // The row to gather for a key slot.  A slot without a key holds ~f, f being a position of the same sample that
 // some row of the tile may attend to: its rows are finite whenever the tile's real rows are, so the zero weights
 // the bitmap gives the slot never meet a non-finite operand (pad rows may hold anything).
 __device__ __forceinline__ int gather_row(int slot_value) { return slot_value ^ (slot_value >> 31); }
 
-template <int D, int S_, bool AUX, typename G>
+// LEAN: the gather's per-lane offsets are computed anew for every tile instead of being held in registers throughout
+template <int D, int S_, bool AUX, typename G, bool LEAN = false>
 struct Pipe {
     static constexpr int BM = G::BM, BN = G::BN, NW = G::NW;
     static constexpr int S = S_;                      // data stages in the ring
@@ -184,7 +194,7 @@ struct Pipe {
     __device__ __forceinline__ void issue_data(int stage, int ps) const
     {
         const int *pb = pos_buf(ps);
-        const int lr = lane / CPR, c = lane % CPR;  // row inside the wave-level load, chunk slot
+        const int ol = LEAN ? opaque(lane) : lane, lr = ol / CPR, c = ol % CPR;  // row inside the wave-level load, chunk slot
 #pragma unroll
         for (int i = 0; i < NI; i++) {
             const int r = wave * LPW + i * RPI + lr;
@@ -305,15 +315,6 @@ __device__ __forceinline__ void stage_own_rows(const P &p, const __bf16 *t, cons
         dma16(t, (uint32_t)rows.g[i] * P::ROWB + (uint32_t)((c ^ swz<P::CPR>(r)) * 16),
               p.smem_addr + lds_off + (uint32_t)((p.wave * 32 + i * P::RPI) * P::ROWB));
     }
-}
-
-// A value the compiler cannot see through: what is derived from it is computed after this point.  Used on
-// the lane index in front of an epilogue, whose per-lane addresses would otherwise be hoisted above the
-// tile loop and held in registers throughout it.
-__device__ __forceinline__ int opaque(int x)
-{
-    asm volatile("" : "+v"(x));
-    return x;
 }
 
 // Epilogue: a wave's 32 x D accumulator block, held transposed in C fragments (lane (row l%32, hf)

@@ -158,3 +158,13 @@ def test_buffer_cache_makes_room_for_the_sizes_in_use(oracle):
     lay = hdt.hdt_build_layout(*ids)
     compare_layout(oracle, lay, wl.level, wl.parent, 128, 64)
     hdt.hdt_release_cached_memory()
+
+
+@pytest.mark.parametrize("tile,heads", [((128, 64), 42), ((128, 64), 43), ((64, 32), 42), ((64, 32), 43)])
+def test_bwd_d128_around_the_size_where_its_roles_change(oracle, tile, heads):
+    # three roles per tile while 2048 waves hold them (512 workgroups of four, 1024 of two): 4 row tiles of 128 (8 of 64)
+    # per head, 42 heads are 504 (1008) workgroups, 43 are 516 (1032) and take two roles
+    level, parent = _padded([inputs.document_from_sections([[60, 50, 33], [80, 70, 41, 44], [30, 20, 48]], 500)], 500)
+    say(f"[bwd edges] d=128, {heads} heads, tile {tile}")
+    run_bwd_case(oracle, level, parent, heads, 128, "bf16", 61, tile=tile)
+    run_bwd_case(oracle, level, parent, heads, 128, "bf16", 62, tile=tile, edges=6)
