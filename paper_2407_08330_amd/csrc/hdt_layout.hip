@@ -562,6 +562,10 @@ struct KeyListArgs {
     int self_reset;  // the counters are a slot that must be zero again when the build has reported
 };
 
+struct KeyListLaunch {
+    KeyListArgs args[2];
+};
+
 // Workgroup barrier for data exchanged through LDS only: unlike __syncthreads() it does not wait for this
 // wave's global loads and stores (a store to HBM takes 2-3 us to be acknowledged).
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -610,7 +614,7 @@ __host__ inline size_t list_lds(int n, int tiles)
 }
 
 template <int kListThreads, int T>
-__global__ __launch_bounds__(kListThreads) void k_key_lists(KeyListArgs a)
+__device__ __forceinline__ void key_lists(const KeyListArgs &a)
 {
     constexpr int W = kListThreads / 64, RT = 128 / T;
     constexpr int kItemGroups = kLdsKeys / 64 + T, kRounds = (kItemGroups + W - 1) / W;  // groups of 64 packed keys
@@ -1086,6 +1090,22 @@ __global__ __launch_bounds__(kListThreads) void k_key_lists(KeyListArgs a)
     }
 }
 
+template <int kListThreads, int T>
+__global__ __launch_bounds__(kListThreads) void k_key_lists(KeyListArgs a)
+{
+    key_lists<kListThreads, T>(a);
+}
+
+// Two builds in one launch (the two schedules of a directed mask), blockIdx.y says which: twice the workgroups, so two of
+// them share a compute unit, which takes registers for 8 waves per SIMD (48 tiles of 64 rows per sample, 16 samples: two
+// launches 35 us, one with the registers of the kernel above 25.8, this one 22.5; a kernel of its own, because the
+// arguments read by index cost the single build 0.5 us).
+template <int kListThreads, int T>
+__global__ __launch_bounds__(kListThreads, 8) void k_key_lists_both(KeyListLaunch builds)
+{
+    key_lists<kListThreads, T>(builds.args[blockIdx.y]);
+}
+
 // ---- bitmaps of a windowed layout: exact evaluation of every candidate tile -----------------------
 // One candidate per workgroup iteration, a pair of waves (entry_bitmaps).  The keys of the tile are a
 // window of the key order; the positions behind its slots are also written to q_keys, which is what the
@@ -1415,6 +1435,47 @@ const char kHierarchyText[] =
     "level/parent arrays are not a valid hierarchy (level outside [-1, 32), parent outside [-1, n_pos), self-parent, "
     "pad with a parent, or pad parent)";
 
+// One launch for one key-list build, or for two that differ in their edges and arrays only.
+hipError_t launch_key_lists(const KeyListArgs *args, int builds, int batch, hipStream_t st)
+{
+    const KeyListArgs &a = args[0];
+    const bool small_wg = a.bm <= 64;
+    // tiles of up to 64 rows: two per workgroup, as long as the two sets of bitmaps fit the LDS beside the
+    // kernel's static arrays (documents of up to 64 K positions)
+    const bool pair = small_wg && list_lds(a.n, 2) <= 33 * 1024;
+    const size_t lds = list_lds(a.n, pair ? 2 : 1);
+    const dim3 grid((unsigned)batch * (pair ? (a.tr + 1) / 2 : a.tr), (unsigned)builds);
+#define LIST_LAUNCH(THREADS, TILES)                                                                                         \
+    do {                                                                                                                    \
+        if (lds > 33 * 1024) { /* with the kernel's static arrays: beyond the 64 KB a launch gets by default */             \
+            const void *f = builds == 2 ? (const void *)k_key_lists_both<THREADS, TILES> : (const void *)k_key_lists<THREADS, TILES>; \
+            const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);              \
+            if (e != hipSuccess) return e;                                                                                  \
+        }                                                                                                                   \
+        HdtTimer t("hdt_layout_key_lists", st);                                                                             \
+        if (builds == 2) {                                                                                                  \
+            const KeyListLaunch two = {{args[0], args[1]}};                                                                 \
+            hipLaunchKernelGGL((k_key_lists_both<THREADS, TILES>), grid, dim3(THREADS), lds, st, two);                      \
+        } else {                                                                                                            \
+            hipLaunchKernelGGL((k_key_lists<THREADS, TILES>), grid, dim3(THREADS), lds, st, a);                             \
+        }                                                                                                                   \
+    } while (0)
+    if (pair)
+        LIST_LAUNCH(1024, 2);
+    else if (small_wg)
+        LIST_LAUNCH(512, 1);
+    else
+        LIST_LAUNCH(1024, 1);
+#undef LIST_LAUNCH
+    return hipGetLastError();
+}
+
+// Two key-list builds that share a launch: the second one makes it.
+struct BothBuilds {
+    KeyListArgs args[2];
+    int n = 0;
+};
+
 }  // namespace
 
 // What a deferred build's report says, read at most once per layout.
@@ -1631,7 +1692,7 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_release_cache
 }
 
 static hdt_status_t build_one(const int32_t *d_level, const int32_t *d_parent, int32_t batch, int32_t n_pos,
-                              const hdt_layout_opts_t *opts, int edges, void *stream, hdt_layout_t **out);
+                              const hdt_layout_opts_t *opts, int edges, void *stream, BothBuilds *both, hdt_layout_t **out);
 
 static int swap_up_down(int edges)
 {
@@ -1649,24 +1710,49 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_layout(
     int edges = opts && opts->edges ? opts->edges : HDT_EDGE_ALL;
     if (edges & ~HDT_EDGE_ALL) return hdt_fail(HDT_ERR_INVALID_ARG, "hdt_build_layout: edges = %d", edges);
     hdt_layout_t *L = nullptr;
-    hdt_status_t st = build_one(d_level, d_parent, batch, n_pos, opts, edges, stream, &L);
-    if (st != HDT_OK) return st;
-    if (swap_up_down(edges) != edges) {
-        // a directed mask: the backward pass also needs the schedule of its transpose, which is the same
-        // construction with the parent and child kinds exchanged
-        st = build_one(d_level, d_parent, batch, n_pos, opts, swap_up_down(edges), stream, &L->transposed);
-        if (st != HDT_OK) {
-            (void)hdt_layout_destroy(L);
-            return st;
-        }
-        L->device_bytes += L->transposed->device_bytes;
+    hdt_status_t st;
+    if (swap_up_down(edges) == edges) {
+        st = build_one(d_level, d_parent, batch, n_pos, opts, edges, stream, nullptr, &L);
+        if (st == HDT_OK) *out = L;
+        return st;
     }
+    // A directed mask: the backward pass also needs the schedule of its transpose, which is the same
+    // construction with the parent and child kinds exchanged.  Key lists: both in one launch, neither waited for before
+    // both are enqueued.
+    const bool lists = batch > 0 && n_pos > 0 && !(opts && (opts->windowed || opts->force_dense));
+    const bool deferred = opts && opts->deferred;
+    for (int attempt = 0; attempt < 2; attempt++) {
+        BothBuilds builds, *both = lists && attempt == 0 ? &builds : nullptr;
+        st = build_one(d_level, d_parent, batch, n_pos, opts, edges, stream, both, &L);
+        if (st != HDT_OK) return st;
+        st = build_one(d_level, d_parent, batch, n_pos, opts, swap_up_down(edges), stream, both, &L->transposed);
+        if (st == HDT_OK && both && !deferred) {
+            st = hdt_layout_resolve(L, true);
+            if (st == HDT_ERR_HIERARCHY) st = hdt_fail(st, "hdt_build_layout: %s", kHierarchyText);
+            if (st == HDT_ERR_SHAPE && !(opts && opts->capacity > 0)) {
+                // the guess of the arrays' sizes was too small (the exact number is known now): one after the other
+                (void)hdt_layout_destroy(L);
+                continue;
+            }
+            if (st == HDT_ERR_SHAPE)
+                st = hdt_fail(st, "hdt_build_layout: the schedule needs %lld list entries, opts->capacity is %lld",
+                              (long long)std::max(L->entries_needed, L->transposed->entries_needed), (long long)opts->capacity);
+        }
+        break;
+    }
+    if (st != HDT_OK) {
+        (void)hdt_layout_destroy(L);
+        return st;
+    }
+    L->device_bytes += L->transposed->device_bytes;
     *out = L;
     return HDT_OK;
 }
 
+// `both`: the kernel is launched with that of the other build, by the second of the two calls; the layout then comes back
+// with its report not yet looked at, as from a deferred build.
 static hdt_status_t build_one(const int32_t *d_level, const int32_t *d_parent, int32_t batch, int32_t n_pos,
-                              const hdt_layout_opts_t *opts, int edges, void *stream, hdt_layout_t **out)
+                              const hdt_layout_opts_t *opts, int edges, void *stream, BothBuilds *both, hdt_layout_t **out)
 {
     *out = nullptr;
     if (batch < 0 || n_pos < 0) return hdt_fail(HDT_ERR_INVALID_ARG, "hdt_build_layout: negative size");
@@ -1843,21 +1929,12 @@ static hdt_status_t build_one(const int32_t *d_level, const int32_t *d_parent, i
                                q.c_cnt, p.level_copy, p.parent_copy, q.q_sub, q.bits_rm,
                                slot_counters ? slot_counters : p.counters, report, p.report_copy, ticket,
                                slot_counters != nullptr};
-                const bool small_wg = bm <= 64;
-                // tiles of up to 64 rows: two per workgroup, as long as the two sets of bitmaps fit the LDS beside the
-                // kernel's static arrays (documents of up to 64 K positions)
-                const bool pair = small_wg && list_lds(n, 2) <= 33 * 1024;
-                const size_t lds = list_lds(n, pair ? 2 : 1);
-                if (lds > 33 * 1024)  // with the kernel's static arrays: beyond the 64 KB a launch gets by default
-                    BUILD_TRY(hipFuncSetAttribute(small_wg ? (const void *)k_key_lists<512, 1> : (const void *)k_key_lists<1024, 1>,
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-                HdtTimer t("hdt_layout_key_lists", st);
-                if (pair)
-                    hipLaunchKernelGGL((k_key_lists<1024, 2>), dim3((unsigned)B * ((tr + 1) / 2)), dim3(1024), lds, st, ka);
-                else if (small_wg)
-                    hipLaunchKernelGGL((k_key_lists<512, 1>), dim3((unsigned)B * tr), dim3(512), lds, st, ka);
-                else
-                    hipLaunchKernelGGL((k_key_lists<1024, 1>), dim3((unsigned)B * tr), dim3(1024), lds, st, ka);
+                if (both) {
+                    both->args[both->n++] = ka;
+                    if (both->n == 2) BUILD_TRY(launch_key_lists(both->args, 2, B, st));
+                } else {
+                    BUILD_TRY(launch_key_lists(&ka, 1, B, st));
+                }
             }
             if (windowed) {
                 const unsigned grid = (unsigned)(cap < 2048 ? (cap > 0 ? cap : 1) : 2048);
@@ -1867,7 +1944,7 @@ static hdt_status_t build_one(const int32_t *d_level, const int32_t *d_parent, i
                                    q.bits_rm, q.c_cnt, q.q_sub);
             }
             BUILD_TRY(hipGetLastError());
-            if (deferred) {
+            if (deferred || both) {
                 // The layout goes out as it is.  What the device reports (through the same word of pinned host
                 // memory, and a copy in the layout's own memory) is read by hdt_layout_resolve, when someone asks.
                 adopt(q, cap);

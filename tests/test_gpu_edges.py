@@ -168,3 +168,28 @@ def test_bwd_d128_around_the_size_where_its_roles_change(oracle, tile, heads):
     say(f"[bwd edges] d=128, {heads} heads, tile {tile}")
     run_bwd_case(oracle, level, parent, heads, 128, "bf16", 61, tile=tile)
     run_bwd_case(oracle, level, parent, heads, 128, "bf16", 62, tile=tile, edges=6)
+
+
+def test_directed_masks_both_schedules_from_one_launch(oracle):
+    # the two builds of a directed mask share a launch: a guess of the arrays' sizes that is too small (many keys per row
+    # after a small document) is made good, a capacity that is too small and invalid ids are refused, waiting or deferred
+    import paper_2407_08330_amd as hdt
+    wl = inputs.make_workload(1)
+    n = 4096
+    level, parent = np.ones((1, n), np.int32), np.zeros((1, n), np.int32)
+    level[0, 0], parent[0, 0] = 0, -1
+    for deferred in (False, True):
+        hdt.hdt_build_layout(to_dev_i32(wl.level), to_dev_i32(wl.parent)).destroy()
+        lay = hdt.hdt_build_layout(to_dev_i32(level), to_dev_i32(parent), edges=6, deferred=deferred)
+        assert lay.status() >= 0
+        compare_layout(oracle, lay, level, parent, 128, 64, edges=6)
+        compare_layout(oracle, lay.transposed(), level, parent, 128, 64, edges=3)
+    for name, ids, kw in (("HDT_ERR_SHAPE", (level, parent), dict(capacity=100)),
+                          ("HDT_ERR_HIERARCHY", (level, np.where(parent < 0, -1, n).astype(np.int32)), {})):
+        with pytest.raises(hdt.HdtError) as e:
+            hdt.hdt_build_layout(to_dev_i32(ids[0]), to_dev_i32(ids[1]), edges=6, **kw)
+        assert e.value.name == name and "deferred" not in str(e.value)
+        lay = hdt.hdt_build_layout(to_dev_i32(ids[0]), to_dev_i32(ids[1]), edges=6, deferred=True, **kw)
+        with pytest.raises(hdt.HdtError) as e:
+            lay.status()
+        assert e.value.name == name
