@@ -33,11 +33,16 @@ struct FwdCfg {
     static constexpr int WAVES = (D == 64) ? 4 : 2;  // waves per SIMD the register budget allows
 };
 
-// One key tile for one wave: its sub-blocks A0 (keys 0..31) and A1 (keys 32..63) of the tile, as selected.
-template <int D, bool A0, bool A1>
+// One key tile for one wave: its sub-blocks A0 (keys 0..31) and A1 (keys 32..63) of the tile, as selected.  `full`: bit 0
+// (1) says that all pairs of A0 (A1) are allowed.  With WHOLE the 16 lane masks of such a sub-block are neither loaded
+// nor applied: in dense cross-attention, where the exponentials and the rest of the vector work are what bounds the
+// kernel, that is the rule (512 x 8192, tokens visible: 81.9 -> 69.7 us; a branch around the selects, because a second
+// path without them takes 53 registers more than there are).  A hierarchical mask hardly has any, and its forward is
+// 0.2 us of 45 slower with the branches.
+template <int D, bool WHOLE, bool A0, bool A1>
 __device__ __forceinline__ void fwd_step(const char *sK, const char *sV, const RowLane &rl, const TrLane &tl,
                                          const bf16x8 (&qf)[D / 16], f32x16 (&oacc)[D / 32], float &m_ref,
-                                         float &l_part, const unsigned long long *mk, int xlane, float scale_log2)
+                                         float &l_part, const unsigned long long *mk, uint32_t full, int xlane, float scale_log2)
 {
     constexpr int ROWB = 2 * D, KSTEPS = D / 16, DBLK = D / 32;
     // S^T sub-blocks = K[kb*32 .. +32) . Q^T, masked
@@ -51,12 +56,12 @@ __device__ __forceinline__ void fwd_step(const char *sK, const char *sV, const R
     }
     float mx = -INFINITY;
     if (A0) {
-        apply_mask(s0, mk, -INFINITY);
+        if (!WHOLE || !(full & 1u)) apply_mask(s0, mk, -INFINITY);
 #pragma unroll
         for (int e = 0; e < 16; e += 2) mx = fmaxf(mx, fmaxf(s0[e], s0[e + 1]));
     }
     if (A1) {
-        apply_mask(s1, mk + 16, -INFINITY);
+        if (!WHOLE || !(full & 2u)) apply_mask(s1, mk + 16, -INFINITY);
 #pragma unroll
         for (int e = 0; e < 16; e += 2) mx = fmaxf(mx, fmaxf(s1[e], s1[e + 1]));
     }
@@ -112,7 +117,7 @@ __device__ __forceinline__ void fwd_step(const char *sK, const char *sV, const R
     }
 }
 
-template <int D, typename G>
+template <int D, typename G, bool WHOLE>
 __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
     HdtSchedule s, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
     __bf16 *__restrict__ o, float *__restrict__ lse, int heads, float scale_log2, unsigned chunk)
@@ -187,13 +192,14 @@ __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
         // per combination, so that the two sub-blocks' loads, MFMA chains and exponentials interleave
         const bool act0 = (sub >> (wave * KB)) & 1u, act1 = KB > 1 && ((sub >> (wave * KB + 1)) & 1u);
         if (!(act0 || act1)) continue;
+        const uint32_t full = sub >> (16 + wave * KB);  // bit: all pairs of the sub-block are allowed
         const unsigned long long *mk = s.bits_rm + ((size_t)bidx * G::NSUB + wave * KB) * 16;
         if (KB > 1 && act0 && act1)
-            fwd_step<D, true, true>(sK, sV, rl, tl, qf, oacc, m_ref, l_part, mk, xlane, scale_log2);
+            fwd_step<D, WHOLE, true, true>(sK, sV, rl, tl, qf, oacc, m_ref, l_part, mk, full, xlane, scale_log2);
         else if (act0)
-            fwd_step<D, true, false>(sK, sV, rl, tl, qf, oacc, m_ref, l_part, mk, xlane, scale_log2);
+            fwd_step<D, WHOLE, true, false>(sK, sV, rl, tl, qf, oacc, m_ref, l_part, mk, full, xlane, scale_log2);
         else if (KB > 1)
-            fwd_step<D, false, true>(sK, sV, rl, tl, qf, oacc, m_ref, l_part, mk, xlane, scale_log2);
+            fwd_step<D, WHOLE, false, true>(sK, sV, rl, tl, qf, oacc, m_ref, l_part, mk, full, xlane, scale_log2);
     }
 
     // epilogue: O = acc / l, LSE = ln(sum exp) = ln2 * (m_ref + log2 l); O leaves through LDS as full rows
@@ -212,17 +218,17 @@ __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
 
 }  // namespace
 
-template <typename G>
+template <int D, typename G>
 static void launch_fwd(const HdtSchedule &s, const void *q, const void *k, const void *v, void *o, float *lse,
-                       int heads, int head_dim, float scale_log2, hipStream_t st)
+                       int heads, float scale_log2, hipStream_t st)
 {
     const unsigned items = (unsigned)((size_t)s.batch * heads * s.tr), chunk = xcd_chunk(items, G::XCD_CHUNK, 1u);
     dim3 grid(padded_grid(items, chunk)), block(G::THREADS);
-    if (head_dim == 64)
-        hipLaunchKernelGGL((k_fwd_bf16<64, G>), grid, block, 0, st, s, (const __bf16 *)q, (const __bf16 *)k,
+    if (s.row_flag == nullptr)  // the rectangle of a cross-attention layout: whole sub-blocks are the rule
+        hipLaunchKernelGGL((k_fwd_bf16<D, G, true>), grid, block, 0, st, s, (const __bf16 *)q, (const __bf16 *)k,
                            (const __bf16 *)v, (__bf16 *)o, lse, heads, scale_log2, chunk);
     else
-        hipLaunchKernelGGL((k_fwd_bf16<128, G>), grid, block, 0, st, s, (const __bf16 *)q, (const __bf16 *)k,
+        hipLaunchKernelGGL((k_fwd_bf16<D, G, false>), grid, block, 0, st, s, (const __bf16 *)q, (const __bf16 *)k,
                            (const __bf16 *)v, (__bf16 *)o, lse, heads, scale_log2, chunk);
 }
 
@@ -232,9 +238,11 @@ hdt_status_t hdt_launch_fwd_bf16(const HdtSchedule &s, const void *q, const void
     const float scale_log2 = scale * LOG2E;
     HdtTimer t(head_dim == 64 ? "hdt_fwd_bf16_d64" : "hdt_fwd_bf16_d128", st);
     if (s.bm == 64)
-        launch_fwd<Geo<64, 32>>(s, q, k, v, o, lse, heads, head_dim, scale_log2, st);
+        head_dim == 64 ? launch_fwd<64, Geo<64, 32>>(s, q, k, v, o, lse, heads, scale_log2, st)
+                       : launch_fwd<128, Geo<64, 32>>(s, q, k, v, o, lse, heads, scale_log2, st);
     else
-        launch_fwd<Geo<128, 64>>(s, q, k, v, o, lse, heads, head_dim, scale_log2, st);
+        head_dim == 64 ? launch_fwd<64, Geo<128, 64>>(s, q, k, v, o, lse, heads, scale_log2, st)
+                       : launch_fwd<128, Geo<128, 64>>(s, q, k, v, o, lse, heads, scale_log2, st);
     HDT_HIP_TRY(hipGetLastError());
     return HDT_OK;
 }
