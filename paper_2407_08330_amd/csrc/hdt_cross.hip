@@ -612,8 +612,8 @@ size_t hdt_cross_compact_workspace_bytes(const hdt_layout_t *l, int heads, int h
 // ---- key lists cut into pieces ---------------------------------------------------------------------------
 // How many pieces for this many heads: enough row tiles for a thousand workgroups (measured on 512 decoder rows x
 // 8192 keys x 48 heads: forward kernel 201 us uncut, 91 in 4 pieces, 85 in 8, 82 in 16 where combining the pieces
-// costs more than that gains), pieces of at least 8 entries, and none at all where the backward works on compact
-// tensors (few keys, short lists).
+// costs more than that gains), pieces of at least 8 entries, and none at all where the transposed schedule tiles the
+// visible positions only (few keys, short lists).
 int hdt_cross_pieces(const hdt_layout_t *l, int heads)
 {
     if (!l->cross || l->compact || !l->cross_split_range[0] || heads <= 0) return 1;

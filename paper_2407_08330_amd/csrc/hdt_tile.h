@@ -7,7 +7,7 @@
 // block diagonal, so with four waves a wave often waits through entries that hold nothing for its rows;
 // the finer shape loses fewer such slots and skips more of the mask, but walks more entries and needs
 // twice the workgroups.  Measured, the two are within a few percent of each other at head size 64 and the
-// finer one is ~5-10 % ahead at head size 128, before the doubled cost of building its layout.
+// finer one is ~5-10 % ahead at head size 128; its layout takes 1-4 us longer to build.
 //
 // The gather uses the CDNA direct-to-LDS loads (global_load_lds_*: every lane supplies a global
 // address, the 64 results land in LDS at M0 + lane*size) into a ring of S stages, so that several
