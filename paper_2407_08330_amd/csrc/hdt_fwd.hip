@@ -183,8 +183,16 @@ __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
         if (i + 1 < n) {
             sub_next = subs[i + 1];
         }
+        // The lines of this entry's masks, on their way while the wave waits for the rows (us per launch, event-bracketed:
+        // 128 x 64 tiles at 8192 positions 47.1 -> 45.4, 4096 44.9 -> 43.4, 2047 15.6 -> 15.0, 1000 12.2 -> 11.1; 64 x 32 at
+        // 8192 45.9 -> 45.6; masks that cost no loads at all would give 43.5 at the first size).  Holding the masks
+        // themselves in scalar registers over the barrier spills.  Not where whole sub-blocks are the rule, and not in
+        // the backward, whose three waves per SIMD hide the loads (64 x 32: 83.4 -> 84.4, dense rectangle 206 -> 211).
+        MaskTouch<KB * 16> masks;
+        if (!WHOLE) masks.request(s.bits_rm + ((size_t)bidx * G::NSUB + wave * KB) * 16);
         R::top(i, n);
         wg_barrier();
+        if (!WHOLE) masks.arrived();
         R::advance(pipe, i, n);
         const char *sK = pipe.tile_a(i % S), *sV = pipe.tile_b(i % S);
 

@@ -411,4 +411,23 @@ __device__ __forceinline__ void apply_mask(f32x16 &x, const unsigned long long *
     for (int e = 0; e < 16; e++) x[e] = __builtin_amdgcn_inverse_ballot_w64(cm[e]) ? x[e] : fill;
 }
 
+// Asking for an entry's masks ahead of their use: one word of each 64-byte line of a wave's masks (WORDS 64-bit masks),
+// requested in front of the wait for the entry's rows and looked at behind the barrier.  apply_mask's own loads then find
+// the lines in the scalar cache; without this they are requested between two contractions and waited for on the spot, and
+// they mostly come from beyond the L2 (a line is read by the few heads of a sample that share an XCD).
+template <int WORDS>
+struct MaskTouch {
+    uint32_t w[WORDS / 8];
+    __device__ __forceinline__ void request(const unsigned long long *mask)
+    {
+#pragma unroll
+        for (int i = 0; i < WORDS / 8; i++) w[i] = as_const(reinterpret_cast<const uint32_t *>(mask))[i * 16];
+    }
+    __device__ __forceinline__ void arrived()
+    {
+#pragma unroll
+        for (int i = 0; i < WORDS / 8; i++) asm volatile("" ::"s"(w[i]));
+    }
+};
+
 }  // namespace hdt_tile
