@@ -5,6 +5,7 @@
 #include <memory>
 #include <stdint.h>
 
+#include <atomic>
 #include <string>
 #include <vector>
 
@@ -121,8 +122,9 @@ struct hdt_layout {
     int32_t *sort_hist, *sort_counters;
     const int32_t *level_copy, *parent_copy;
     // A deferred build (hdt_layout_opts_t.deferred) has not looked at the device's report yet: whether the
-    // hierarchy was valid and how many list entries it needed.  hdt_layout_resolve reads it (once).
-    mutable bool pending;
+    // hierarchy was valid and how many list entries it needed.  hdt_layout_resolve reads it (once); cleared when the
+    // outcome stands in the fields below, which nobody writes from then on.
+    mutable std::atomic<bool> pending;
     mutable hdt_status_t build_status;     // what the report said, once it has been read
     mutable int64_t entries_needed;        // list entries the build needed (-1: not known yet)
     mutable char build_error[320];         // text of build_status
@@ -144,8 +146,10 @@ hdt_status_t hdt_fail(hdt_status_t st, const char *fmt, ...);
 bool hdt_layout_ok(const hdt_layout_t *l);
 // Reads the report of a deferred build: with `wait` it returns once the report is in (it waits for the build
 // kernel, not for the stream), without it only looks.  Returns the build's status as far as it is known (HDT_OK
-// while nothing is known); covers the transposed schedule a directed mask brings.  (hdt_layout.hip)
-hdt_status_t hdt_layout_resolve(const hdt_layout_t *l, bool wait);
+// while nothing is known); covers the transposed schedule a directed mask brings.  A waiting caller holds no lock, so
+// calls on other layouts pass.  `built_on`: the stream of the build, where that is known to exist still; should no
+// report come within the time limit, it is drained (NULL: the whole device).  (hdt_layout.hip)
+hdt_status_t hdt_layout_resolve(const hdt_layout_t *l, bool wait, const hipStream_t *built_on = nullptr);
 hdt_status_t hdt_layout_ensure_kperm(const hdt_layout_t *l);  // sorts s.kperm if the build did not (waits for the device) (hdt_layout.hip)
 hdt_status_t hdt_layout_stats(const hdt_layout_t *l);  // fills h_stats once (waits for the device) (hdt_layout.hip)
 // What the next owner of a released buffer has to wait for.  A stream on which layouts are also built is only

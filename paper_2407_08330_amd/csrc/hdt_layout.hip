@@ -1478,55 +1478,58 @@ struct BothBuilds {
 
 }  // namespace
 
-// What a deferred build's report says, read at most once per layout.
-static hdt_status_t resolve_one(const hdt_layout_t *L, bool wait)
+// What the report of a build says that went out with it unread; recorded at most once per layout.
+static hdt_status_t resolve_one(const hdt_layout_t *L, bool wait, const hipStream_t *built_on)
 {
-    static std::mutex resolve_mutex;
-    std::lock_guard<std::mutex> lk(resolve_mutex);
-    if (L->pending) {
+    if (L->pending.load(std::memory_order_acquire)) {
         unsigned long long word = __atomic_load_n(L->report, __ATOMIC_ACQUIRE);
         bool have = (uint32_t)(word >> 40) == L->ticket;
         if (!have && !wait) return HDT_OK;
+        // No lock is held here: a build behind a busy stream keeps its caller waiting and nobody else.
         if (!have) have = wait_for_report(L->report, L->ticket, L->ticket_before, &word);
         if (!have) {
             // the slot has gone to a later build (or nothing came for 10 s): the copy in the layout's own memory
             int dev = 0;
             HDT_HIP_TRY(hipGetDevice(&dev));
             if (dev != L->device) HDT_HIP_TRY(hipSetDevice(L->device));
-            hipError_t e = hipDeviceSynchronize();
+            hipError_t e = built_on ? hipStreamSynchronize(*built_on) : hipDeviceSynchronize();
             if (e == hipSuccess) e = hipMemcpy(&word, L->report_dev, sizeof(word), hipMemcpyDeviceToHost);
             if (dev != L->device) (void)hipSetDevice(dev);
             if (e != hipSuccess) return hdt_fail(HDT_ERR_HIP, "hdt_layout_resolve: %s", hipGetErrorString(e));
             if ((uint32_t)(word >> 40) != L->ticket)
                 return hdt_fail(HDT_ERR_HIP, "hdt_layout_resolve: the build kernel finished without its report");
         }
-        const int64_t need = (int64_t)(word & 0xffffffffu);
-        L->entries_needed = need;
-        if ((word >> 39) & 1u) {
-            L->build_status = HDT_ERR_HIERARCHY;
-            snprintf(L->build_error, sizeof(L->build_error), "deferred hdt_build_layout: %s", kHierarchyText);
-        } else if (need > L->capacity) {
-            L->build_status = HDT_ERR_SHAPE;
-            snprintf(L->build_error, sizeof(L->build_error),
-                     "deferred hdt_build_layout: the schedule needs %lld list entries, the layout holds %lld "
-                     "(build again with opts->capacity)", (long long)need, (long long)L->capacity);
-        } else {
-            L->n_entries = need;
+        static std::mutex record_mutex;
+        std::lock_guard<std::mutex> lk(record_mutex);
+        if (L->pending.load(std::memory_order_relaxed)) {
+            const int64_t need = (int64_t)(word & 0xffffffffu);
+            L->entries_needed = need;
+            if ((word >> 39) & 1u) {
+                L->build_status = HDT_ERR_HIERARCHY;
+                snprintf(L->build_error, sizeof(L->build_error), "deferred hdt_build_layout: %s", kHierarchyText);
+            } else if (need > L->capacity) {
+                L->build_status = HDT_ERR_SHAPE;
+                snprintf(L->build_error, sizeof(L->build_error),
+                         "deferred hdt_build_layout: the schedule needs %lld list entries, the layout holds %lld "
+                         "(build again with opts->capacity)", (long long)need, (long long)L->capacity);
+            } else {
+                L->n_entries = need;
+            }
+            if (!((word >> 39) & 1u)) {
+                std::lock_guard<std::mutex> lk2(g_pool_mutex);
+                g_capacity_hint = need;
+            }
+            L->pending.store(false, std::memory_order_release);
         }
-        if (!((word >> 39) & 1u)) {
-            std::lock_guard<std::mutex> lk2(g_pool_mutex);
-            g_capacity_hint = need;
-        }
-        L->pending = false;
     }
     if (L->build_status != HDT_OK) return hdt_fail(L->build_status, "%s", L->build_error);
     return HDT_OK;
 }
 
-hdt_status_t hdt_layout_resolve(const hdt_layout_t *L, bool wait)
+hdt_status_t hdt_layout_resolve(const hdt_layout_t *L, bool wait, const hipStream_t *built_on)
 {
-    if (hdt_status_t st = resolve_one(L, wait)) return st;
-    if (L->transposed) return resolve_one(L->transposed, wait);
+    if (hdt_status_t st = resolve_one(L, wait, built_on)) return st;
+    if (L->transposed) return resolve_one(L->transposed, wait, built_on);
     return HDT_OK;
 }
 
@@ -1727,7 +1730,8 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_layout(
         if (st != HDT_OK) return st;
         st = build_one(d_level, d_parent, batch, n_pos, opts, swap_up_down(edges), stream, both, &L->transposed);
         if (st == HDT_OK && both && !deferred) {
-            st = hdt_layout_resolve(L, true);
+            const hipStream_t built_on = (hipStream_t)stream;
+            st = hdt_layout_resolve(L, true, &built_on);
             if (st == HDT_ERR_HIERARCHY) st = hdt_fail(st, "hdt_build_layout: %s", kHierarchyText);
             if (st == HDT_ERR_SHAPE && !(opts && opts->capacity > 0)) {
                 // the guess of the arrays' sizes was too small (the exact number is known now): one after the other

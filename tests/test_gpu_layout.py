@@ -414,3 +414,38 @@ def test_layout_empty_inputs():
         lay = hdt.hdt_build_layout(z, z.clone())
         info = lay.info()
         assert info["n_tiles"] == 0 and info["nnz"] == 0 and info["batch"] == shape[0]
+
+
+@pytest.mark.parametrize("edges", [6, 7])
+def test_attention_calls_pass_while_another_thread_waits_for_its_build(edges):
+    # a waiting build (both schedules of a directed mask, and one schedule) behind a busy stream keeps its own thread:
+    # calls of this one, on a layout and a stream of its own, come back meanwhile
+    import threading
+    import time
+    import torch
+    import paper_2407_08330_amd as hdt
+    wl = inputs.make_workload(1)
+    ids = to_dev_i32(wl.level), to_dev_i32(wl.parent)
+    mine = hdt.hdt_build_layout(*ids)
+    q, k, v = (torch.randn((1, 2, wl.n_pos, 64), device="cuda").bfloat16() for _ in range(3))
+    o, lse = hdt.hdt_attn_fwd(mine, q, k, v, 0.125)
+    a = torch.zeros((8192, 8192), dtype=torch.bfloat16, device="cuda")
+    busy, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(busy):
+        c = torch.mm(a, a)   # (the library's first call, outside the time that counts)
+        torch.cuda.synchronize()
+        for _ in range(1000):   # about 0.7 s
+            torch.mm(a, a, out=c)
+    built = []
+    builder = threading.Thread(target=lambda: built.append(hdt.hdt_build_layout(*ids, edges=edges, stream=busy)))
+    builder.start()
+    time.sleep(0.05)
+    for _ in range(3):
+        hdt.hdt_attn_fwd(mine, q, k, v, 0.125, o=o, lse=lse, stream=other)
+    time.sleep(0.02)   # a thread whose build has come back is gone by then
+    waiting = builder.is_alive()
+    builder.join(timeout=60)
+    torch.cuda.synchronize()
+    assert built and built[0].status() > 0
+    assert waiting, "the attention calls came back only when the other thread's build had"
