@@ -42,8 +42,8 @@ __device__ __forceinline__ int2 my_share(int n, int shares)  // [first, last) of
 // parent[i] = the nearest earlier position whose level is level[i] - 1 (none: -1).  Inside a wave by ballots, across
 // the waves of a chunk and in front of it through LDS (the last position of every level).  The positions in front of a
 // share are read backwards until every level that somebody still misses has been seen.
-__global__ __launch_bounds__(kOrdThreads) void k_parents_from_levels(const int32_t *__restrict__ level, int n, int shares,
-                                                                      int32_t *__restrict__ parent)
+// With one share `parent` may be `level`: a position's level is read by its own thread alone, before its parent is written.
+__global__ __launch_bounds__(kOrdThreads) void k_parents_from_levels(const int32_t *level, int n, int shares, int32_t *parent)
 {
     __shared__ int s_last[kOrdWaves][32];  // last position of each level in each wave of the chunk (-1: none)
     __shared__ int s_carry[32];            // last position of each level in front of the chunk
@@ -368,8 +368,10 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_parents_from_
     if ((int64_t)batch * n_pos > (1LL << 30)) return hdt_fail(HDT_ERR_SHAPE, "hdt_parents_from_levels: batch * n_pos too large");
     hipStream_t st = (hipStream_t)stream;
     HdtTimer t("hdt_hpe_parents_from_levels", st);
-    hipLaunchKernelGGL(k_parents_from_levels, dim3((unsigned)batch * hpe_shares(n_pos)), dim3(kOrdThreads), 0, st, d_level, n_pos,
-                       hpe_shares(n_pos), d_parent);
+    // in place: the levels in front of a share would be gone by the time it reads them, so one workgroup has the whole sample
+    const int shares = d_parent == d_level ? 1 : hpe_shares(n_pos);
+    hipLaunchKernelGGL(k_parents_from_levels, dim3((unsigned)batch * shares), dim3(kOrdThreads), 0, st, d_level, n_pos, shares,
+                       d_parent);
     HDT_HIP_TRY(hipGetLastError());
     return HDT_OK;
 }
