@@ -12,7 +12,6 @@
 // token in its sentence), so the encoding of a position is the sum of L rows of a small table that stays in
 // L2: the add is then bound by reading and writing x once, not by 2*L*d_model sine evaluations per position.
 // Indices beyond the table are evaluated directly.
-#include <limits.h>
 #include <math.h>
 
 #include <algorithm>
@@ -29,8 +28,15 @@ constexpr int kBack = 8;        // groups of 64 positions a wave has in flight w
 // has to know about the positions in front of its share it finds by reading them, all waves together.  That reads up
 // to `shares` / 2 times the sample's ids (a few hundred KB, out of L2), and takes less time than carrying the state from
 // chunk to chunk in one workgroup per sample, whose chunks follow one another (8192 positions x 4 samples: parents
-// 31 -> 6.7 us, ordinals 20.8 -> 8.2; 32768 positions, 1 sample: 126 -> 11 and 78 -> 18).
-__host__ inline int hpe_shares(int n) { return std::min((n + kOrdThreads - 1) / kOrdThreads, kMaxShares); }
+// 31 -> 6.7 us, ordinals 20.8 -> 8.2; 32768 positions, 1 sample: 126 -> 11 and 78 -> 18), as long as the workgroups of all
+// samples are on the chip at the same time, one per compute unit: further ones only wait, and read more.  8192 positions,
+// us for parents / index vectors, one workgroup per sample - a share per 1024 positions - at most 256 workgroups:
+// 64 samples 31 / 29 - 12 / 22 - 8.6 / 16; 256 samples 32 / 47 - 46 / 80 - 20 / 41; 512 samples 61 / 89 - 91 / 152 - 37 / 63.
+constexpr int kOnChip = 256;
+__host__ inline int hpe_shares(int batch, int n)
+{
+    return std::min({(n + kOrdThreads - 1) / kOrdThreads, kMaxShares, std::max(kOnChip / batch, 1)});
+}
 __device__ __forceinline__ int2 my_share(int n, int shares)  // [first, last) of workgroup blockIdx.x = b * shares + k
 {
     const int chunks = (n + kOrdThreads - 1) / kOrdThreads, per = (chunks + shares - 1) / shares;
@@ -120,8 +126,16 @@ __global__ __launch_bounds__(kOrdThreads) void k_parents_from_levels(const int32
 //     + (its offset inside its run).
 // Roots (parent -1) count as children of one virtual parent, n.  Pads and positions past the share are a group of their
 // own (-1), which only serves to end the runs before them.  The counters cover a window of the parents at a time: one
-// window up to kOrdWindow positions, as many LDS words as that takes; beyond, the windows in which parents of the share lie.
+// window up to kOrdWindow positions, as many LDS words as that takes; beyond, the windows in which parents of the share
+// lie, each of which reads the positions in front of the share again.  In a document these are the share's own window and
+// the first one; parents anywhere are in all of them, and the time would grow with the square of the length.  So with
+// several windows the kernel is used up to kMaxWindowed positions and with at least kMinShares shares (16 samples), and
+// k_sibling_ordinals_chain, whose time is linear whatever the parents are, otherwise.  us for the index vectors of
+// documents / of runs of 64 siblings with parents anywhere, chain - windows: 70001 x 1 sample 176 / 135 - 74 / 95,
+// 131072 x 1 304 / 217 - 96 / 177, 131072 x 16 331 / 396 - 196 / 461; beyond the lines 131072 x 32 346 / 591 - 257 / 693,
+// 524288 x 1 1203 / 809 - 520 / 2389.
 constexpr int kOrdSplit = 16, kOrdWindow = 33 * 1024;
+constexpr int kMinShares = 16, kMaxWindowed = 1 << 17;
 
 __device__ __forceinline__ int ord_group(int level, int parent, int n)
 {
@@ -144,29 +158,25 @@ __global__ __launch_bounds__(kOrdThreads) void k_sibling_ordinals(const int32_t 
     extern __shared__ int s_count[];  // children seen so far of the parents w0 .. w0 + window - 1
     __shared__ int s_run_grp[kOrdThreads], s_run_len[kOrdThreads], s_run_base[kOrdThreads];
     __shared__ int s_wave_runs[kOrdWaves];
-    __shared__ int s_lo, s_hi;  // the groups of the share
+    __shared__ unsigned s_windows;  // the windows in which groups of the share lie
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const size_t o = (size_t)(blockIdx.x / shares) * n;
     const int2 share = my_share(n, shares);
     if (share.x >= share.y) return;
     const int window = min(n + 1, kOrdWindow);
-    if (tid == 0) {
-        s_lo = INT_MAX;
-        s_hi = -1;
-    }
+    if (tid == 0) s_windows = n + 1 > kOrdWindow ? 0u : 1u;
     __syncthreads();
     if (n + 1 > kOrdWindow) {
+        unsigned mine = 0u;
         for (int i = share.x + tid; i < share.y; i += kOrdThreads) {
             const int g = ord_group(level[o + i], parent[o + i], n);
-            if (g >= 0) {
-                atomicMin(&s_lo, g);
-                atomicMax(&s_hi, g);
-            }
+            if (g >= 0) mine |= 1u << (g / kOrdWindow);
         }
+        if (mine) atomicOr(&s_windows, mine);
         __syncthreads();
     }
-    for (int w0 = 0; w0 <= n; w0 += window) {
-        if (n + 1 > kOrdWindow && (s_hi < w0 || s_lo >= w0 + window)) continue;
+    for (unsigned todo = s_windows; todo; todo &= todo - 1u) {
+        const int w0 = (__ffs(todo) - 1) * window;
         for (int t = tid; t < window; t += kOrdThreads) s_count[t] = 0;
         __syncthreads();
         for (int j0 = 0; j0 < share.x; j0 += kBack * kOrdThreads) {
@@ -222,6 +232,129 @@ __global__ __launch_bounds__(kOrdThreads) void k_sibling_ordinals(const int32_t 
             }
             __syncthreads();
         }
+    }
+}
+
+// The same by one workgroup per sample, chunk of 1024 * kChainV positions after chunk (a thread takes kChainV consecutive
+// ones), the siblings in earlier chunks counted per parent in global memory (2.4 us per 1024 positions of a document).  A
+// run may be as long as the chunk here.
+constexpr int kChainV = 4, kChainChunk = kOrdThreads * kChainV;
+
+__global__ __launch_bounds__(kOrdThreads) void k_sibling_ordinals_chain(const int32_t *__restrict__ level,
+                                                                         const int32_t *__restrict__ parent, int n,
+                                                                         int32_t *cnt,  // [B][n + 1] scratch
+                                                                         int32_t *ord)  // [B][n]
+{
+    // per run head of the chunk: its group, its first position in the chunk; per position of the chunk that
+    // starts a run: siblings before that run (s_run_base)
+    __shared__ int s_head_parent[kChainChunk], s_head_start[kChainChunk], s_run_base[kChainChunk];
+    __shared__ int s_last_grp[kOrdThreads];
+    __shared__ int s_wave_max[kOrdWaves], s_wave_heads[kOrdWaves];
+    const int b = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const size_t o = (size_t)b * n;
+    int32_t *my_cnt = cnt + (size_t)b * (n + 1);
+    for (int i = tid; i <= n; i += kOrdThreads) my_cnt[i] = 0;
+    __syncthreads();
+    for (int c0 = 0; c0 < n; c0 += kChainChunk) {
+        const int idx0 = tid * kChainV;  // this thread's first position inside the chunk
+        int grp[kChainV];                // the parent (n for roots), -1 for pads and positions past n
+#pragma unroll
+        for (int u = 0; u < kChainV; u++) {
+            const int i = c0 + idx0 + u;
+            grp[u] = -1;
+            if (i < n && level[o + i] >= 0) {
+                const int p = parent[o + i];
+                grp[u] = (p >= 0 && p < n) ? p : n;
+            }
+        }
+        s_last_grp[tid] = grp[kChainV - 1];
+        __syncthreads();
+        // run heads; the last head at or before every position: a running maximum over the threads
+        int before = tid == 0 ? -2 : s_last_grp[tid - 1];
+        bool head[kChainV];
+        int n_mine = 0, last_head = -1;
+#pragma unroll
+        for (int u = 0; u < kChainV; u++) {
+            head[u] = grp[u] != before;
+            before = grp[u];
+            if (head[u]) {
+                n_mine++;
+                last_head = idx0 + u;
+            }
+        }
+        int run_max = last_head, heads_incl = n_mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(run_max, d), z = __shfl_up(heads_incl, d);
+            if (lane >= d) {
+                run_max = max(run_max, y);
+                heads_incl += z;
+            }
+        }
+        if (lane == 63) {
+            s_wave_max[wave] = run_max;
+            s_wave_heads[wave] = heads_incl;
+        }
+        __syncthreads();
+        int start_in = __shfl_up(run_max, 1);  // last head before this thread's positions
+        if (lane == 0) start_in = -1;
+        int my_head = heads_incl - n_mine, n_heads = 0;
+        for (int w = 0; w < kOrdWaves; w++) {
+            if (w < wave) {
+                start_in = max(start_in, s_wave_max[w]);
+                my_head += s_wave_heads[w];
+            }
+            n_heads += s_wave_heads[w];
+        }
+        int start[kChainV];
+        {
+            int cur = start_in, h = my_head;
+#pragma unroll
+            for (int u = 0; u < kChainV; u++) {
+                if (head[u]) {
+                    cur = idx0 + u;
+                    s_head_parent[h] = grp[u];
+                    s_head_start[h] = cur;
+                    h++;
+                }
+                start[u] = cur;
+            }
+        }
+        __syncthreads();
+        // siblings in earlier runs of this chunk: kOrdSplit lanes share the scan over the earlier heads of one head
+        for (int h = tid / kOrdSplit; h < n_heads; h += kOrdThreads / kOrdSplit) {
+            const int g = s_head_parent[h];
+            if (g < 0) continue;
+            int k = 0;
+            for (int e = tid % kOrdSplit; e < h; e += kOrdSplit)
+                if (s_head_parent[e] == g) k += s_head_start[e + 1] - s_head_start[e];
+#pragma unroll
+            for (int d = 1; d < kOrdSplit; d <<= 1) k += __shfl_xor(k, d);
+            if (tid % kOrdSplit == 0) {
+                // siblings in earlier chunks (the counter last changed before the barrier that ended the previous chunk)
+                const int base = __hip_atomic_load(&my_cnt[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                s_run_base[s_head_start[h]] = base + k;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kChainV; u++)
+            if (grp[u] >= 0) ord[o + c0 + idx0 + u] = 1 + s_run_base[start[u]] + (idx0 + u - start[u]);
+        // add this chunk's runs to the counters; the returned value makes the thread wait for the atomic
+        {
+            int h = my_head;
+#pragma unroll
+            for (int u = 0; u < kChainV; u++) {
+                if (!head[u]) continue;
+                if (grp[u] >= 0) {
+                    const int end = h + 1 < n_heads ? s_head_start[h + 1] : kChainChunk;
+                    const int old = atomicAdd(&my_cnt[grp[u]], end - (idx0 + u));
+                    asm volatile("" ::"v"(old));
+                }
+                h++;
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -369,7 +502,7 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_parents_from_
     hipStream_t st = (hipStream_t)stream;
     HdtTimer t("hdt_hpe_parents_from_levels", st);
     // in place: the levels in front of a share would be gone by the time it reads them, so one workgroup has the whole sample
-    const int shares = d_parent == d_level ? 1 : hpe_shares(n_pos);
+    const int shares = d_parent == d_level ? 1 : hpe_shares(batch, n_pos);
     hipLaunchKernelGGL(k_parents_from_levels, dim3((unsigned)batch * shares), dim3(kOrdThreads), 0, st, d_level, n_pos, shares,
                        d_parent);
     HDT_HIP_TRY(hipGetLastError());
@@ -379,7 +512,7 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_parents_from_
 extern "C" __attribute__((visibility("default"))) size_t hdt_index_vectors_workspace_bytes(int32_t batch, int32_t n_pos)
 {
     if (batch <= 0 || n_pos <= 0) return 0;
-    // per-parent counters [B][N+1] and sibling ordinals [B][N]
+    // per-parent counters [B][N+1] (of k_sibling_ordinals_chain) and sibling ordinals [B][N]
     const size_t ints = (size_t)batch * ((size_t)n_pos + 1) + (size_t)batch * (size_t)n_pos;
     return (ints * sizeof(int32_t) + 255) & ~(size_t)255;
 }
@@ -401,12 +534,18 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_index_vectors
     int32_t *cnt = static_cast<int32_t *>(workspace);
     int32_t *ord = cnt + (size_t)batch * ((size_t)n_pos + 1);
     {
+        const int shares = hpe_shares(batch, n_pos);
         const size_t lds = (size_t)std::min(n_pos + 1, kOrdWindow) * sizeof(int);
-        if (lds > 48 * 1024)  // with the static arrays: beyond the 64 KB a launch gets by default
-            HDT_HIP_TRY(hipFuncSetAttribute((const void *)k_sibling_ordinals, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         HdtTimer t("hdt_hpe_sibling_ordinals", st);
-        hipLaunchKernelGGL(k_sibling_ordinals, dim3((unsigned)batch * hpe_shares(n_pos)), dim3(kOrdThreads), lds, st, d_level,
-                           d_parent, n_pos, hpe_shares(n_pos), ord);
+        if (n_pos >= kOrdWindow && (shares < kMinShares || n_pos > kMaxWindowed)) {
+            hipLaunchKernelGGL(k_sibling_ordinals_chain, dim3((unsigned)batch), dim3(kOrdThreads), 0, st, d_level, d_parent, n_pos,
+                               cnt, ord);
+        } else {
+            if (lds > 48 * 1024)  // with the static arrays: beyond the 64 KB a launch gets by default
+                HDT_HIP_TRY(hipFuncSetAttribute((const void *)k_sibling_ordinals, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            hipLaunchKernelGGL(k_sibling_ordinals, dim3((unsigned)batch * shares), dim3(kOrdThreads), lds, st, d_level, d_parent,
+                               n_pos, shares, ord);
+        }
     }
     {
         const int64_t total = (int64_t)batch * n_pos;
