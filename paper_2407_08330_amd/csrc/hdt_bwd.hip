@@ -25,8 +25,8 @@
 // Both roles recompute the scores, which costs two extra contractions but keeps dQ out of HBM as fp32
 // partial sums.  Where a call of head size 128 does not fill the chip, the dK/dV role is split once more, into a dV role
 // and a dK role (three workgroups per tile, see launch_roles).  The workgroups of a tile are neighbours in the launch
-// order and run on the same XCD at the same time.  That is what the pairing is for: the dQ role reads the tile's Q, dO rows and gathers
-// K, V rows of the neighbourhood, the dK/dV role reads the tile's K, V rows and gathers Q, dO rows of the
+// order and run on the same XCD at the same time.  That is what the pairing is for: the dQ role reads the tile's Q, dO
+// rows and gathers K, V rows of the neighbourhood, the dK/dV role reads the tile's K, V rows and gathers Q, dO rows of the
 // same neighbourhood, so each role finds in the XCD's L2 what the other (or a neighbouring pair) has just
 // fetched, and Q, K, V, dO come from HBM once per backward pass instead of once per role (measured: the
 // L2 fetch volume of this kernel is that of four tensors; as two separate passes it was that of eight).
@@ -43,8 +43,9 @@ struct BwdCfg {
     // against 99 with two, whose allocation the compiler then leaves unconstrained).
     static constexpr int S_DQ = (D == 64) ? 3 : 2;
     static constexpr int S_DKV = 2;
-    // The INDEXED form on 128 x 64 tiles gets one wave less: it would spill a few registers there, which the counted
-    // waits do not allow, and its few workgroups do not need the third (second) wave.
+    // The INDEXED form on 128 x 64 tiles is compiled for one wave less: bounded to the third (second) it would spill a
+    // few registers, which the counted waits do not allow.  It gets two per SIMD (178 registers at head size 64, 247 at
+    // 128); at head size 128 with the split roles only, see launch_roles.
     template <typename G, bool INDEXED>
     static constexpr int WAVES = G::BM == 128 ? (D == 64 ? 3 : 2) - (INDEXED ? 1 : 0) : 2;
 };
@@ -430,8 +431,8 @@ __device__ __forceinline__ void zero_role(const HdtSchedule &s, __bf16 *__restri
     }
 }
 
-// SPLIT: a dV and a dK role instead of one for both.  INDEXED: s_tr covers visible positions only (HdtSchedule::own_index); the workgroups behind the grid of the roles
-// write the zeros of the rows it leaves out.
+// SPLIT: a dV and a dK role instead of one for both.  INDEXED: s_tr covers visible positions only
+// (HdtSchedule::own_index); the workgroups behind the grid of the roles write the zeros of the rows it leaves out.
 template <int D, typename G, bool INDEXED, bool SPLIT>
 __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)) void k_bwd_bf16(
     HdtSchedule s, HdtSchedule s_tr, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k,
@@ -505,6 +506,9 @@ static void launch_kernel(const HdtSchedule &s, const HdtSchedule &s_tr, const _
 // and the rows gathered), two are the shorter chain.  Two as long as their workgroups, two waves per SIMD, are all on the
 // chip at the same time; measured, one role / two: 32768 positions x 16 heads 230 / 261 us (64 x 32 tiles) and 264 / 307
 // (128 x 64); 3000 x 16 (2 samples x 8 heads) 33.4 / 33.2 and 37.1 / 37.0; 1000 x 4 heads 16.9 / 14.3.
+// Always two where the rows are indexed and the tiles 128 x 64: one role takes 307 registers there, a single wave per SIMD
+// (whole backward, one role / two: 512 x 8192 x 48 heads, 500 positions visible, 68.9 / 61.3 us, 750 81.3 / 68.6, 2000
+// 185 / 130; 2048 x 8192 x 64 heads, 2000 visible, 716 / 540).  On 64 x 32 tiles it keeps two.
 template <int D, typename G, bool INDEXED>
 static void launch_roles(const HdtSchedule &s, const HdtSchedule &s_tr, const __bf16 *Q, const __bf16 *K, const __bf16 *V,
                          const float *lse, const __bf16 *DO, const float2 *row_scalars, void *dq, void *dk, void *dv,
@@ -512,10 +516,11 @@ static void launch_roles(const HdtSchedule &s, const HdtSchedule &s_tr, const __
 {
     constexpr unsigned kResident = 256u * 8u / G::NW;  // workgroups on the chip at two waves per SIMD
     const size_t nq = (size_t)s.batch * heads * s.tr, nk = (size_t)s_tr.batch * heads * s_tr.tr;
-    if (D == 128 && nq + 2 * nk <= kResident)
+    constexpr bool ALWAYS = D == 128 && INDEXED && G::BM == 128;
+    if (ALWAYS || (D == 128 && nq + 2 * nk <= kResident))
         launch_kernel<D, G, INDEXED, D == 128>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st);
     else
-        launch_kernel<D, G, INDEXED, false>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st);
+        launch_kernel<D, G, INDEXED, ALWAYS>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st);
 }
 
 template <typename G>

@@ -46,6 +46,20 @@ def test_cross_few_visible_positions_at_tile_edges(oracle, tile, D):
     run_cross_case(oracle, level, 100, 2, 2, D, "bf16", 41, tile=tile, poison_invisible=True)
 
 
+@pytest.mark.parametrize("tile,heads", [((128, 64), 10), ((128, 64), 11), ((64, 32), 12), ((64, 32), 13)])
+def test_cross_few_visible_positions_d128_in_large_grids(oracle, tile, heads):
+    # three roles per tile are 49 workgroups per head (84 on 64-row tiles): fewer and more than the 512 (1024) that are on the
+    # chip at the same time; on 64 x 32 tiles dK and dV take one role where there are more
+    n_enc = 1217
+    counts = (2, 32, 33, 127, 128, 129, 304)
+    level = np.full((len(counts), n_enc), 3, np.int32)
+    rng = np.random.default_rng(7)
+    for b, c in enumerate(counts):
+        level[b, rng.choice(n_enc, c, replace=False)] = 1
+    say(f"[cross edges] d=128, {heads} heads, tile {tile}")
+    run_cross_case(oracle, level, 100, 2, heads, 128, "bf16", 43, tile=tile, poison_invisible=True)
+
+
 def test_cross_select_on_long_encoders(oracle):
     # more than 8 groups of 64 positions per wave of the selecting workgroup, a ragged last group
     import paper_2407_08330_amd as hdt
