@@ -431,6 +431,26 @@ __device__ __forceinline__ void zero_role(const HdtSchedule &s, __bf16 *__restri
     }
 }
 
+// The grid of the roles: workgroups of the tiles both sides have, then those of the longer side's rest (padding included), and
+// what logical_block deals out at a time in each.  In dense cross-attention the two kinds of workgroup last differently
+// long: spread evenly as one row of items, some XCDs get a chunk more of the longer ones.  Whole backward of full chunks
+// of both - one row spread evenly - each part by itself: 2048 x 2048 x 48 heads, 128 x 64 tiles, 225 - 246 - 216 us;
+// 512 x 8192 x 48, 64 x 32 tiles, 224 - 236 - 217; 512 x 8192 x 8, 128 x 64, 54.7 - 45.2 - 41.3.
+struct RoleGrid {
+    unsigned tiles, chunk, rest, rest_chunk;
+};
+template <typename G>
+static RoleGrid role_grid(unsigned nq, unsigned nk, unsigned roles)
+{
+    const unsigned common = nq < nk ? nq : nk, unit = nq > nk ? 1u : roles - 1u, rest = nq + (roles - 1u) * nk - roles * common;
+    RoleGrid g;
+    g.chunk = xcd_chunk(roles * common, roles * G::XCD_CHUNK, roles);
+    g.tiles = padded_grid(roles * common, g.chunk);
+    g.rest_chunk = xcd_chunk(rest, unit * G::XCD_CHUNK, unit);
+    g.rest = padded_grid(rest, g.rest_chunk);
+    return g;
+}
+
 // SPLIT: a dV and a dK role instead of one for both.  INDEXED: s_tr covers visible positions only
 // (HdtSchedule::own_index); the workgroups behind the grid of the roles write the zeros of the rows it leaves out.
 template <int D, typename G, bool INDEXED, bool SPLIT>
@@ -438,7 +458,7 @@ __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)
     HdtSchedule s, HdtSchedule s_tr, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k,
     const __bf16 *__restrict__ v, const float *__restrict__ lse, const __bf16 *__restrict__ d_o,
     const float2 *__restrict__ row_scalars, __bf16 *__restrict__ dq, __bf16 *__restrict__ dk,
-    __bf16 *__restrict__ dv, int heads, float scale, unsigned chunk)
+    __bf16 *__restrict__ dv, int heads, float scale, RoleGrid grid)
 {
     using PQ = Pipe<D, BwdCfg<D>::S_DQ, false, G>;
     using PK = Pipe<D, BwdCfg<D>::S_DKV, true, G>;
@@ -447,19 +467,24 @@ __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     // The roles tile different tensors (the same ones for self-attention): the workgroups of one tile follow each
-    // other as far as both sides have that tile, the rest of the longer side comes behind them.
+    // other as far as both sides have that tile, the rest of the longer side comes behind them, each of the two spread
+    // evenly over the XCDs by itself (see role_grid).
     constexpr unsigned R = SPLIT ? 3u : 2u;  // roles per tile: dQ, then dK/dV or dV, dK
     const unsigned nq = (unsigned)s.batch * heads * s.tr, nk = (unsigned)s_tr.batch * heads * s_tr.tr;
-    if (INDEXED) {
-        const unsigned roles = padded_grid(nq + (R - 1u) * nk, chunk);
-        if (blockIdx.x >= roles) {
-            zero_role<D, G>(s_tr, dk, dv, blockIdx.x - roles, heads);
+    const unsigned common = nq < nk ? nq : nk, items = nq + (R - 1u) * nk;
+    unsigned w;
+    if (blockIdx.x < grid.tiles) {
+        w = logical_block(blockIdx.x, grid.chunk);
+        if (w >= R * common) return;  // padding of the grid
+    } else {
+        const unsigned at = blockIdx.x - grid.tiles;
+        if (INDEXED && at >= grid.rest) {
+            zero_role<D, G>(s_tr, dk, dv, at - grid.rest, heads);
             return;
         }
+        w = R * common + logical_block(at, grid.rest_chunk);
+        if (w >= items) return;
     }
-    const unsigned w = logical_block(blockIdx.x, chunk);
-    const unsigned common = nq < nk ? nq : nk;
-    if (w >= nq + (R - 1u) * nk) return;  // padding of the grid
     unsigned role, lb;
     if (w < R * common) {
         role = w % R;
@@ -496,10 +521,10 @@ static void launch_kernel(const HdtSchedule &s, const HdtSchedule &s_tr, const _
     const unsigned nq = (unsigned)s.batch * heads * s.tr, nk = (unsigned)s_tr.batch * heads * s_tr.tr;
     constexpr unsigned roles = SPLIT ? 3u : 2u, zr = ZeroRows<D, G>::ROWS;
     const unsigned zeros = INDEXED ? (unsigned)s_tr.batch * heads * (((unsigned)s_tr.own_stride + zr - 1u) / zr) : 0u;
-    const unsigned items = nq + (roles - 1u) * nk, chunk = xcd_chunk(items, roles * G::XCD_CHUNK, roles);
-    dim3 grid(padded_grid(items, chunk) + zeros), block(G::THREADS);
+    const RoleGrid g = role_grid<G>(nq, nk, roles);
+    dim3 grid(g.tiles + g.rest + zeros), block(G::THREADS);
     hipLaunchKernelGGL((k_bwd_bf16<D, G, INDEXED, SPLIT>), grid, block, 0, st, s, s_tr, Q, K, V, lse, DO, row_scalars,
-                       (__bf16 *)dq, (__bf16 *)dk, (__bf16 *)dv, heads, scale, chunk);
+                       (__bf16 *)dq, (__bf16 *)dk, (__bf16 *)dv, heads, scale, g);
 }
 
 // At head size 128 one role for dK and dV is less work than two (the scores are computed twice instead of three times,

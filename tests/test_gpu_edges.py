@@ -60,6 +60,18 @@ def test_cross_few_visible_positions_d128_in_large_grids(oracle, tile, heads):
     run_cross_case(oracle, level, 100, 2, heads, 128, "bf16", 43, tile=tile, poison_invisible=True)
 
 
+@pytest.mark.parametrize("n_dec,n_enc,heads", [(60, 700, 1), (60, 700, 9), (700, 60, 9), (129, 1500, 17), (1500, 129, 17), (65, 4100, 3)])
+def test_cross_backward_tiles_of_both_sides_and_the_longer_sides_rest(oracle, n_dec, n_enc, heads):
+    # the grid of the backward's roles has two parts, each cut into equal shares by itself: the tiles that the decoder's and
+    # the encoder's rows both have, and the rest of the longer side (the last case: lists cut into pieces, more dQ tiles)
+    level = np.full((2, n_enc), 3, np.int32)
+    level[1, n_enc // 2:] = -1
+    for tile in ((128, 64), (64, 32)):
+        for D in (64, 128):
+            say(f"[cross edges] {n_dec} x {n_enc} x {heads} heads, tile {tile} d={D}")
+            run_cross_case(oracle, level, n_dec, 8, heads, D, "bf16", 44, tile=tile)
+
+
 def test_cross_select_on_long_encoders(oracle):
     # more than 8 groups of 64 positions per wave of the selecting workgroup, a ragged last group
     import paper_2407_08330_amd as hdt
