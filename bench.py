@@ -50,12 +50,14 @@ def algorithmic_bytes_per_unit(kernel: str, d: int) -> int:
     raise KeyError(kernel)
 
 
-def mfma_flop_per_subblock(kernel: str, d: int) -> int:
-    """MFMA work a kernel executes per 32x32 sub-block it does not skip: the forward two contractions
-    (S = K Q^T, O += V^T P), the backward kernel seven (the dQ role S, dP, dQ; the dK/dV role S, dP,
-    dK, dV)."""
-    per_gemm = 2 * 32 * 32 * d
-    return (2 if kernel.startswith("hdt_fwd") else 7) * per_gemm
+def contractions_per_subblock(kernel: str, d: int, row_tiles: int, tile_m: int) -> int:
+    """Contractions a kernel executes per 32x32 sub-block it does not skip: the forward two (S = K Q^T, O += V^T P), the
+    backward kernel seven (the dQ role S, dP, dQ; the dK/dV role S, dP, dK, dV), or eight where a call of head size 128 has a
+    dV role (S, dV) and a dK role (S, dP, dK): while three workgroups per row tile (`row_tiles` of the whole call) are
+    on the chip at the same time, two waves per SIMD."""
+    if kernel.startswith("hdt_fwd"):
+        return 2
+    return 8 if d == 128 and 3 * row_tiles <= 256 * 8 // (tile_m // 32) else 7
 
 
 def kernel_source_hash() -> str:
@@ -391,8 +393,8 @@ def main() -> int:
         if not name:
             continue
         us = per_kernel[name]["avg_us"]
-        gemms = 2 if phase == "fwd" else 7
-        executed = executed_subblocks * H * mfma_flop_per_subblock(name, D)
+        gemms = contractions_per_subblock(name, D, B * H * info["q_tiles"], info["tile_m"])
+        executed = executed_subblocks * H * gemms * 2 * 32 * 32 * D
         issued = n_tiles * info["tile_m"] * info["tile_n"] * H * gemms * 2 * D
         out[phase] = {
             "avg_us": round(us, 2),
@@ -435,6 +437,8 @@ def main() -> int:
         dk_ = {n: 1e3 * ms / c for n, (c, ms) in hdt.hdt_timing_read().items() if c}
         hdt.hdt_timing_enable(False)
         dense_sub = dinfo["n_tiles"] * (dinfo["tile_m"] // 32) * (dinfo["tile_n"] // 32)
+        dense_flop = {k: dense_sub * H * 2 * 32 * 32 * D * contractions_per_subblock(k, D, B * H * dinfo["q_tiles"], dinfo["tile_m"])
+                      for k in ("hdt_fwd", "hdt_bwd_bf16")}
         f_us = dk_.get(f"hdt_fwd_bf16_d{D}")
         b_us = dk_.get(f"hdt_bwd_bf16_d{D}")
         sparse_attn_ms = (phase_us["fwd"] + phase_us["bwd"]) * 1e-3
@@ -443,10 +447,10 @@ def main() -> int:
             "tile": f"{dinfo['tile_m']}x{dinfo['tile_n']}", "n_tiles": dinfo["n_tiles"], "ms_fwd_bwd": round(dense_ms, 3),
             "tokens_per_s": round(tokens / (dense_ms * 1e-3), 1),
             "kernels_us": {n: round(v, 1) for n, v in dk_.items()},
-            "fwd_mfma_tflops": None if not f_us else round(dense_sub * H * mfma_flop_per_subblock("hdt_fwd", D) / (f_us * 1e-6) / 1e12, 1),
-            "fwd_mfma_frac": None if not f_us else round(dense_sub * H * mfma_flop_per_subblock("hdt_fwd", D) / (f_us * 1e-6) / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4),
-            "bwd_mfma_tflops": None if not b_us else round(dense_sub * H * mfma_flop_per_subblock("hdt_bwd_bf16", D) / (b_us * 1e-6) / 1e12, 1),
-            "bwd_mfma_frac": None if not b_us else round(dense_sub * H * mfma_flop_per_subblock("hdt_bwd_bf16", D) / (b_us * 1e-6) / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4),
+            "fwd_mfma_tflops": None if not f_us else round(dense_flop["hdt_fwd"] / (f_us * 1e-6) / 1e12, 1),
+            "fwd_mfma_frac": None if not f_us else round(dense_flop["hdt_fwd"] / (f_us * 1e-6) / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4),
+            "bwd_mfma_tflops": None if not b_us else round(dense_flop["hdt_bwd_bf16"] / (b_us * 1e-6) / 1e12, 1),
+            "bwd_mfma_frac": None if not b_us else round(dense_flop["hdt_bwd_bf16"] / (b_us * 1e-6) / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4),
             "sparse_fwd_bwd_ms": round(sparse_attn_ms, 4),
             "speedup_of_the_sparse_schedule": round(dense_ms / sparse_attn_ms, 1) if sparse_attn_ms > 0 else None,
         }
