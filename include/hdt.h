@@ -241,10 +241,12 @@ hdt_status_t hdt_layout_export(const hdt_layout_t *layout, int32_t sample, int32
                                int64_t tile_capacity);
 
 /* Destroys the layout.  NULL is accepted, and the call does not wait: attention calls that use the layout may
- * still be queued or running.  Its device buffers go to a cache (at most 16 buffers / 1 GiB per process; the oldest make room) that
+ * still be queued or running.  Its device buffers go to a cache (at most 16 buffers / 1 GiB per process) that
  * later hdt_build_layout calls draw from; a build that takes them orders itself behind everything enqueued so far
  * on the streams this layout was built and used on (an event per other stream, nothing for its own stream, no
- * host wait).  The streams of those calls must still exist then, or the build waits for the device instead. */
+ * host wait).  The streams of those calls must still exist then, or the build waits for the device instead.
+ * Only where the cache has no room are buffers given back to the system (the ones that have been there longest, or
+ * one larger than the whole cache), and that waits for the device. */
 hdt_status_t hdt_layout_destroy(hdt_layout_t *layout);
 
 /* The same for a caller that has waited for the layout's build and for every call that used it (an event of its

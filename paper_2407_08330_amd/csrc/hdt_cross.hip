@@ -17,8 +17,9 @@
 // positions from the device, and when they are at most a quarter of the encoder's positions it adds a second
 // transposed schedule in the index space of the visible positions (row = rank among them): the dK/dV role of
 // hdt_attn_bwd then reads its K and V rows and writes its dK and dV rows through the list of visible positions,
-// and further workgroups of the same launch write the zeros of the rows that are not visible (512 x 8192, [SEC] and [SENT] visible: one
-// launch of 24 us where gathering compact copies, the roles and scattering the results took 5 + 21 + 24).
+// and further workgroups of the same launch write the zeros of the rows that are not visible (512 x 8192, [SEC] and
+// [SENT] visible: one launch of 24 us where gathering compact copies, the roles and scattering the results took
+// 5 + 21 + 24).
 //
 // With the regular tokens visible the opposite happens: a handful of decoder row tiles each walk a key list of
 // more than a hundred entries one after the other, on a few workgroups.  The list of a row tile is the same for

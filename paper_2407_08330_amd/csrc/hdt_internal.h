@@ -187,6 +187,7 @@ hdt_status_t hdt_cross_bwd_split(const hdt_layout_t *l, const void *q, const voi
                                  const float *lse, const void *d_o, void *dq, void *dk, void *dv, int heads,
                                  int head_dim, float scale, void *workspace, hipStream_t st);
 
+// (workspace a layout with a compact schedule asks for beyond what its kernels use, see hdt_attn_bwd_workspace_bytes)
 size_t hdt_cross_compact_workspace_bytes(const hdt_layout_t *l, int heads, int head_dim, int elem_bytes);
 
 // --- the device's report to a waiting host: one 64-bit word of pinned host memory per build in flight, and a slot of
@@ -213,12 +214,12 @@ hdt_status_t hdt_launch_fwd_bf16(const HdtSchedule &s, const void *q, const void
 hdt_status_t hdt_launch_fwd_f32(const HdtSchedule &s, const float *q, const float *k, const float *v, float *o,
                                 float *lse, int heads, int head_dim, float scale, hipStream_t st);
 // backward launchers: `s` schedules the dQ pass, `s_transposed` (the transposed mask's schedule; the same as `s` for
-// symmetric masks) the dK/dV pass.  `ws_delta` (bf16): room for the rows' scalars, hdt_bwd_row_scalars_bytes(batch * heads
+// symmetric masks) the dK/dV pass.  `delta` (bf16): room for the rows' scalars, hdt_bwd_row_scalars_bytes(batch * heads
 // * n_pos), two floats per row: -D and -LSE / scale side by side.
 inline size_t hdt_bwd_row_scalars_bytes(size_t rows) { return (2 * rows * sizeof(float) + 255) & ~(size_t)255; }
 hdt_status_t hdt_launch_bwd_bf16(const HdtSchedule &s, const HdtSchedule &s_transposed, const void *q, const void *k, const void *v,
                                  const void *o, const float *lse, const void *d_o, void *dq, void *dk,
-                                 void *dv, int heads, int head_dim, float scale, float *ws_delta,
+                                 void *dv, int heads, int head_dim, float scale, float *delta,
                                  hipStream_t st);
 hdt_status_t hdt_launch_bwd_f32(const HdtSchedule &s, const HdtSchedule &s_transposed, const float *q, const float *k, const float *v,
                                 const float *o, const float *lse, const float *d_o, float *dq, float *dk,

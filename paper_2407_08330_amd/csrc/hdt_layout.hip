@@ -1099,7 +1099,8 @@ __global__ __launch_bounds__(kListThreads) void k_key_lists(KeyListArgs a)
 // Two builds in one launch (the two schedules of a directed mask), blockIdx.y says which: twice the workgroups, so two of
 // them share a compute unit, which takes registers for 8 waves per SIMD (48 tiles of 64 rows per sample, 16 samples: two
 // launches 35 us, one with the registers of the kernel above 25.8, this one 22.5; a kernel of its own, because the
-// arguments read by index cost the single build 0.5 us).
+// arguments read by index cost the single build 0.5 us).  With T = 2 the bound spills 5 registers (24 bytes of scratch per
+// lane) and keeps 32 scalars in vector lanes, which the last figure includes.
 template <int kListThreads, int T>
 __global__ __launch_bounds__(kListThreads, 8) void k_key_lists_both(KeyListLaunch builds)
 {
@@ -1441,7 +1442,7 @@ hipError_t launch_key_lists(const KeyListArgs *args, int builds, int batch, hipS
     const KeyListArgs &a = args[0];
     const bool small_wg = a.bm <= 64;
     // tiles of up to 64 rows: two per workgroup, as long as the two sets of bitmaps fit the LDS beside the
-    // kernel's static arrays (documents of up to 64 K positions)
+    // kernel's static arrays (documents of up to 67 K positions)
     const bool pair = small_wg && list_lds(a.n, 2) <= 33 * 1024;
     const size_t lds = list_lds(a.n, pair ? 2 : 1);
     const dim3 grid((unsigned)batch * (pair ? (a.tr + 1) / 2 : a.tr), (unsigned)builds);

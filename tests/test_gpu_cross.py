@@ -120,7 +120,7 @@ def run_cross_case(oracle, level, n_dec, level_mask, H, D, dtype, seed, tile=(0,
         kd, vd = np.where(w, junk, k), np.where(w, junk[..., ::-1], v)
         k_, v_ = (to_dev_bf16(x) if dtype == "bf16" else torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (kd, vd))
     lay = hdt.hdt_build_cross_layout(to_dev_i32(level), n_dec, level_mask, tile_m=tile[0], tile_n=tile[1])
-    # the backward runs on compact copies of K and V iff at most a quarter of the positions are visible
+    # the dK/dV pass tiles the visible positions alone iff at most a quarter of the positions are visible
     c_max = max(int(oracle.cross_select(l, level_mask).size) for l in level)
     compact_rows = lay.info()["compact_rows"]
     say(f"    visible at most {c_max} of {n_enc}: compact rows {compact_rows}")
@@ -230,8 +230,8 @@ def test_cross_attention_long_key_lists_cut_into_pieces(oracle, D):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_cross_attention_ignores_what_invisible_rows_hold(oracle, dtype):
-    # pads in front and behind, NaN / Inf in every K, V row the level mask hides: anchors only (the backward works on
-    # compact copies), and everything but [DOC] (the backward tiles the encoder rows, hidden ones among them)
+    # pads in front and behind, NaN / Inf in every K, V row the level mask hides: anchors only (the dK/dV pass tiles the
+    # visible rows alone), and everything but [DOC] (it tiles the encoder rows, hidden ones among them)
     level = _long_encoder_levels(1536, (51, 52), fill=0.8)
     level = np.concatenate([np.full((2, 40), -1, np.int32), level[:, :-40]], axis=1)
     for level_mask in (SEC | SENT, SEC | SENT | TOK):
