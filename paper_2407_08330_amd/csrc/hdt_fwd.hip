@@ -184,15 +184,18 @@ __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
             sub_next = subs[i + 1];
         }
         // The lines of this entry's masks, on their way while the wave waits for the rows (us per launch, event-bracketed:
-        // 128 x 64 tiles at 8192 positions 47.1 -> 45.4, 4096 44.9 -> 43.4, 2047 15.6 -> 15.0, 1000 12.2 -> 11.1; 64 x 32 at
-        // 8192 45.9 -> 45.6; masks that cost no loads at all would give 43.5 at the first size).  Holding the masks
-        // themselves in scalar registers over the barrier spills.  Not where whole sub-blocks are the rule, and not in
-        // the backward, whose three waves per SIMD hide the loads (64 x 32: 83.4 -> 84.4, dense rectangle 206 -> 211).
+        // 128 x 64 tiles at 8192 positions 47.1 -> 45.4, 4096 44.9 -> 43.4, 2047 15.6 -> 15.0, 1000 12.2 -> 11.1; masks that
+        // cost no loads at all would give 43.5 at the first size).  Holding the masks themselves in scalar registers over the
+        // barrier spills.  On 128 x 64 tiles only: on 64 x 32 it is worth 0-2 % where lists are short (11.5 -> 11.2 on
+        // ListOps-shaped trees, 38.8 -> 38.7 at 8192) and costs 2-5 % where they are long (one group of 2048 positions 68.6 ->
+        // 72.4, 4096 shuffled ones 87.2 -> 89.2).  Not where whole sub-blocks are the rule either, and not in the
+        // backward, whose three waves per SIMD hide the loads (64 x 32: 83.4 -> 84.4, dense rectangle 206 -> 211).
+        constexpr bool TOUCH = !WHOLE && G::BM == 128;
         MaskTouch<KB * 16> masks;
-        if (!WHOLE) masks.request(s.bits_rm + ((size_t)bidx * G::NSUB + wave * KB) * 16);
+        if (TOUCH) masks.request(s.bits_rm + ((size_t)bidx * G::NSUB + wave * KB) * 16);
         R::top(i, n);
         wg_barrier();
-        if (!WHOLE) masks.arrived();
+        if (TOUCH) masks.arrived();
         R::advance(pipe, i, n);
         const char *sK = pipe.tile_a(i % S), *sV = pipe.tile_b(i % S);
 
