@@ -339,7 +339,7 @@ hdt_status_t hdt_attn_bwd_no_alloc(const hdt_layout_t *layout, const void *q, co
  *   documents in the layout of Sec. 3.2 (every anchor in front of what it summarises, i.e. pre-order): the
  *   parent of a position of level l > 0 is the nearest earlier position of level l - 1; level 0, pads, levels
  *   outside [0, HDT_MAX_LEVELS) and positions without such a predecessor get -1.  The front end for callers
- *   that only know where sections and sentences start.
+ *   that only know where sections and sentences start.  d_parent may be d_level itself (one workgroup per sample then).
  * hdt_index_vectors -- level/parent ids (as for hdt_build_layout) -> d_p [batch][n_pos][n_levels] int32,
  *   device: entry l-1 of position i = the 1-based ordinal, among the children of its parent in document
  *   order, of i's ancestor-or-self whose level is l; 0 if there is none ([DOC] = (0,0,0), k-th [SEC] =
