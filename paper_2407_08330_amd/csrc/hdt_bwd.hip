@@ -161,9 +161,7 @@ __device__ __forceinline__ void dq_role(char *smem, const HdtSchedule &s, const 
 
     f32x16 dqacc[DBLK];
 #pragma unroll
-    for (int i = 0; i < DBLK; i++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) dqacc[i][e] = 0.f;
+    for (int i = 0; i < DBLK; i++) dqacc[i] = zero_block();
 
     uint32_t sub_next = n > 0 ? subs[0] : 0u;
     for (int i = 0; i < n; i++) {
@@ -172,9 +170,9 @@ __device__ __forceinline__ void dq_role(char *smem, const HdtSchedule &s, const 
         if (i + 1 < n) {
             sub_next = subs[i + 1];
         }
-        R::top(i, n);
+        const typename P::Offsets next = R::top(pipe, i, n);
         wg_barrier();
-        R::advance(pipe, i, n);
+        R::advance(pipe, i, n, next);
         const char *sK = pipe.tile_a(i % S), *sV = pipe.tile_b(i % S);
 
 #pragma unroll
@@ -309,9 +307,10 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
 
     f32x16 dkacc[DBLK], dvacc[DBLK];
 #pragma unroll
-    for (int i = 0; i < DBLK; i++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) dkacc[i][e] = dvacc[i][e] = 0.f;
+    for (int i = 0; i < DBLK; i++) {
+        if (DO_DK) dkacc[i] = zero_block();
+        if (DO_DV) dvacc[i] = zero_block();
+    }
 
     uint32_t sub_next = n > 0 ? subs[0] : 0u;
     for (int i = 0; i < n; i++) {
@@ -320,9 +319,9 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
         if (i + 1 < n) {
             sub_next = subs[i + 1];
         }
-        R::top(i, n);
+        const typename P::Offsets next = R::top(pipe, i, n);
         wg_barrier();
-        R::advance(pipe, i, n);
+        R::advance(pipe, i, n, next);
         const char *sQ = pipe.tile_a(i % S), *sDO = pipe.tile_b(i % S);
         const float *sInitS = pipe.aux_buf(i % S, 0), *sInitDP = pipe.aux_buf(i % S, 1);  // -LSE / scale, -D
 
@@ -437,17 +436,26 @@ __device__ __forceinline__ void zero_role(const HdtSchedule &s, __bf16 *__restri
 // of both - one row spread evenly - each part by itself: 2048 x 2048 x 48 heads, 128 x 64 tiles, 225 - 246 - 216 us;
 // 512 x 8192 x 48, 64 x 32 tiles, 224 - 236 - 217; 512 x 8192 x 8, 128 x 64, 54.7 - 45.2 - 41.3.
 struct RoleGrid {
-    unsigned tiles, chunk, rest, rest_chunk;
+    unsigned tiles, rest;
+    FastDiv chunk, rest_chunk;
+    unsigned nq, nk;          // row tiles of the two sides, all samples and heads
+    FastDiv tr_q, tr_k, heads;
 };
 template <typename G>
-static RoleGrid role_grid(unsigned nq, unsigned nk, unsigned roles)
+static RoleGrid role_grid(const HdtSchedule &s, const HdtSchedule &s_tr, int heads, unsigned roles)
 {
-    const unsigned common = nq < nk ? nq : nk, unit = nq > nk ? 1u : roles - 1u, rest = nq + (roles - 1u) * nk - roles * common;
     RoleGrid g;
-    g.chunk = xcd_chunk(roles * common, roles * G::XCD_CHUNK, roles);
-    g.tiles = padded_grid(roles * common, g.chunk);
-    g.rest_chunk = xcd_chunk(rest, unit * G::XCD_CHUNK, unit);
-    g.rest = padded_grid(rest, g.rest_chunk);
+    g.nq = (unsigned)s.batch * heads * s.tr;
+    g.nk = (unsigned)s_tr.batch * heads * s_tr.tr;
+    const unsigned nq = g.nq, nk = g.nk, common = nq < nk ? nq : nk, unit = nq > nk ? 1u : roles - 1u;
+    const unsigned rest = nq + (roles - 1u) * nk - roles * common;
+    g.chunk = FastDiv(xcd_chunk(roles * common, roles * G::XCD_CHUNK, roles));
+    g.tiles = padded_grid(roles * common, g.chunk.d);
+    g.rest_chunk = FastDiv(xcd_chunk(rest, unit * G::XCD_CHUNK, unit));
+    g.rest = padded_grid(rest, g.rest_chunk.d);
+    g.tr_q = FastDiv(s.tr);
+    g.tr_k = FastDiv(s_tr.tr);
+    g.heads = FastDiv(heads);
     return g;
 }
 
@@ -458,7 +466,7 @@ __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)
     HdtSchedule s, HdtSchedule s_tr, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k,
     const __bf16 *__restrict__ v, const float *__restrict__ lse, const __bf16 *__restrict__ d_o,
     const float2 *__restrict__ row_scalars, __bf16 *__restrict__ dq, __bf16 *__restrict__ dk,
-    __bf16 *__restrict__ dv, int heads, float scale, RoleGrid grid)
+    __bf16 *__restrict__ dv, float scale, RoleGrid grid)
 {
     using PQ = Pipe<D, BwdCfg<D>::S_DQ, false, G>;
     using PK = Pipe<D, BwdCfg<D>::S_DKV, true, G>;
@@ -470,7 +478,7 @@ __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)
     // other as far as both sides have that tile, the rest of the longer side comes behind them, each of the two spread
     // evenly over the XCDs by itself (see role_grid).
     constexpr unsigned R = SPLIT ? 3u : 2u;  // roles per tile: dQ, then dK/dV or dV, dK
-    const unsigned nq = (unsigned)s.batch * heads * s.tr, nk = (unsigned)s_tr.batch * heads * s_tr.tr;
+    const unsigned nq = grid.nq, nk = grid.nk;
     const unsigned common = nq < nk ? nq : nk, items = nq + (R - 1u) * nk;
     unsigned w;
     if (blockIdx.x < grid.tiles) {
@@ -479,7 +487,7 @@ __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)
     } else {
         const unsigned at = blockIdx.x - grid.tiles;
         if (INDEXED && at >= grid.rest) {
-            zero_role<D, G>(s_tr, dk, dv, at - grid.rest, heads);
+            zero_role<D, G>(s_tr, dk, dv, at - grid.rest, grid.heads.d);
             return;
         }
         w = R * common + logical_block(at, grid.rest_chunk);
@@ -498,10 +506,10 @@ __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)
         lb = common + rest / (R - 1u);
     }
     if (role == 0u) {
-        const int I = lb % s.tr, bh = lb / s.tr, b = bh / heads;
+        const int bh = grid.tr_q.div(lb), I = lb - bh * grid.tr_q.d, b = grid.heads.div(bh);
         dq_role<D, G>(smem, s, q, k, v, lse, d_o, row_scalars, dq, wave, I, bh, b, scale);
     } else {
-        const int I = lb % s_tr.tr, bh = lb / s_tr.tr, b = bh / heads;
+        const int bh = grid.tr_k.div(lb), I = lb - bh * grid.tr_k.d, b = grid.heads.div(bh);
         if (!SPLIT)
             dkv_role<D, G, 0, INDEXED>(smem, s_tr, q, k, v, d_o, row_scalars, dk, dv, wave, I, bh, b, scale);
         else if (role == 1u)
@@ -518,13 +526,12 @@ static void launch_kernel(const HdtSchedule &s, const HdtSchedule &s_tr, const _
                           const float *lse, const __bf16 *DO, const float2 *row_scalars, void *dq, void *dk, void *dv,
                           int heads, float scale, hipStream_t st)
 {
-    const unsigned nq = (unsigned)s.batch * heads * s.tr, nk = (unsigned)s_tr.batch * heads * s_tr.tr;
     constexpr unsigned roles = SPLIT ? 3u : 2u, zr = ZeroRows<D, G>::ROWS;
     const unsigned zeros = INDEXED ? (unsigned)s_tr.batch * heads * (((unsigned)s_tr.own_stride + zr - 1u) / zr) : 0u;
-    const RoleGrid g = role_grid<G>(nq, nk, roles);
+    const RoleGrid g = role_grid<G>(s, s_tr, heads, roles);
     dim3 grid(g.tiles + g.rest + zeros), block(G::THREADS);
     hipLaunchKernelGGL((k_bwd_bf16<D, G, INDEXED, SPLIT>), grid, block, 0, st, s, s_tr, Q, K, V, lse, DO, row_scalars,
-                       (__bf16 *)dq, (__bf16 *)dk, (__bf16 *)dv, heads, scale, g);
+                       (__bf16 *)dq, (__bf16 *)dk, (__bf16 *)dv, scale, g);
 }
 
 // At head size 128 one role for dK and dV is less work than two (the scores are computed twice instead of three times,

@@ -120,7 +120,7 @@ __device__ __forceinline__ void fwd_step(const char *sK, const char *sV, const R
 template <int D, typename G, bool WHOLE>
 __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
     HdtSchedule s, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
-    __bf16 *__restrict__ o, float *__restrict__ lse, int heads, float scale_log2, unsigned chunk)
+    __bf16 *__restrict__ o, float *__restrict__ lse, unsigned items, FastDiv heads, FastDiv tr, float scale_log2, FastDiv chunk)
 {
     using P = Pipe<D, FwdCfg<D>::S, false, G>;
     using R = Ring<P>;
@@ -132,8 +132,8 @@ __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int qn = lane & 31, hf = lane >> 5;
     const unsigned lb = logical_block(blockIdx.x, chunk);
-    if (lb >= (unsigned)s.batch * heads * s.tr) return;  // padding of the grid
-    const int I = lb % s.tr, bh = lb / s.tr, b = bh / heads;
+    if (lb >= items) return;  // padding of the grid
+    const int bh = tr.div(lb), I = lb - bh * tr.d, b = heads.div(bh);
     const int I_own = I % s.tr_own;  // the rows this tile works on (several tiles share them when key lists are cut)
     const size_t base = (size_t)bh * s.n_pos * D, own_base = (size_t)bh * s.n_own * D, kv_base = (size_t)bh * s.n_kv * D;
 
@@ -170,9 +170,7 @@ __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
 
     f32x16 oacc[DBLK];
 #pragma unroll
-    for (int i = 0; i < DBLK; i++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) oacc[i][e] = 0.f;
+    for (int i = 0; i < DBLK; i++) oacc[i] = zero_block();
     float m_ref = -INFINITY, l_part = 0.f;
     const int xlane = (lane ^ 32) << 2;  // ds_bpermute address of the partner lane in the other half-wave
 
@@ -193,10 +191,10 @@ __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
         constexpr bool TOUCH = !WHOLE && G::BM == 128;
         MaskTouch<KB * 16> masks;
         if (TOUCH) masks.request(s.bits_rm + ((size_t)bidx * G::NSUB + wave * KB) * 16);
-        R::top(i, n);
+        const typename P::Offsets next = R::top(pipe, i, n);
         wg_barrier();
         if (TOUCH) masks.arrived();
-        R::advance(pipe, i, n);
+        R::advance(pipe, i, n, next);
         const char *sK = pipe.tile_a(i % S), *sV = pipe.tile_b(i % S);
 
         // this wave's two 32x32 sub-blocks of the tile (wave-uniform flags); one straight-line code path
@@ -237,10 +235,10 @@ static void launch_fwd(const HdtSchedule &s, const void *q, const void *k, const
     dim3 grid(padded_grid(items, chunk)), block(G::THREADS);
     if (s.row_flag == nullptr)  // the rectangle of a cross-attention layout: whole sub-blocks are the rule
         hipLaunchKernelGGL((k_fwd_bf16<D, G, true>), grid, block, 0, st, s, (const __bf16 *)q, (const __bf16 *)k,
-                           (const __bf16 *)v, (__bf16 *)o, lse, heads, scale_log2, chunk);
+                           (const __bf16 *)v, (__bf16 *)o, lse, items, FastDiv(heads), FastDiv(s.tr), scale_log2, FastDiv(chunk));
     else
         hipLaunchKernelGGL((k_fwd_bf16<D, G, false>), grid, block, 0, st, s, (const __bf16 *)q, (const __bf16 *)k,
-                           (const __bf16 *)v, (__bf16 *)o, lse, heads, scale_log2, chunk);
+                           (const __bf16 *)v, (__bf16 *)o, lse, items, FastDiv(heads), FastDiv(s.tr), scale_log2, FastDiv(chunk));
 }
 
 hdt_status_t hdt_launch_fwd_bf16(const HdtSchedule &s, const void *q, const void *k, const void *v, void *o,
