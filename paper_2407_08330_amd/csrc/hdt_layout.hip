@@ -604,8 +604,12 @@ constexpr int kLdsKeys = 2048;  // key lists up to this length stay in LDS betwe
 // The lists are in LDS by the time the reservation of their entries (a returning device-scope atomic, about 2 us) is
 // back.  Lists beyond kLdsKeys keys in all are packed straight into global memory instead, with a contiguous share of
 // the document per wave, and read again from there.
-// 1024 threads; 512 for T = 1 with tiles of up to 64 rows, which make twice the workgroups (two of 512 threads share a
-// compute unit where one of 1024 fills it).
+// 512 threads for documents whose scan is a single batch of their 8 waves, 4096 positions: a barrier is shorter, and two or
+// three workgroups share a compute unit where one of 1024 fills it.  Event-bracketed us, 1024 - 512 threads: sections,
+// 64 x 32 tiles, 1 sample of 1000 positions 11.8 - 11.0, 16 of 1536 12.3 - 11.6, 8 of 4096 13.0 - 12.4, 32 of 2048 20.7 - 15.8;
+// 128 x 64 the same or a little more; two schedules of ListOps-shaped trees, 16 of 1536, 21.5 - 17.2; but 4 of 8192
+// 13.1 - 15.5, 1 of 32768 20.8 - 23.8.  (256: 12.5, 13.1, 17.1 and 16.6 in the first four.)  Longer documents get 1024, with
+// T = 1 and tiles of up to 64 rows, which make twice the workgroups, 512.
 __host__ __device__ inline int list_words(int n) { return (((n + 31) >> 5) + 4) & ~3; }  // of `pars`, per tile: a zero word behind
 __host__ inline size_t list_lds(int n, int tiles)
 {
@@ -1096,12 +1100,12 @@ __global__ __launch_bounds__(kListThreads) void k_key_lists(KeyListArgs a)
 }
 
 // Two builds in one launch (the two schedules of a directed mask), blockIdx.y says which: twice the workgroups, so two of
-// them share a compute unit, which takes registers for 8 waves per SIMD (48 tiles of 64 rows per sample, 16 samples: two
-// launches 35 us, one with the registers of the kernel above 25.8, this one 22.5; a kernel of its own, because the
-// arguments read by index cost the single build 0.5 us).  With T = 2 the bound spills 5 registers (24 bytes of scratch per
-// lane) and keeps 32 scalars in vector lanes, which the last figure includes.
+// them share a compute unit, which with 1024 threads takes registers for 8 waves per SIMD (48 tiles of 64 rows per sample, 16
+// samples: two launches 35 us, one with the registers of the kernel above 25.8, this one 22.5, and 17.2 with 512 threads; a
+// kernel of its own, because the arguments read by index cost the single build 0.5 us).  With 1024 threads and T = 2 the
+// bound spills 5 registers (24 bytes of scratch per lane) and keeps 32 scalars in vector lanes, which the figure includes.
 template <int kListThreads, int T>
-__global__ __launch_bounds__(kListThreads, 8) void k_key_lists_both(KeyListLaunch builds)
+__global__ __launch_bounds__(kListThreads, kListThreads == 1024 ? 8 : 4) void k_key_lists_both(KeyListLaunch builds)
 {
     key_lists<kListThreads, T>(builds.args[blockIdx.y]);
 }
@@ -1460,9 +1464,13 @@ hipError_t launch_key_lists(const KeyListArgs *args, int builds, int batch, hipS
             hipLaunchKernelGGL((k_key_lists<THREADS, TILES>), grid, dim3(THREADS), lds, st, a);                             \
         }                                                                                                                   \
     } while (0)
-    if (pair)
+    // 512 threads where the scan then still is a single batch (see key_lists)
+    const bool short_doc = a.n <= 512 * kBatch;
+    if (pair && short_doc)
+        LIST_LAUNCH(512, 2);
+    else if (pair)
         LIST_LAUNCH(1024, 2);
-    else if (small_wg)
+    else if (small_wg || short_doc)
         LIST_LAUNCH(512, 1);
     else
         LIST_LAUNCH(1024, 1);

@@ -219,3 +219,19 @@ def test_directed_masks_both_schedules_from_one_launch(oracle):
         with pytest.raises(hdt.HdtError) as e:
             lay.status()
         assert e.value.name == name
+
+
+@pytest.mark.parametrize("bm,bn", [(128, 64), (64, 32)])
+@pytest.mark.parametrize("n", [4095, 4096, 4097])
+@pytest.mark.parametrize("edges", [7, 6])
+def test_key_lists_around_the_length_where_workgroups_grow(oracle, bm, bn, n, edges):
+    # 512 threads per workgroup up to 4096 positions (one batch of 8 groups per wave), 1024 beyond, one schedule and two
+    import paper_2407_08330_amd as hdt
+    rng = np.random.default_rng(n)
+    tree = inputs.listops_like_tree(rng, n)
+    pair = [tree, _shuffled(*inputs.pseudo_section_document(rng, n)[:2], rng)]
+    level, parent = np.stack([d[0] for d in pair]), np.stack([d[1] for d in pair])
+    lay = hdt.hdt_build_layout(to_dev_i32(level), to_dev_i32(parent), tile_m=bm, tile_n=bn, edges=edges)
+    compare_layout(oracle, lay, level, parent, bm, bn, edges=edges)
+    if edges == 6:
+        compare_layout(oracle, lay.transposed(), level, parent, bm, bn, edges=3)
