@@ -123,6 +123,21 @@ __device__ __forceinline__ int wave_bucket_count(bool in, int bucket)
     return mine;
 }
 
+// the lanes with `in` that hold this lane's bucket (below 64), from the bits of the buckets: time does not depend on how
+// many different ones there are, and bits that all lanes agree on (all but two in a document) cost a ballot
+__device__ __forceinline__ unsigned long long wave_bucket_match(bool in, int bucket)
+{
+    const unsigned long long all = __ballot(in);
+    unsigned long long m = all;
+#pragma unroll
+    for (int bit = 0; bit < 6; bit++) {
+        const bool set = (bucket >> bit) & 1;
+        const unsigned long long b = __ballot(in && set);
+        if (b != 0ull && b != all) m &= set ? b : ~b;
+    }
+    return m;
+}
+
 __device__ __forceinline__ void mark_tiles(uint32_t *bits, int tlo, int thi)
 {
     for (int w = tlo >> 5; w <= (thi >> 5); w++) {
@@ -478,15 +493,42 @@ __device__ __forceinline__ EntryPart entry_bitmaps(bool active, int64_t c, int w
 // Lane c stands for key slot k0 + c and builds that key's COLUMN of the tile: bit r%32 of col[r/32] <=> row r
 // may attend to it.  Rows see a key through their own parent in two ways - the key is that parent, or the
 // key has the same parent - so for both the rows are R(v) = {rows whose parent is v}, with v the key's
-// position or the key's parent; R is tabulated once per tile for the distinct parents of its rows (a
-// handful, since the tokens of a sentence share theirs).  The key itself and the key's own parent are
-// single rows.  The lane masks of the MFMA kernels need no transposition from there: mask e of sub-block
+// position or the key's parent; R is tabulated once per tile, in a hash table over the distinct parents of its
+// rows.  (A handful in a document, since the tokens of a sentence share theirs, dozens in a tree or among shuffled
+// positions: a list of them that one wave makes, one by one, and every key is compared with was the longest phase of
+// such builds.  Event-bracketed us, with such a list and a sort that takes the levels one by one - as it is: 16
+// ListOps-shaped trees of 1536 positions, 64 x 32 tiles, 16.2 - 10.7, 128 x 64 19.4 - 10.4, both schedules of a directed mask
+// 17.2 - 11.8 and 20.5 - 11.2; documents of 1000 positions 10.2 - 9.7, of 8192 the same.)  The key itself and the key's own
+// parent are single rows.  The lane masks of the MFMA kernels need no transposition from there: mask e of sub-block
 // (rblk, cblk) is the column word of key 32*cblk + 8*(e/4) + e%4 (lanes 0..31) next to that of key
 // 32*cblk + 4 + 8*(e/4) + e%4 (lanes 32..63), so every lane stores its own words.
 struct ParentTable {
-    int n;
-    const int *v;         // [n] distinct parents of the tile's rows
-    const uint4 *rows;    // [n] the rows with that parent, 32 per word
+    static constexpr int kSlots = 256;  // of a workgroup's tiles together, twice the rows they can have
+    int slots;                          // of this tile, a power of two
+    int *v;                             // [slots] a parent, or -1
+    uint4 *rows;                        // [slots] the rows with that parent, 32 per word
+    __device__ __forceinline__ int home(int p) const { return (int)(((uint32_t)p * 0x9e3779b1u) >> 16) & (slots - 1); }
+    // row r has parent p.  (At most half of the slots are ever taken, so a search ends.)
+    __device__ __forceinline__ void add(int p, int r) const
+    {
+        int at = home(p);
+        for (;;) {
+            const int old = atomicCAS(&v[at], -1, p);
+            if (old == -1 || old == p) break;
+            at = (at + 1) & (slots - 1);
+        }
+        atomicOr(reinterpret_cast<uint32_t *>(&rows[at]) + (r >> 5), 1u << (r & 31));
+    }
+    // the slot of p, -1 if there is none (p < 0: none)
+    __device__ __forceinline__ int find(int p) const
+    {
+        int at = home(p), x = p < 0 ? -1 : v[at];
+        while (x != p && x != -1) {
+            at = (at + 1) & (slots - 1);
+            x = v[at];
+        }
+        return x == -1 ? -1 : at;
+    }
 };
 
 __device__ __forceinline__ EntryPart entry_columns(int64_t c, int k0, int lane, const ParentTable &tab, const int *ek,
@@ -499,24 +541,15 @@ __device__ __forceinline__ EntryPart entry_columns(int64_t c, int k0, int lane, 
     const int kj = slot ? ek[k] : -1, kr = slot ? ep[k] : -1;  // -1: no key
     const int v_up = (edges & HDT_EDGE_UP) ? kj : -1, v_sib = (edges & HDT_EDGE_SIBLING) ? kr : -1;
     uint32_t col[4] = {0u, 0u, 0u, 0u};
-    // (The parents in registers, an entry per lane: out of LDS every step would wait for its read.  The rows of an entry are
-    // brought, out of LDS, only where some key has that parent: a tile of a document in pre-order has two or three
-    // parents, one of shuffled positions dozens.  Whole builds, 64 x 32 tiles, shuffled documents, rows out of registers for
-    // every entry - this: 4 samples of 1000 positions 27.8 - 23.4 us, 8192 132 - 96; in pre-order no difference.)
-    auto look_up = [&](int v, int t) {
-        const bool hit = v_up == v || v_sib == v;  // v >= 0
-        if (__ballot(hit) == 0ull) return;
-        const uint4 r = tab.rows[t];
-        col[0] |= hit ? r.x : 0u;
-        col[1] |= hit ? r.y : 0u;
-        col[2] |= hit ? r.z : 0u;
-        col[3] |= hit ? r.w : 0u;
-    };
-    const int tv = lane < tab.n ? tab.v[lane] : -1;
-#pragma unroll 1
-    for (int t = 0; t < min(tab.n, 64); t++) look_up(__builtin_amdgcn_readlane(tv, t), t);
-#pragma unroll 1
-    for (int t = 64; t < tab.n; t++) look_up(tab.v[t], t);
+    const int at_up = tab.find(v_up), at_sib = tab.find(v_sib);
+    if (at_up >= 0) {
+        const uint4 r = tab.rows[at_up];
+        col[0] = r.x, col[1] = r.y, col[2] = r.z, col[3] = r.w;
+    }
+    if (at_sib >= 0) {
+        const uint4 r = tab.rows[at_sib];
+        col[0] |= r.x, col[1] |= r.y, col[2] |= r.z, col[3] |= r.w;
+    }
     // the key itself; the key's parent (the key is that row's child).  A key or a key's parent inside the
     // tile's range is a real position, hence a valid row.
     const int r_self = kj - row0, r_down = (edges & HDT_EDGE_DOWN) ? kr - row0 : -1;
@@ -607,7 +640,7 @@ constexpr int kLdsKeys = 2048;  // key lists up to this length stay in LDS betwe
 // 512 threads for documents whose scan is a single batch of their 8 waves, 4096 positions: a barrier is shorter, and two or
 // three workgroups share a compute unit where one of 1024 fills it.  Event-bracketed us, 1024 - 512 threads: sections,
 // 64 x 32 tiles, 1 sample of 1000 positions 11.8 - 11.0, 16 of 1536 12.3 - 11.6, 8 of 4096 13.0 - 12.4, 32 of 2048 20.7 - 15.8;
-// 128 x 64 the same or a little more; two schedules of ListOps-shaped trees, 16 of 1536, 21.5 - 17.2; but 4 of 8192
+// 128 x 64 the same or a little more; two schedules of ListOps-shaped trees, 16 of 1536, 21.5 - 17.2 (both before the parents were hashed); but 4 of 8192
 // 13.1 - 15.5, 1 of 32768 20.8 - 23.8.  (256: 12.5, 13.1, 17.1 and 16.6 in the first four.)  Longer documents get 1024, with
 // T = 1 and tiles of up to 64 rows, which make twice the workgroups, 512.
 __host__ __device__ inline int list_words(int n) { return (((n + 31) >> 5) + 4) & ~3; }  // of `pars`, per tile: a zero word behind
@@ -626,14 +659,13 @@ __device__ __forceinline__ void key_lists(const KeyListArgs &a)
     // group of 64 positions (16 bits, group g of tile h at [g * T + h]).  keys: the same order, so that the words of all
     // tiles for 64 positions are 8 T consecutive bytes.
     extern __shared__ __attribute__((aligned(16))) uint32_t s_dyn[];
-    __shared__ int2 s_row[128];          // (position, parent) of the rows: tile h at [h * RT, h * RT + RT); position -2: no such row
     __shared__ int s_lcnt[kItemGroups][kBuckets];  // keys per (group of 64 packed keys, level)
     __shared__ int s_cnt[2][W];          // partial results of an entry's two waves (tile_n > 64), by parity of the round
     __shared__ uint32_t s_any[2][W], s_all[2][W];
     __shared__ int s_base, s_wtotal[T][W], s_total[T];
     __shared__ __attribute__((aligned(16))) int s_keys[kLdsKeys], s_kpar[kLdsKeys];
-    __shared__ int s_tab_v[128], s_ntab[T];  // distinct parents of a tile's rows, and the rows of each
-    __shared__ uint4 s_tab_rows[128];
+    __shared__ int s_tab_v[ParentTable::kSlots];  // the tiles' parent tables
+    __shared__ uint4 s_tab_rows[ParentTable::kSlots];
     __shared__ int s_first[T];               // first real row of a tile (a position), INT_MAX if it has none
     const int per_sample = (a.tr + T - 1) / T;
     const int b = blockIdx.x / per_sample, I0 = (blockIdx.x - b * per_sample) * T, n = a.n;
@@ -672,6 +704,17 @@ __device__ __forceinline__ void key_lists(const KeyListArgs &a)
     }
     load_batch(0, klv, kp);
     for (int w = tid; w < T * (pw + 2 * ng); w += kListThreads) s_dyn[w] = 0u;
+    if (tid < ParentTable::kSlots) {
+        s_tab_v[tid] = -1;
+        s_tab_rows[tid] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    ParentTable tab[T];
+#pragma unroll
+    for (int h = 0; h < T; h++) {
+        tab[h].slots = ParentTable::kSlots / T;
+        tab[h].v = s_tab_v + h * (ParentTable::kSlots / T);
+        tab[h].rows = s_tab_rows + h * (ParentTable::kSlots / T);
+    }
     if (tid < T) s_first[tid] = INT_MAX;
     lds_barrier();
     bool check_parent = false;
@@ -682,7 +725,6 @@ __device__ __forceinline__ void key_lists(const KeyListArgs &a)
             my_level = -1;
         }
         const bool real = have_row && my_level >= 0;
-        s_row[tid] = real ? make_int2(my_row, p) : make_int2(-2, -2);
         // this wave's rows: two words of the bitmaps
         const unsigned long long rows = __ballot(real);
         if (lane < 2 && rows) {
@@ -693,6 +735,7 @@ __device__ __forceinline__ void key_lists(const KeyListArgs &a)
             if (lane == 0) atomicMin(&s_first[my_tile], my_row + __ffsll((long long)rows) - 1);
         }
         if (real && p >= 0) {
+            (my_tile ? tab[T - 1] : tab[0]).add(p, tid % RT);
             if (e_sib) atomicOr(&s_pars[(p >> 5) * T + my_tile], 1u << (p & 31));
             if (e_up) atomicOr(&s_need[(p >> 5) * T + my_tile], 1u << (p & 31));
             check_parent = true;
@@ -766,26 +809,6 @@ __device__ __forceinline__ void key_lists(const KeyListArgs &a)
         }
         if (lane == 0) reserved = reserve_entries(a.counters, entries);
     }
-    if (wave >= 2 && wave < 2 + T) {  // the table of the rows' parents (see entry_columns)
-        const int h = wave - 2;
-        const int2 ra = s_row[h * RT + lane], rb = T == 1 ? s_row[64 + lane] : make_int2(-2, -2);
-        const int pa = ra.x >= 0 ? ra.y : -1, pb = rb.x >= 0 ? rb.y : -1;
-        unsigned long long rem_a = __ballot(pa >= 0), rem_b = __ballot(pb >= 0);
-        int nt = h * RT;
-        while (rem_a | rem_b) {
-            const int v = rem_a ? __builtin_amdgcn_readlane(pa, __ffsll((long long)rem_a) - 1)
-                                : __builtin_amdgcn_readlane(pb, __ffsll((long long)rem_b) - 1);
-            const unsigned long long ma = __ballot(pa == v), mb = __ballot(pb == v);
-            if (lane == 0) {
-                s_tab_v[nt] = v;
-                s_tab_rows[nt] = make_uint4((uint32_t)ma, (uint32_t)(ma >> 32), (uint32_t)mb, (uint32_t)(mb >> 32));
-            }
-            rem_a &= ~ma;
-            rem_b &= ~mb;
-            nt++;
-        }
-        if (lane == 0) s_ntab[h] = nt - h * RT;
-    }
     if (wave >= 4 && wave < 4 + T) {  // the needed keys of a tile in front of every group of 64 positions
         const int h = wave - 4;
         int first = 0;
@@ -858,7 +881,7 @@ __device__ __forceinline__ void key_lists(const KeyListArgs &a)
             i0[h] = h ? igroups[0] : 0;
         }
         const int n_groups = igroups[0] + (T > 1 ? igroups[T - 1] : 0);
-        int key[kRounds], par[kRounds];
+        int key[kRounds], par[kRounds], rank[kRounds];  // rank: keys of this one's level in front of it in its group
         auto tile_of = [&](int k) { return T > 1 && k >= igroups[0] ? T - 1 : 0; };
 #pragma unroll
         for (int x = 0; x < kRounds; x++) {
@@ -867,8 +890,10 @@ __device__ __forceinline__ void key_lists(const KeyListArgs &a)
             const int h = tile_of(k), t = (k - i0[h]) * 64 + lane, at = (h ? total[0] : 0) + t;
             key[x] = t < total[h] ? s_keys[at] : -1;
             par[x] = t < total[h] ? s_kpar[at] : -1;
-            const int mine = wave_bucket_count(key[x] >= 0, key[x] >> 24);
-            if (lane < kBuckets) s_lcnt[k][lane] = mine;
+            const unsigned long long same = wave_bucket_match(key[x] >= 0, key[x] >> 24);
+            rank[x] = __popcll(same & lanemask_lt());
+            if (lane < kBuckets) s_lcnt[k][lane] = 0;
+            if (key[x] >= 0 && rank[x] == 0) s_lcnt[k][key[x] >> 24] = __popcll(same);
         }
         lds_barrier();
         // Slots behind the last key name no key: they hold ~f, f = the tile's first real row (a list with a key has
@@ -893,15 +918,7 @@ __device__ __forceinline__ void key_lists(const KeyListArgs &a)
                 }
             const int first_of_level = koff[h] + wave_scan(all) - all + before;
             const bool in = key[x] >= 0;
-            const int bk_mine = key[x] >> 24;
-            int t = 0;
-            unsigned long long remaining = __ballot(in);
-            while (remaining) {
-                const int bk = __builtin_amdgcn_readlane(bk_mine, __ffsll((long long)remaining) - 1);
-                const unsigned long long m = __ballot(in && bk_mine == bk);
-                if (in && bk_mine == bk) t = __builtin_amdgcn_readlane(first_of_level, bk) + __popcll(m & lanemask_lt());
-                remaining &= ~m;
-            }
+            const int t = __shfl(first_of_level, in ? key[x] >> 24 : 0) + rank[x];
             if (in) {
                 s_keys[t] = key[x] & 0xffffff;
                 s_kpar[t] = par[x];
@@ -1017,13 +1034,6 @@ __device__ __forceinline__ void key_lists(const KeyListArgs &a)
     // sequence; lists that did not fit are brought back tile by tile, as many entries at a time as fit.
     const int wpe = (bn + 63) >> 6, per_round = W / wpe;  // waves per entry, entries per round
     const int quad = wave / wpe, k0 = (wave - quad * wpe) * 64;
-    ParentTable tab[T];
-#pragma unroll
-    for (int h = 0; h < T; h++) {
-        tab[h].n = s_ntab[h];
-        tab[h].v = s_tab_v + h * RT;
-        tab[h].rows = s_tab_rows + h * RT;
-    }
     int parity = 0;
     auto finish = [&](bool active, int64_t c, const EntryPart &part) {  // pair count and summary of entry c
         if (wpe == 1) {
