@@ -38,11 +38,9 @@ using namespace hdt_tile;
 
 template <int D>
 struct BwdCfg {
-    // ring stages of the two roles and waves per SIMD (register budget) of the kernel.  Three waves at head size
+    // waves per SIMD (register budget) of the kernel.  Three waves at head size
     // 64 pay on 128 x 64 tiles only (measured, config 4: 107 us against 122 with two; on 64 x 32 tiles 101
     // against 99 with two, whose allocation the compiler then leaves unconstrained).
-    static constexpr int S_DQ = (D == 64) ? 3 : 2;
-    static constexpr int S_DKV = 2;
     // The INDEXED form on 128 x 64 tiles is compiled for one wave less: bounded to the third (second) it would spill a
     // few registers, which the counted waits do not allow.  It gets two per SIMD (178 registers at head size 64, 247 at
     // 128); at head size 128 with the split roles only, see launch_roles.
@@ -98,7 +96,7 @@ __device__ __forceinline__ void dq_role(char *smem, const HdtSchedule &s, const 
                                          const float2 *__restrict__ row_scalars, __bf16 *__restrict__ dq, int wave,
                                          int I, int bh, int b, float scale)
 {
-    using P = Pipe<D, BwdCfg<D>::S_DQ, false, G>;
+    using P = Pipe<D, false, G>;
     using R = Ring<P>;
     constexpr int BM = G::BM, BN = G::BN, KB = G::KB;
     constexpr int ROWB = P::ROWB, KSTEPS = P::KSTEPS, DBLK = P::DBLK, S = P::S;
@@ -127,16 +125,14 @@ __device__ __forceinline__ void dq_role(char *smem, const HdtSchedule &s, const 
     const RowLane rl = row_lane<P::CPR>(lane);
     const TrLane tl = tr_lane<P::CPR>(lane);
 
-    // Q and dO rows of this wave go through the two highest ring stages (full-row loads into LDS);
-    // the B fragments are read back from there.  The ring may only take those stages over after a
-    // barrier, so the prologue is issued in two pieces.
-    constexpr uint32_t STG_Q = (uint32_t)(S - 1) * 2 * P::TILE, STG_DO = (uint32_t)(S - 2) * 2 * P::TILE;
+    // Q and dO rows of this wave go through the two ring stages (full-row loads into LDS); the B fragments are read back
+    // from there.  The ring may only take the stages over after a barrier.
+    constexpr uint32_t STG_Q = 2 * P::TILE, STG_DO = 0;
     const OwnRows<P> own = own_rows(pipe, I_own * BM, s.n_own);
     stage_own_rows(pipe, q + own_base, own, STG_Q);
     stage_own_rows(pipe, d_o + own_base, own, STG_DO);
     R::start(pipe, n);
-    R::template prologue<0, S - 2>(pipe, n);
-    if (S == 2 || n == 0) wait_vmcnt<0>();  // otherwise the prologue's first wait covered the staged rows
+        wait_vmcnt<0>();
     bf16x8 qf[KSTEPS], dof[KSTEPS];
 #pragma unroll
     for (int st = 0; st < KSTEPS; st++) {
@@ -157,7 +153,7 @@ __device__ __forceinline__ void dq_role(char *smem, const HdtSchedule &s, const 
     // the compiler must finish its own loads before the hand-scheduled ones continue
     asm volatile("" ::"v"(dp_init), "v"(s_init), "v"(lse_i));
     wg_barrier();  // every wave has read its fragments: the ring may use all stages
-    R::template prologue<S - 2, S - 1>(pipe, n);
+    R::prologue(pipe, n);
 
     f32x16 dqacc[DBLK];
 #pragma unroll
@@ -170,7 +166,7 @@ __device__ __forceinline__ void dq_role(char *smem, const HdtSchedule &s, const 
         if (i + 1 < n) {
             sub_next = subs[i + 1];
         }
-        const typename P::Offsets next = R::top(pipe, i, n);
+        const typename P::Offsets next = R::top(pipe, i);
         wg_barrier();
         R::advance(pipe, i, n, next);
         const char *sK = pipe.tile_a(i % S), *sV = pipe.tile_b(i % S);
@@ -233,7 +229,7 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
     // SIMD.  What can be computed anew per entry or sub-block from the lane number is (LEAN): held in registers throughout
     // the loop, as the compiler would have it, 30 to 56 registers did not fit.
     constexpr bool LEAN = D == 128 && WHICH == 0;
-    using P = Pipe<D, BwdCfg<D>::S_DKV, true, G, LEAN>;
+    using P = Pipe<D, true, G, LEAN>;
     using R = Ring<P>;
     constexpr int BM = G::BM, BN = G::BN, KB = G::KB;
     constexpr int ROWB = P::ROWB, KSTEPS = P::KSTEPS, DBLK = P::DBLK, S = P::S;
@@ -272,8 +268,8 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
     const int32_t *flag_at = s.row_flag ? s.row_flag + ((size_t)b * s.n_pos + own_row) : s.q_range;
     int own_flag = *flag_at;
 
-    // K and V rows of this wave: through the two highest ring stages, as Q and dO in the dQ pass
-    constexpr uint32_t STG_K = (uint32_t)(S - 1) * 2 * P::TILE, STG_V = (uint32_t)(S - 2) * 2 * P::TILE;
+    // K and V rows of this wave: through the two ring stages, as Q and dO in the dQ pass
+    constexpr uint32_t STG_K = 2 * P::TILE, STG_V = 0;
     const OwnRows<P> own = own_rows(pipe, I * BM, n_rows, index);
     // where this wave's rows go: kept in LDS until the epilogue (registers are short, scalar ones included)
     int *row_at = reinterpret_cast<int *>(smem + P::SMEM_BYTES) + wave * 32;
@@ -284,8 +280,7 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
     stage_own_rows(pipe, k + base, own, STG_K);
     if (DO_DK) stage_own_rows(pipe, v + base, own, STG_V);  // V only enters dP
     R::start(pipe, n);
-    R::template prologue<0, S - 2>(pipe, n);
-    if (S == 2 || n == 0) wait_vmcnt<0>();
+        wait_vmcnt<0>();
     bf16x8 kf[KSTEPS], vf[KSTEPS];
 #pragma unroll
     for (int st = 0; st < KSTEPS; st++) {
@@ -303,7 +298,7 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
         }
     }
     wg_barrier();
-    R::template prologue<S - 2, S - 1>(pipe, n);
+    R::prologue(pipe, n);
 
     f32x16 dkacc[DBLK], dvacc[DBLK];
 #pragma unroll
@@ -319,7 +314,7 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
         if (i + 1 < n) {
             sub_next = subs[i + 1];
         }
-        const typename P::Offsets next = R::top(pipe, i, n);
+        const typename P::Offsets next = R::top(pipe, i);
         wg_barrier();
         R::advance(pipe, i, n, next);
         const char *sQ = pipe.tile_a(i % S), *sDO = pipe.tile_b(i % S);
@@ -468,8 +463,8 @@ __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)
     const float2 *__restrict__ row_scalars, __bf16 *__restrict__ dq, __bf16 *__restrict__ dk,
     __bf16 *__restrict__ dv, float scale, RoleGrid grid)
 {
-    using PQ = Pipe<D, BwdCfg<D>::S_DQ, false, G>;
-    using PK = Pipe<D, BwdCfg<D>::S_DKV, true, G>;
+    using PQ = Pipe<D, false, G>;
+    using PK = Pipe<D, true, G>;
     constexpr int SMEM_K = PK::SMEM_BYTES + (INDEXED ? G::BM * 4 : 0);
     constexpr int SMEM = PQ::SMEM_BYTES > SMEM_K ? PQ::SMEM_BYTES : SMEM_K;
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];

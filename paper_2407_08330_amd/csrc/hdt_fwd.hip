@@ -29,7 +29,6 @@ using namespace hdt_tile;
 
 template <int D>
 struct FwdCfg {
-    static constexpr int S = 2;                      // ring stages (LDS at 128 x 64: 36 KB / 68 KB per workgroup)
     static constexpr int WAVES = (D == 64) ? 4 : 2;  // waves per SIMD the register budget allows
 };
 
@@ -122,7 +121,7 @@ __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
     HdtSchedule s, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
     __bf16 *__restrict__ o, float *__restrict__ lse, unsigned items, FastDiv heads, FastDiv tr, float scale_log2, FastDiv chunk)
 {
-    using P = Pipe<D, FwdCfg<D>::S, false, G>;
+    using P = Pipe<D, false, G>;
     using R = Ring<P>;
     constexpr int BM = G::BM, BN = G::BN, KB = G::KB;
     constexpr int ROWB = P::ROWB, KSTEPS = P::KSTEPS, DBLK = P::DBLK, S = P::S;
@@ -163,7 +162,7 @@ __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
     if (n > 0) {
         stage_own_rows(pipe, q + own_base, own_rows(pipe, I_own * BM, s.n_own), Q_STAGE);
         R::start(pipe, n);
-        R::template prologue<0, S - 1>(pipe, n);  // its first wait covers the Q rows
+        R::prologue(pipe, n);  // its first wait covers the Q rows
 #pragma unroll
         for (int st = 0; st < KSTEPS; st++) qf[st] = read_row<ROWB>(smem + Q_STAGE, rl, wave * 32, st);
     }
@@ -191,7 +190,7 @@ __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
         constexpr bool TOUCH = !WHOLE && G::BM == 128;
         MaskTouch<KB * 16> masks;
         if (TOUCH) masks.request(s.bits_rm + ((size_t)bidx * G::NSUB + wave * KB) * 16);
-        const typename P::Offsets next = R::top(pipe, i, n);
+        const typename P::Offsets next = R::top(pipe, i);
         wg_barrier();
         if (TOUCH) masks.arrived();
         R::advance(pipe, i, n, next);

@@ -10,9 +10,9 @@
 // finer one is ~5-10 % ahead at head size 128; its layout takes 1-4 us longer to build.
 //
 // The gather uses the CDNA direct-to-LDS loads (global_load_lds_*: every lane supplies a global
-// address, the 64 results land in LDS at M0 + lane*size) into a ring of S stages, so that several
-// tiles are in flight per workgroup without holding them in registers:
-//   iteration t:  wait until tile t has landed -> barrier -> start tile t+S-1 -> compute tile t.
+// address, the 64 results land in LDS at M0 + lane*size) into a ring of two stages, so that a
+// tile is in flight per workgroup without being held in registers:
+//   iteration t:  wait until tile t has landed -> barrier -> start tile t+1 -> compute tile t.
 // The key positions of an entry are read the same way, one tile further ahead than the rows they
 // address, and the entries' summaries with scalar loads, so no iteration waits on a chain of dependent
 // loads.
@@ -165,10 +165,10 @@ __device__ __forceinline__ int opaque(int x)
 __device__ __forceinline__ int gather_row(int slot_value) { return slot_value ^ (slot_value >> 31); }
 
 // LEAN: the gather's per-lane offsets are computed anew for every tile instead of being held in registers throughout
-template <int D, int S_, bool AUX, typename G, bool LEAN = false>
+template <int D, bool AUX, typename G, bool LEAN = false>
 struct Pipe {
     static constexpr int BM = G::BM, BN = G::BN, NW = G::NW;
-    static constexpr int S = S_;                      // data stages in the ring
+    static constexpr int S = 2;                       // data stages in the ring
     static constexpr int PS = 4;                      // position stages
     static constexpr int KSTEPS = D / 16;             // MFMA steps over the head dimension
     static constexpr int DBLK = D / 32;               // 32-wide blocks of the head dimension
@@ -250,19 +250,22 @@ struct Pipe {
     }
 };
 
-// Ring schedule (positions run one tile ahead of their rows).  Per wave the vector-memory
+// Ring schedule (two stages; positions run one tile ahead of their rows).  Per wave the vector-memory
 // instructions are issued in the order  pos(0), pos(1), data(0), pos(2), data(1), ..., pos(j+1), data(j), ...
-// where data(j) is NDMA instructions and pos(j) one.
-//   start(n), prologue(n): start pos(0..S-1) and data(0..S-2) as far as they exist
-//   top(i, n):         call at the top of iteration i: waits until data(i) and pos(i+S-1) have landed in LDS for this
-//                      wave and returns where the rows of data(i+S-1) are (every wave reads its own copy of the
+//   start(n), prologue(n): start pos(0), pos(1); and data(0)
+//   top(i):            call at the top of iteration i: waits until data(i) and pos(i+1) have landed in LDS for this
+//                      wave and returns where the rows of data(i+1) are (every wave reads its own copy of the
 //                      positions, so this needs no barrier); the caller then executes a workgroup barrier
-//   advance(i, n, o):  after the barrier: starts pos(i+S) and data(i+S-1), whose rows are at o
+//   advance(i, n, o):  after the barrier: starts pos(i+2) and data(i+1), whose rows are at o
+// A third stage does not pay: in the backward at head size 64 the dQ role had one and is as fast or faster without (dense
+// cross-attention 190 -> 183 us, 8192 positions on 64 x 32 tiles 80.9 -> 80.4, on 128 x 64 91.4 -> 90.5; nowhere slower by
+// more than 0.3 %), and in the dK/dV role it takes registers that cost a wave per SIMD (81 -> 101).
 template <typename P>
 struct Ring {
-    static constexpr int S = P::S, NDMA = P::NDMA, PS = P::PS;
+    static constexpr int S = P::S, PS = P::PS;
+    static_assert(S == 2, "the waits are those of two stages");
 
-    // first half of the prologue: pos(0), pos(1).  The caller may issue its own (compiler-scheduled)
+    // first half of the prologue.  The caller may issue its own (compiler-scheduled)
     // loads after this and before prologue(); the compiler's wait for those also covers these two.
     static __device__ __forceinline__ void start(const P &p, int n)
     {
@@ -270,42 +273,25 @@ struct Ring {
         if (n > 1) p.issue_pos(1, 1);
     }
 
-    // second half: pos(j+1), data(j) for j in [J0, J1) (the whole prologue is J0 = 0, J1 = S-1; it may be
-    // issued in two pieces when some ring stages are still in use, see the backward kernels)
-    template <int J0, int J1>
+    // second half
     static __device__ __forceinline__ void prologue(const P &p, int n)
     {
-#pragma unroll
-        for (int j = J0; j < J1; j++) {
-            if (j > 0 && j + 1 < n) p.issue_pos(j + 1, (j + 1) % PS);
-            if (j < n) {
-                // pos(j) must have landed; issued after it: [data(j-1)], [pos(j+1)]
-                if (j == 0) {
-                    if (1 < n) wait_vmcnt<1>(); else wait_vmcnt<0>();
-                } else {
-                    if (j + 1 < n) wait_vmcnt<NDMA + 1>(); else wait_vmcnt<NDMA>();
-                }
-                p.issue_data(j % S, p.offsets(j % PS));
-            }
+        if (n > 0) {
+            if (n > 1) wait_vmcnt<1>(); else wait_vmcnt<0>();  // pos(0) must have landed; issued after it: [pos(1)]
+            p.issue_data(0, p.offsets(0));
         }
     }
 
-    static __device__ __forceinline__ typename P::Offsets top(const P &p, int i, int n)
+    static __device__ __forceinline__ typename P::Offsets top(const P &p, int i)
     {
-        // S == 2: data(i) is what was issued last.  S == 3: behind it came pos(i+2) and data(i+1) as far as they exist;
-        // data(i+1) may stay in flight.
-        static_assert(S == 2 || S == 3, "unsupported ring");
-        if (S == 3 && i + 1 < n)
-            wait_vmcnt<NDMA>();
-        else
-            wait_vmcnt<0>();
-        return p.offsets((i + S - 1) % PS);  // (read, and not used, also where there is no such entry)
+        wait_vmcnt<0>();
+        return p.offsets((i + 1) % PS);  // (read, and not used, also where there is no such entry)
     }
 
     static __device__ __forceinline__ void advance(const P &p, int i, int n, const typename P::Offsets &o)
     {
-        if (i + S < n) p.issue_pos(i + S, (i + S) % PS);
-        if (i + S - 1 < n) p.issue_data((i + S - 1) % S, o);
+        if (i + 2 < n) p.issue_pos(i + 2, (i + 2) % PS);
+        if (i + 1 < n) p.issue_data((i + 1) % S, o);
     }
 };
 
