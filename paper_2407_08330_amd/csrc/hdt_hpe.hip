@@ -47,8 +47,12 @@ __device__ __forceinline__ int2 my_share(int n, int shares)  // [first, last) of
 // ---- parents of a document laid out with its anchors in front (pre-order) ---------------------------
 // parent[i] = the nearest earlier position whose level is level[i] - 1 (none: -1).  Inside a wave by ballots, across
 // the waves of a chunk and in front of it through LDS (the last position of every level).  The positions in front of a
-// share are read backwards until every level that somebody still misses has been seen.
+// share are read backwards until every level that somebody still misses has been seen; the first 8192 of them are requested
+// with the share itself (event-bracketed us, where an empty kernel takes 6.1: 8192 positions x 4 samples 8.6 -> 8.1, 32768 x 1
+// 13.2 -> 11.2; batches with one share per sample, without the search, 8192 x 512 40.0 -> 38.3, 512 x 1024 13.7 -> 13.0).
 // With one share `parent` may be `level`: a position's level is read by its own thread alone, before its parent is written.
+// SPREAD: several shares per sample; otherwise nothing stands in front of a share, and nothing is looked for there.
+template <bool SPREAD>
 __global__ __launch_bounds__(kOrdThreads) void k_parents_from_levels(const int32_t *level, int n, int shares, int32_t *parent)
 {
     __shared__ int s_last[kOrdWaves][32];  // last position of each level in each wave of the chunk (-1: none)
@@ -58,12 +62,24 @@ __global__ __launch_bounds__(kOrdThreads) void k_parents_from_levels(const int32
     const size_t o = (size_t)(blockIdx.x / shares) * n;
     const int2 share = my_share(n, shares);
     unsigned searched = 0u;  // levels looked for in front of the share
+    // the kBack * 1024 positions that end at `end`
+    auto load_back = [&](int end, int (&l)[kBack]) {
+#pragma unroll
+        for (int u = 0; u < kBack; u++) {
+            const int j = end - (u + 1) * kOrdThreads + tid;
+            l[u] = j >= 0 ? level[o + j] : -1;
+        }
+    };
+    // the first chunk and the positions in front of the share are requested together, whoever turns out to need the latter
+    const int first_level = share.x + tid < share.y ? level[o + share.x + tid] : -1;
+    int back[kBack];
+    if (SPREAD && share.x > 0) load_back(share.x, back);
     if (tid < 32) s_carry[tid] = -1;
     if (tid == 0) s_missing = 0u;
     __syncthreads();
     for (int c0 = share.x; c0 < share.y; c0 += kOrdThreads) {
         const int i = c0 + tid;
-        int lv = i < share.y ? level[o + i] : -1;
+        int lv = c0 == share.x ? first_level : (i < share.y ? level[o + i] : -1);
         if (lv < 0 || lv >= 32) lv = -1;
         // level by level of those in this wave: its last position (kept by lane = level), and for the positions one
         // level down the nearest earlier one
@@ -81,26 +97,22 @@ __global__ __launch_bounds__(kOrdThreads) void k_parents_from_levels(const int32
         if (lv > 0)  // not in this wave: earlier waves of the chunk, then earlier chunks of the share
             for (int w = wave - 1; w >= 0 && par < 0; w--) par = s_last[w][lv - 1];
         const bool miss = lv > 0 && par < 0;
-        if (miss && s_carry[lv - 1] < 0) atomicOr(&s_missing, 1u << (lv - 1));
-        __syncthreads();
-        unsigned missing = s_missing & ~searched;
-        searched |= missing;
-        for (int end = share.x; missing && end > 0; end -= kBack * kOrdThreads) {
-            int l[kBack];
-#pragma unroll
-            for (int u = 0; u < kBack; u++) {
-                const int j = end - (u + 1) * kOrdThreads + tid;
-                l[u] = j >= 0 ? level[o + j] : -1;
-            }
-#pragma unroll
-            for (int u = 0; u < kBack; u++) {
-                const int j = end - (u + 1) * kOrdThreads + tid;
-                if (l[u] >= 0 && l[u] < 32 && ((missing >> l[u]) & 1u) && s_carry[l[u]] < j) atomicMax(&s_carry[l[u]], j);
-            }
+        if (SPREAD) {
+            if (miss && s_carry[lv - 1] < 0) atomicOr(&s_missing, 1u << (lv - 1));
             __syncthreads();
-            for (int t = 0; t < 32; t++)
-                if (s_carry[t] >= 0) missing &= ~(1u << t);
-            __syncthreads();  // everybody has looked before the next round writes
+            unsigned missing = s_missing & ~searched;
+            searched |= missing;
+            for (int end = share.x; missing && end > 0; end -= kBack * kOrdThreads) {
+                if (end < share.x || c0 > share.x) load_back(end, back);
+#pragma unroll
+                for (int u = 0; u < kBack; u++) {
+                    const int j = end - (u + 1) * kOrdThreads + tid;
+                    if (back[u] >= 0 && back[u] < 32 && ((missing >> back[u]) & 1u) && s_carry[back[u]] < j) atomicMax(&s_carry[back[u]], j);
+                }
+                __syncthreads();
+                missing &= ~(unsigned)__ballot(lane < 32 && s_carry[lane & 31] >= 0);
+                __syncthreads();  // everybody has looked before the next round writes
+            }
         }
         if (miss) par = s_carry[lv - 1];
         if (i < share.y) parent[o + i] = par;
@@ -112,7 +124,7 @@ __global__ __launch_bounds__(kOrdThreads) void k_parents_from_levels(const int32
                     break;
                 }
         }
-        if (tid == 0) s_missing = 0u;
+        if (SPREAD && tid == 0) s_missing = 0u;
         __syncthreads();
     }
 }
@@ -503,8 +515,11 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_parents_from_
     HdtTimer t("hdt_hpe_parents_from_levels", st);
     // in place: the levels in front of a share would be gone by the time it reads them, so one workgroup has the whole sample
     const int shares = d_parent == d_level ? 1 : hpe_shares(batch, n_pos);
-    hipLaunchKernelGGL(k_parents_from_levels, dim3((unsigned)batch * shares), dim3(kOrdThreads), 0, st, d_level, n_pos, shares,
-                       d_parent);
+    const dim3 grid((unsigned)batch * shares), block(kOrdThreads);
+    if (shares > 1)
+        hipLaunchKernelGGL(k_parents_from_levels<true>, grid, block, 0, st, d_level, n_pos, shares, d_parent);
+    else
+        hipLaunchKernelGGL(k_parents_from_levels<false>, grid, block, 0, st, d_level, n_pos, shares, d_parent);
     HDT_HIP_TRY(hipGetLastError());
     return HDT_OK;
 }
