@@ -36,17 +36,17 @@ HBM_PEAK_GBS = 8000.0           # MI355X HBM3E
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16
 
 
-def algorithmic_bytes_per_unit(kernel: str, d: int) -> int:
+def algorithmic_bytes_per_unit(kernel: str, d: int, d_pass: bool) -> int:
     """Compulsory HBM bytes per (position, head) of one launch of `kernel` (bf16 tensors, fp32 row scalars):
     forward reads Q,K,V and writes O,LSE; the D pass reads O,dO,LSE and writes the pair (-D, -LSE/scale); the
-    backward kernel reads Q,K,V,dO,LSE and that pair and writes dQ,dK,dV."""
+    backward kernel reads Q,K,V,dO,LSE and that pair, or O where there is no D pass, and writes dQ,dK,dV."""
     row = 2 * d
     if kernel.startswith("hdt_fwd"):
         return 4 * row + 4
     if kernel.startswith("hdt_bwd_delta"):
         return 2 * row + 12
     if kernel.startswith("hdt_bwd_bf16"):
-        return 7 * row + 12
+        return 7 * row + 12 if d_pass else 8 * row + 4
     raise KeyError(kernel)
 
 
@@ -361,9 +361,10 @@ def main() -> int:
 
     units = B * H * N
     attn = {n: kv for n, kv in per_kernel.items() if not n.startswith("hdt_layout")}
+    d_pass = any(n.startswith("hdt_bwd_delta") for n in per_kernel)
     if attn:
         dom = max(attn, key=lambda n: attn[n]["avg_us"] * attn[n]["launches"])
-        alg_bytes = algorithmic_bytes_per_unit(dom, D) * units
+        alg_bytes = algorithmic_bytes_per_unit(dom, D, d_pass) * units
         achieved = alg_bytes / (attn[dom]["avg_us"] * 1e-6) / 1e9
         # HBM bytes per launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (scaled by a copy kernel of
         # known size).  Counters cannot be read from inside this process: the figure of the last profiled run of
@@ -407,8 +408,8 @@ def main() -> int:
             "mfma_frac_of_practical_peak": round(executed / (us * 1e-6) / 1e12 / mfma_tflops, 4),
             # every sub-block of every issued tile, skipped or not
             "whole_tile_tflops_incl_skipped_subblocks": round(issued / (us * 1e-6) / 1e12, 2),
-            "hbm_gbs_algorithmic": round(algorithmic_bytes_per_unit(name, D) * units / (us * 1e-6) / 1e9, 1),
-            "hbm_frac": round(algorithmic_bytes_per_unit(name, D) * units / (us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
+            "hbm_gbs_algorithmic": round(algorithmic_bytes_per_unit(name, D, d_pass) * units / (us * 1e-6) / 1e9, 1),
+            "hbm_frac": round(algorithmic_bytes_per_unit(name, D, d_pass) * units / (us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
         }
 
     if do_bwd and not args.no_dense and N <= 8192:

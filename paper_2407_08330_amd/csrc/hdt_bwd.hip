@@ -5,7 +5,7 @@
 // walks:  D_i = sum_c dO_ic O_ic,  P = exp(S - LSE),  dV = P^T dO,  dP = dO V^T,
 //         dS = P o (dP - D),  dQ = scale dS K,  dK = scale dS^T Q.
 //
-// Deterministic, no atomics.  Two launches:
+// Deterministic, no atomics.  Two launches, or the second alone, whose roles then compute D themselves (roles_compute_d):
 //   k_bwd_delta  D for every row (a streaming pass over O and dO).
 //   k_bwd_bf16   two workgroups per row tile I (rows in document order), one per role, both with the
 //                forward kernel's skeleton (hdt_tile.h):
@@ -24,7 +24,7 @@
 //                  parent and child kinds exchanged.
 // Both roles recompute the scores, which costs two extra contractions but keeps dQ out of HBM as fp32
 // partial sums.  Where a call of head size 128 does not fill the chip, the dK/dV role is split once more, into a dV role
-// and a dK role (three workgroups per tile, see launch_roles).  The workgroups of a tile are neighbours in the launch
+// and a dK role (three workgroups per tile, see launch_bwd).  The workgroups of a tile are neighbours in the launch
 // order and run on the same XCD at the same time.  That is what the pairing is for: the dQ role reads the tile's Q, dO
 // rows and gathers K, V rows of the neighbourhood, the dK/dV role reads the tile's K, V rows and gathers Q, dO rows of the
 // same neighbourhood, so each role finds in the XCD's L2 what the other (or a neighbouring pair) has just
@@ -43,7 +43,7 @@ struct BwdCfg {
     // against 99 with two, whose allocation the compiler then leaves unconstrained).
     // The INDEXED form on 128 x 64 tiles is compiled for one wave less: bounded to the third (second) it would spill a
     // few registers, which the counted waits do not allow.  It gets two per SIMD (178 registers at head size 64, 247 at
-    // 128); at head size 128 with the split roles only, see launch_roles.
+    // 128); at head size 128 with the split roles only, see launch_bwd.
     template <typename G, bool INDEXED>
     static constexpr int WAVES = G::BM == 128 ? (D == 64 ? 3 : 2) - (INDEXED ? 1 : 0) : 2;
 };
@@ -56,6 +56,8 @@ struct BwdCfg {
 //   .y = -LSE_i / scale  scale S - LSE = scale (-LSE / scale + Q K^T)   (accumulator of S preset to it)
 // which takes a subtraction and a multiplication per score out of both roles.  Rows without a key (LSE = -inf:
 // pads) get 0 for both: they are masked, and their dO may hold anything.
+// The sum is taken the same way wherever it is taken, here or in the roles (WITH_D): 8 columns by dot_8, then neighbours
+// in pairs, pairs of pairs, and so on, so that the results of a backward do not depend on which of the two computes D.
 template <int D>
 __global__ __launch_bounds__(256) void k_bwd_delta(const __bf16 *__restrict__ o, const __bf16 *__restrict__ d_o,
                                                    const float *__restrict__ lse, float inv_scale,
@@ -75,9 +77,7 @@ __global__ __launch_bounds__(256) void k_bwd_delta(const __bf16 *__restrict__ o,
     }
 #pragma unroll
     for (int u = 0; u < kRows; u++) {
-        float part = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; e++) part += (float)a[u][e] * (float)b[u][e];
+        float part = dot_8(a[u], b[u], 0.f);
 #pragma unroll
         for (int m = 1; m < CPR; m <<= 1) part += __shfl_xor(part, m);
         const long long r = r0 + (long long)u * RPB;
@@ -89,14 +89,23 @@ __global__ __launch_bounds__(256) void k_bwd_delta(const __bf16 *__restrict__ o,
 }
 
 // ------------------------------------------------------------------------------------------- dQ
-template <int D, typename G>
+// WITH_D: the rows' D is computed here, see k_bwd_bf16.  Own rows of O have a place of their own behind the ring.
+template <int D, typename G, bool WITH_D>
+struct DqLds {
+    using P = Pipe<D, Aux::NONE, G>;
+    static constexpr int O_AT = (P::SMEM_BYTES + 255) / 256 * 256;
+    static constexpr int BYTES = WITH_D ? O_AT + G::BM * P::ROWB : P::SMEM_BYTES;
+};
+
+template <int D, typename G, bool WITH_D>
 __device__ __forceinline__ void dq_role(char *smem, const HdtSchedule &s, const __bf16 *__restrict__ q,
                                          const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
-                                         const float *__restrict__ lse, const __bf16 *__restrict__ d_o,
-                                         const float2 *__restrict__ row_scalars, __bf16 *__restrict__ dq, int wave,
-                                         int I, int bh, int b, float scale)
+                                         const __bf16 *__restrict__ o, const float *__restrict__ lse,
+                                         const __bf16 *__restrict__ d_o, const float2 *__restrict__ row_scalars,
+                                         __bf16 *__restrict__ dq, int wave, int I, int bh, int b, float scale,
+                                         float inv_scale)
 {
-    using P = Pipe<D, false, G>;
+    using P = Pipe<D, Aux::NONE, G>;
     using R = Ring<P>;
     constexpr int BM = G::BM, BN = G::BN, KB = G::KB;
     constexpr int ROWB = P::ROWB, KSTEPS = P::KSTEPS, DBLK = P::DBLK, S = P::S;
@@ -131,8 +140,10 @@ __device__ __forceinline__ void dq_role(char *smem, const HdtSchedule &s, const 
     const OwnRows<P> own = own_rows(pipe, I_own * BM, s.n_own);
     stage_own_rows(pipe, q + own_base, own, STG_Q);
     stage_own_rows(pipe, d_o + own_base, own, STG_DO);
+    constexpr uint32_t STG_O = DqLds<D, G, WITH_D>::O_AT;
+    if (WITH_D) stage_own_rows(pipe, o + own_base, own, STG_O);
     R::start(pipe, n);
-        wait_vmcnt<0>();
+    wait_vmcnt<0>();
     bf16x8 qf[KSTEPS], dof[KSTEPS];
 #pragma unroll
     for (int st = 0; st < KSTEPS; st++) {
@@ -141,8 +152,25 @@ __device__ __forceinline__ void dq_role(char *smem, const HdtSchedule &s, const 
     }
     const int qrow_ld = min(qrow, s.n_own - 1);
     const float lse_i = lse[(size_t)bh * s.n_own + qrow_ld];
-    const float2 init = row_scalars[(size_t)bh * s.n_own + qrow_ld];  // 0, 0 for a row without a key
-    const float dp_init = init.x, s_init = init.y;                    // -D_i, -LSE_i / scale
+    float dp_init, s_init;  // -D_i, -LSE_i / scale; 0, 0 for a row without a key
+    if (WITH_D) {
+        float part[KSTEPS];  // 8 columns from this half-wave, the next 8 from the other
+#pragma unroll
+        for (int st = 0; st < KSTEPS; st++) {
+            part[st] = dot_8(dof[st], read_row<ROWB>(smem + STG_O, rl, wave * 32, st), 0.f);
+            part[st] += __shfl_xor(part[st], 32);
+        }
+#pragma unroll
+        for (int m = 1; m < KSTEPS; m <<= 1)
+#pragma unroll
+            for (int st = 0; st < KSTEPS; st += 2 * m) part[st] += part[st + m];
+        dp_init = lse_i == -INFINITY ? 0.f : -part[0];
+        s_init = lse_i == -INFINITY ? 0.f : -lse_i * inv_scale;
+    } else {
+        const float2 init = row_scalars[(size_t)bh * s.n_own + qrow_ld];
+        dp_init = init.x;
+        s_init = init.y;
+    }
     // A row without any key (a pad: LSE = -inf) is masked by the bitmap, but its Q and dO may hold anything,
     // NaN included, which a zero weight would not remove: it takes part as a row of zeros.
     const bool dead_row = lse_i == -INFINITY;
@@ -218,18 +246,28 @@ __device__ __forceinline__ void dq_role(char *smem, const HdtSchedule &s, const 
 
 // ---------------------------------------------------------------------------------------- dK, dV
 // WHICH: 0 = dK and dV, 1 = dV only, 2 = dK only.  INDEXED: the rows are those own_index names (see HdtSchedule).
-template <int D, typename G, int WHICH, bool INDEXED>
+// WITH_D: O and LSE of an entry's queries are gathered with Q and dO, and the workgroup computes D when they have landed.
+template <int D, typename G, int WHICH, bool INDEXED, bool WITH_D>
+struct DkvLds {
+    static constexpr bool LEAN = D == 128 && WHICH == 0;
+    using P = Pipe<D, WITH_D ? Aux::THIRD : Aux::PAIRS, G, LEAN>;
+    static constexpr int ROW_AT = P::SMEM_BYTES, INIT_AT = ROW_AT + (INDEXED ? G::BM * 4 : 0);
+    static constexpr int BYTES = INIT_AT + (WITH_D ? 2 * G::BN * 4 : 0);
+};
+template <int D, typename G, int WHICH, bool INDEXED, bool WITH_D>
 __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const __bf16 *__restrict__ q,
                                           const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
+                                          const __bf16 *__restrict__ o, const float *__restrict__ lse,
                                           const __bf16 *__restrict__ d_o, const float2 *__restrict__ row_scalars,
                                           __bf16 *__restrict__ dk, __bf16 *__restrict__ dv, int wave, int I, int bh,
-                                          int b, float scale)
+                                          int b, float scale, float inv_scale)
 {
     // Head size 128 and both results: 128 accumulator and 64 operand registers leave 64 of the 256 a wave gets at two per
     // SIMD.  What can be computed anew per entry or sub-block from the lane number is (LEAN): held in registers throughout
     // the loop, as the compiler would have it, 30 to 56 registers did not fit.
-    constexpr bool LEAN = D == 128 && WHICH == 0;
-    using P = Pipe<D, true, G, LEAN>;
+    using Lds = DkvLds<D, G, WHICH, INDEXED, WITH_D>;
+    constexpr bool LEAN = Lds::LEAN;
+    using P = typename Lds::P;
     using R = Ring<P>;
     constexpr int BM = G::BM, BN = G::BN, KB = G::KB;
     constexpr int ROWB = P::ROWB, KSTEPS = P::KSTEPS, DBLK = P::DBLK, S = P::S;
@@ -257,8 +295,13 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
     pipe.keys = s.q_keys + (size_t)t0 * BN;
     pipe.a = q + q_base;
     pipe.b = d_o + q_base;
-    pipe.aux0 = reinterpret_cast<const float *>(row_scalars + (size_t)bh * s.n_kv) + 1;  // -LSE / scale of a position
-    pipe.aux1 = reinterpret_cast<const float *>(row_scalars + (size_t)bh * s.n_kv);      // -D
+    if (WITH_D) {
+        pipe.aux0 = pipe.aux1 = lse + (size_t)bh * s.n_kv;
+        pipe.c = o + q_base;
+    } else {
+        pipe.aux0 = reinterpret_cast<const float *>(row_scalars + (size_t)bh * s.n_kv) + 1;  // -LSE / scale of a position
+        pipe.aux1 = reinterpret_cast<const float *>(row_scalars + (size_t)bh * s.n_kv);      // -D
+    }
     const RowLane rl = row_lane<P::CPR>(lane);
     const TrLane tl = tr_lane<P::CPR>(lane);
     // is this lane's own row a real position?  (Requested first, looked at once the rows are in registers.)
@@ -272,7 +315,7 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
     constexpr uint32_t STG_K = 2 * P::TILE, STG_V = 0;
     const OwnRows<P> own = own_rows(pipe, I * BM, n_rows, index);
     // where this wave's rows go: kept in LDS until the epilogue (registers are short, scalar ones included)
-    int *row_at = reinterpret_cast<int *>(smem + P::SMEM_BYTES) + wave * 32;
+    int *row_at = reinterpret_cast<int *>(smem + Lds::ROW_AT) + wave * 32;
     if (INDEXED && lane % P::CPR == 0) {
 #pragma unroll
         for (int i = 0; i < 32 / P::RPI; i++) row_at[i * P::RPI + lane / P::CPR] = own.g[i];
@@ -280,7 +323,7 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
     stage_own_rows(pipe, k + base, own, STG_K);
     if (DO_DK) stage_own_rows(pipe, v + base, own, STG_V);  // V only enters dP
     R::start(pipe, n);
-        wait_vmcnt<0>();
+    wait_vmcnt<0>();
     bf16x8 kf[KSTEPS], vf[KSTEPS];
 #pragma unroll
     for (int st = 0; st < KSTEPS; st++) {
@@ -318,7 +361,33 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
         wg_barrier();
         R::advance(pipe, i, n, next);
         const char *sQ = pipe.tile_a(i % S), *sDO = pipe.tile_b(i % S);
-        const float *sInitS = pipe.aux_buf(i % S, 0), *sInitDP = pipe.aux_buf(i % S, 1);  // -LSE / scale, -D
+        // -LSE / scale, -D of the entry's queries
+        float *init = reinterpret_cast<float *>(smem + Lds::INIT_AT);
+        const float *sInitS = WITH_D ? init : pipe.aux_buf(i % S, 0), *sInitDP = WITH_D ? init + BN : pipe.aux_buf(i % S, 1);
+        if (WITH_D) {
+            static_assert(!WITH_D || WHICH == 0, "D is computed where both results are");
+            // four lanes per query, a quarter of the columns each
+            const int t = wave * 64 + opaque(lane), r = t >> 2, quarter = t & 3;
+            const float lse_r = pipe.aux_buf(i % S, wave)[r];
+            float part[P::CPR / 4];
+#pragma unroll
+            for (int u = 0; u < P::CPR / 4; u++) {
+                const int at = r * ROWB + (((quarter * (P::CPR / 4) + u) ^ swz<P::CPR>(r)) << 4);
+                part[u] = dot_8(lds_read_8(sDO + at), lds_read_8(pipe.tile_c(i % S) + at), 0.f);
+            }
+#pragma unroll
+            for (int m = 1; m < P::CPR / 4; m <<= 1)
+#pragma unroll
+                for (int u = 0; u < P::CPR / 4; u += 2 * m) part[u] += part[u + m];
+            float d = part[0];
+            d += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, d), 0xb1, 0xf, 0xf, true));  // lane ^ 1
+            d += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, d), 0x4e, 0xf, 0xf, true));  // lane ^ 2
+            if (quarter == 0) {
+                init[r] = lse_r == -INFINITY ? 0.f : -lse_r * inv_scale;
+                init[BN + r] = lse_r == -INFINITY ? 0.f : -d;
+            }
+            wg_barrier();  // (the next entry's values come behind its own first barrier)
+        }
 
 #pragma unroll
         for (int kb = 0; kb < KB; kb++) {  // 32 query slots
@@ -456,17 +525,15 @@ static RoleGrid role_grid(const HdtSchedule &s, const HdtSchedule &s_tr, int hea
 
 // SPLIT: a dV and a dK role instead of one for both.  INDEXED: s_tr covers visible positions only
 // (HdtSchedule::own_index); the workgroups behind the grid of the roles write the zeros of the rows it leaves out.
-template <int D, typename G, bool INDEXED, bool SPLIT>
+template <int D, typename G, bool INDEXED, bool SPLIT, bool WITH_D>
 __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)) void k_bwd_bf16(
     HdtSchedule s, HdtSchedule s_tr, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k,
-    const __bf16 *__restrict__ v, const float *__restrict__ lse, const __bf16 *__restrict__ d_o,
-    const float2 *__restrict__ row_scalars, __bf16 *__restrict__ dq, __bf16 *__restrict__ dk,
-    __bf16 *__restrict__ dv, float scale, RoleGrid grid)
+    const __bf16 *__restrict__ v, const __bf16 *__restrict__ o, const float *__restrict__ lse,
+    const __bf16 *__restrict__ d_o, const float2 *__restrict__ row_scalars, __bf16 *__restrict__ dq,
+    __bf16 *__restrict__ dk, __bf16 *__restrict__ dv, float scale, float inv_scale, RoleGrid grid)
 {
-    using PQ = Pipe<D, false, G>;
-    using PK = Pipe<D, true, G>;
-    constexpr int SMEM_K = PK::SMEM_BYTES + (INDEXED ? G::BM * 4 : 0);
-    constexpr int SMEM = PQ::SMEM_BYTES > SMEM_K ? PQ::SMEM_BYTES : SMEM_K;
+    constexpr int SMEM_Q = DqLds<D, G, WITH_D>::BYTES, SMEM_K = DkvLds<D, G, SPLIT ? 2 : 0, INDEXED, WITH_D>::BYTES;
+    constexpr int SMEM = SMEM_Q > SMEM_K ? SMEM_Q : SMEM_K;
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     // The roles tile different tensors (the same ones for self-attention): the workgroups of one tile follow each
@@ -502,31 +569,31 @@ __global__ __launch_bounds__(G::THREADS, (BwdCfg<D>::template WAVES<G, INDEXED>)
     }
     if (role == 0u) {
         const int bh = grid.tr_q.div(lb), I = lb - bh * grid.tr_q.d, b = grid.heads.div(bh);
-        dq_role<D, G>(smem, s, q, k, v, lse, d_o, row_scalars, dq, wave, I, bh, b, scale);
+        dq_role<D, G, WITH_D>(smem, s, q, k, v, o, lse, d_o, row_scalars, dq, wave, I, bh, b, scale, inv_scale);
     } else {
         const int bh = grid.tr_k.div(lb), I = lb - bh * grid.tr_k.d, b = grid.heads.div(bh);
-        if (!SPLIT)
-            dkv_role<D, G, 0, INDEXED>(smem, s_tr, q, k, v, d_o, row_scalars, dk, dv, wave, I, bh, b, scale);
+        if constexpr (!SPLIT)
+            dkv_role<D, G, 0, INDEXED, WITH_D>(smem, s_tr, q, k, v, o, lse, d_o, row_scalars, dk, dv, wave, I, bh, b, scale, inv_scale);
         else if (role == 1u)
-            dkv_role<D, G, 1, INDEXED>(smem, s_tr, q, k, v, d_o, row_scalars, dk, dv, wave, I, bh, b, scale);
+            dkv_role<D, G, 1, INDEXED, WITH_D>(smem, s_tr, q, k, v, o, lse, d_o, row_scalars, dk, dv, wave, I, bh, b, scale, inv_scale);
         else
-            dkv_role<D, G, 2, INDEXED>(smem, s_tr, q, k, v, d_o, row_scalars, dk, dv, wave, I, bh, b, scale);
+            dkv_role<D, G, 2, INDEXED, WITH_D>(smem, s_tr, q, k, v, o, lse, d_o, row_scalars, dk, dv, wave, I, bh, b, scale, inv_scale);
     }
 }
 
 }  // namespace
 
-template <int D, typename G, bool INDEXED, bool SPLIT>
+template <int D, typename G, bool INDEXED, bool SPLIT, bool WITH_D>
 static void launch_kernel(const HdtSchedule &s, const HdtSchedule &s_tr, const __bf16 *Q, const __bf16 *K, const __bf16 *V,
-                          const float *lse, const __bf16 *DO, const float2 *row_scalars, void *dq, void *dk, void *dv,
+                          const __bf16 *O, const float *lse, const __bf16 *DO, const float2 *row_scalars, void *dq, void *dk, void *dv,
                           int heads, float scale, hipStream_t st)
 {
     constexpr unsigned roles = SPLIT ? 3u : 2u, zr = ZeroRows<D, G>::ROWS;
     const unsigned zeros = INDEXED ? (unsigned)s_tr.batch * heads * (((unsigned)s_tr.own_stride + zr - 1u) / zr) : 0u;
     const RoleGrid g = role_grid<G>(s, s_tr, heads, roles);
     dim3 grid(g.tiles + g.rest + zeros), block(G::THREADS);
-    hipLaunchKernelGGL((k_bwd_bf16<D, G, INDEXED, SPLIT>), grid, block, 0, st, s, s_tr, Q, K, V, lse, DO, row_scalars,
-                       (__bf16 *)dq, (__bf16 *)dk, (__bf16 *)dv, scale, g);
+    hipLaunchKernelGGL((k_bwd_bf16<D, G, INDEXED, SPLIT, WITH_D>), grid, block, 0, st, s, s_tr, Q, K, V, O, lse, DO, row_scalars,
+                       (__bf16 *)dq, (__bf16 *)dk, (__bf16 *)dv, scale, 1.f / scale, g);
 }
 
 // At head size 128 one role for dK and dV is less work than two (the scores are computed twice instead of three times,
@@ -536,58 +603,83 @@ static void launch_kernel(const HdtSchedule &s, const HdtSchedule &s_tr, const _
 // Always two where the rows are indexed and the tiles 128 x 64: one role takes 307 registers there, a single wave per SIMD
 // (whole backward, one role / two: 512 x 8192 x 48 heads, 500 positions visible, 68.9 / 61.3 us, 750 81.3 / 68.6, 2000
 // 185 / 130; 2048 x 8192 x 64 heads, 2000 visible, 716 / 540).  On 64 x 32 tiles it keeps two.
-template <int D, typename G, bool INDEXED>
-static void launch_roles(const HdtSchedule &s, const HdtSchedule &s_tr, const __bf16 *Q, const __bf16 *K, const __bf16 *V,
-                         const float *lse, const __bf16 *DO, const float2 *row_scalars, void *dq, void *dk, void *dv,
-                         int heads, float scale, hipStream_t st)
+// Whether the roles compute D themselves (head size 64), from what the host knows.  What that saves is a launch (about 4 us)
+// and a pass over O and dO; what it costs is D of a query once per list entry that names it, and a barrier and a
+// third more rows per entry.  us for the pass and the backward kernel - with D in the roles, hipGraph of backward calls:
+//   4 x 12 heads, 8192 positions, 64 x 32 tiles 96.2 - 93.7, 128 x 64 103.7 - 100.0; 3 x 12 x 2047 28.5 - 27.0 and 31.3 - 28.9;
+//   1 x 12 x 1000 11.1 - 9.6; 16 x 4 ListOps-shaped trees of 1536 27.1 - 23.7; but where groups of 200 siblings make
+//   the lists long 4 % more, of 500 12 % and of 2000 17 % (64 x 32 tiles; 1, 5 and 9 % on 128 x 64).
+// So for lists of at most 224 (320) keys on average; documents have 150 (230).  A deferred build whose report is not in is
+// taken for a document.  Either way D is the same to the last bit, so the choice shows in nothing but the time.
+//   Cross-attention: 512 x 8192 x 48, 750 visible 24.4 - 22.2; 512 x 512 x 48, all visible 22.5 - 21.8; 300 x 512 x 16, 47
+//   visible 13.5 - 12.3; 100 x 1000 x 4 17.7 - 15.2; but 512 x 8192 x 48, all visible 199 - 205; 2048 x 8192 x 48, 750 visible
+//   68.1 - 71.5: for up to 512 decoder rows, and as long as there are not more (row tile, entry) pairs than the chip goes
+//   through in a few us.
+// At head size 128 the third tensor's tiles cost a workgroup per compute unit (16384 positions x 16 heads 136 - 157).
+template <typename G>
+static bool roles_compute_d(const HdtSchedule &s_tr, int heads, HdtLists lists)
 {
+    const long long tiles = (long long)s_tr.batch * s_tr.tr;
+    if (!lists.cross) return lists.entries < 0 || lists.entries * G::BN <= tiles * (G::BM == 64 ? 224 : 320);
+    const long long entries = tiles * ((s_tr.n_kv + G::BN - 1) / G::BN);  // every tile with a visible row lists all decoder rows
+    return s_tr.n_kv <= 512 && entries * heads <= (G::BM == 64 ? 8000 : 5000);
+}
+
+template <int D, typename G, bool INDEXED>
+static void launch_bwd(const HdtSchedule &s, const HdtSchedule &s_tr, const __bf16 *Q, const __bf16 *K, const __bf16 *V,
+                       const __bf16 *O, const float *lse, const __bf16 *DO, void *dq, void *dk, void *dv, int heads,
+                       float scale, float *delta, HdtLists lists, hipStream_t st)
+{
+    // the rows' two scalars (-D, -LSE / scale), see hdt_bwd_row_scalars_bytes for the room they take
+    float2 *row_scalars = reinterpret_cast<float2 *>(delta);
+    if constexpr (D == 64) {
+        if (roles_compute_d<G>(s_tr, heads, lists)) {
+            HdtTimer t("hdt_bwd_bf16_d64", st);
+            launch_kernel<D, G, INDEXED, false, true>(s, s_tr, Q, K, V, O, lse, DO, nullptr, dq, dk, dv, heads, scale, st);
+            return;
+        }
+    }
+    {
+        const long long rows = (long long)s.batch * heads * s.n_own;  // the real rows, also when key lists are cut
+        HdtTimer t(D == 64 ? "hdt_bwd_delta_d64" : "hdt_bwd_delta_d128", st);
+        const int rpb = (256 / (D / 8)) * 4;
+        hipLaunchKernelGGL(k_bwd_delta<D>, dim3((unsigned)((rows + rpb - 1) / rpb)), dim3(256), 0, st, O, DO, lse, 1.f / scale,
+                           row_scalars, rows);
+    }
+    HdtTimer t(D == 64 ? "hdt_bwd_bf16_d64" : "hdt_bwd_bf16_d128", st);
     constexpr unsigned kResident = 256u * 8u / G::NW;  // workgroups on the chip at two waves per SIMD
     const size_t nq = (size_t)s.batch * heads * s.tr, nk = (size_t)s_tr.batch * heads * s_tr.tr;
     constexpr bool ALWAYS = D == 128 && INDEXED && G::BM == 128;
     if (ALWAYS || (D == 128 && nq + 2 * nk <= kResident))
-        launch_kernel<D, G, INDEXED, D == 128>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st);
+        launch_kernel<D, G, INDEXED, D == 128, false>(s, s_tr, Q, K, V, O, lse, DO, row_scalars, dq, dk, dv, heads, scale, st);
     else
-        launch_kernel<D, G, INDEXED, ALWAYS>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st);
+        launch_kernel<D, G, INDEXED, ALWAYS, false>(s, s_tr, Q, K, V, O, lse, DO, row_scalars, dq, dk, dv, heads, scale, st);
 }
 
 template <typename G>
-static void launch_bwd(const HdtSchedule &s, const HdtSchedule &s_tr, const __bf16 *Q, const __bf16 *K, const __bf16 *V,
-                       const __bf16 *O, const float *lse, const __bf16 *DO, void *dq, void *dk, void *dv, int heads,
-                       int head_dim, float scale, float *delta, hipStream_t st)
+static void launch_shape(const HdtSchedule &s, const HdtSchedule &s_tr, const __bf16 *Q, const __bf16 *K, const __bf16 *V,
+                         const __bf16 *O, const float *lse, const __bf16 *DO, void *dq, void *dk, void *dv, int heads,
+                         int head_dim, float scale, float *delta, HdtLists lists, hipStream_t st)
 {
-    // the rows' two scalars (-D, -LSE / scale), see hdt_bwd_row_scalars_bytes for the room they take
-    const long long rows = (long long)s.batch * heads * s.n_own;  // the real rows, also when key lists are cut
-    float2 *row_scalars = reinterpret_cast<float2 *>(delta);
-    {
-        HdtTimer t(head_dim == 64 ? "hdt_bwd_delta_d64" : "hdt_bwd_delta_d128", st);
-        const int rpb = (256 / (head_dim / 8)) * 4;
-        dim3 grid((unsigned)((rows + rpb - 1) / rpb)), block(256);
-        if (head_dim == 64)
-            hipLaunchKernelGGL(k_bwd_delta<64>, grid, block, 0, st, O, DO, lse, 1.f / scale, row_scalars, rows);
-        else
-            hipLaunchKernelGGL(k_bwd_delta<128>, grid, block, 0, st, O, DO, lse, 1.f / scale, row_scalars, rows);
-    }
-    {
-        HdtTimer t(head_dim == 64 ? "hdt_bwd_bf16_d64" : "hdt_bwd_bf16_d128", st);
-        if (head_dim == 64)
-            s_tr.own_index ? launch_roles<64, G, true>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st)
-                           : launch_roles<64, G, false>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st);
-        else
-            s_tr.own_index ? launch_roles<128, G, true>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st)
-                           : launch_roles<128, G, false>(s, s_tr, Q, K, V, lse, DO, row_scalars, dq, dk, dv, heads, scale, st);
-    }
+    if (head_dim == 64)
+        s_tr.own_index ? launch_bwd<64, G, true>(s, s_tr, Q, K, V, O, lse, DO, dq, dk, dv, heads, scale, delta, lists, st)
+                       : launch_bwd<64, G, false>(s, s_tr, Q, K, V, O, lse, DO, dq, dk, dv, heads, scale, delta, lists, st);
+    else
+        s_tr.own_index ? launch_bwd<128, G, true>(s, s_tr, Q, K, V, O, lse, DO, dq, dk, dv, heads, scale, delta, lists, st)
+                       : launch_bwd<128, G, false>(s, s_tr, Q, K, V, O, lse, DO, dq, dk, dv, heads, scale, delta, lists, st);
 }
 
 hdt_status_t hdt_launch_bwd_bf16(const HdtSchedule &s, const HdtSchedule &st_, const void *q, const void *k,
                                  const void *v, const void *o, const float *lse, const void *d_o, void *dq, void *dk,
-                                 void *dv, int heads, int head_dim, float scale, float *delta, hipStream_t st)
+                                 void *dv, int heads, int head_dim, float scale, float *delta, HdtLists lists,
+                                 hipStream_t st)
 {
     const __bf16 *Q = (const __bf16 *)q, *K = (const __bf16 *)k, *V = (const __bf16 *)v;
     const __bf16 *O = (const __bf16 *)o, *DO = (const __bf16 *)d_o;
     if (s.bm == 64)
-        launch_bwd<Geo<64, 32>>(s, st_, Q, K, V, O, lse, DO, dq, dk, dv, heads, head_dim, scale, delta, st);
+        launch_shape<Geo<64, 32>>(s, st_, Q, K, V, O, lse, DO, dq, dk, dv, heads, head_dim, scale, delta, lists, st);
     else
-        launch_bwd<Geo<128, 64>>(s, st_, Q, K, V, O, lse, DO, dq, dk, dv, heads, head_dim, scale, delta, st);
+        launch_shape<Geo<128, 64>>(s, st_, Q, K, V, O, lse, DO, dq, dk, dv, heads, head_dim, scale, delta, lists, st);
     HDT_HIP_TRY(hipGetLastError());
     return HDT_OK;
 }

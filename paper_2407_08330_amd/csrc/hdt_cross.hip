@@ -692,7 +692,7 @@ hdt_status_t hdt_cross_bwd_split(const hdt_layout_t *l, const void *q, const voi
     void *dq_part = w + d_bytes;
     // D is computed over the real rows (the D pass takes its row count from the first schedule's n_own)
     if (hdt_status_t status = hdt_launch_bwd_bf16(s, l->transposed->s, q, k, v, o, lse, d_o, dq_part, dk, dv, heads, head_dim,
-                                                  scale, delta, st))
+                                                  scale, delta, HdtLists{true, -1}, st))
         return status;
     const int rows_pad = l->s.tr * l->s.bm;
     const long long total = (long long)l->s.batch * heads * l->s.n_pos * (head_dim / 8);

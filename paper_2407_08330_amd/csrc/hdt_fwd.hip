@@ -121,7 +121,7 @@ __global__ __launch_bounds__(G::THREADS, FwdCfg<D>::WAVES) void k_fwd_bf16(
     HdtSchedule s, const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
     __bf16 *__restrict__ o, float *__restrict__ lse, unsigned items, FastDiv heads, FastDiv tr, float scale_log2, FastDiv chunk)
 {
-    using P = Pipe<D, false, G>;
+    using P = Pipe<D, Aux::NONE, G>;
     using R = Ring<P>;
     constexpr int BM = G::BM, BN = G::BN, KB = G::KB;
     constexpr int ROWB = P::ROWB, KSTEPS = P::KSTEPS, DBLK = P::DBLK, S = P::S;

@@ -215,11 +215,16 @@ hdt_status_t hdt_launch_fwd_f32(const HdtSchedule &s, const float *q, const floa
                                 float *lse, int heads, int head_dim, float scale, hipStream_t st);
 // backward launchers: `s` schedules the dQ pass, `s_transposed` (the transposed mask's schedule; the same as `s` for
 // symmetric masks) the dK/dV pass.  `delta` (bf16): room for the rows' scalars, hdt_bwd_row_scalars_bytes(batch * heads
-// * n_pos), two floats per row: -D and -LSE / scale side by side.
+// * n_pos), two floats per row: -D and -LSE / scale side by side.  `lists` (bf16): what the host knows of the lists of
+// s_transposed, for a choice between kernels with the same results.
+struct HdtLists {
+    bool cross;         // a cross-attention layout's
+    long long entries;  // of all samples; -1: not known yet (a deferred build whose report is not in)
+};
 inline size_t hdt_bwd_row_scalars_bytes(size_t rows) { return (2 * rows * sizeof(float) + 255) & ~(size_t)255; }
 hdt_status_t hdt_launch_bwd_bf16(const HdtSchedule &s, const HdtSchedule &s_transposed, const void *q, const void *k, const void *v,
                                  const void *o, const float *lse, const void *d_o, void *dq, void *dk,
-                                 void *dv, int heads, int head_dim, float scale, float *delta,
+                                 void *dv, int heads, int head_dim, float scale, float *delta, HdtLists lists,
                                  hipStream_t st);
 hdt_status_t hdt_launch_bwd_f32(const HdtSchedule &s, const HdtSchedule &s_transposed, const float *q, const float *k, const float *v,
                                 const float *o, const float *lse, const float *d_o, float *dq, float *dk,

@@ -56,6 +56,18 @@ __device__ __forceinline__ bf16x8 zero_bf16x8()
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// acc + the dot product of 8 bf16 pairs, in fp32
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+__device__ __forceinline__ float dot_8(bf16x8 a, bf16x8 b, float acc)
+{
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+        const bf16x2 x = {a[i], a[i + 1]}, y = {b[i], b[i + 1]};
+        acc = __builtin_amdgcn_fdot2_f32_bf16(x, y, acc, false);
+    }
+    return acc;
+}
+
 __device__ __forceinline__ bf16x8 pack_bf16x8(const f32x16 &p, int first)
 {
     bf16x8 r;

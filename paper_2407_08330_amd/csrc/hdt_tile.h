@@ -164,12 +164,16 @@ __device__ __forceinline__ int opaque(int x)
 // the bitmap gives the slot never meet a non-finite operand (pad rows may hold anything).
 __device__ __forceinline__ int gather_row(int slot_value) { return slot_value ^ (slot_value >> 31); }
 
+// What is gathered of an entry's positions besides the rows of two tensors: nothing, the two components of an array of float
+// pairs, or the rows of a third tensor and one float each.
+enum class Aux { NONE, PAIRS, THIRD };
+
 // LEAN: the gather's per-lane offsets are computed anew for every tile instead of being held in registers throughout
-template <int D, bool AUX, typename G, bool LEAN = false>
+template <int D, Aux AUX, typename G, bool LEAN = false>
 struct Pipe {
     static constexpr int BM = G::BM, BN = G::BN, NW = G::NW;
     static constexpr int S = 2;                       // data stages in the ring
-    static constexpr int PS = 4;                      // position stages
+    static constexpr int PS = 2;                      // position stages: one being read, one on its way
     static constexpr int KSTEPS = D / 16;             // MFMA steps over the head dimension
     static constexpr int DBLK = D / 32;               // 32-wide blocks of the head dimension
     static constexpr int ROWB = D * 2;                // bytes per LDS row (unpadded)
@@ -179,19 +183,20 @@ struct Pipe {
     static constexpr int LPW = BN / NW;               // rows of a tile each wave loads (16)
     static constexpr int NI = LPW / RPI;              // wave-level loads per tensor per tile per wave
     static constexpr int POSW = 64;                   // ints per position buffer (one wave-level load; BN are used)
-    static constexpr int NDMA = 2 * NI + (AUX ? 1 : 0);  // vector-memory instructions per tile per wave
     static constexpr int DATA_BYTES = S * 2 * TILE;
     static constexpr int POS_BYTES = PS * NW * POSW * 4;
-    static constexpr int AUX_BYTES = AUX ? S * NW * POSW * 4 : 0;
-    static constexpr int SMEM_BYTES = DATA_BYTES + POS_BYTES + AUX_BYTES;
+    static constexpr int AUX_BYTES = AUX != Aux::NONE ? S * NW * POSW * 4 : 0;
+    static constexpr int THIRD_AT = DATA_BYTES + POS_BYTES + AUX_BYTES;  // tiles of the third tensor, by stage
+    static constexpr int SMEM_BYTES = THIRD_AT + (AUX == Aux::THIRD ? S * TILE : 0);
 
     char *smem;
     uint32_t smem_addr;
     int wave, lane;
     const int32_t *keys;       // key positions of this row tile's entries: [n][BN]
     const __bf16 *a, *b;       // the two gathered tensors, already offset to this (sample, head)
-    const float *aux0, *aux1;  // per-position floats gathered with the rows (AUX only): the two halves of an array
-                               // of float pairs, hence 8 bytes from one position to the next
+    const float *aux0, *aux1;  // per-position floats gathered with the rows: the two halves of an array of float pairs, hence
+                               // 8 bytes from one position to the next; or an array of floats (aux0)
+    const __bf16 *c;           // the third tensor
 
     __device__ __forceinline__ const char *tile_a(int stage) const { return smem + (stage * 2 + 0) * TILE; }
     __device__ __forceinline__ const char *tile_b(int stage) const { return smem + (stage * 2 + 1) * TILE; }
@@ -199,7 +204,8 @@ struct Pipe {
     {
         return reinterpret_cast<const int *>(smem + DATA_BYTES) + (ps * NW + wave) * POSW;
     }
-    // aux values of the 64 slots: array 0 is written by wave 0, array 1 by wave 1
+    __device__ __forceinline__ const char *tile_c(int stage) const { return smem + THIRD_AT + stage * TILE; }
+    // aux values of the 64 slots: of pairs, array 0 is written by wave 0, array 1 by wave 1; of floats, every wave has a copy
     __device__ __forceinline__ const float *aux_buf(int stage, int which) const
     {
         return reinterpret_cast<const float *>(smem + DATA_BYTES + POS_BYTES) + (stage * NW + which) * POSW;
@@ -224,14 +230,14 @@ struct Pipe {
         int pos[NI], pos_aux = 0;
 #pragma unroll
         for (int i = 0; i < NI; i++) pos[i] = pb[wave * LPW + i * RPI + lr];
-        if (AUX) pos_aux = pb[ol & (BN - 1)];
+        if (AUX != Aux::NONE) pos_aux = pb[ol & (BN - 1)];
         Offsets o;
 #pragma unroll
         for (int i = 0; i < NI; i++) {
             const int r = wave * LPW + i * RPI + lr;
             o.row[i] = (uint32_t)gather_row(pos[i]) * ROWB + (uint32_t)((c ^ swz<CPR>(r)) * 16);  // bytes
         }
-        o.aux = AUX ? (uint32_t)gather_row(pos_aux) * 8u : 0u;
+        o.aux = AUX != Aux::NONE ? (uint32_t)gather_row(pos_aux) * (AUX == Aux::PAIRS ? 8u : 4u) : 0u;
         return o;
     }
     // start gathering them into ring stage `stage`
@@ -242,9 +248,10 @@ struct Pipe {
             const uint32_t dst = (uint32_t)((wave * LPW + i * RPI) * ROWB);
             dma16(a, o.row[i], smem_addr + (stage * 2 + 0) * TILE + dst);
             dma16(b, o.row[i], smem_addr + (stage * 2 + 1) * TILE + dst);
+            if (AUX == Aux::THIRD) dma16(c, o.row[i], smem_addr + THIRD_AT + stage * TILE + dst);
         }
-        if (AUX) {
-            const float *src = (wave & 1) ? aux1 : aux0;
+        if (AUX != Aux::NONE) {
+            const float *src = AUX == Aux::PAIRS && (wave & 1) ? aux1 : aux0;
             dma4(src, o.aux, smem_addr + DATA_BYTES + POS_BYTES + ((stage * NW + wave) * POSW) * 4);
         }
     }

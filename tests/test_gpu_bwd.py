@@ -205,3 +205,38 @@ def test_bwd_dense_baseline_layout(oracle, dtype, D, tile):
     level, parent = wl.level[:, :1024].copy(), wl.parent[:, :1024].copy()
     say(f"[bwd] force_dense layout, {dtype} d={D} tile {tile}")
     run_bwd_case(oracle, level, parent, 3, D, dtype, 4200 + D, tile=tile, force_dense=True)
+
+
+@BOTH_TILES
+@pytest.mark.parametrize("n", [65, 700])
+def test_bwd_is_the_same_whether_a_pass_of_its_own_computes_d_or_the_roles_do(tile, n):
+    """Long lists that the host knows of get a D pass; a deferred build whose report is not in when the backward is called is
+    taken for a document, and the roles compute D.  Same sums in the same order: the results agree bit for bit."""
+    import torch
+    import paper_2407_08330_amd as hdt
+    level, parent = np.ones((2, n), np.int32), np.zeros((2, n), np.int32)   # a root and its children: every row sees every key
+    level[:, 0], parent[:, 0] = 0, -1
+    level[1, n - 9:], parent[1, n - 9:] = -1, -1
+    lv, pr = to_dev_i32(level), to_dev_i32(parent)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    q, k, v, d_o = (torch.randn((2, 3, n, 64), device="cuda", generator=g).to(torch.bfloat16) for _ in range(4))
+    known = hdt.hdt_build_layout(lv, pr, tile_m=tile[0], tile_n=tile[1])
+    o, lse = hdt.hdt_attn_fwd(known, q, k, v, 0.125)
+    hdt.hdt_timing_enable(True)
+    hdt.hdt_timing_reset()
+    want = hdt.hdt_attn_bwd(known, q, k, v, o, lse, d_o, 0.125)
+    torch.cuda.synchronize()
+    assert ("hdt_bwd_delta_d64" in hdt.hdt_timing_read()) == (n == 700)
+    a = torch.randn((4096, 4096), device="cuda")
+    torch.cuda.synchronize()
+    hdt.hdt_timing_reset()
+    for _ in range(40):                      # some tens of milliseconds in front of the build
+        a = a @ a * 1e-3
+    lay = hdt.hdt_build_layout(lv, pr, tile_m=tile[0], tile_n=tile[1], deferred=True)
+    got = hdt.hdt_attn_bwd(lay, q, k, v, o, lse, d_o, 0.125)
+    torch.cuda.synchronize()
+    assert "hdt_bwd_delta_d64" not in hdt.hdt_timing_read()
+    hdt.hdt_timing_enable(False)
+    for x, y in zip(got, want):
+        assert torch.equal(x.view(torch.int16), y.view(torch.int16))
