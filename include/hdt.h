@@ -182,8 +182,10 @@ hdt_status_t hdt_build_layout(const int32_t *d_level, const int32_t *d_parent, i
  * hdt_attn_bwd tiles the visible rows instead of all encoder rows.  (hdt_attn_bwd_workspace_bytes asks for four tensors
  * of that many rows more on such a layout.)  Results and arguments are the same either way.
  *
- * Kernels are enqueued on `stream`; the call waits for the first of them once (it reports the number of visible
- * positions); device memory as for hdt_build_layout, sized for the case that every position is visible.
+ * Kernels are enqueued on `stream`; the call does not wait for them.  The number of visible positions, which the first of
+ * them reports, is looked at (and waited for, should the report not be in) by the calls that depend on it: the workspace
+ * queries, hdt_attn_fwd_ws with a workspace, hdt_attn_bwd, hdt_layout_info.  Device memory as for hdt_build_layout, sized
+ * for the case that every position is visible.
  * batch == 0 gives an empty layout on which the attention calls are no-ops.
  * Errors: HDT_ERR_INVALID_ARG (NULL, negative sizes), HDT_ERR_SHAPE (a length of 0 or > 2^19, too many
  * entries), HDT_ERR_UNSUPPORTED (tile shape, other options), HDT_ERR_OOM, HDT_ERR_HIP.  On error *out is NULL.

@@ -284,8 +284,8 @@ static hdt_status_t destroy_layout(hdt_layout_t *layout, bool completed)
     if (layout->magic != HDT_LAYOUT_MAGIC) return hdt_fail(HDT_ERR_INVALID_ARG, "hdt_layout_destroy: not a layout");
     // the build and every attention call went through this handle: its streams cover the layouts it owns
     const HdtUsers users = completed ? HdtUsers() : hdt_users_at_release(hdt_layout_streams(layout));
-    hdt_layout_t *owned[2] = {layout->compact, layout->transposed};
-    layout->compact = layout->transposed = nullptr;
+    hdt_layout_t *owned[2] = {layout->compact_built, layout->transposed};
+    layout->compact_built = layout->compact = layout->transposed = nullptr;
     for (hdt_layout_t *t : owned) {
         if (!t) continue;
         t->transposed = nullptr;
@@ -333,6 +333,7 @@ extern "C" __attribute__((visibility("default"))) size_t hdt_attn_fwd_workspace_
                                                                                        int32_t head_dim, hdt_dtype_t dt)
 {
     if (!hdt_layout_ok(layout) || heads <= 0 || dt != HDT_BF16 || (head_dim != 64 && head_dim != 128)) return 0;
+    if (hdt_layout_resolve(layout, layout->cross != 0) != HDT_OK) return 0;  // (how long are its key lists?)
     return hdt_cross_fwd_workspace_bytes(layout, heads, head_dim);
 }
 
@@ -361,8 +362,11 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_attn_fwd_ws(c
     hipStream_t hs = (hipStream_t)stream;
     hdt_layout_note_stream(layout, hs);  // whoever gets this layout's buffers later waits for this stream
     // long key lists of a cross-attention layout, cut into pieces, when the caller brings room for the partial results
-    const size_t ws_need = dt == HDT_BF16 ? hdt_cross_fwd_workspace_bytes(layout, heads, head_dim) : 0;
-    if (ws_need > 0 && workspace != nullptr && workspace_bytes >= ws_need) {
+    if (dt == HDT_BF16 && workspace != nullptr && layout->cross) {
+        if (hdt_status_t known = hdt_layout_resolve(layout, true)) return known;
+    }
+    const size_t ws_need = dt == HDT_BF16 && workspace != nullptr ? hdt_cross_fwd_workspace_bytes(layout, heads, head_dim) : 0;
+    if (ws_need > 0 && workspace_bytes >= ws_need) {
         if (misaligned(workspace)) return hdt_fail(HDT_ERR_INVALID_ARG, "hdt_attn_fwd_ws: the workspace must be 16-byte aligned");
         return hdt_cross_fwd_split(layout, q, k, v, o, lse, heads, head_dim, scale, workspace, hs);
     }
@@ -375,6 +379,7 @@ extern "C" __attribute__((visibility("default"))) size_t hdt_attn_bwd_workspace_
                                                hdt_dtype_t dt)
 {
     if (!hdt_layout_ok(layout) || heads < 0) return 0;
+    if (layout->cross && hdt_layout_resolve(layout, true) != HDT_OK) return 0;  // (how many positions are visible?)
     // two floats per (batch, head, position): D_i = sum_c dO_ic O_ic and LSE_i in the form the kernels start from
     size_t n = hdt_bwd_row_scalars_bytes((size_t)layout->s.batch * (size_t)heads * (size_t)layout->s.n_pos);
     // a cross-attention layout with a compact schedule: room for compact copies of K, V and their gradients, which
@@ -443,6 +448,9 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_attn_bwd(cons
     const HdtSchedule &s = layout->s;
     const HdtSchedule &s_tr = layout->transposed ? layout->transposed->s : s;
     if (s.batch == 0 || s.n_pos == 0 || heads == 0) return HDT_OK;
+    if (layout->cross) {
+        if (hdt_status_t known = hdt_layout_resolve(layout, true)) return known;
+    }
     if (!q || !k || !v || !o || !lse || !d_o || !dq || !dk || !dv)
         return hdt_fail(HDT_ERR_INVALID_ARG, "hdt_attn_bwd: NULL tensor pointer");
     const void *ptrs[] = {q, k, v, o, d_o, dq, dk, dv, workspace};

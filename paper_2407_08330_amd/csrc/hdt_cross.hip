@@ -13,10 +13,12 @@
 // are marked empty, and a tile's range covers the ones in use.
 //
 // The dK/dV pass of the backward tiles the ENCODER rows, and with a few anchors visible nearly every 32-row
-// block of them holds one allowed row among 31 idle ones.  The build therefore learns the number of visible
-// positions from the device, and when they are at most a quarter of the encoder's positions it adds a second
-// transposed schedule in the index space of the visible positions (row = rank among them): the dK/dV role of
-// hdt_attn_bwd then reads its K and V rows and writes its dK and dV rows through the list of visible positions,
+// block of them holds one allowed row among 31 idle ones.  When the visible positions are at most a quarter of the
+// encoder's, the build therefore makes a second transposed schedule in the index space of the visible positions (row =
+// rank among them).  Whether they are, the device finds out: the entry kernel makes that schedule or leaves it, in arrays
+// that hold a quarter of the encoder's positions, and the host reads the count when a call depends on it, so the build
+// waits for nothing (512 x 8192, anchors visible, build, forward and backward: 56.3 -> 43.4 us; a wait for the count and a
+// launch for that schedule before).  The dK/dV role of hdt_attn_bwd then reads its K and V rows and writes its dK and dV rows through the list of visible positions,
 // and further workgroups of the same launch write the zeros of the rows that are not visible (512 x 8192, [SEC] and
 // [SENT] visible: one launch of 24 us where gathering compact copies, the roles and scattering the results took
 // 5 + 21 + 24).
@@ -31,6 +33,7 @@
 // results live in the caller's workspace (hdt_attn_fwd_ws, hdt_attn_bwd).
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 #include <vector>
 
@@ -39,6 +42,7 @@
 namespace {
 
 constexpr int kSelThreads = 1024;
+constexpr int kSplitEntries = 16;  // lists of this many entries are worth cutting
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ bool visible(int level, uint32_t level_mask)
@@ -50,7 +54,7 @@ __device__ __forceinline__ bool visible(int level, uint32_t level_mask)
 // their number (count).  A wave takes a contiguous share of the positions, kSelBatch groups of 64 in flight at a time:
 // it counts its visible positions, and once the shares in front of it are known hands out the ranks (8192 positions x 4
 // samples: 5.3 us; one chunk of 1024 positions after the other, three barriers each, took 9.2).  The last workgroup to
-// finish tells the host, which waits for this word, the largest count.
+// finish tells the host the largest count.
 constexpr int kSelBatch = 8;
 __global__ __launch_bounds__(kSelThreads) void k_cross_select(const int32_t *__restrict__ level, int n_enc,
                                                                uint32_t level_mask, int32_t *__restrict__ sel,
@@ -111,8 +115,9 @@ __global__ __launch_bounds__(kSelThreads) void k_cross_select(const int32_t *__r
                 const int most = __hip_atomic_load(&report.counters[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&report.counters[0], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&report.counters[1], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(report.word, ((unsigned long long)(report.ticket & 0xffffffu) << 40) | (uint32_t)most,
-                                   __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+                const unsigned long long word = ((unsigned long long)(report.ticket & 0xffffffu) << 40) | (uint32_t)most;
+                *report.copy = word;
+                __hip_atomic_store(report.word, word, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
             }
         }
     }
@@ -126,26 +131,45 @@ struct CrossArgs {
     int n_enc, n_dec, bm, bn;
     int transposed;  // 0: rows = decoder positions, keys = visible encoder positions; 1: rows = encoder positions
                      // (allowed iff visible), keys = decoder positions
-    int tr, e_max;   // row tiles per sample, list entries reserved per row tile
-    int compact;     // transposed schedule: 0, or its rows per sample when they are the visible positions by rank
+    int compact;     // transposed schedule whose rows are the visible positions by rank
+    int batch;
+    int tr, e_max;   // row tiles per sample (compact: as many as its rows take), list entries reserved per row tile
     int entries;     // reserved entries: workgroups this schedule takes
     int32_t *q_range, *c_row, *c_cnt, *q_keys;
     uint32_t *q_sub;
     unsigned long long *bits_rm;
+    int32_t *split_range[3];  // forward schedule: entry ranges with the lists cut, see below; NULL: no list can be long
 };
 
-// One wave per reserved list entry (b, I, e): its keys, bitmaps and summary, or the "empty" marks.  Two schedules per
-// launch (a launch costs about what its entries do).
-__global__ __launch_bounds__(64) void k_cross_entries(CrossArgs a0, CrossArgs a1)
+// rows per sample of the compact schedule for c_max visible positions, 0: there is none
+__host__ __device__ __forceinline__ int compact_rows(int c_max, int n_enc)
+{
+    return c_max > 0 && (long long)c_max * 4 <= n_enc ? (c_max + 31) / 32 * 32 : 0;
+}
+
+// One wave per reserved list entry (b, I, e): its keys, bitmaps and summary, or the "empty" marks.  All schedules of a
+// layout in one launch (a launch costs about what its entries do).  The first entry of a forward row tile also writes the
+// tile's entry ranges with every key list cut into 2, 4 and 8 pieces: row tile p * tr + I of sample b gets entries
+// [p * chunk, (p + 1) * chunk) of the list of tile (b, I), chunk = ceil(entries / pieces).
+__global__ __launch_bounds__(64) void k_cross_entries(CrossArgs a0, CrossArgs a1, CrossArgs a2)
 {
     __shared__ uint32_t s_row[4], s_col[4];  // allowed rows / filled key slots of the entry, bit masks
     const int lane = threadIdx.x;
-    const bool first = (int)blockIdx.x < a0.entries;
-    const CrossArgs &a = first ? a0 : a1;
-    const int64_t entry = first ? (int)blockIdx.x : (int)blockIdx.x - a0.entries;
+    const int x1 = (int)blockIdx.x - a0.entries, x2 = x1 - a1.entries;
+    const CrossArgs &a = x1 < 0 ? a0 : (x2 < 0 ? a1 : a2);
+    const int64_t entry = x1 < 0 ? (int)blockIdx.x : (x2 < 0 ? x1 : x2);
+    int n_rows = a.transposed ? a.n_enc : a.n_dec, tr = a.tr;
+    if (a.compact) {
+        int c_max = 0;
+        for (int i = lane; i < a.batch; i += 64) c_max = max(c_max, a.count[i]);
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) c_max = max(c_max, __shfl_xor(c_max, d));
+        n_rows = compact_rows(c_max, a.n_enc);
+        tr = (n_rows + a.bm - 1) / a.bm;
+        if (entry >= (int64_t)a.batch * tr * a.e_max) return;  // reserved for more rows; all of them, if there is no such schedule
+    }
     const int e = (int)entry % a.e_max, tile = (int)entry / a.e_max;  // tile = b * tr + I
-    const int b = tile / a.tr, I = tile % a.tr;
-    const int n_rows = a.transposed ? (a.compact ? a.compact : a.n_enc) : a.n_dec;
+    const int b = tile / tr, I = tile % tr;
     const int n_keys = a.transposed ? a.n_dec : a.count[b];
     // rows of the tile
     bool any_row = false;
@@ -164,6 +188,18 @@ __global__ __launch_bounds__(64) void k_cross_entries(CrossArgs a0, CrossArgs a1
     if (e == 0 && lane == 0) {
         a.q_range[2 * tile] = (int32_t)entry;
         a.q_range[2 * tile + 1] = (int32_t)entry + n_ent;
+    }
+    if (e == 0 && a.split_range[0]) {
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            const int pieces = 2 << k, chunk = (n_ent + pieces - 1) / pieces;
+            if (lane < pieces) {
+                const int first = min(lane * chunk, n_ent), last = min(first + chunk, n_ent);
+                int32_t *out = a.split_range[k] + 2 * ((size_t)(b * pieces + lane) * tr + I);
+                out[0] = (int32_t)entry + first;
+                out[1] = (int32_t)entry + last;
+            }
+        }
     }
     if (lane == 0) a.c_row[entry] = tile;
     if (e >= n_ent) {  // reserved, not in use
@@ -217,26 +253,6 @@ __global__ __launch_bounds__(64) void k_cross_entries(CrossArgs a0, CrossArgs a1
         a.c_cnt[entry] = nr * nc;
         a.q_sub[entry] = any | (all << 16);
     }
-}
-
-struct SplitRanges {
-    int32_t *out[3];
-};
-// Entry ranges of the forward schedule with every key list cut into 2, 4 and 8 pieces (blockIdx.y): row tile p * tr + I
-// of sample b gets entries [p * chunk, (p + 1) * chunk) of the list of tile (b, I), chunk = ceil(entries / pieces).
-__global__ __launch_bounds__(256) void k_cross_split_ranges(const int32_t *__restrict__ count, int batch, int tr, int bn,
-                                                             int e_max, SplitRanges ranges)
-{
-    const int pieces = 2 << blockIdx.y;
-    int32_t *out = ranges.out[blockIdx.y];
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= batch * pieces * tr) return;
-    const int b = t / (pieces * tr), r = t % (pieces * tr), p = r / tr, I = r % tr;
-    const int n_ent = (count[b] + bn - 1) / bn, chunk = (n_ent + pieces - 1) / pieces;
-    const int first = min(p * chunk, n_ent), last = min(first + chunk, n_ent);
-    const int base = (b * tr + I) * e_max;
-    out[2 * t] = base + first;
-    out[2 * t + 1] = base + last;
 }
 
 // O, LSE of row (bh, r) from the partial results of the pieces: o_part [bh][PIECES * rows_pad][D] bf16 (piece p of
@@ -325,6 +341,7 @@ __global__ __launch_bounds__(256) void k_cross_sum_dq(const u32x4 *__restrict__ 
 struct CrossBuffers {
     int32_t *split_range[3];                // first arena, forward schedule only: entry ranges with the lists cut in 2, 4, 8
     int32_t *sel, *rank, *count, *q_range;  // first arena
+    unsigned long long *report;             // first arena: the build's report once more
     int32_t *c_row, *c_cnt, *q_keys;  // second arena
     uint32_t *q_sub;
     unsigned long long *bits_rm;
@@ -347,6 +364,7 @@ CrossBuffers carve_cross(char *a1, char *a2, int B, int n_enc, int tr, int64_t e
         c.sel = carve<int32_t>(a1, o1, (size_t)B * n_enc);
         c.rank = carve<int32_t>(a1, o1, (size_t)B * n_enc);
         c.count = carve<int32_t>(a1, o1, (size_t)B);
+        c.report = carve<unsigned long long>(a1, o1, 1);
         for (int k = 0; k < 3; k++) c.split_range[k] = carve<int32_t>(a1, o1, (size_t)B * tr * (2 << k) * 2);
     }
     c.q_range = carve<int32_t>(a1, o1, (size_t)B * tr * 2);
@@ -381,8 +399,10 @@ hdt_layout_t *new_layout(int batch, int n_rows, int n_kv, int bm, int bn)
     L->edges = 0;
     L->cross = 1;
     L->transposed = nullptr;
-    L->compact = nullptr;
+    L->compact = L->compact_built = nullptr;
     L->n_compact = 0;
+    L->pending = false;
+    L->build_status = HDT_OK;
     for (auto &r : L->cross_split_range) r = nullptr;
     L->cross_entries_max = 0;
     L->device_bytes = 0;
@@ -456,7 +476,7 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_cross_l
     }
     L->transposed = T;
     L->cross_level_mask = T->cross_level_mask = level_mask;
-    hdt_layout_t *Tc = nullptr;  // the compact schedule while it is being built
+    hdt_layout_t *Tc = nullptr;  // the compact schedule, for as many rows as it can have
     HdtReport report{};
     bool reported = false;
     hdt_status_t status = HDT_OK;
@@ -465,8 +485,9 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_cross_l
     hdt_note_build_stream(st);
     HdtUsers build_only;  // what the buffers of a failed build have been touched by
     build_only.lazy.add(st);
-    const int e_fwd = (n_enc + bn - 1) / bn, e_tr = (n_dec + bn - 1) / bn;
+    const int e_fwd = (n_enc + bn - 1) / bn, e_tr = (n_dec + bn - 1) / bn, n_c = compact_rows(n_enc / 4, n_enc);
     const int64_t ent_fwd = (int64_t)batch * L->s.tr * e_fwd, ent_tr = (int64_t)batch * T->s.tr * e_tr;
+    const int64_t ent_c = (int64_t)batch * ((n_c + bm - 1) / bm) * e_tr;
     if (ent_fwd >= (1LL << 31) || ent_tr >= (1LL << 31)) {
         status = hdt_fail(HDT_ERR_SHAPE, "hdt_build_cross_layout: %lld list entries", (long long)(ent_fwd > ent_tr ? ent_fwd : ent_tr));
         goto fail;
@@ -480,103 +501,87 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_cross_l
             goto fail;                                                                                 \
         }                                                                                              \
     } while (0)
+    if (n_c > 0 && !empty) {
+        Tc = new_layout(batch, n_c, n_dec, bm, bn);
+        if (!Tc) {
+            status = hdt_fail(HDT_ERR_OOM, "hdt_build_cross_layout: host allocation failed");
+            goto fail;
+        }
+        Tc->cross_level_mask = level_mask;
+    }
     {
-        CrossBuffers f = carve_cross(nullptr, nullptr, batch, n_enc, L->s.tr, ent_fwd, bm, bn, true);
-        CrossBuffers t = carve_cross(nullptr, nullptr, batch, n_enc, T->s.tr, ent_tr, bm, bn, false);
-        CROSS_TRY(hdt_pool_alloc(&L->arena, f.bytes1 + 256, &L->arena_bytes, st));
-        CROSS_TRY(hdt_pool_alloc(&L->arena2, f.bytes2 + 256, &L->arena2_bytes, st));
-        CROSS_TRY(hdt_pool_alloc(&T->arena, t.bytes1 + 256, &T->arena_bytes, st));
-        CROSS_TRY(hdt_pool_alloc(&T->arena2, t.bytes2 + 256, &T->arena2_bytes, st));
-        f = carve_cross((char *)L->arena, (char *)L->arena2, batch, n_enc, L->s.tr, ent_fwd, bm, bn, true);
-        t = carve_cross((char *)T->arena, (char *)T->arena2, batch, n_enc, T->s.tr, ent_tr, bm, bn, false);
+        struct {
+            hdt_layout_t *l;
+            int64_t n;
+            CrossBuffers c;
+        } all[3] = {{L, empty ? 0 : ent_fwd, {}}, {T, empty ? 0 : ent_tr, {}}, {Tc, empty ? 0 : ent_c, {}}};
+        for (auto &x : all) {
+            if (!x.l) continue;
+            const bool with_sel = x.l == L;
+            const CrossBuffers need = carve_cross(nullptr, nullptr, batch, n_enc, x.l->s.tr, x.n, bm, bn, with_sel);
+            CROSS_TRY(hdt_pool_alloc(&x.l->arena, need.bytes1 + 256, &x.l->arena_bytes, st));
+            CROSS_TRY(hdt_pool_alloc(&x.l->arena2, need.bytes2 + 256, &x.l->arena2_bytes, st));
+            x.c = carve_cross((char *)x.l->arena, (char *)x.l->arena2, batch, n_enc, x.l->s.tr, x.n, bm, bn, with_sel);
+            adopt(x.l, x.c, x.n);
+        }
+        const CrossBuffers &f = all[0].c;
+        T->s.row_flag = f.rank;  // encoder rows that are not visible (pads among them) may hold anything
+        L->device_bytes += T->device_bytes + (Tc ? Tc->device_bytes : 0);
+        if (Tc) {
+            Tc->s.own_index = f.sel;
+            Tc->s.own_count = f.count;
+            Tc->s.own_rank = f.rank;
+            Tc->s.own_stride = n_enc;
+        }
         if (!empty) {
             // (a stream that is being captured runs nothing now: no report would come)
             hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
             reported = hipStreamIsCapturing(st, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone &&
                        hdt_report_open(L->device, &report);
             if (!reported) report = HdtReport{};
+            report.copy = f.report;
             {
                 HdtTimer tm("hdt_cross_select", st);
                 hipLaunchKernelGGL(k_cross_select, dim3((unsigned)batch), dim3(kSelThreads), 0, st, d_level_enc, n_enc,
                                    level_mask, f.sel, f.rank, f.count, report);
             }
-            CrossArgs a{d_level_enc, f.sel, f.count, level_mask, n_enc, n_dec, bm, bn, 0, L->s.tr, e_fwd, 0, (int)ent_fwd,
-                        f.q_range, f.c_row, f.c_cnt, f.q_keys, f.q_sub, f.bits_rm};
-            CrossArgs at{d_level_enc, f.sel, f.count, level_mask, n_enc, n_dec, bm, bn, 1, T->s.tr, e_tr, 0, (int)ent_tr,
-                         t.q_range, t.c_row, t.c_cnt, t.q_keys, t.q_sub, t.bits_rm};
+            CrossArgs args[3];
+            for (int k = 0; k < 3; k++) {
+                const CrossBuffers &c = all[k].c;
+                const int64_t n = all[k].l ? all[k].n : 0;
+                args[k] = CrossArgs{d_level_enc, f.sel, f.count, level_mask, n_enc, n_dec, bm, bn, k > 0, k == 2, batch,
+                                    all[k].l ? all[k].l->s.tr : 1, k == 0 ? e_fwd : e_tr, (int)n, c.q_range, c.c_row, c.c_cnt,
+                                    c.q_keys, c.q_sub, c.bits_rm, {}};
+            }
+            if (e_fwd >= kSplitEntries)
+                for (int k = 0; k < 3; k++) L->cross_split_range[k] = args[0].split_range[k] = f.split_range[k];
             {
                 HdtTimer tm("hdt_cross_entries", st);
-                if (ent_fwd + ent_tr < (1LL << 25)) {
-                    hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)(ent_fwd + ent_tr)), dim3(64), 0, st, a, at);
+                if (ent_fwd + ent_tr + ent_c < (1LL << 25)) {
+                    hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)(args[0].entries + args[1].entries + args[2].entries)),
+                                       dim3(64), 0, st, args[0], args[1], args[2]);
                 } else {  // a grid holds less than 2^32 threads
-                    hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)ent_fwd), dim3(64), 0, st, a, a);
-                    hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)ent_tr), dim3(64), 0, st, at, at);
+                    for (const CrossArgs &x : args)
+                        if (x.entries > 0) hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)x.entries), dim3(64), 0, st, x, x, x);
                 }
             }
             CROSS_TRY(hipGetLastError());
-            // How many positions are visible?  The select kernel reports the largest count while the entries are being
-            // written; without a report it is read back the slow way.
-            int c_max = 0;
-            unsigned long long word = 0;
-            if (reported && hdt_report_wait(report, &word)) {
-                c_max = (int)(uint32_t)(word & 0xffffffffu);
-            } else {
+            L->compact_built = Tc;  // owned by L from here on
+            if (reported) {
+                L->report = report.word;
+                L->report_dev = f.report;
+                L->ticket = report.ticket;
+                L->ticket_before = report.ticket_before;
+                L->pending.store(true, std::memory_order_release);
+            } else {  // no report: the counts are read back
                 std::vector<int32_t> h_count((size_t)batch, 0);
+                L->compact_built = nullptr;
                 CROSS_TRY(hipMemcpyAsync(h_count.data(), f.count, sizeof(int32_t) * batch, hipMemcpyDeviceToHost, st));
                 CROSS_TRY(hipStreamSynchronize(st));
-                for (int32_t c : h_count) c_max = c > c_max ? c : c_max;
-            }
-            L->cross_entries_max = (c_max + bn - 1) / bn;
-            if (L->cross_entries_max >= 16) {  // lists worth cutting: the entry ranges for 2, 4 and 8 pieces
-                SplitRanges ranges;
-                for (int k = 0; k < 3; k++) L->cross_split_range[k] = ranges.out[k] = f.split_range[k];
-                const int total = batch * 8 * L->s.tr;
-                hipLaunchKernelGGL(k_cross_split_ranges, dim3((unsigned)((total + 255) / 256), 3), dim3(256), 0, st, f.count,
-                                   batch, L->s.tr, bn, e_fwd, ranges);
-                CROSS_TRY(hipGetLastError());
-            }
-            if (c_max > 0 && (int64_t)c_max * 4 <= n_enc) {
-                // the compact transposed schedule: ranks x decoder rows
-                const int n_c = (c_max + 31) / 32 * 32;
-                Tc = new_layout(batch, n_c, n_dec, bm, bn);
-                if (!Tc) {
-                    status = hdt_fail(HDT_ERR_OOM, "hdt_build_cross_layout: host allocation failed");
-                    goto fail;
-                }
-                Tc->cross_level_mask = level_mask;
-                const int64_t ent_tc = (int64_t)batch * Tc->s.tr * e_tr;
-                CrossBuffers tc = carve_cross(nullptr, nullptr, batch, n_enc, Tc->s.tr, ent_tc, bm, bn, false);
-                CROSS_TRY(hdt_pool_alloc(&Tc->arena, tc.bytes1 + 256, &Tc->arena_bytes, st));
-                CROSS_TRY(hdt_pool_alloc(&Tc->arena2, tc.bytes2 + 256, &Tc->arena2_bytes, st));
-                tc = carve_cross((char *)Tc->arena, (char *)Tc->arena2, batch, n_enc, Tc->s.tr, ent_tc, bm, bn, false);
-                CrossArgs atc{d_level_enc, f.sel, f.count, level_mask, n_enc, n_dec, bm, bn, 1, Tc->s.tr, e_tr, n_c, (int)ent_tc,
-                              tc.q_range, tc.c_row, tc.c_cnt, tc.q_keys, tc.q_sub, tc.bits_rm};
-                {
-                    HdtTimer tm("hdt_cross_entries_compact", st);
-                    hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)ent_tc), dim3(64), 0, st, atc, atc);
-                }
-                CROSS_TRY(hipGetLastError());
-                adopt(Tc, tc, ent_tc);
-                Tc->s.own_index = f.sel;
-                Tc->s.own_count = f.count;
-                Tc->s.own_rank = f.rank;
-                Tc->s.own_stride = n_enc;
-                L->compact = Tc;
-                L->n_compact = n_c;
-                L->device_bytes += Tc->device_bytes;
-                Tc = nullptr;  // owned by L from here on
+                L->compact_built = Tc;
+                hdt_cross_record(L, *std::max_element(h_count.begin(), h_count.end()));
             }
         }
-        struct {
-            hdt_layout_t *l;
-            CrossBuffers *c;
-            int64_t n;
-        } both[2] = {{L, &f, empty ? 0 : ent_fwd}, {T, &t, empty ? 0 : ent_tr}};
-        const int64_t compact_bytes = L->device_bytes;  // added above, if a compact pair was built
-        for (auto &x : both) adopt(x.l, *x.c, x.n);
-        T->s.row_flag = f.rank;  // encoder rows that are not visible (pads among them) may hold anything
-        L->device_bytes += compact_bytes;
-        L->device_bytes += T->device_bytes;
         *out = L;
         return HDT_OK;
     }
@@ -595,6 +600,21 @@ fail:
     delete L;
     return status;
 #undef CROSS_TRY
+}
+
+void hdt_cross_record(const hdt_layout_t *l, int c_max)
+{
+    l->cross_entries_max = (c_max + l->s.bn - 1) / l->s.bn;
+    const int n_c = compact_rows(c_max, l->s.n_kv);
+    hdt_layout_t *c = l->compact_built;
+    if (n_c == 0 || !c) return;
+    // as the entry kernel has laid it out: for the rows there are, not for those there was room for
+    HdtSchedule &s = c->s;
+    s.n_pos = s.n_own = n_c;
+    s.tr = s.tr_own = (n_c + s.bm - 1) / s.bm;
+    c->n_entries = c->capacity = (int64_t)s.batch * s.tr * ((s.n_kv + s.bn - 1) / s.bn);
+    l->n_compact = n_c;
+    l->compact = c;
 }
 
 static size_t compact_tensor_bytes(const hdt_layout_t *l, int heads, int head_dim, int elem_bytes)
@@ -617,7 +637,7 @@ size_t hdt_cross_compact_workspace_bytes(const hdt_layout_t *l, int heads, int h
 // visible positions only (few keys, short lists).
 int hdt_cross_pieces(const hdt_layout_t *l, int heads)
 {
-    if (!l->cross || l->compact || !l->cross_split_range[0] || heads <= 0) return 1;
+    if (!l->cross || l->compact || l->cross_entries_max < kSplitEntries || heads <= 0) return 1;
     const long long tiles = (long long)l->s.batch * l->s.tr * heads;
     int pieces = 1;
     while (pieces < 8 && tiles * pieces < 1024 && l->cross_entries_max / (2 * pieces) >= 8) pieces *= 2;

@@ -95,14 +95,16 @@ struct hdt_layout {
     // directed masks (edges without up/down symmetry): the schedule of the transposed mask (rows = keys,
     // list entries = the queries attending to them), owned by this layout; NULL for symmetric masks
     hdt_layout *transposed;
-    // Cross-attention layouts with few visible positions (hdt_cross.hip): the schedule of the dK/dV pass in the index
-    // space of the visible positions (row = rank among them), owned by this layout.  NULL: there is none.
-    hdt_layout *compact;
-    int32_t n_compact;           // rows per sample of the compact schedule
-    // Long key lists cut into 2, 4 or 8 pieces (hdt_cross.hip): the entry ranges of the row tiles of every piece,
-    // [batch][pieces * tr][2] each (device, in this layout's first arena); NULL if the lists are short
+    // Cross-attention layouts (hdt_cross.hip): the schedule of the dK/dV pass in the index space of the visible positions
+    // (row = rank among them), owned by this layout; the build enqueues it in any case, and once the build's report is
+    // in (`pending` cleared) `compact` points to it if few enough positions are visible.  NULL: there is none.
+    hdt_layout *compact_built;
+    mutable hdt_layout *compact;
+    mutable int32_t n_compact;           // rows per sample of the compact schedule
+    // Key lists cut into 2, 4 or 8 pieces (hdt_cross.hip): the entry ranges of the row tiles of every piece,
+    // [batch][pieces * tr][2] each (device, in this layout's first arena); NULL if no list can be long
     const int32_t *cross_split_range[3];
-    int32_t cross_entries_max;   // entries of the longest key list (host copy)
+    mutable int32_t cross_entries_max;   // entries of the longest key list, once the report is in
     int64_t capacity;    // entries the per-tile arrays can hold
     int64_t device_bytes;
     void *arena;         // key order, list pointers, scratch of the build
@@ -177,6 +179,10 @@ HdtStreams hdt_layout_streams(const hdt_layout_t *l);
 // `next_user`: the stream on which the buffer's new owner enqueues its work
 hipError_t hdt_pool_alloc(void **out, size_t bytes, size_t *got, hipStream_t next_user);
 
+// What a cross-attention build's report says, the largest number of visible positions of a sample, goes into the layout
+// (hdt_cross.hip).
+void hdt_cross_record(const hdt_layout_t *l, int c_max);
+
 // --- key lists of a cross-attention layout cut into pieces that separate workgroups walk (hdt_cross.hip) ---
 int hdt_cross_pieces(const hdt_layout_t *l, int heads);  // 1, 2, 4 or 8 for this many heads
 size_t hdt_cross_fwd_workspace_bytes(const hdt_layout_t *l, int heads, int head_dim);
@@ -196,9 +202,9 @@ struct HdtReport {
     unsigned long long *word;  // [63:40] ticket of the build, [39] error, [31:0] value
     int32_t *counters;         // 64 device words, zero; the kernel leaves them zero
     uint32_t ticket, ticket_before;
+    unsigned long long *copy;  // the same word in the layout's own device memory
 };
 bool hdt_report_open(int device, HdtReport *r);                       // false: no memory for it
-bool hdt_report_wait(const HdtReport &r, unsigned long long *word);   // false: nothing came within the time limit
 
 // --- per-kernel timing (hdt_api.hip) ---
 struct HdtTimer {  // brackets one kernel launch with events when timing is enabled

@@ -1519,7 +1519,10 @@ static hdt_status_t resolve_one(const hdt_layout_t *L, bool wait, const hipStrea
         }
         static std::mutex record_mutex;
         std::lock_guard<std::mutex> lk(record_mutex);
-        if (L->pending.load(std::memory_order_relaxed)) {
+        if (L->pending.load(std::memory_order_relaxed) && L->cross) {
+            hdt_cross_record(L, (int)(uint32_t)(word & 0xffffffffu));
+            L->pending.store(false, std::memory_order_release);
+        } else if (L->pending.load(std::memory_order_relaxed)) {
             const int64_t need = (int64_t)(word & 0xffffffffu);
             L->entries_needed = need;
             if ((word >> 39) & 1u) {
@@ -1561,11 +1564,6 @@ bool hdt_report_open(int device, HdtReport *r)
     r->word = report_slot(&r->ticket, &r->ticket_before);
     r->counters = r->word ? counter_slot(device, r->ticket) : nullptr;
     return r->counters != nullptr;
-}
-
-bool hdt_report_wait(const HdtReport &r, unsigned long long *word)
-{
-    return wait_for_report(r.word, r.ticket, r.ticket_before, word);
 }
 
 void hdt_layout_release(hdt_layout_t *L, const HdtUsers &users)
@@ -1817,7 +1815,7 @@ static hdt_status_t build_one(const int32_t *d_level, const int32_t *d_parent, i
     L->cross = 0;
     L->cross_level_mask = 0;
     L->transposed = nullptr;
-    L->compact = nullptr;
+    L->compact = L->compact_built = nullptr;
     L->n_compact = 0;
     L->device_bytes = 0;
     L->device = 0;

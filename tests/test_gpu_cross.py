@@ -239,6 +239,42 @@ def test_cross_attention_ignores_what_invisible_rows_hold(oracle, dtype):
         run_cross_case(oracle, level, 200, level_mask, 2, 64, dtype, 1000 + level_mask, poison_invisible=True)
 
 
+@pytest.mark.parametrize("n_enc", [3, 4, 1000, 2000])
+@pytest.mark.parametrize("level_mask", [SEC, SEC | SENT | TOK, 1 << 7], ids=["sec", "tokens", "nothing"])
+def test_cross_build_waits_for_nothing(n_enc, level_mask):
+    """Build, forward and backward enqueued behind tens of milliseconds of other work, so that the calls find the number of
+    visible positions unknown: the same results, bit for bit, as with a layout whose count has been read (few positions visible
+    and a schedule over those alone, many, none; lengths with room for such a schedule and without)."""
+    import torch
+    import paper_2407_08330_amd as hdt
+    B, H, n_dec, D = 2, 3, 70, 64
+    level = np.full((B, n_enc), 3, np.int32)
+    level[:, ::17] = 1
+    level[1, n_enc - 1] = -1
+    lv = to_dev_i32(level)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n_enc)
+    q, d_o = (torch.randn((B, H, n_dec, D), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    k, v = (torch.randn((B, H, n_enc, D), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    lay = hdt.hdt_build_cross_layout(lv, n_dec, level_mask)
+    rows = lay.info()["compact_rows"]
+    visible = int((((level >= 0) & ((level_mask >> np.maximum(level, 0)) & 1 == 1)).sum(axis=1)).max())
+    assert (rows > 0) == (0 < visible and 4 * visible <= n_enc)
+    o, lse = hdt.hdt_attn_fwd(lay, q, k, v, 0.125)
+    want = [o, lse, *hdt.hdt_attn_bwd(lay, q, k, v, o, lse, d_o, 0.125)]
+    a = torch.randn((4096, 4096), device="cuda")
+    torch.cuda.synchronize()
+    for _ in range(40):
+        a = a @ a * 1e-3
+    late = hdt.hdt_build_cross_layout(lv, n_dec, level_mask)
+    o2, lse2 = hdt.hdt_attn_fwd(late, q, k, v, 0.125)
+    got = [o2, lse2, *hdt.hdt_attn_bwd(late, q, k, v, o2, lse2, d_o, 0.125)]
+    late.destroy()
+    torch.cuda.synchronize()
+    for x, y in zip(got, want):
+        assert torch.equal(x.view(torch.int16), y.view(torch.int16))
+
+
 def test_cross_argument_errors():
     import torch
     import paper_2407_08330_amd as hdt
