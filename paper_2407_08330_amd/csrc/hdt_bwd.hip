@@ -50,7 +50,10 @@ struct BwdCfg {
 
 // ---------------------------------------------------------------------------------------- D
 // For all rows of [rows][D] tensors: D_i = sum_c dO_ic O_ic (every lane multiplies 8 values, 16 bytes of each
-// tensor; the lanes of a row are added up; kRows rows per lane in flight).  What the main kernel wants of a row
+// tensor; the lanes of a row are added up; kDeltaRows rows per lane in flight).  Bound by reading the two: O, which
+// nothing behind this pass wants, by streaming (non-temporal) loads, so that dO, which the main kernel reads next, is still
+// in the caches then.  32768 positions x 16 heads of 128, pass + main kernel: plain loads, 4 rows 49.2 + 220.7 us;
+// streaming O 45.0 + 218.3 (2 rows 44.4, 8 rows 46.1: 6.0 TB/s), dO too 44.4 + 220.4.  What the main kernel wants of a row
 // are the two values its contractions start from, so those are what is written, side by side:
 //   .x = -D_i            dP - D        = -D + dO V^T          (accumulator of dP preset to it)
 //   .y = -LSE_i / scale  scale S - LSE = scale (-LSE / scale + Q K^T)   (accumulator of S preset to it)
@@ -58,12 +61,13 @@ struct BwdCfg {
 // pads) get 0 for both: they are masked, and their dO may hold anything.
 // The sum is taken the same way wherever it is taken, here or in the roles (WITH_D): 8 columns by dot_8, then neighbours
 // in pairs, pairs of pairs, and so on, so that the results of a backward do not depend on which of the two computes D.
+constexpr int kDeltaRows = 2;
 template <int D>
 __global__ __launch_bounds__(256) void k_bwd_delta(const __bf16 *__restrict__ o, const __bf16 *__restrict__ d_o,
                                                    const float *__restrict__ lse, float inv_scale,
                                                    float2 *__restrict__ row_scalars, long long rows)
 {
-    constexpr int CPR = D / 8, RPB = 256 / CPR, kRows = 4;
+    constexpr int CPR = D / 8, RPB = 256 / CPR, kRows = kDeltaRows;
     const int lr = threadIdx.x / CPR, c = threadIdx.x % CPR;
     const long long r0 = (long long)blockIdx.x * (RPB * kRows) + lr;
     bf16x8 a[kRows], b[kRows];
@@ -71,7 +75,7 @@ __global__ __launch_bounds__(256) void k_bwd_delta(const __bf16 *__restrict__ o,
 #pragma unroll
     for (int u = 0; u < kRows; u++) {
         const long long r = min(r0 + (long long)u * RPB, rows - 1);
-        a[u] = *reinterpret_cast<const bf16x8 *>(o + (size_t)r * D + c * 8);
+        a[u] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(o + (size_t)r * D + c * 8));
         b[u] = *reinterpret_cast<const bf16x8 *>(d_o + (size_t)r * D + c * 8);
         l[u] = c == 0 ? lse[r] : 0.f;
     }
@@ -642,7 +646,7 @@ static void launch_bwd(const HdtSchedule &s, const HdtSchedule &s_tr, const __bf
     {
         const long long rows = (long long)s.batch * heads * s.n_own;  // the real rows, also when key lists are cut
         HdtTimer t(D == 64 ? "hdt_bwd_delta_d64" : "hdt_bwd_delta_d128", st);
-        const int rpb = (256 / (D / 8)) * 4;
+        const int rpb = (256 / (D / 8)) * kDeltaRows;
         hipLaunchKernelGGL(k_bwd_delta<D>, dim3((unsigned)((rows + rpb - 1) / rpb)), dim3(256), 0, st, O, DO, lse, 1.f / scale,
                            row_scalars, rows);
     }
