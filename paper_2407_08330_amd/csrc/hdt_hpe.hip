@@ -17,12 +17,11 @@
 #include <algorithm>
 
 #include "hdt_internal.h"
+#include "hdt_share.h"
 
 namespace {
 
-constexpr int kOrdThreads = 1024, kOrdWaves = kOrdThreads / 64;
-constexpr int kMaxShares = 64;  // workgroups per sample
-constexpr int kBack = 8;        // groups of 64 positions a wave has in flight while it looks at earlier positions
+constexpr int kOrdWaves = kOrdThreads / 64;
 
 // Both kernels below give a workgroup a contiguous share of a sample's positions, which it takes 1024 at a time; what it
 // has to know about the positions in front of its share it finds by reading them, all waves together.  That reads up
@@ -32,17 +31,7 @@ constexpr int kBack = 8;        // groups of 64 positions a wave has in flight w
 // samples are on the chip at the same time, one per compute unit: further ones only wait, and read more.  8192 positions,
 // us for parents / index vectors, one workgroup per sample - a share per 1024 positions - at most 256 workgroups:
 // 64 samples 31 / 29 - 12 / 22 - 8.6 / 16; 256 samples 32 / 47 - 46 / 80 - 20 / 41; 512 samples 61 / 89 - 91 / 152 - 37 / 63.
-constexpr int kOnChip = 256;
-__host__ inline int hpe_shares(int batch, int n)
-{
-    return std::min({(n + kOrdThreads - 1) / kOrdThreads, kMaxShares, std::max(kOnChip / batch, 1)});
-}
-__device__ __forceinline__ int2 my_share(int n, int shares)  // [first, last) of workgroup blockIdx.x = b * shares + k
-{
-    const int chunks = (n + kOrdThreads - 1) / kOrdThreads, per = (chunks + shares - 1) / shares;
-    const int first = min((int)(blockIdx.x % shares) * per, chunks);
-    return make_int2(first * kOrdThreads, min(min(first + per, chunks) * kOrdThreads, n));
-}
+// (hdt_share.h)
 
 // ---- parents of a document laid out with its anchors in front (pre-order) ---------------------------
 // parent[i] = the nearest earlier position whose level is level[i] - 1 (none: -1).  Inside a wave by ballots, across
@@ -60,26 +49,27 @@ __global__ __launch_bounds__(kOrdThreads) void k_parents_from_levels(const int32
     __shared__ unsigned s_missing;         // levels that positions of the chunk look for and the share has not seen
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const size_t o = (size_t)(blockIdx.x / shares) * n;
-    const int2 share = my_share(n, shares);
+    const HpeShare share = hpe_share(blockIdx.x % shares, n, shares);
+    if (share.empty()) return;
     unsigned searched = 0u;  // levels looked for in front of the share
     // the kBack * 1024 positions that end at `end`
     auto load_back = [&](int end, int (&l)[kBack]) {
 #pragma unroll
         for (int u = 0; u < kBack; u++) {
-            const int j = end - (u + 1) * kOrdThreads + tid;
+            const int j = hpe_position_in_front(share, end, u, tid);
             l[u] = j >= 0 ? level[o + j] : -1;
         }
     };
     // the first chunk and the positions in front of the share are requested together, whoever turns out to need the latter
-    const int first_level = share.x + tid < share.y ? level[o + share.x + tid] : -1;
+    const int first_level = share.first + tid < share.last ? level[o + share.first + tid] : -1;
     int back[kBack];
-    if (SPREAD && share.x > 0) load_back(share.x, back);
+    if (SPREAD && share.first > 0) load_back(share.first, back);
     if (tid < 32) s_carry[tid] = -1;
     if (tid == 0) s_missing = 0u;
     __syncthreads();
-    for (int c0 = share.x; c0 < share.y; c0 += kOrdThreads) {
+    for (int c0 = share.first; c0 < share.last; c0 += kOrdThreads) {
         const int i = c0 + tid;
-        int lv = c0 == share.x ? first_level : (i < share.y ? level[o + i] : -1);
+        int lv = c0 == share.first ? first_level : (i < share.last ? level[o + i] : -1);
         if (lv < 0 || lv >= 32) lv = -1;
         // level by level of those in this wave: its last position (kept by lane = level), and for the positions one
         // level down the nearest earlier one
@@ -102,11 +92,11 @@ __global__ __launch_bounds__(kOrdThreads) void k_parents_from_levels(const int32
             __syncthreads();
             unsigned missing = s_missing & ~searched;
             searched |= missing;
-            for (int end = share.x; missing && end > 0; end -= kBack * kOrdThreads) {
-                if (end < share.x || c0 > share.x) load_back(end, back);
+            for (int end = share.first; missing && end > 0; end -= kBack * kOrdThreads) {
+                if (end < share.first || c0 > share.first) load_back(end, back);
 #pragma unroll
                 for (int u = 0; u < kBack; u++) {
-                    const int j = end - (u + 1) * kOrdThreads + tid;
+                    const int j = hpe_position_in_front(share, end, u, tid);
                     if (back[u] >= 0 && back[u] < 32 && ((missing >> back[u]) & 1u) && s_carry[back[u]] < j) atomicMax(&s_carry[back[u]], j);
                 }
                 __syncthreads();
@@ -115,7 +105,7 @@ __global__ __launch_bounds__(kOrdThreads) void k_parents_from_levels(const int32
             }
         }
         if (miss) par = s_carry[lv - 1];
-        if (i < share.y) parent[o + i] = par;
+        if (i < share.last) parent[o + i] = par;
         __syncthreads();
         if (tid < 32) {
             for (int w = kOrdWaves - 1; w >= 0; w--)
@@ -173,14 +163,14 @@ __global__ __launch_bounds__(kOrdThreads) void k_sibling_ordinals(const int32_t 
     __shared__ unsigned s_windows;  // the windows in which groups of the share lie
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const size_t o = (size_t)(blockIdx.x / shares) * n;
-    const int2 share = my_share(n, shares);
-    if (share.x >= share.y) return;
+    const HpeShare share = hpe_share(blockIdx.x % shares, n, shares);
+    if (share.empty()) return;
     const int window = min(n + 1, kOrdWindow);
     if (tid == 0) s_windows = n + 1 > kOrdWindow ? 0u : 1u;
     __syncthreads();
     if (n + 1 > kOrdWindow) {
         unsigned mine = 0u;
-        for (int i = share.x + tid; i < share.y; i += kOrdThreads) {
+        for (int i = share.first + tid; i < share.last; i += kOrdThreads) {
             const int g = ord_group(level[o + i], parent[o + i], n);
             if (g >= 0) mine |= 1u << (g / kOrdWindow);
         }
@@ -191,13 +181,13 @@ __global__ __launch_bounds__(kOrdThreads) void k_sibling_ordinals(const int32_t 
         const int w0 = (__ffs(todo) - 1) * window;
         for (int t = tid; t < window; t += kOrdThreads) s_count[t] = 0;
         __syncthreads();
-        for (int j0 = 0; j0 < share.x; j0 += kBack * kOrdThreads) {
+        for (int j0 = 0; j0 < share.first; j0 += kBack * kOrdThreads) {
             int g[kBack];
 #pragma unroll
             for (int u = 0; u < kBack; u++) {
                 const int j = j0 + u * kOrdThreads + tid;
                 g[u] = -1;
-                if (j < share.x) g[u] = ord_group(level[o + j], parent[o + j], n);
+                if (j < share.first) g[u] = ord_group(level[o + j], parent[o + j], n);
             }
 #pragma unroll
             for (int u = 0; u < kBack; u++) {
@@ -206,9 +196,9 @@ __global__ __launch_bounds__(kOrdThreads) void k_sibling_ordinals(const int32_t 
                 if (head && g[u] >= w0 && g[u] < w0 + window) atomicAdd(&s_count[g[u] - w0], len);
             }
         }
-        for (int c0 = share.x; c0 < share.y; c0 += kOrdThreads) {
+        for (int c0 = share.first; c0 < share.last; c0 += kOrdThreads) {
             const int i = c0 + tid;
-            const int grp = i < share.y ? ord_group(level[o + i], parent[o + i], n) : -1;
+            const int grp = i < share.last ? ord_group(level[o + i], parent[o + i], n) : -1;
             int len;
             const bool head = run_head(grp, lane, &len);
             const unsigned long long heads = __ballot(head);
@@ -240,7 +230,7 @@ __global__ __launch_bounds__(kOrdThreads) void k_sibling_ordinals(const int32_t 
             if (grp >= w0 && grp < w0 + window) {
                 const int start = 63 - __builtin_clzll(heads & ((2ull << lane) - 1ull));
                 ord[o + i] = 1 + s_run_base[run] + (lane - start);
-                if (head && c0 + kOrdThreads < share.y) atomicAdd(&s_count[grp - w0], len);
+                if (head && c0 + kOrdThreads < share.last) atomicAdd(&s_count[grp - w0], len);
             }
             __syncthreads();
         }

@@ -160,6 +160,17 @@ def test_parents_written_over_their_levels(oracle, n):
         np.testing.assert_array_equal(both.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("batch,n", [(1, 65537), (2, 66000), (40, 8000), (64, 5000), (65, 3073), (85, 3584)])
+def test_parents_where_the_last_workgroups_of_a_sample_have_no_positions(oracle, batch, n):
+    # chunks that do not divide evenly: the shares behind the last chunk are empty
+    rng = np.random.default_rng(n)
+    kinds = [inputs.pseudo_section_document(rng, n)[0], rng.integers(-1, 6, size=n).astype(np.int32)]
+    want = [oracle.parents_from_levels(lv) for lv in kinds]
+    got = _parents(np.stack([kinds[b % 2] for b in range(batch)]))
+    for k, w in enumerate(want[:batch]):
+        assert (got[k::2] == w[None]).all()
+
+
 def _ordinals_walked_up(level, parent, L):
     """Index vectors of one sample in whole-array steps, for lengths the oracle takes minutes for."""
     n = level.shape[0]
