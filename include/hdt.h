@@ -148,7 +148,7 @@ typedef struct {
  * The room is opts->capacity list entries if given (also for a call that waits: HDT_ERR_SHAPE instead of a
  * second attempt); otherwise a deferred build takes the most any document can need, batch * q_tiles *
  * k_tiles, as far as that stays within 256 MiB (n_pos up to about 32768 for one sample), and beyond
- * that what 256 MiB hold.  At most 1024 builds may be in flight per process.
+ * that what 256 MiB hold.  At most 1024 builds of hdt_build_layout may be in flight per process.
  *
  * Errors: HDT_ERR_INVALID_ARG (NULL, negative sizes, edges outside HDT_EDGE_ALL), HDT_ERR_SHAPE (n_pos > 2^19),
  * HDT_ERR_UNSUPPORTED (tile shape), HDT_ERR_HIERARCHY (level outside [-1, HDT_MAX_LEVELS),
@@ -183,9 +183,13 @@ hdt_status_t hdt_build_layout(const int32_t *d_level, const int32_t *d_parent, i
  * of that many rows more on such a layout.)  Results and arguments are the same either way.
  *
  * Kernels are enqueued on `stream`; the call does not wait for them.  The number of visible positions, which the first of
- * them reports, is looked at (and waited for, should the report not be in) by the calls that depend on it: the workspace
- * queries, hdt_attn_fwd_ws with a workspace, hdt_attn_bwd, hdt_layout_info.  Device memory as for hdt_build_layout, sized
- * for the case that every position is visible.
+ * them reports, is looked at by the calls that depend on it: the workspace queries, hdt_attn_fwd_ws with a workspace,
+ * hdt_attn_bwd and hdt_attn_bwd_no_alloc, hdt_layout_status, hdt_layout_info, hdt_layout_sample_info, hdt_layout_export.  The
+ * first of them on a layout waits for that kernel, and for what was enqueued on `stream` before it, should the report not be
+ * in.  The wait itself asks nothing of the device: these calls (but not the last three, which synchronise the device) may be
+ * made while a stream is being captured, on a layout that was built outside the capture.  Any number of such builds may be in
+ * flight.  Device memory as for hdt_build_layout, sized for the case that every position is visible, and from four encoder
+ * positions on for a schedule over a quarter of them besides, whether or not that is used in the end.
  * batch == 0 gives an empty layout on which the attention calls are no-ops.
  * Errors: HDT_ERR_INVALID_ARG (NULL, negative sizes), HDT_ERR_SHAPE (a length of 0 or > 2^19, too many
  * entries), HDT_ERR_UNSUPPORTED (tile shape, other options), HDT_ERR_OOM, HDT_ERR_HIP.  On error *out is NULL.
@@ -203,8 +207,9 @@ hdt_status_t hdt_layout_transposed(const hdt_layout_t *layout, const hdt_layout_
 /* The outcome of a deferred build (opts->deferred): waits until the build kernel has reported (not for the
  * stream), then returns HDT_OK, HDT_ERR_HIERARCHY or HDT_ERR_SHAPE as hdt_build_layout would have.
  * *h_entries_needed (may be NULL) receives the number of list entries the schedule needs, which is what
- * opts->capacity must be at least for the build to succeed.  On a layout built without `deferred` it returns
- * HDT_OK at once. */
+ * opts->capacity must be at least for the build to succeed.  On a layout of hdt_build_layout without `deferred` it returns
+ * HDT_OK at once; on a cross-attention layout it waits for the number of visible positions (see hdt_build_cross_layout),
+ * returns HDT_OK and needs 0. */
 hdt_status_t hdt_layout_status(const hdt_layout_t *layout, int64_t *h_entries_needed);
 
 /* Sizes of a layout (host struct).  n_tiles and nnz are read back from the device by the first call

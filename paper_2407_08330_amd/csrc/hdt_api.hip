@@ -284,6 +284,7 @@ static hdt_status_t destroy_layout(hdt_layout_t *layout, bool completed)
     if (layout->magic != HDT_LAYOUT_MAGIC) return hdt_fail(HDT_ERR_INVALID_ARG, "hdt_layout_destroy: not a layout");
     // the build and every attention call went through this handle: its streams cover the layouts it owns
     const HdtUsers users = completed ? HdtUsers() : hdt_users_at_release(hdt_layout_streams(layout));
+    if (layout->cross && layout->pending.load(std::memory_order_acquire)) hdt_report_close(layout->device, layout->own_report);
     hdt_layout_t *owned[2] = {layout->compact_built, layout->transposed};
     layout->compact_built = layout->compact = layout->transposed = nullptr;
     for (hdt_layout_t *t : owned) {

@@ -116,7 +116,6 @@ __global__ __launch_bounds__(kSelThreads) void k_cross_select(const int32_t *__r
                 __hip_atomic_store(&report.counters[0], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&report.counters[1], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const unsigned long long word = ((unsigned long long)(report.ticket & 0xffffffu) << 40) | (uint32_t)most;
-                *report.copy = word;
                 __hip_atomic_store(report.word, word, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
             }
         }
@@ -341,7 +340,6 @@ __global__ __launch_bounds__(256) void k_cross_sum_dq(const u32x4 *__restrict__ 
 struct CrossBuffers {
     int32_t *split_range[3];                // first arena, forward schedule only: entry ranges with the lists cut in 2, 4, 8
     int32_t *sel, *rank, *count, *q_range;  // first arena
-    unsigned long long *report;             // first arena: the build's report once more
     int32_t *c_row, *c_cnt, *q_keys;  // second arena
     uint32_t *q_sub;
     unsigned long long *bits_rm;
@@ -364,7 +362,6 @@ CrossBuffers carve_cross(char *a1, char *a2, int B, int n_enc, int tr, int64_t e
         c.sel = carve<int32_t>(a1, o1, (size_t)B * n_enc);
         c.rank = carve<int32_t>(a1, o1, (size_t)B * n_enc);
         c.count = carve<int32_t>(a1, o1, (size_t)B);
-        c.report = carve<unsigned long long>(a1, o1, 1);
         for (int k = 0; k < 3; k++) c.split_range[k] = carve<int32_t>(a1, o1, (size_t)B * tr * (2 << k) * 2);
     }
     c.q_range = carve<int32_t>(a1, o1, (size_t)B * tr * 2);
@@ -539,7 +536,6 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_cross_l
             reported = hipStreamIsCapturing(st, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone &&
                        hdt_report_open(L->device, &report);
             if (!reported) report = HdtReport{};
-            report.copy = f.report;
             {
                 HdtTimer tm("hdt_cross_select", st);
                 hipLaunchKernelGGL(k_cross_select, dim3((unsigned)batch), dim3(kSelThreads), 0, st, d_level_enc, n_enc,
@@ -568,10 +564,9 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_cross_l
             CROSS_TRY(hipGetLastError());
             L->compact_built = Tc;  // owned by L from here on
             if (reported) {
+                L->own_report = report;
                 L->report = report.word;
-                L->report_dev = f.report;
                 L->ticket = report.ticket;
-                L->ticket_before = report.ticket_before;
                 L->pending.store(true, std::memory_order_release);
             } else {  // no report: the counts are read back
                 std::vector<int32_t> h_count((size_t)batch, 0);
@@ -586,6 +581,7 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_cross_l
         return HDT_OK;
     }
 fail:
+    if (reported) hdt_report_close(L->device, report);
     if (Tc) {
         hdt_layout_release(Tc, build_only);
         Tc->magic = 0;

@@ -82,6 +82,14 @@ struct HdtStreams {
     }
 };
 
+// What a cross-attention build reports to the host with: a 64-bit word of pinned host memory and device counters that are zero
+// between builds, both this build's own until its report is in, so that any number of builds may be in flight.
+struct HdtReport {
+    unsigned long long *word;  // [63:40] ticket of the build, [31:0] value
+    int32_t *counters;         // 64 device words, zero; the kernel leaves them zero
+    uint32_t ticket;           // of the builds that use this word, the next one's differs
+};
+
 struct hdt_layout {
     uint32_t magic;
     mutable HdtStreams streams;  // of the handle the caller holds; the layouts it owns are used through it
@@ -133,6 +141,7 @@ struct hdt_layout {
     const unsigned long long *report;      // the build's word of pinned host memory
     const unsigned long long *report_dev;  // the same word in the layout's own device memory
     uint32_t ticket, ticket_before;        // the build's ticket; the one its report slot held when it was enqueued
+    HdtReport own_report;                  // cross-attention layouts: where `report` and `ticket` are from
 };
 
 // --- error reporting (hdt_api.hip) ---
@@ -196,15 +205,9 @@ hdt_status_t hdt_cross_bwd_split(const hdt_layout_t *l, const void *q, const voi
 // (workspace a layout with a compact schedule asks for beyond what its kernels use, see hdt_attn_bwd_workspace_bytes)
 size_t hdt_cross_compact_workspace_bytes(const hdt_layout_t *l, int heads, int head_dim, int elem_bytes);
 
-// --- the device's report to a waiting host: one 64-bit word of pinned host memory per build in flight, and a slot of
-// device counters that is zero between builds (hdt_layout.hip) ---
-struct HdtReport {
-    unsigned long long *word;  // [63:40] ticket of the build, [39] error, [31:0] value
-    int32_t *counters;         // 64 device words, zero; the kernel leaves them zero
-    uint32_t ticket, ticket_before;
-    unsigned long long *copy;  // the same word in the layout's own device memory
-};
-bool hdt_report_open(int device, HdtReport *r);                       // false: no memory for it
+// --- words and counters of cross-attention builds, see HdtReport (hdt_layout.hip) ---
+bool hdt_report_open(int device, HdtReport *r);          // false: no memory for it
+void hdt_report_close(int device, const HdtReport &r);   // for the next build that comes once the report is in
 
 // --- per-kernel timing (hdt_api.hip) ---
 struct HdtTimer {  // brackets one kernel launch with events when timing is enabled

@@ -41,6 +41,7 @@
 #include <limits.h>
 #include <stdio.h>
 #include <string.h>
+#include <unistd.h>
 
 #include <algorithm>
 #include <chrono>
@@ -1445,6 +1446,31 @@ bool wait_for_report(const unsigned long long *slot, uint32_t ticket, uint32_t t
     }
 }
 
+// The same for a cross-attention build, whose word no other build writes before its report is in: until it is, however long
+// the stream takes, and without a call that a stream being captured would refuse.  False: another thread has recorded the
+// report meanwhile (the word may be another build's by now).
+bool wait_for_own_report(const hdt_layout_t *L, unsigned long long *word)
+{
+    const auto t0 = std::chrono::steady_clock::now();
+    for (uint64_t spins = 1;; spins++) {
+        const unsigned long long w = __atomic_load_n(L->report, __ATOMIC_ACQUIRE);
+        if ((uint32_t)(w >> 40) == L->ticket) {
+            *word = w;
+            return true;
+        }
+        if (!L->pending.load(std::memory_order_acquire)) return false;
+        if ((spins & 0x3ff) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::seconds(1)) usleep(100);
+        __builtin_ia32_pause();
+    }
+}
+
+// Words and counters of cross-attention builds, per device: the ones without a layout that reads them, longest there first.
+// One whose layout was destroyed early may still be waiting for its report.  Never freed: a kernel may still write at exit,
+// and a layout may be destroyed then.
+constexpr int kReportPage = 256;
+std::mutex &g_reports_mutex = *new std::mutex();
+std::vector<HdtReport> *const g_free_reports = new std::vector<HdtReport>[kCounterDevices];
+
 const char kHierarchyText[] =
     "level/parent arrays are not a valid hierarchy (level outside [-1, 32), parent outside [-1, n_pos), self-parent, "
     "pad with a parent, or pad parent)";
@@ -1504,8 +1530,8 @@ static hdt_status_t resolve_one(const hdt_layout_t *L, bool wait, const hipStrea
         bool have = (uint32_t)(word >> 40) == L->ticket;
         if (!have && !wait) return HDT_OK;
         // No lock is held here: a build behind a busy stream keeps its caller waiting and nobody else.
-        if (!have) have = wait_for_report(L->report, L->ticket, L->ticket_before, &word);
-        if (!have) {
+        if (!have) have = L->cross ? wait_for_own_report(L, &word) : wait_for_report(L->report, L->ticket, L->ticket_before, &word);
+        if (!have && !L->cross) {
             // the slot has gone to a later build (or nothing came for 10 s): the copy in the layout's own memory
             int dev = 0;
             HDT_HIP_TRY(hipGetDevice(&dev));
@@ -1522,6 +1548,7 @@ static hdt_status_t resolve_one(const hdt_layout_t *L, bool wait, const hipStrea
         if (L->pending.load(std::memory_order_relaxed) && L->cross) {
             hdt_cross_record(L, (int)(uint32_t)(word & 0xffffffffu));
             L->pending.store(false, std::memory_order_release);
+            hdt_report_close(L->device, L->own_report);
         } else if (L->pending.load(std::memory_order_relaxed)) {
             const int64_t need = (int64_t)(word & 0xffffffffu);
             L->entries_needed = need;
@@ -1561,9 +1588,46 @@ hipError_t hdt_pool_alloc(void **out, size_t bytes, size_t *got, hipStream_t nex
 
 bool hdt_report_open(int device, HdtReport *r)
 {
-    r->word = report_slot(&r->ticket, &r->ticket_before);
-    r->counters = r->word ? counter_slot(device, r->ticket) : nullptr;
-    return r->counters != nullptr;
+    if (device < 0 || device >= kCounterDevices) return false;
+    std::lock_guard<std::mutex> lk(g_reports_mutex);
+    std::vector<HdtReport> &free = g_free_reports[device];
+    for (size_t i = 0; i < free.size(); i++) {
+        if ((uint32_t)(__atomic_load_n(free[i].word, __ATOMIC_ACQUIRE) >> 40) != free[i].ticket) continue;  // not in yet
+        *r = free[i];
+        r->ticket = (r->ticket + 1) & 0xffffffu;
+        free.erase(free.begin() + (ptrdiff_t)i);
+        return true;
+    }
+    // none: kReportPage more (a line per word, 256 bytes per build's counters), cleared on a stream that waits for no other
+    void *words = nullptr, *counters = nullptr;
+    hipStream_t st = nullptr;
+    const size_t counter_bytes = (size_t)kReportPage * 64 * sizeof(int32_t);
+    bool ok = hipHostMalloc(&words, kReportPage * 64, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess &&
+              hipMalloc(&counters, counter_bytes) == hipSuccess &&
+              hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess;
+    if (ok) {
+        ok = hipMemsetAsync(counters, 0, counter_bytes, st) == hipSuccess && hipStreamSynchronize(st) == hipSuccess;
+        (void)hipStreamDestroy(st);
+    }
+    if (!ok) {
+        (void)hipGetLastError();
+        if (words) (void)hipHostFree(words);
+        if (counters) (void)hipFree(counters);
+        return false;
+    }
+    memset(words, 0, kReportPage * 64);
+    for (size_t i = 0; i < kReportPage; i++)
+        free.push_back({static_cast<unsigned long long *>(words) + i * 8, static_cast<int32_t *>(counters) + i * 64, 0});
+    *r = free[free.size() - kReportPage];
+    r->ticket = 1;
+    free.erase(free.end() - kReportPage);
+    return true;
+}
+
+void hdt_report_close(int device, const HdtReport &r)
+{
+    std::lock_guard<std::mutex> lk(g_reports_mutex);
+    g_free_reports[device].push_back(r);
 }
 
 void hdt_layout_release(hdt_layout_t *L, const HdtUsers &users)

@@ -275,6 +275,40 @@ def test_cross_build_waits_for_nothing(n_enc, level_mask):
         assert torch.equal(x.view(torch.int16), y.view(torch.int16))
 
 
+def test_cross_calls_captured_on_a_layout_that_many_builds_have_followed():
+    """The number of visible positions is asked for while a graph is being captured, where nothing may be waited for on the
+    device, and more than a thousand builds after the one that reported it."""
+    import torch
+    import paper_2407_08330_amd as hdt
+    level = to_dev_i32(_long_encoder_levels(2048, (7,)))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    q, d_o = (torch.randn((1, 2, 100, 64), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    k, v = (torch.randn((1, 2, 2048, 64), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    for level_mask in (SEC, SEC | SENT | TOK):
+        known = hdt.hdt_build_cross_layout(level, 100, level_mask)
+        room = [torch.empty(max(need, 16), dtype=torch.uint8, device="cuda")
+                for need in (hdt.hdt_attn_fwd_workspace_bytes(known, 2, 64, 0), hdt.hdt_attn_bwd_workspace_bytes(known, 2, 64, 0))]
+        o, lse = hdt.hdt_attn_fwd(known, q, k, v, 0.125, workspace=room[0])
+        want = [o, lse, *hdt.hdt_attn_bwd(known, q, k, v, o, lse, d_o, 0.125, workspace=room[1])]
+        lay = hdt.hdt_build_cross_layout(level, 100, level_mask)
+        for _ in range(1030):
+            hdt.hdt_build_cross_layout(level, 100, SEC).destroy()
+        got = [torch.empty_like(x) for x in want]
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            hdt.hdt_attn_fwd(lay, q, k, v, 0.125, o=got[0], lse=got[1], workspace=room[0])
+            hdt.hdt_attn_bwd(lay, q, k, v, got[0], got[1], d_o, 0.125, *got[2:], workspace=room[1])
+        for _ in range(3):
+            for x in got:
+                x.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            for x, y in zip(got, want):
+                assert torch.equal(x.view(torch.int16), y.view(torch.int16))
+
+
 def test_cross_argument_errors():
     import torch
     import paper_2407_08330_amd as hdt
