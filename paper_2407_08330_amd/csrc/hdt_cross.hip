@@ -436,7 +436,7 @@ void adopt(hdt_layout_t *l, const CrossBuffers &c, int64_t n)
     l->d_row = c.c_row;
     l->n_entries = n;
     l->capacity = n;
-    l->device_bytes = (int64_t)(l->arena_bytes + l->arena2_bytes);
+    l->device_bytes = (int64_t)(c.bytes1 + c.bytes2);
     if (n == 0) l->stats_ready = true;
 }
 
@@ -512,18 +512,28 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_cross_l
             int64_t n;
             CrossBuffers c;
         } all[3] = {{L, empty ? 0 : ent_fwd, {}}, {T, empty ? 0 : ent_tr, {}}, {Tc, empty ? 0 : ent_c, {}}};
+        // The schedules share the two buffers of L, which goes through the cache of buffers with two of them: with two per
+        // schedule, the cache's 16 held two layouts at a time, and a third one destroyed gave buffers back to the system.
+        size_t bytes1 = 0, bytes2 = 0;
         for (auto &x : all) {
             if (!x.l) continue;
-            const bool with_sel = x.l == L;
-            const CrossBuffers need = carve_cross(nullptr, nullptr, batch, n_enc, x.l->s.tr, x.n, bm, bn, with_sel);
-            CROSS_TRY(hdt_pool_alloc(&x.l->arena, need.bytes1 + 256, &x.l->arena_bytes, st));
-            CROSS_TRY(hdt_pool_alloc(&x.l->arena2, need.bytes2 + 256, &x.l->arena2_bytes, st));
-            x.c = carve_cross((char *)x.l->arena, (char *)x.l->arena2, batch, n_enc, x.l->s.tr, x.n, bm, bn, with_sel);
+            x.c = carve_cross(nullptr, nullptr, batch, n_enc, x.l->s.tr, x.n, bm, bn, x.l == L);
+            bytes1 += x.c.bytes1;
+            bytes2 += x.c.bytes2;
+        }
+        CROSS_TRY(hdt_pool_alloc(&L->arena, bytes1 + 256, &L->arena_bytes, st));
+        CROSS_TRY(hdt_pool_alloc(&L->arena2, bytes2 + 256, &L->arena2_bytes, st));
+        char *at1 = (char *)L->arena, *at2 = (char *)L->arena2;
+        for (auto &x : all) {
+            if (!x.l) continue;
+            x.c = carve_cross(at1, at2, batch, n_enc, x.l->s.tr, x.n, bm, bn, x.l == L);
+            at1 += x.c.bytes1;
+            at2 += x.c.bytes2;
             adopt(x.l, x.c, x.n);
         }
+        L->device_bytes = (int64_t)(L->arena_bytes + L->arena2_bytes);
         const CrossBuffers &f = all[0].c;
         T->s.row_flag = f.rank;  // encoder rows that are not visible (pads among them) may hold anything
-        L->device_bytes += T->device_bytes + (Tc ? Tc->device_bytes : 0);
         if (Tc) {
             Tc->s.own_index = f.sel;
             Tc->s.own_count = f.count;
@@ -583,11 +593,9 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_cross_l
 fail:
     if (reported) hdt_report_close(L->device, report);
     if (Tc) {
-        hdt_layout_release(Tc, build_only);
         Tc->magic = 0;
         delete Tc;
     }
-    hdt_layout_release(T, build_only);
     T->magic = 0;
     delete T;
     L->transposed = nullptr;

@@ -309,6 +309,27 @@ def test_cross_calls_captured_on_a_layout_that_many_builds_have_followed():
                 assert torch.equal(x.view(torch.int16), y.view(torch.int16))
 
 
+def test_cross_layouts_of_a_decoder_stay_in_the_buffer_cache():
+    """Four layouts at a time, built and destroyed step by step (a decoder with several settings of what it sees): the cache
+    holds the buffers of all four, and none goes back to the system, which would wait for the device."""
+    import torch
+    import paper_2407_08330_amd as hdt
+    level = to_dev_i32(_long_encoder_levels(8192, (1, 2)))
+    torch.cuda.synchronize()
+    hdt.hdt_release_cached_memory()
+    free = []
+    for _ in range(3):
+        lays = [hdt.hdt_build_cross_layout(level, 512, m) for m in (SEC, SENT, SEC | SENT, SEC | SENT | TOK)]
+        torch.cuda.synchronize()
+        free.append(torch.cuda.mem_get_info()[0])
+        for lay in lays:
+            lay.destroy()
+        free.append(torch.cuda.mem_get_info()[0])
+    hdt.hdt_release_cached_memory()
+    assert torch.cuda.mem_get_info()[0] > free[0]
+    assert len(set(free)) == 1, free
+
+
 def test_cross_argument_errors():
     import torch
     import paper_2407_08330_amd as hdt
