@@ -607,26 +607,34 @@ static void launch_kernel(const HdtSchedule &s, const HdtSchedule &s_tr, const _
 // Always two where the rows are indexed and the tiles 128 x 64: one role takes 307 registers there, a single wave per SIMD
 // (whole backward, one role / two: 512 x 8192 x 48 heads, 500 positions visible, 68.9 / 61.3 us, 750 81.3 / 68.6, 2000
 // 185 / 130; 2048 x 8192 x 64 heads, 2000 visible, 716 / 540).  On 64 x 32 tiles it keeps two.
-// Whether the roles compute D themselves (head size 64), from what the host knows.  What that saves is a launch (about 4 us)
-// and a pass over O and dO; what it costs is D of a query once per list entry that names it, and a barrier and a
-// third more rows per entry.  us for the pass and the backward kernel - with D in the roles, hipGraph of backward calls:
-//   4 x 12 heads, 8192 positions, 64 x 32 tiles 96.2 - 93.7, 128 x 64 103.7 - 100.0; 3 x 12 x 2047 28.5 - 27.0 and 31.3 - 28.9;
-//   1 x 12 x 1000 11.1 - 9.6; 16 x 4 ListOps-shaped trees of 1536 27.1 - 23.7; but where groups of 200 siblings make
-//   the lists long 4 % more, of 500 12 % and of 2000 17 % (64 x 32 tiles; 1, 5 and 9 % on 128 x 64).
-// So for lists of at most 224 (320) keys on average; documents have 150 (230).  A deferred build whose report is not in is
-// taken for a document.  Either way D is the same to the last bit, so the choice shows in nothing but the time.
-//   Cross-attention: 512 x 8192 x 48, 750 visible 24.4 - 22.2; 512 x 512 x 48, all visible 22.5 - 21.8; 300 x 512 x 16, 47
-//   visible 13.5 - 12.3; 100 x 1000 x 4 17.7 - 15.2; but 512 x 8192 x 48, all visible 199 - 205; 2048 x 8192 x 48, 750 visible
-//   68.1 - 71.5: for up to 512 decoder rows, and as long as there are not more (row tile, entry) pairs than the chip goes
-//   through in a few us.
+// Whether the roles compute D themselves (head size 64), from what the host knows.  What that saves is a launch (about 2 us in
+// a graph, 4 outside) and a pass over O and dO; what it costs is D of a query once per list entry that names it, and a barrier
+// and a third more rows per entry.  So it pays for short lists, and the less so the more rows there are, since the launch then
+// weighs less.  Either way D is the same to the last bit, so the choice shows in nothing but the time.  A hipGraph of backward
+// calls, time with the roles over time with the pass, rows = batch x heads x positions:
+//   Self-attention, 64 x 32 tiles, documents: up to 200 K rows and 165 keys a list on average 0.86-0.99 (1 x 12 x 512 10.8 - 10.0
+//   us, 3 x 12 x 2047 27.1 - 25.9, 16 x 12 x 1000 50.8 - 48.6), beyond that length 169 keys 1.006, 187 1.011, 210 1.04;
+//   393-524 K rows 141-147 keys 0.98-1.01, 152-155 0.98-1.02, 163 1.01, 196 1.04, 216 1.075 (120 - 129 us).  128 x 64 tiles: up
+//   to 200 K rows and 290 keys 0.85-0.98, 306 0.99, 320 1.00; 393-524 K rows 219-248 keys 0.95-1.00, 252-285 1.00-1.02, 302
+//   1.02 (126 - 128).  ListOps-shaped trees (30-190 keys) 0.72-0.97, and long lists - hundreds of siblings - up to 1.22.
+//   Cross-attention: every row tile with a visible row lists all decoder rows, and while there are few tiles the time is that of
+//   one walk along a list.  Lists of 2, 4, 6, 8, 10 and 12 entries 0.83, 0.91, 0.96, 0.97-1.01, 1.02 and 1.04 (128 x 64: 128 to 768
+//   decoder rows; 512 x 8192 x 48, 750 visible, 26 - 24 us), on 64 x 32 tiles 0.81, 0.85, 0.91, 0.93-0.98, 1.00 and 1.04 (64 to
+//   384).  Full grids stop paying earlier, after about so many (list entry, head) pairs as stand below for lists of 8
+//   entries: 128 x 64, 6 entries 1.03 at 4608 pairs (50 - 51 us), 4 entries 0.98 at 4096; 64 x 32, 8 entries 0.96-0.98 at 3072
+//   and 1.01 at 4096, 4 entries 0.99 at 6144.
 // At head size 128 the third tensor's tiles cost a workgroup per compute unit (16384 positions x 16 heads 136 - 157).
 template <typename G>
 static bool roles_compute_d(const HdtSchedule &s_tr, int heads, HdtLists lists)
 {
+    constexpr bool SMALL = G::BM == 64;
     const long long tiles = (long long)s_tr.batch * s_tr.tr;
-    if (!lists.cross) return lists.entries < 0 || lists.entries * G::BN <= tiles * (G::BM == 64 ? 224 : 320);
-    const long long entries = tiles * ((s_tr.n_kv + G::BN - 1) / G::BN);  // every tile with a visible row lists all decoder rows
-    return s_tr.n_kv <= 512 && entries * heads <= (G::BM == 64 ? 8000 : 5000);
+    if (!lists.cross) {
+        const bool few = (long long)s_tr.batch * heads * s_tr.n_pos <= 200000;
+        return lists.entries < 0 || lists.entries * G::BN <= tiles * (SMALL ? (few ? 165 : 148) : (few ? 290 : 250));
+    }
+    const long long list = (s_tr.n_kv + G::BN - 1) / G::BN, pairs = tiles * list * heads;
+    return list <= 8 && pairs <= (SMALL ? 8000 : 5000) && pairs * list <= 8 * (SMALL ? 3100 : 2100);
 }
 
 template <int D, typename G, bool INDEXED>

@@ -275,6 +275,57 @@ def test_cross_build_waits_for_nothing(n_enc, level_mask):
         assert torch.equal(x.view(torch.int16), y.view(torch.int16))
 
 
+@pytest.mark.parametrize("tile,n_enc,n_dec,every,heads", [
+    ((128, 64), 8192, 500, 1, 4), ((64, 32), 8192, 250, 1, 3),      # long lists of keys, cut into pieces
+    ((128, 64), 2048, 500, 4, 65), ((64, 32), 2048, 250, 4, 48),    # a schedule over the visible positions
+    ((128, 64), 1000, 300, 2, 84), ((64, 32), 500, 100, 2, 193)])    # neither
+def test_cross_bwd_is_the_same_on_both_sides_of_the_line_where_the_roles_compute_d(tile, n_enc, n_dec, every, heads):
+    """With `heads` heads the roles compute D, with one more a pass of its own does: the heads that both calls have come out the
+    same, bit for bit."""
+    import torch
+    import paper_2407_08330_amd as hdt
+    level = np.full((1, n_enc), 3, np.int32)
+    level[:, ::every] = 1
+    level[0, -5:] = -1
+    lay = hdt.hdt_build_cross_layout(to_dev_i32(level), n_dec, SEC, tile_m=tile[0], tile_n=tile[1])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n_enc + n_dec)
+    more = heads + 1
+    q, d_o = (torch.randn((1, more, n_dec, 64), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    k, v = (torch.randn((1, more, n_enc, 64), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    o, lse = hdt.hdt_attn_fwd(lay, q, k, v, 0.125)
+    results = []
+    hdt.hdt_timing_enable(True)
+    try:
+        for h, d_pass in ((heads, False), (more, True)):
+            hdt.hdt_timing_reset()
+            results.append(hdt.hdt_attn_bwd(lay, *(x[:, :h].contiguous() for x in (q, k, v, o, lse, d_o)), 0.125))
+            torch.cuda.synchronize()
+            assert ("hdt_bwd_delta_d64" in hdt.hdt_timing_read()) == d_pass
+    finally:
+        hdt.hdt_timing_enable(False)
+    for x, y in zip(*results):
+        assert torch.equal(x.view(torch.int16), y[:, :heads].contiguous().view(torch.int16))
+
+
+@pytest.mark.parametrize("tile", [(128, 64), (64, 32)], ids=["128x64", "64x32"])
+def test_cross_bwd_has_a_d_pass_where_lists_are_longer_than_eight_entries(tile):
+    import torch
+    import paper_2407_08330_amd as hdt
+    for n_dec, d_pass in ((8 * tile[1], False), (8 * tile[1] + 1, True)):
+        lay = hdt.hdt_build_cross_layout(to_dev_i32(np.ones((1, 300), np.int32)), n_dec, SEC, tile_m=tile[0], tile_n=tile[1])
+        q, d_o = (torch.randn((1, 2, n_dec, 64), device="cuda").to(torch.bfloat16) for _ in range(2))
+        k, v = (torch.randn((1, 2, 300, 64), device="cuda").to(torch.bfloat16) for _ in range(2))
+        o, lse = hdt.hdt_attn_fwd(lay, q, k, v, 0.125)
+        hdt.hdt_timing_enable(True)
+        try:
+            hdt.hdt_timing_reset()
+            hdt.hdt_attn_bwd(lay, q, k, v, o, lse, d_o, 0.125)
+            assert ("hdt_bwd_delta_d64" in hdt.hdt_timing_read()) == d_pass
+        finally:
+            hdt.hdt_timing_enable(False)
+
+
 def test_cross_calls_captured_on_a_layout_that_many_builds_have_followed():
     """The number of visible positions is asked for while a graph is being captured, where nothing may be waited for on the
     device, and more than a thousand builds after the one that reported it."""
