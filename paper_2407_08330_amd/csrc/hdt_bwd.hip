@@ -609,14 +609,14 @@ static void launch_kernel(const HdtSchedule &s, const HdtSchedule &s_tr, const _
 // 185 / 130; 2048 x 8192 x 64 heads, 2000 visible, 716 / 540).  On 64 x 32 tiles it keeps two.
 // Whether the roles compute D themselves (head size 64), from what the host knows.  What that saves is a launch (about 2 us in
 // a graph, 4 outside) and a pass over O and dO; what it costs is D of a query once per list entry that names it, and a barrier
-// and a third more rows per entry.  So it pays for short lists, and the less so the more rows there are, since the launch then
-// weighs less.  Either way D is the same to the last bit, so the choice shows in nothing but the time.  A hipGraph of backward
-// calls, time with the roles over time with the pass, rows = batch x heads x positions:
-//   Self-attention, 64 x 32 tiles, documents: up to 200 K rows and 165 keys a list on average 0.86-0.99 (1 x 12 x 512 10.8 - 10.0
-//   us, 3 x 12 x 2047 27.1 - 25.9, 16 x 12 x 1000 50.8 - 48.6), beyond that length 169 keys 1.006, 187 1.011, 210 1.04;
-//   393-524 K rows 141-147 keys 0.98-1.01, 152-155 0.98-1.02, 163 1.01, 196 1.04, 216 1.075 (120 - 129 us).  128 x 64 tiles: up
-//   to 200 K rows and 290 keys 0.85-0.98, 306 0.99, 320 1.00; 393-524 K rows 219-248 keys 0.95-1.00, 252-285 1.00-1.02, 302
-//   1.02 (126 - 128).  ListOps-shaped trees (30-190 keys) 0.72-0.97, and long lists - hundreds of siblings - up to 1.22.
+// and a third more rows per entry.  So it pays for short lists.  Either way D is the same to the last bit, so the choice shows
+// in nothing but the time.  hipGraphs, time with the roles over time with the pass:
+//   Self-attention, forward and backward on several sets of tensors in turn (what a layer finds is not in the caches), documents
+//   with other sentences, 6 K to 524 K rows (batch x heads x positions).  64 x 32 tiles, keys a list on average: 120-155
+//   0.90-0.99 (8192 x 4 x 12 140.4 - 138.1 us), 158-169 0.96-0.99, 174 1.02, 187-200 0.98-1.03, 209-220 1.00-1.04 (1 x 32768 x 16
+//   227.6 - 236.2); 128 x 64: 192-248 0.91-0.99, 252-292 0.96-1.00, 300-310 0.97-1.01.  Again on one set, part of which the caches
+//   hold, the lines lie at about 180 and 320 keys below 200 K rows, 155 and 270 beyond (8192 x 4 x 12, 64 x 32, 163 keys 140.3 -
+//   142.2).  ListOps-shaped trees (30-190 keys) 0.72-0.97 of the backward, hundreds of siblings up to 1.22.
 //   Cross-attention: every row tile with a visible row lists all decoder rows, and while there are few tiles the time is that of
 //   one walk along a list.  Lists of 2, 4, 6, 8, 10 and 12 entries 0.83, 0.91, 0.96, 0.97-1.01, 1.02 and 1.04 (128 x 64: 128 to 768
 //   decoder rows; 512 x 8192 x 48, 750 visible, 26 - 24 us), on 64 x 32 tiles 0.81, 0.85, 0.91, 0.93-0.98, 1.00 and 1.04 (64 to
@@ -629,10 +629,7 @@ static bool roles_compute_d(const HdtSchedule &s_tr, int heads, HdtLists lists)
 {
     constexpr bool SMALL = G::BM == 64;
     const long long tiles = (long long)s_tr.batch * s_tr.tr;
-    if (!lists.cross) {
-        const bool few = (long long)s_tr.batch * heads * s_tr.n_pos <= 200000;
-        return lists.entries < 0 || lists.entries * G::BN <= tiles * (SMALL ? (few ? 165 : 148) : (few ? 290 : 250));
-    }
+    if (!lists.cross) return lists.entries < 0 || lists.entries * G::BN <= tiles * (SMALL ? 170 : 290);
     const long long list = (s_tr.n_kv + G::BN - 1) / G::BN, pairs = tiles * list * heads;
     return list <= 8 && pairs <= (SMALL ? 8000 : 5000) && pairs * list <= 8 * (SMALL ? 3100 : 2100);
 }
