@@ -481,7 +481,7 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_attn_bwd(cons
         const hdt_layout_t *tr = layout->transposed ? layout->transposed : layout;
         const bool known = !tr->pending.load(std::memory_order_acquire);  // (the fields below stand from then on)
         return hdt_launch_bwd_bf16(s, s_tr, q, k, v, o, lse, d_o, dq, dk, dv, heads, head_dim, scale, (float *)workspace,
-                                   HdtLists{layout->cross != 0, known ? (long long)tr->n_entries : -1}, hs);
+                                   HdtLists{layout->cross != 0, known ? tr->n_entries : tr->entries_like}, hs);
     }
     return hdt_launch_bwd_f32(s, s_tr, (const float *)q, (const float *)k, (const float *)v, (const float *)o, lse,
                               (const float *)d_o, (float *)dq, (float *)dk, (float *)dv, heads, head_dim, scale, hs);

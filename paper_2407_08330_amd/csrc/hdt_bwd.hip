@@ -616,7 +616,8 @@ static void launch_kernel(const HdtSchedule &s, const HdtSchedule &s_tr, const _
 //   0.90-0.99 (8192 x 4 x 12 140.4 - 138.1 us), 158-169 0.96-0.99, 174 1.02, 187-200 0.98-1.03, 209-220 1.00-1.04 (1 x 32768 x 16
 //   227.6 - 236.2); 128 x 64: 192-248 0.91-0.99, 252-292 0.96-1.00, 300-310 0.97-1.01.  Again on one set, part of which the caches
 //   hold, the lines lie at about 180 and 320 keys below 200 K rows, 155 and 270 beyond (8192 x 4 x 12, 64 x 32, 163 keys 140.3 -
-//   142.2).  ListOps-shaped trees (30-190 keys) 0.72-0.97 of the backward, hundreds of siblings up to 1.22.
+//   142.2).  ListOps-shaped trees (30-190 keys) 0.72-0.97 of the backward, hundreds of siblings up to 1.22.  (A
+//   deferred build whose report is not in counts as the last one of its shape that has reported.)
 //   Cross-attention: every row tile with a visible row lists all decoder rows, and while there are few tiles the time is that of
 //   one walk along a list.  Lists of 2, 4, 6, 8, 10 and 12 entries 0.83, 0.91, 0.96, 0.97-1.01, 1.02 and 1.04 (128 x 64: 128 to 768
 //   decoder rows; 512 x 8192 x 48, 750 visible, 26 - 24 us), on 64 x 32 tiles 0.81, 0.85, 0.91, 0.93-0.98, 1.00 and 1.04 (64 to
@@ -629,7 +630,10 @@ static bool roles_compute_d(const HdtSchedule &s_tr, int heads, HdtLists lists)
 {
     constexpr bool SMALL = G::BM == 64;
     const long long tiles = (long long)s_tr.batch * s_tr.tr;
-    if (!lists.cross) return lists.entries < 0 || lists.entries * G::BN <= tiles * (SMALL ? 170 : 290);
+    if (!lists.cross) {
+        const long long entries = lists.entries >= 0 ? lists.entries : tiles * s_tr.tc;  // (not known: as long as they can be)
+        return entries * G::BN <= tiles * (SMALL ? 170 : 290);
+    }
     const long long list = (s_tr.n_kv + G::BN - 1) / G::BN, pairs = tiles * list * heads;
     return list <= 8 && pairs <= (SMALL ? 8000 : 5000) && pairs * list <= 8 * (SMALL ? 3100 : 2100);
 }

@@ -137,6 +137,7 @@ struct hdt_layout {
     mutable std::atomic<bool> pending;
     mutable hdt_status_t build_status;     // what the report said, once it has been read
     mutable int64_t entries_needed;        // list entries the build needed (-1: not known yet)
+    int64_t entries_like;                  // what an earlier build of the same shape needed (-1: none has reported)
     mutable char build_error[320];         // text of build_status
     const unsigned long long *report;      // the build's word of pinned host memory
     const unsigned long long *report_dev;  // the same word in the layout's own device memory
@@ -228,7 +229,7 @@ hdt_status_t hdt_launch_fwd_f32(const HdtSchedule &s, const float *q, const floa
 // s_transposed, for a choice between kernels with the same results.
 struct HdtLists {
     bool cross;         // a cross-attention layout's
-    long long entries;  // of all samples; -1: not known yet (a deferred build whose report is not in)
+    long long entries;  // of all samples; while a deferred build's report is not in, those of an earlier one like it; -1: not known
 };
 inline size_t hdt_bwd_row_scalars_bytes(size_t rows) { return (2 * rows * sizeof(float) + 255) & ~(size_t)255; }
 hdt_status_t hdt_launch_bwd_bf16(const HdtSchedule &s, const HdtSchedule &s_transposed, const void *q, const void *k, const void *v,

@@ -1406,6 +1406,57 @@ unsigned long long *report_slot(uint32_t *ticket, uint32_t *ticket_before)
     return slot;
 }
 
+// How many list entries builds of a shape need: a build whose report nobody waits for has lists about as long as the last one
+// of its shape that has reported (documents of one kind, step after step, while the host runs ahead).  The reports are
+// read in the order of the builds, as far as they are in, whenever a build is noted; the last kShapes shapes are kept.
+struct BuildShape {
+    int32_t batch, n, bm, bn, edges;
+    bool operator==(const BuildShape &o) const
+    {
+        return batch == o.batch && n == o.n && bm == o.bm && bn == o.bn && edges == o.edges;
+    }
+};
+struct SlotBuild {
+    BuildShape shape;
+    uint32_t ticket;
+} g_slot_builds[kReportSlots] = {};  // who owns or owned a report slot
+struct ShapeEntries {
+    BuildShape shape;
+    int64_t entries;
+};
+constexpr int kShapes = 32;
+std::vector<ShapeEntries> &g_shapes = *new std::vector<ShapeEntries>();  // oldest first
+uint32_t g_unread = 1;                                                   // the first ticket whose report has not been read
+
+// Notes the build of `ticket`; list entries of the last build before it that had its shape, -1: none is known.
+int64_t entries_of_one_like(uint32_t ticket, const BuildShape &shape)
+{
+    std::lock_guard<std::mutex> lk(g_pool_mutex);
+    auto find = [](const BuildShape &what) {
+        size_t i = 0;
+        while (i < g_shapes.size() && !(g_shapes[i].shape == what)) i++;
+        return i;
+    };
+    if (((ticket - g_unread) & 0xffffffu) >= (uint32_t)kReportSlots) g_unread = (ticket - kReportSlots + 1) & 0xffffffu;
+    for (; g_unread != ticket; g_unread = (g_unread + 1) & 0xffffffu) {
+        const SlotBuild &x = g_slot_builds[g_unread % kReportSlots];
+        if (g_unread == 0 || x.ticket != g_unread) continue;  // a build of another kind
+        const unsigned long long word = __atomic_load_n(g_reports + (size_t)(g_unread % kReportSlots) * 8, __ATOMIC_ACQUIRE);
+        if ((uint32_t)(word >> 40) != g_unread) break;
+        if ((word >> 39) & 1u) continue;
+        const size_t at = find(x.shape);
+        if (at < g_shapes.size()) {
+            g_shapes[at].entries = (int64_t)(word & 0xffffffffu);
+            continue;
+        }
+        if (g_shapes.size() == kShapes) g_shapes.erase(g_shapes.begin());
+        g_shapes.push_back({x.shape, (int64_t)(word & 0xffffffffu)});
+    }
+    g_slot_builds[ticket % kReportSlots] = {shape, ticket};
+    const size_t at = find(shape);
+    return at < g_shapes.size() ? g_shapes[at].entries : -1;
+}
+
 // The counters of a key-list build: device memory, one 256-byte slot per build in flight (chosen by the
 // ticket, like the report word), zero whenever no build owns it: the kernel's last workgroup clears the slot
 // before it reports, so a build needs no clearing launch of its own.  Never freed.
@@ -1886,6 +1937,7 @@ static hdt_status_t build_one(const int32_t *d_level, const int32_t *d_parent, i
     L->pending = false;
     L->build_status = HDT_OK;
     L->entries_needed = 0;
+    L->entries_like = -1;
     L->build_error[0] = 0;
     L->report = L->report_dev = nullptr;
     L->ticket = L->ticket_before = 0;
@@ -2013,6 +2065,7 @@ static hdt_status_t build_one(const int32_t *d_level, const int32_t *d_parent, i
                                q.c_cnt, p.level_copy, p.parent_copy, q.q_sub, q.bits_rm,
                                slot_counters ? slot_counters : p.counters, report, p.report_copy, ticket,
                                slot_counters != nullptr};
+                L->entries_like = entries_of_one_like(ticket, {batch, n, bm, bn, edges});
                 if (both) {
                     both->args[both->n++] = ka;
                     if (both->n == 2) BUILD_TRY(launch_key_lists(both->args, 2, B, st));

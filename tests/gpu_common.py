@@ -48,6 +48,19 @@ class GuardedWorkspace:
         assert bool((tail == 0x5A).all()), "the call wrote behind the workspace it was given"
 
 
+def busy():
+    """Some tens of milliseconds of work on the current stream; an event behind it.  What a test enqueues next runs after it:
+    as long as the event has not come, the host knows nothing that those kernels report."""
+    import torch
+    a = torch.randn((4096, 4096), device="cuda")
+    torch.cuda.synchronize()
+    for _ in range(80):
+        a = a @ a * 1e-3
+    done = torch.cuda.Event()
+    done.record()
+    return done
+
+
 def make_inputs(B, H, N, D, seed, dtype, n_tensors=3):
     """Seeded N(0,1) tensors; for bf16 they are rounded first so that both sides see the same values."""
     xs = inputs.make_qkv(B, H, N, D, seed, n_tensors)

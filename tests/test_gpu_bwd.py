@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2407_08330_amd import inputs
-from gpu_common import GuardedWorkspace, from_dev, make_inputs, say, to_dev_i32
+from gpu_common import GuardedWorkspace, busy, from_dev, make_inputs, say, to_dev_i32
 
 pytestmark = pytest.mark.gpu
 
@@ -208,35 +208,57 @@ def test_bwd_dense_baseline_layout(oracle, dtype, D, tile):
 
 
 @BOTH_TILES
-@pytest.mark.parametrize("n", [65, 700])
+@pytest.mark.parametrize("n", [347, 709])   # lengths that no other test builds
 def test_bwd_is_the_same_whether_a_pass_of_its_own_computes_d_or_the_roles_do(tile, n):
-    """Long lists that the host knows of get a D pass; a deferred build whose report is not in when the backward is called is
-    taken for a document, and the roles compute D.  Same sums in the same order: the results agree bit for bit."""
+    """Long lists get a D pass, with short ones the roles compute D.  A deferred build whose report is not in when the backward
+    is called has lists as the last build of the same shape that has reported, and without one long lists.  Same sums in the same
+    order: the results agree bit for bit, whichever it is."""
     import torch
     import paper_2407_08330_amd as hdt
     level, parent = np.ones((2, n), np.int32), np.zeros((2, n), np.int32)   # a root and its children: every row sees every key
     level[:, 0], parent[:, 0] = 0, -1
     level[1, n - 9:], parent[1, n - 9:] = -1, -1
-    lv, pr = to_dev_i32(level), to_dev_i32(parent)
+    long_ids = to_dev_i32(level), to_dev_i32(parent)
+    short_ids = to_dev_i32(np.zeros_like(level)), to_dev_i32(np.full_like(parent, -1))   # roots: every row sees itself
     g = torch.Generator(device="cuda")
     g.manual_seed(n)
     q, k, v, d_o = (torch.randn((2, 3, n, 64), device="cuda", generator=g).to(torch.bfloat16) for _ in range(4))
-    known = hdt.hdt_build_layout(lv, pr, tile_m=tile[0], tile_n=tile[1])
+
+    def build(ids, **kw):
+        return hdt.hdt_build_layout(*ids, tile_m=tile[0], tile_n=tile[1], **kw)
+
+    def backward(lay):                  # the gradients, and whether a D pass ran
+        hdt.hdt_timing_enable(True)
+        try:
+            hdt.hdt_timing_reset()
+            grads = hdt.hdt_attn_bwd(lay, q, k, v, o, lse, d_o, 0.125)
+            return grads, lambda: "hdt_bwd_delta_d64" in hdt.hdt_timing_read()
+        finally:
+            hdt.hdt_timing_enable(False)
+
+    def backward_unreported(ids):
+        running = busy()
+        lay = build(ids, deferred=True)
+        grads, d_pass = backward(lay)
+        assert not running.query(), "the build had reported: nothing was tested"
+        torch.cuda.synchronize()
+        lay.destroy()
+        return grads, d_pass()
+
+    o, lse = torch.randn_like(q), torch.zeros((2, 3, n), device="cuda")
+    _, d_pass = backward_unreported(long_ids)
+    assert d_pass                                   # nothing known of this shape
+    known = build(long_ids)
     o, lse = hdt.hdt_attn_fwd(known, q, k, v, 0.125)
-    hdt.hdt_timing_enable(True)
-    hdt.hdt_timing_reset()
-    want = hdt.hdt_attn_bwd(known, q, k, v, o, lse, d_o, 0.125)
-    torch.cuda.synchronize()
-    assert ("hdt_bwd_delta_d64" in hdt.hdt_timing_read()) == (n == 700)
-    a = torch.randn((4096, 4096), device="cuda")
-    torch.cuda.synchronize()
-    hdt.hdt_timing_reset()
-    for _ in range(40):                      # some tens of milliseconds in front of the build
-        a = a @ a * 1e-3
-    lay = hdt.hdt_build_layout(lv, pr, tile_m=tile[0], tile_n=tile[1], deferred=True)
-    got = hdt.hdt_attn_bwd(lay, q, k, v, o, lse, d_o, 0.125)
-    torch.cuda.synchronize()
-    assert "hdt_bwd_delta_d64" not in hdt.hdt_timing_read()
-    hdt.hdt_timing_enable(False)
+    want, d_pass = backward(known)
+    assert d_pass()
+    got, d_pass = backward_unreported(long_ids)
+    assert d_pass                                   # long, as before
+    for x, y in zip(got, want):
+        assert torch.equal(x.view(torch.int16), y.view(torch.int16))
+    _, d_pass = backward(build(short_ids))
+    assert not d_pass()
+    got, d_pass = backward_unreported(long_ids)
+    assert not d_pass                               # taken for short ones
     for x, y in zip(got, want):
         assert torch.equal(x.view(torch.int16), y.view(torch.int16))
