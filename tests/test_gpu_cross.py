@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2407_08330_amd import inputs
-from gpu_common import GuardedWorkspace, from_dev, say, to_dev_bf16, to_dev_i32
+from gpu_common import GuardedWorkspace, busy, from_dev, say, to_dev_bf16, to_dev_i32
 
 pytestmark = pytest.mark.gpu
 
@@ -242,9 +242,10 @@ def test_cross_attention_ignores_what_invisible_rows_hold(oracle, dtype):
 @pytest.mark.parametrize("n_enc", [3, 4, 1000, 2000])
 @pytest.mark.parametrize("level_mask", [SEC, SEC | SENT | TOK, 1 << 7], ids=["sec", "tokens", "nothing"])
 def test_cross_build_waits_for_nothing(n_enc, level_mask):
-    """Build, forward and backward enqueued behind tens of milliseconds of other work, so that the calls find the number of
-    visible positions unknown: the same results, bit for bit, as with a layout whose count has been read (few positions visible
-    and a schedule over those alone, many, none; lengths with room for such a schedule and without)."""
+    """Build, forward and backward enqueued behind tens of milliseconds of other work: the build and a forward without a workspace
+    come back while that still runs, and whichever call is the first to depend on the number of visible positions, the results
+    are the same, bit for bit, as with a layout whose count has been read (few positions visible and a schedule over those alone,
+    many, none; lengths with room for such a schedule and without)."""
     import torch
     import paper_2407_08330_amd as hdt
     B, H, n_dec, D = 2, 3, 70, 64
@@ -260,19 +261,30 @@ def test_cross_build_waits_for_nothing(n_enc, level_mask):
     rows = lay.info()["compact_rows"]
     visible = int((((level >= 0) & ((level_mask >> np.maximum(level, 0)) & 1 == 1)).sum(axis=1)).max())
     assert (rows > 0) == (0 < visible and 4 * visible <= n_enc)
+    room = [hdt.hdt_attn_fwd_workspace_bytes(lay, H, D, 0), hdt.hdt_attn_bwd_workspace_bytes(lay, H, D, 0)]
+    assert (room[0] > 0) == (n_enc >= 1000 and level_mask == SEC | SENT | TOK)     # lists of 16 entries and more are cut
+    ws = torch.empty(max(room[0], 1 << 20), dtype=torch.uint8, device="cuda")
     o, lse = hdt.hdt_attn_fwd(lay, q, k, v, 0.125)
-    want = [o, lse, *hdt.hdt_attn_bwd(lay, q, k, v, o, lse, d_o, 0.125)]
-    a = torch.randn((4096, 4096), device="cuda")
-    torch.cuda.synchronize()
-    for _ in range(40):
-        a = a @ a * 1e-3
-    late = hdt.hdt_build_cross_layout(lv, n_dec, level_mask)
-    o2, lse2 = hdt.hdt_attn_fwd(late, q, k, v, 0.125)
-    got = [o2, lse2, *hdt.hdt_attn_bwd(late, q, k, v, o2, lse2, d_o, 0.125)]
-    late.destroy()
-    torch.cuda.synchronize()
-    for x, y in zip(got, want):
-        assert torch.equal(x.view(torch.int16), y.view(torch.int16))
+    want = [o, lse, *hdt.hdt_attn_fwd(lay, q, k, v, 0.125, workspace=ws), *hdt.hdt_attn_bwd(lay, q, k, v, o, lse, d_o, 0.125)]
+    for first in ("backward", "forward with a workspace", "forward's query", "backward's query", "status"):
+        running = busy()
+        late = hdt.hdt_build_cross_layout(lv, n_dec, level_mask)
+        got = [*hdt.hdt_attn_fwd(late, q, k, v, 0.125)]
+        assert not running.query(), "the build or the forward waited for its number of visible positions"
+        grads = hdt.hdt_attn_bwd(late, q, k, v, *got, d_o, 0.125) if first == "backward" else None
+        if first == "forward's query":
+            assert hdt.hdt_attn_fwd_workspace_bytes(late, H, D, 0) == room[0]
+        if first == "backward's query":
+            assert hdt.hdt_attn_bwd_workspace_bytes(late, H, D, 0) == room[1]
+        if first == "status":
+            assert late.status() == 0
+        got += hdt.hdt_attn_fwd(late, q, k, v, 0.125, workspace=ws)
+        assert running.query(), "the first call that depends on it had not waited"
+        got += grads or hdt.hdt_attn_bwd(late, q, k, v, got[0], got[1], d_o, 0.125)
+        late.destroy()
+        torch.cuda.synchronize()
+        for x, y in zip(got, want):
+            assert torch.equal(x.view(torch.int16), y.view(torch.int16))
 
 
 @pytest.mark.parametrize("tile,n_enc,n_dec,every,heads", [
