@@ -372,6 +372,36 @@ def test_cross_calls_captured_on_a_layout_that_many_builds_have_followed():
                 assert torch.equal(x.view(torch.int16), y.view(torch.int16))
 
 
+def test_cross_builds_in_flight_by_the_hundreds_keep_their_reports_apart():
+    """More builds than report words are made at a time, none of which has run when the last one is enqueued, some destroyed before
+    that, on two streams: every layout gets its own number of visible positions, and so do those that take the words next."""
+    import torch
+    import paper_2407_08330_amd as hdt
+    n_enc = 1024
+    level = np.full((600, 1, n_enc), 3, np.int32)
+    for i in range(600):
+        level[i, 0, :1 + i % 250] = 1
+    lv = to_dev_i32(level.reshape(600, n_enc)).view(600, 1, n_enc)
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(2):
+        running = busy()
+        other.wait_event(running)
+        lays = []
+        for i in range(600):
+            lay = hdt.hdt_build_cross_layout(lv[i], 64, SEC, stream=other if i % 3 == 1 else None)
+            lays.append(None if i % 3 == 2 else lay)     # (a third of them is destroyed here)
+            del lay
+        assert not running.query(), "the builds had reported: nothing was tested"
+        for i, lay in enumerate(lays):
+            if lay is not None:
+                assert lay.status() == 0
+        for i, lay in enumerate(lays):
+            if lay is not None:
+                assert lay.info()["compact_rows"] == (1 + i % 250 + 31) // 32 * 32
+                lay.destroy()
+
+
 def test_cross_layouts_of_a_decoder_stay_in_the_buffer_cache():
     """Four layouts at a time, built and destroyed step by step (a decoder with several settings of what it sees): the cache
     holds the buffers of all four, and none goes back to the system, which would wait for the device."""
