@@ -41,9 +41,10 @@ struct BwdCfg {
     // waves per SIMD (register budget) of the kernel.  Three waves at head size
     // 64 pay on 128 x 64 tiles only (measured, config 4: 107 us against 122 with two; on 64 x 32 tiles 101
     // against 99 with two, whose allocation the compiler then leaves unconstrained).
-    // The INDEXED form on 128 x 64 tiles is compiled for one wave less: bounded to the third (second) it would spill a
-    // few registers, which the counted waits do not allow.  It gets two per SIMD (178 registers at head size 64, 247 at
-    // 128); at head size 128 with the split roles only, see launch_bwd.
+    // The INDEXED form on 128 x 64 tiles is compiled for one wave less.  Bounded to the third, it spills 8 registers at head
+    // size 64 where D comes from a pass, and takes longer (three waves - two, 1024 x 4096 x 16 heads 35.9 - 31.3 us, 2048 x
+    // 8192 x 48 79.8 - 71.3); where the roles compute D it makes no difference (512 x 8192 x 48 24.1 - 24.0).  It gets two per
+    // SIMD (175 registers at head size 64, 247 at 128); at head size 128 with the split roles only, see launch_bwd.
     template <typename G, bool INDEXED>
     static constexpr int WAVES = G::BM == 128 ? (D == 64 ? 3 : 2) - (INDEXED ? 1 : 0) : 2;
 };
@@ -306,8 +307,7 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
         pipe.aux0 = reinterpret_cast<const float *>(row_scalars + (size_t)bh * s.n_kv) + 1;  // -LSE / scale of a position
         pipe.aux1 = reinterpret_cast<const float *>(row_scalars + (size_t)bh * s.n_kv);      // -D
     }
-    const RowLane rl = row_lane<P::CPR>(lane);
-    const TrLane tl = tr_lane<P::CPR>(lane);
+    const RowLane own_rl = row_lane<P::CPR>(lane);
     // is this lane's own row a real position?  (Requested first, looked at once the rows are in registers.)
     // (An unconditional load: inside a branch the compiler would wait for it on the spot.  Without flags any
     // readable word will do, its value is not used.)
@@ -331,8 +331,8 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
     bf16x8 kf[KSTEPS], vf[KSTEPS];
 #pragma unroll
     for (int st = 0; st < KSTEPS; st++) {
-        kf[st] = read_row<ROWB>(smem + STG_K, rl, wave * 32, st);
-        if (DO_DK) vf[st] = read_row<ROWB>(smem + STG_V, rl, wave * 32, st);
+        kf[st] = read_row<ROWB>(smem + STG_K, own_rl, wave * 32, st);
+        if (DO_DK) vf[st] = read_row<ROWB>(smem + STG_V, own_rl, wave * 32, st);
     }
     // A row that is no real position (a pad, an encoder position the decoder does not see) is masked by the
     // bitmap, but its K and V may hold anything, NaN included, which a zero weight would not remove: it takes
@@ -600,13 +600,6 @@ static void launch_kernel(const HdtSchedule &s, const HdtSchedule &s_tr, const _
                        (__bf16 *)dq, (__bf16 *)dk, (__bf16 *)dv, scale, 1.f / scale, g);
 }
 
-// At head size 128 one role for dK and dV is less work than two (the scores are computed twice instead of three times,
-// and the rows gathered), two are the shorter chain.  Two as long as their workgroups, two waves per SIMD, are all on the
-// chip at the same time; measured, one role / two: 32768 positions x 16 heads 230 / 261 us (64 x 32 tiles) and 264 / 307
-// (128 x 64); 3000 x 16 (2 samples x 8 heads) 33.4 / 33.2 and 37.1 / 37.0; 1000 x 4 heads 16.9 / 14.3.
-// Always two where the rows are indexed and the tiles 128 x 64: one role takes 307 registers there, a single wave per SIMD
-// (whole backward, one role / two: 512 x 8192 x 48 heads, 500 positions visible, 68.9 / 61.3 us, 750 81.3 / 68.6, 2000
-// 185 / 130; 2048 x 8192 x 64 heads, 2000 visible, 716 / 540).  On 64 x 32 tiles it keeps two.
 // Whether the roles compute D themselves (head size 64), from what the host knows.  What that saves is a launch (about 2 us in
 // a graph, 4 outside) and a pass over O and dO; what it costs is D of a query once per list entry that names it, and a barrier
 // and a third more rows per entry.  So it pays for short lists.  Either way D is the same to the last bit, so the choice shows
@@ -638,6 +631,13 @@ static bool roles_compute_d(const HdtSchedule &s_tr, int heads, HdtLists lists)
     return list <= 8 && pairs <= (SMALL ? 8000 : 5000) && pairs * list <= 8 * (SMALL ? 3100 : 2100);
 }
 
+// At head size 128 one role for dK and dV is less work than two (the scores are computed twice instead of three times,
+// and the rows gathered), two are the shorter chain.  Two as long as their workgroups, two waves per SIMD, are all on the
+// chip at the same time; measured, one role / two: 32768 positions x 16 heads 230 / 261 us (64 x 32 tiles) and 264 / 307
+// (128 x 64); 3000 x 16 (2 samples x 8 heads) 33.4 / 33.2 and 37.1 / 37.0; 1000 x 4 heads 16.9 / 14.3.
+// Always two where the rows are indexed and the tiles 128 x 64: one role takes 307 registers there, a single wave per SIMD
+// (whole backward, one role / two: 512 x 8192 x 48 heads, 500 positions visible, 68.9 / 61.3 us, 750 81.3 / 68.6, 2000
+// 185 / 130; 2048 x 8192 x 64 heads, 2000 visible, 716 / 540).  On 64 x 32 tiles it keeps two.
 template <int D, typename G, bool INDEXED>
 static void launch_bwd(const HdtSchedule &s, const HdtSchedule &s_tr, const __bf16 *Q, const __bf16 *K, const __bf16 *V,
                        const __bf16 *O, const float *lse, const __bf16 *DO, void *dq, void *dk, void *dv, int heads,

@@ -18,10 +18,10 @@
 // rank among them).  Whether they are, the device finds out: the entry kernel makes that schedule or leaves it, in arrays
 // that hold a quarter of the encoder's positions, and the host reads the count when a call depends on it, so the build
 // waits for nothing (512 x 8192, anchors visible, build, forward and backward: 56.3 -> 43.4 us; a wait for the count and a
-// launch for that schedule before).  The dK/dV role of hdt_attn_bwd then reads its K and V rows and writes its dK and dV rows through the list of visible positions,
-// and further workgroups of the same launch write the zeros of the rows that are not visible (512 x 8192, [SEC] and
-// [SENT] visible: one launch of 24 us where gathering compact copies, the roles and scattering the results took
-// 5 + 21 + 24).
+// launch for that schedule before).  The dK/dV role of hdt_attn_bwd then reads its K and V rows and writes its dK and dV
+// rows through the list of visible positions, and further workgroups of the same launch write the zeros of the rows that
+// are not visible (512 x 8192, [SEC] and [SENT] visible: one launch of 24 us where gathering compact copies, the roles and
+// scattering the results took 5 + 21 + 24).
 //
 // With the regular tokens visible the opposite happens: a handful of decoder row tiles each walk a key list of
 // more than a hundred entries one after the other, on a few workgroups.  The list of a row tile is the same for

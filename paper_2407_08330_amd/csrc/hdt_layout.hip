@@ -499,8 +499,9 @@ __device__ __forceinline__ EntryPart entry_bitmaps(bool active, int64_t c, int w
 // positions: a list of them that one wave makes, one by one, and every key is compared with was the longest phase of
 // such builds.  Event-bracketed us, with such a list and a sort that takes the levels one by one - as it is: 16
 // ListOps-shaped trees of 1536 positions, 64 x 32 tiles, 16.2 - 10.7, 128 x 64 19.4 - 10.4, both schedules of a directed mask
-// 17.2 - 11.8 and 20.5 - 11.2; documents of 1000 positions 10.2 - 9.7, of 8192 the same.)  The key itself and the key's own
-// parent are single rows.  The lane masks of the MFMA kernels need no transposition from there: mask e of sub-block
+// 17.2 - 11.8 and 20.5 - 11.2; documents of 1000 positions 10.2 - 9.7, of 8192 the same; lists of 500 keys of two or three
+// parents, 64 x 32 tiles, 4 samples of 4500 11.1 - 11.5, of 16384 28.0 - 28.7.)  The key itself and the key's own parent
+// are single rows.  The lane masks of the MFMA kernels need no transposition from there: mask e of sub-block
 // (rblk, cblk) is the column word of key 32*cblk + 8*(e/4) + e%4 (lanes 0..31) next to that of key
 // 32*cblk + 4 + 8*(e/4) + e%4 (lanes 32..63), so every lane stores its own words.
 struct ParentTable {
@@ -641,9 +642,9 @@ constexpr int kLdsKeys = 2048;  // key lists up to this length stay in LDS betwe
 // 512 threads for documents whose scan is a single batch of their 8 waves, 4096 positions: a barrier is shorter, and two or
 // three workgroups share a compute unit where one of 1024 fills it.  Event-bracketed us, 1024 - 512 threads: sections,
 // 64 x 32 tiles, 1 sample of 1000 positions 11.8 - 11.0, 16 of 1536 12.3 - 11.6, 8 of 4096 13.0 - 12.4, 32 of 2048 20.7 - 15.8;
-// 128 x 64 the same or a little more; two schedules of ListOps-shaped trees, 16 of 1536, 21.5 - 17.2 (both before the parents were hashed); but 4 of 8192
-// 13.1 - 15.5, 1 of 32768 20.8 - 23.8.  (256: 12.5, 13.1, 17.1 and 16.6 in the first four.)  Longer documents get 1024, with
-// T = 1 and tiles of up to 64 rows, which make twice the workgroups, 512.
+// 128 x 64 the same or a little more; two schedules of ListOps-shaped trees, 16 of 1536, 21.5 - 17.2 (before the parents were
+// hashed, all of them); but 4 of 8192 13.1 - 15.5, 1 of 32768 20.8 - 23.8.  (256: 12.5, 13.1, 17.1 and 16.6 in the first
+// four.)  Longer documents get 1024, with T = 1 and tiles of up to 64 rows, which make twice the workgroups, 512.
 __host__ __device__ inline int list_words(int n) { return (((n + 31) >> 5) + 4) & ~3; }  // of `pars`, per tile: a zero word behind
 __host__ inline size_t list_lds(int n, int tiles)
 {

@@ -16,8 +16,9 @@
 // The key positions of an entry are read the same way, one tile further ahead than the rows they
 // address, and the entries' summaries with scalar loads, so no iteration waits on a chain of dependent
 // loads.
-// The only vector-memory instructions inside the loop are those issued here with inline asm, which
-// is what makes the hand-counted s_waitcnt vmcnt(N) exact.
+// The vector-memory instructions inside the loop are those issued here with inline asm, which the compiler does not
+// count: the waits for them stand here too.  With two stages an iteration waits for all of them; in front of the loop the
+// first entry's positions are waited for with the second entry's in flight (a load more would make that wait longer, not wrong).
 //
 // A wave of the backward on 64 x 32 tiles works on 4 to 5 entries, so what stands around its loop counts as much as the
 // loop: counters put 540 of 980 vector instructions and 500 of 600 scalar ones there, with a vector instruction in
@@ -83,7 +84,7 @@ __host__ __device__ __forceinline__ unsigned padded_grid(unsigned n_items, unsig
 {
     return (n_items + 8u * chunk - 1u) / (8u * chunk) * (8u * chunk);
 }
-// Division by a divisor the host knows, of numbers below 2^31: three scalar instructions where the compiler's own takes
+// Division by a divisor the host knows, by the multiplication of Granlund and Montgomery (PLDI 1994), of numbers below 2^31: three scalar instructions where the compiler's own takes
 // about 25, vector ones and a reciprocal among them.  With l = ceil(log2 d) and mul = ceil(2^(31 + l) / d) (at most 2^32 - 1),
 // n * mul = (2^(31 + l) n + e n) / d with e < d <= 2^l, so the error e n / d stays below 2^(31 + l) / d and the quotient is exact.
 struct FastDiv {
