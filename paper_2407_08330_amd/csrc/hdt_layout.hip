@@ -1438,8 +1438,10 @@ int64_t entries_of_one_like(uint32_t ticket, const BuildShape &shape)
         while (i < g_shapes.size() && !(g_shapes[i].shape == what)) i++;
         return i;
     };
-    if (((ticket - g_unread) & 0xffffffu) >= (uint32_t)kReportSlots) g_unread = (ticket - kReportSlots + 1) & 0xffffffu;
-    for (; g_unread != ticket; g_unread = (g_unread + 1) & 0xffffffu) {
+    // (a build of another thread with a later ticket may have been here before: then there is nothing to read)
+    const uint32_t ahead = (ticket - g_unread) & 0xffffffu, until = ahead < 0x800000u ? ticket : g_unread;
+    if (until == ticket && ahead >= (uint32_t)kReportSlots) g_unread = (ticket - kReportSlots + 1) & 0xffffffu;
+    for (; g_unread != until; g_unread = (g_unread + 1) & 0xffffffu) {
         const SlotBuild &x = g_slot_builds[g_unread % kReportSlots];
         if (g_unread == 0 || x.ticket != g_unread) continue;  // a build of another kind
         const unsigned long long word = __atomic_load_n(g_reports + (size_t)(g_unread % kReportSlots) * 8, __ATOMIC_ACQUIRE);
