@@ -287,7 +287,7 @@ __device__ __forceinline__ void dkv_role(char *smem, const HdtSchedule &s, const
     if (INDEXED && I * BM >= n_rows) return;  // the whole workgroup: no visible position in this tile
     const float scale_log2 = scale * LOG2E;
 
-    const size_t row = (size_t)b * s.tr + I;
+    const size_t row = (size_t)b * (INDEXED ? s.own_tiles : s.tr) + I;
     const cptr_i32 range = as_const(s.q_range);
     const int t0 = range[2 * row], n = range[2 * row + 1] - t0;
     const cptr_u32 subs = as_const(s.q_sub) + t0;

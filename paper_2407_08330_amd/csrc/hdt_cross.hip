@@ -15,7 +15,7 @@
 // The dK/dV pass of the backward tiles the ENCODER rows, and with a few anchors visible nearly every 32-row
 // block of them holds one allowed row among 31 idle ones.  When the visible positions are at most a quarter of the
 // encoder's, the build therefore makes a second transposed schedule in the index space of the visible positions (row =
-// rank among them).  Whether they are, the device finds out: the entry kernel makes that schedule or leaves it, in arrays
+// rank among them).  Whether they are, the device finds out: the build makes that schedule or leaves it, in arrays
 // that hold a quarter of the encoder's positions, and the host reads the count when a call depends on it, so the build
 // waits for nothing (512 x 8192, anchors visible, build, forward and backward: 56.3 -> 43.4 us; a wait for the count and a
 // launch for that schedule before).  The dK/dV role of hdt_attn_bwd then reads its K and V rows and writes its dK and dV
@@ -41,7 +41,6 @@
 
 namespace {
 
-constexpr int kSelThreads = 1024;
 constexpr int kSplitEntries = 16;  // lists of this many entries are worth cutting
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -50,94 +49,25 @@ __device__ __forceinline__ bool visible(int level, uint32_t level_mask)
     return level >= 0 && level < 32 && ((level_mask >> level) & 1u);
 }
 
-// One workgroup per sample: the visible positions in document order (sel), every position's rank among them, and
-// their number (count).  A wave takes a contiguous share of the positions, kSelBatch groups of 64 in flight at a time:
-// it counts its visible positions, and once the shares in front of it are known hands out the ranks (8192 positions x 4
-// samples: 5.3 us; one chunk of 1024 positions after the other, three barriers each, took 9.2).  The last workgroup to
-// finish tells the host the largest count.
-constexpr int kSelBatch = 8;
-__global__ __launch_bounds__(kSelThreads) void k_cross_select(const int32_t *__restrict__ level, int n_enc,
-                                                               uint32_t level_mask, int32_t *__restrict__ sel,
-                                                               int32_t *__restrict__ rank, int32_t *__restrict__ count,
-                                                               HdtReport report)
-{
-    constexpr int W = kSelThreads / 64;
-    __shared__ int s_wave[W];
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int32_t *lv = level + (size_t)b * n_enc;
-    int32_t *out = sel + (size_t)b * n_enc, *rk = rank + (size_t)b * n_enc;
-    const int groups = (n_enc + 63) >> 6, share = (groups + W - 1) / W;
-    const int g0 = min(wave * share, groups), g1 = min(g0 + share, groups);
-    unsigned long long seen[kSelBatch];  // of the batch looked at last
-    auto look = [&](int gb) {
-        int l[kSelBatch];
-#pragma unroll
-        for (int u = 0; u < kSelBatch; u++) {
-            const int i = (gb + u) * 64 + lane;
-            l[u] = gb + u < g1 && i < n_enc ? lv[i] : -1;
-        }
-#pragma unroll
-        for (int u = 0; u < kSelBatch; u++) seen[u] = __ballot(visible(l[u], level_mask));
-    };
-    int mine = 0;
-    for (int gb = g0; gb < g1; gb += kSelBatch) {
-        look(gb);
-#pragma unroll
-        for (int u = 0; u < kSelBatch; u++) mine += __popcll(seen[u]);
-    }
-    if (lane == 0) s_wave[wave] = mine;
-    __syncthreads();
-    int at = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < W; w++) {
-        at += w < wave ? s_wave[w] : 0;
-        total += s_wave[w];
-    }
-    for (int gb = g0; gb < g1; gb += kSelBatch) {
-        if (share > kSelBatch) look(gb);  // otherwise the masks are still there
-#pragma unroll
-        for (int u = 0; u < kSelBatch; u++) {
-            const int i = (gb + u) * 64 + lane;
-            const bool vis = (seen[u] >> lane) & 1ull;
-            const int r = at + __popcll(seen[u] & ((1ull << lane) - 1ull));
-            if (vis) out[r] = i;
-            if (gb + u < g1 && i < n_enc) rk[i] = vis ? r : -1;
-            at += __popcll(seen[u]);
-        }
-    }
-    if (tid == 0) {
-        count[b] = total;
-        if (report.word) {
-            // the maximum first, and only when it is in place the arrival (returning atomics: each waits for the one before)
-            const int before = atomicMax(&report.counters[0], total);
-            asm volatile("" ::"v"(before));
-            if (atomicAdd(&report.counters[1], 1) == (int)gridDim.x - 1) {
-                const int most = __hip_atomic_load(&report.counters[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&report.counters[0], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&report.counters[1], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const unsigned long long word = ((unsigned long long)(report.ticket & 0xffffffu) << 40) | (uint32_t)most;
-                __hip_atomic_store(report.word, word, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-            }
-        }
-    }
-}
-
-struct CrossArgs {
-    const int32_t *level;  // [B][n_enc]
-    const int32_t *sel;    // [B][n_enc] visible positions
-    const int32_t *count;  // [B]
-    uint32_t level_mask;
-    int n_enc, n_dec, bm, bn;
-    int transposed;  // 0: rows = decoder positions, keys = visible encoder positions; 1: rows = encoder positions
-                     // (allowed iff visible), keys = decoder positions
-    int compact;     // transposed schedule whose rows are the visible positions by rank
-    int batch;
-    int tr, e_max;   // row tiles per sample (compact: as many as its rows take), list entries reserved per row tile
-    int entries;     // reserved entries: workgroups this schedule takes
+// One of the schedules of a layout: 0 rows = decoder positions, keys = visible encoder positions; 1 rows = encoder positions
+// (allowed iff visible), keys = decoder positions; 2 the same with rows = visible positions by rank.
+struct CrossSide {
+    int tr, e_max;  // row tiles per sample (2: room for as many), list entries reserved per row tile
     int32_t *q_range, *c_row, *c_cnt, *q_keys;
     uint32_t *q_sub;
     unsigned long long *bits_rm;
+};
+struct CrossArgs {
+    const int32_t *level;  // [B][n_enc]
+    uint32_t level_mask;
+    int batch, n_enc, n_dec, bm, bn;
+    int shares;            // workgroups per sample
+    int32_t *sel;          // [B][n_enc] visible positions in document order
+    int32_t *rank;         // [B][n_enc] every position's rank among them, or -1
+    int32_t *count;        // [B]
+    CrossSide side[3];
     int32_t *split_range[3];  // forward schedule: entry ranges with the lists cut, see below; NULL: no list can be long
+    HdtReport report;
 };
 
 // rows per sample of the compact schedule for c_max visible positions, 0: there is none
@@ -146,112 +76,230 @@ __host__ __device__ __forceinline__ int compact_rows(int c_max, int n_enc)
     return c_max > 0 && (long long)c_max * 4 <= n_enc ? (c_max + 31) / 32 * 32 : 0;
 }
 
-// One wave per reserved list entry (b, I, e): its keys, bitmaps and summary, or the "empty" marks.  All schedules of a
-// layout in one launch (a launch costs about what its entries do).  The first entry of a forward row tile also writes the
-// tile's entry ranges with every key list cut into 2, 4 and 8 pieces: row tile p * tr + I of sample b gets entries
-// [p * chunk, (p + 1) * chunk) of the list of tile (b, I), chunk = ceil(entries / pieces).
-__global__ __launch_bounds__(64) void k_cross_entries(CrossArgs a0, CrossArgs a1, CrossArgs a2)
+// the lowest n bits (none for n <= 0, all for n >= 32)
+__device__ __forceinline__ uint32_t low_bits(int n) { return n >= 32 ? 0xffffffffu : (n <= 0 ? 0u : (1u << n) - 1u); }
+
+// position of the k-th set bit (k counts from 0; there is one)
+__device__ __forceinline__ int select_bit(unsigned long long m, int k)
 {
-    __shared__ uint32_t s_row[4], s_col[4];  // allowed rows / filled key slots of the entry, bit masks
-    const int lane = threadIdx.x;
-    const int x1 = (int)blockIdx.x - a0.entries, x2 = x1 - a1.entries;
-    const CrossArgs &a = x1 < 0 ? a0 : (x2 < 0 ? a1 : a2);
-    const int64_t entry = x1 < 0 ? (int)blockIdx.x : (x2 < 0 ? x1 : x2);
-    int n_rows = a.transposed ? a.n_enc : a.n_dec, tr = a.tr;
-    if (a.compact) {
-        int c_max = 0;
-        for (int i = lane; i < a.batch; i += 64) c_max = max(c_max, a.count[i]);
+    int at = 0;
 #pragma unroll
-        for (int d = 32; d > 0; d >>= 1) c_max = max(c_max, __shfl_xor(c_max, d));
-        n_rows = compact_rows(c_max, a.n_enc);
-        tr = (n_rows + a.bm - 1) / a.bm;
-        if (entry >= (int64_t)a.batch * tr * a.e_max) return;  // reserved for more rows; all of them, if there is no such schedule
-    }
-    const int e = (int)entry % a.e_max, tile = (int)entry / a.e_max;  // tile = b * tr + I
-    const int b = tile / tr, I = tile % tr;
-    const int n_keys = a.transposed ? a.n_dec : a.count[b];
-    // rows of the tile
-    bool any_row = false;
-    for (int h = 0; h < 2; h++) {
-        const int r = h * 64 + lane, i = I * a.bm + r;
-        bool ok = r < a.bm && i < n_rows;
-        if (ok && a.transposed) ok = a.compact ? i < a.count[b] : visible(a.level[(size_t)b * a.n_enc + i], a.level_mask);
-        const unsigned long long m = __ballot(ok);
-        if (lane == 0) {
-            s_row[2 * h] = (uint32_t)m;
-            s_row[2 * h + 1] = (uint32_t)(m >> 32);
+    for (int half = 32; half > 0; half >>= 1) {
+        const int low = __popcll((m >> at) & ((1ull << half) - 1ull));
+        if (k >= low) {
+            k -= low;
+            at += half;
         }
-        any_row |= m != 0ull;
     }
-    const int n_ent = (a.transposed && !any_row) ? 0 : (n_keys + a.bn - 1) / a.bn;
-    if (e == 0 && lane == 0) {
-        a.q_range[2 * tile] = (int32_t)entry;
-        a.q_range[2 * tile + 1] = (int32_t)entry + n_ent;
-    }
-    if (e == 0 && a.split_range[0]) {
+    return at;
+}
+
+// The list entries of a sample, written a wave each.
+struct CrossEntries {
+    const unsigned long long *seen;  // [groups] the sample's visible positions, in LDS
+    const int *before;               // [groups] visible positions in front of every group of 64, in LDS
+    int groups, count;               // count: visible positions of the sample
+    int b, lane;
+
+    // the entries x, x + step, ... of side K, whose first one is number `first`; returns where that ended
+    template <int K>
+    __device__ __forceinline__ int write(const CrossArgs &a, int x, int step, int first) const
+    {
+        const CrossSide s = a.side[K];
+        const int bm = a.bm, bn = a.bn, wpr = bn >> 5, nrb = bm >> 5, nsub = nrb * wpr, div_wpr = 65536 / wpr + 1;  // (of numbers below 16)
+        const int n_keys = K == 0 ? count : a.n_dec, last = first + s.tr * s.e_max;
+        for (; x < last; x += step) {
+            const int I = (x - first) / s.e_max, e = x - first - I * s.e_max;
+            const int64_t tile = (int64_t)b * s.tr + I, entry = tile * s.e_max + e;
+            // allowed rows of the tile, 32 at a time
+            uint32_t rows[4], any_row = 0u;
 #pragma unroll
-        for (int k = 0; k < 3; k++) {
-            const int pieces = 2 << k, chunk = (n_ent + pieces - 1) / pieces;
-            if (lane < pieces) {
-                const int first = min(lane * chunk, n_ent), last = min(first + chunk, n_ent);
-                int32_t *out = a.split_range[k] + 2 * ((size_t)(b * pieces + lane) * tr + I);
-                out[0] = (int32_t)entry + first;
-                out[1] = (int32_t)entry + last;
+            for (int h = 0; h < 4; h++) {
+                const int r0 = I * bm + h * 32;
+                const uint32_t m = K == 1 ? reinterpret_cast<const uint32_t *>(seen)[min(r0 >> 5, 2 * groups - 1)]
+                                          : low_bits((K == 0 ? a.n_dec : count) - r0);
+                rows[h] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(h < nrb && (K != 1 || r0 < 64 * groups) ? m : 0u));
+                any_row |= rows[h];
+            }
+            const int n_ent = K > 0 && any_row == 0u ? 0 : (n_keys + bn - 1) / bn;
+            if (e == 0) {
+                if (lane < 2) s.q_range[2 * tile + lane] = (int32_t)entry + (lane ? n_ent : 0);
+                if (K == 0 && a.split_range[0]) {
+#pragma unroll
+                    for (int c = 0; c < 3; c++) {
+                        const int pieces = 2 << c, chunk = (n_ent + pieces - 1) / pieces;
+                        if (lane < pieces) {
+                            const int from = min(lane * chunk, n_ent), to = min(from + chunk, n_ent);
+                            int32_t *out = a.split_range[c] + 2 * ((size_t)(b * pieces + lane) * s.tr + I);
+                            out[0] = (int32_t)entry + from;
+                            out[1] = (int32_t)entry + to;
+                        }
+                    }
+                }
+            }
+            const int n_cols = e < n_ent ? min(n_keys - e * bn, bn) : 0;  // 0: reserved, not in use
+            uint32_t any = 0u, all = 0u;
+            int n_rows = 0;
+#pragma unroll
+            for (int rblk = 0; rblk < 4; rblk++) {
+                n_rows += __popc(rows[rblk]);
+                if (rows[rblk] != 0u) any |= low_bits((n_cols + 31) >> 5) << (rblk * wpr);
+                if (rows[rblk] == 0xffffffffu) all |= low_bits(n_cols >> 5) << (rblk * wpr);
+            }
+            if (lane == 0) {
+                s.c_row[entry] = (int32_t)tile;
+                s.c_cnt[entry] = n_rows * n_cols;
+                s.q_sub[entry] = any | (all << 16);
+            }
+            if (n_cols == 0) continue;
+            // The group of the entry's first key (K = 0): the last one with no more than its rank in front of it, found 64
+            // groups at a time; and how many groups from there on hold keys of the entry.
+            int g0 = 0, span = 0;
+            if (K == 0) {
+                for (int n = groups; n > 1;) {
+                    const int stride = (n + 63) >> 6, off = lane * stride;
+                    const int c = __popcll(__ballot(off < n && before[min(g0 + off, groups - 1)] <= e * bn));
+                    g0 += (c - 1) * stride;
+                    n = min(stride, n - (c - 1) * stride);
+                }
+                span = __popcll(__ballot(g0 + lane < groups && before[min(g0 + lane, groups - 1)] < e * bn + n_cols));
+            }
+            // key slots; one past the last key holds ~f, f = the entry's first key: the row gathered in its place
+            for (int c = lane; c < bn; c += 64) {
+                const bool ok = c < n_cols;
+                int key = ok ? e * bn + c : e * bn;
+                if (K == 0) {  // the position of that rank
+                    int g = g0;
+                    if (span <= 4) {
+                        for (int u = 1; u < span; u++) g += before[g0 + u] <= key ? 1 : 0;
+                    } else {
+                        for (int hi = groups - 1; g < hi;) {
+                            const int mid = (g + hi + 1) >> 1;
+                            if (before[mid] <= key)
+                                g = mid;
+                            else
+                                hi = mid - 1;
+                        }
+                    }
+                    key = g * 64 + select_bit(seen[g], key - before[g]);
+                }
+                s.q_keys[entry * bn + c] = ok ? key : ~key;
+            }
+            // lane masks of the MFMA accumulator registers: sub-block (rblk, cblk), register r: bit l <=> row
+            // rblk*32 + l%32, column cblk*32 + (l/32)*4 + 8*(r/4) + r%4
+            for (int m = lane; m < nsub * 16; m += 64) {
+                const int sb = m >> 4, r = m & 15, rblk = (sb * div_wpr) >> 16, cblk = sb - rblk * wpr;
+                const uint32_t row = rblk == 0 ? rows[0] : (rblk == 1 ? rows[1] : (rblk == 2 ? rows[2] : rows[3]));
+                const int left = n_cols - cblk * 32 - 8 * (r >> 2) - (r & 3);  // columns from this one on
+                s.bits_rm[((size_t)entry * nsub + sb) * 16 + r] = (unsigned long long)(left > 4 ? row : 0u) << 32 | (left > 0 ? row : 0u);
             }
         }
+        return x;
     }
-    if (lane == 0) a.c_row[entry] = tile;
-    if (e >= n_ent) {  // reserved, not in use
-        if (lane == 0) {
-            a.c_cnt[entry] = 0;
-            a.q_sub[entry] = 0u;
+};
+
+// The whole build in one launch.  Every workgroup goes over its sample's levels by itself (kBuildBatch groups of 64 positions
+// per wave in flight) and keeps a bit per position and the visible positions in front of every group in LDS; from there its
+// waves write its share of sel and rank and take the sample's reserved list entries in turn, one each: keys, bitmaps and
+// summary, or the "empty" marks.  An entry's rows and columns follow from the counts, its keys are found by rank (a binary
+// search over the groups and one inside a group, per key slot).  The first entry of a forward row tile also writes the
+// tile's entry ranges with every key list cut into 2, 4 and 8 pieces: row tile p * tr + I of sample b gets entries
+// [p * chunk, (p + 1) * chunk) of the list of tile (b, I), chunk = ceil(entries / pieces).  A workgroup knows the number of
+// visible positions of its own sample only: the compact schedule's tiles sit at a fixed stride, and are left out where the
+// sample alone has too many.  The last of the samples' first workgroups tells the host the largest count.
+//
+// Bound by latencies: a chain of a load, three barriers and an entry's stores, with a launch around it.  A kernel that
+// selected the positions, a workgroup per sample, and one that wrote the entries behind it took longer at all sizes
+// (us from start to end, both kernels - this one; [SEC] / all tokens visible): 512 x 64 decoder rows, 1 sample 14.2 / 14.8 - 7.2 / 7.0;
+// 8192 x 512, 4 samples 16.2 / 17.4 - 8.5 / 9.1, 16 samples 20.9 / 26.7 - 14.9 / 17.3; 524288 x 512 226 / 255 - 101 / 113; 512 x 512,
+// 1024 samples 71 / 76 - 43 / 46; 8192 x 64, 256 samples 44 / 48 - 28 / 39.  512 x 8192 x 4 x 12 heads, anchors visible, build, forward
+// and backward: 42.9 -> 39.2 us.  Workgroups for half of the compute units' LDS instead of one each (512): 8.5 -> 12.3 at 8192 x
+// 4 samples.  One loop over all sides instead of one per side: 9.1 at 8192 x 4, 60.8 at 8192 x 256, tokens visible.
+constexpr int kBuildThreads = 1024, kBuildBatch = 8;
+__global__ __launch_bounds__(kBuildThreads) void k_cross_build(CrossArgs a)
+{
+    constexpr int W = kBuildThreads / 64;
+    extern __shared__ unsigned long long s_seen[];  // [groups] visible positions of every group of 64, and behind them
+    __shared__ int s_wave[W];
+    const int n_enc = a.n_enc, groups = (n_enc + 63) >> 6;
+    int *s_before = reinterpret_cast<int *>(s_seen + groups);  // [groups] visible positions in front of the group
+    const int b = blockIdx.x / a.shares, w = blockIdx.x % a.shares;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int32_t *lv = a.level + (size_t)b * n_enc;
+    for (int g0 = wave; g0 < groups; g0 += W * kBuildBatch) {
+        int l[kBuildBatch];
+#pragma unroll
+        for (int u = 0; u < kBuildBatch; u++) {
+            const int i = (g0 + u * W) * 64 + lane;
+            l[u] = i < n_enc ? lv[i] : -1;
         }
-        return;
-    }
-    // key slots
-    for (int h = 0; h < 2; h++) {
-        const int c = h * 64 + lane, idx = e * a.bn + c;
-        const bool ok = c < a.bn && idx < n_keys;
-        // a slot past the last key holds ~f, f = the entry's first key: the row gathered in its place
-        const int at = ok ? idx : e * a.bn;
-        const int key = a.transposed ? at : a.sel[(size_t)b * a.n_enc + at];
-        if (c < a.bn) a.q_keys[entry * a.bn + c] = ok ? key : ~key;
-        const unsigned long long m = __ballot(ok);
-        if (lane == 0) {
-            s_col[2 * h] = (uint32_t)m;
-            s_col[2 * h + 1] = (uint32_t)(m >> 32);
+#pragma unroll
+        for (int u = 0; u < kBuildBatch; u++) {
+            const unsigned long long m = __ballot(visible(l[u], a.level_mask));
+            if (lane == 0 && g0 + u * W < groups) s_seen[g0 + u * W] = m;
         }
     }
     __syncthreads();
-    const int wpr = a.bn >> 5, nrb = a.bm >> 5, nsub = nrb * wpr;
-    // lane masks of the MFMA accumulator registers: sub-block (rblk, cblk), register x: bit l <=> row
-    // rblk*32 + l%32, column cblk*32 + (l/32)*4 + 8*(x/4) + x%4
-    for (int w = lane; w < nsub * 16; w += 64) {
-        const int sb = w >> 4, x = w & 15, rblk = sb / wpr, cblk = sb % wpr;
-        const uint32_t rows = s_row[rblk], cols = s_col[cblk];
-        unsigned long long m = 0;
-        for (int h = 0; h < 2; h++) {
-            const int col = h * 4 + 8 * (x >> 2) + (x & 3);
-            if ((cols >> col) & 1u) m |= (unsigned long long)rows << (32 * h);
-        }
-        a.bits_rm[((size_t)entry * nsub + sb) * 16 + x] = m;
+    // visible positions in front of every group: a thread takes `per` consecutive ones
+    const int per = (groups + kBuildThreads - 1) / kBuildThreads, first = min(tid * per, groups), last = min(first + per, groups);
+    int mine = 0;
+    for (int g = first; g < last; g++) mine += __popcll(s_seen[g]);
+    int incl = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(incl, d);
+        if (lane >= d) incl += y;
     }
-    if (lane == 0) {
-        uint32_t any = 0, all = 0;
-        int nr = 0, nc = 0;
-        for (int i = 0; i < 4; i++) {
-            nr += __popc(s_row[i]);
-            nc += __popc(s_col[i]);
-        }
-        for (int rblk = 0; rblk < nrb; rblk++)
-            for (int cblk = 0; cblk < wpr; cblk++) {
-                const int sb = rblk * wpr + cblk;
-                if (s_row[rblk] != 0u && s_col[cblk] != 0u) any |= 1u << sb;
-                if (s_row[rblk] == 0xffffffffu && s_col[cblk] == 0xffffffffu) all |= 1u << sb;
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    int at = incl - mine, count = 0;
+#pragma unroll
+    for (int k = 0; k < W; k++) {
+        at += k < wave ? s_wave[k] : 0;
+        count += s_wave[k];
+    }
+    for (int g = first; g < last; g++) {
+        s_before[g] = at;
+        at += __popcll(s_seen[g]);
+    }
+    count = __builtin_amdgcn_readfirstlane(count);
+    __syncthreads();
+
+    if (w == 0 && tid == kBuildThreads - 64) {  // (a wave that gets the fewest entries)
+        a.count[b] = count;
+        if (a.report.word) {
+            // the maximum first, and only when it is in place the arrival (returning atomics: each waits for the one before)
+            const int before = atomicMax(&a.report.counters[0], count);
+            asm volatile("" ::"v"(before));
+            if (atomicAdd(&a.report.counters[1], 1) == a.batch - 1) {
+                const int most = __hip_atomic_load(&a.report.counters[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&a.report.counters[0], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&a.report.counters[1], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const unsigned long long word = ((unsigned long long)(a.report.ticket & 0xffffffu) << 40) | (uint32_t)most;
+                __hip_atomic_store(a.report.word, word, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
             }
-        a.c_cnt[entry] = nr * nc;
-        a.q_sub[entry] = any | (all << 16);
+        }
     }
+
+    {  // sel and rank of this workgroup's share of the groups
+        const int share = (groups + a.shares - 1) / a.shares, g1 = min((w + 1) * share, groups);
+        int32_t *out = a.sel + (size_t)b * n_enc, *rk = a.rank + (size_t)b * n_enc;
+        for (int g = w * share + wave; g < g1; g += W) {
+            const unsigned long long seen = s_seen[g];
+            const int i = g * 64 + lane, r = s_before[g] + __popcll(seen & ((1ull << lane) - 1ull));
+            const bool vis = (seen >> lane) & 1ull;
+            if (vis) out[r] = i;
+            if (i < n_enc) rk[i] = vis ? r : -1;
+        }
+    }
+
+    // the list entries, side by side
+    int x = wave * a.shares + w;
+    const int step = W * a.shares;
+    const CrossEntries en{s_seen, s_before, groups, count, b, lane};
+    x = en.write<0>(a, x, step, 0);
+    x = en.write<1>(a, x, step, a.side[0].tr * a.side[0].e_max);
+    if (4ll * count <= n_enc) en.write<2>(a, x, step, a.side[0].tr * a.side[0].e_max + a.side[1].tr * a.side[1].e_max);
 }
 
 // O, LSE of row (bh, r) from the partial results of the pieces: o_part [bh][PIECES * rows_pad][D] bf16 (piece p of
@@ -539,6 +587,7 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_cross_l
             Tc->s.own_count = f.count;
             Tc->s.own_rank = f.rank;
             Tc->s.own_stride = n_enc;
+            Tc->s.own_tiles = Tc->s.tr;
         }
         if (!empty) {
             // (a stream that is being captured runs nothing now: no report would come)
@@ -546,30 +595,25 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_cross_l
             reported = hipStreamIsCapturing(st, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone &&
                        hdt_report_open(L->device, &report);
             if (!reported) report = HdtReport{};
-            {
-                HdtTimer tm("hdt_cross_select", st);
-                hipLaunchKernelGGL(k_cross_select, dim3((unsigned)batch), dim3(kSelThreads), 0, st, d_level_enc, n_enc,
-                                   level_mask, f.sel, f.rank, f.count, report);
-            }
-            CrossArgs args[3];
+            CrossArgs args{d_level_enc, level_mask, batch, n_enc, n_dec, bm, bn, 1, f.sel, f.rank, f.count, {}, {}, report};
+            int64_t per_sample = 0;  // list entries
             for (int k = 0; k < 3; k++) {
                 const CrossBuffers &c = all[k].c;
-                const int64_t n = all[k].l ? all[k].n : 0;
-                args[k] = CrossArgs{d_level_enc, f.sel, f.count, level_mask, n_enc, n_dec, bm, bn, k > 0, k == 2, batch,
-                                    all[k].l ? all[k].l->s.tr : 1, k == 0 ? e_fwd : e_tr, (int)n, c.q_range, c.c_row, c.c_cnt,
-                                    c.q_keys, c.q_sub, c.bits_rm, {}};
+                if (!all[k].l) continue;
+                args.side[k] = CrossSide{all[k].l->s.tr, k == 0 ? e_fwd : e_tr, c.q_range, c.c_row, c.c_cnt, c.q_keys, c.q_sub, c.bits_rm};
+                per_sample += all[k].n / batch;
             }
             if (e_fwd >= kSplitEntries)
-                for (int k = 0; k < 3; k++) L->cross_split_range[k] = args[0].split_range[k] = f.split_range[k];
+                for (int k = 0; k < 3; k++) L->cross_split_range[k] = args.split_range[k] = f.split_range[k];
+            // a wave per entry, as far as the workgroups are all on the chip at the same time, one per compute unit
+            constexpr int kWaves = kBuildThreads / 64, kOnChip = 256;
+            args.shares = (int)std::max<int64_t>(1, std::min<int64_t>((per_sample + kWaves - 1) / kWaves, kOnChip / batch));
+            const size_t lds = (size_t)((n_enc + 63) / 64) * (sizeof(unsigned long long) + sizeof(int));
+            if (lds > 60 * 1024)  // with the static array: beyond the 64 KB a launch gets by default
+                CROSS_TRY(hipFuncSetAttribute((const void *)k_cross_build, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
             {
-                HdtTimer tm("hdt_cross_entries", st);
-                if (ent_fwd + ent_tr + ent_c < (1LL << 25)) {
-                    hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)(args[0].entries + args[1].entries + args[2].entries)),
-                                       dim3(64), 0, st, args[0], args[1], args[2]);
-                } else {  // a grid holds less than 2^32 threads
-                    for (const CrossArgs &x : args)
-                        if (x.entries > 0) hipLaunchKernelGGL(k_cross_entries, dim3((unsigned)x.entries), dim3(64), 0, st, x, x, x);
-                }
+                HdtTimer tm("hdt_cross_build", st);
+                hipLaunchKernelGGL(k_cross_build, dim3((unsigned)batch * args.shares), dim3(kBuildThreads), lds, st, args);
             }
             CROSS_TRY(hipGetLastError());
             L->compact_built = Tc;  // owned by L from here on
@@ -612,7 +656,7 @@ void hdt_cross_record(const hdt_layout_t *l, int c_max)
     const int n_c = compact_rows(c_max, l->s.n_kv);
     hdt_layout_t *c = l->compact_built;
     if (n_c == 0 || !c) return;
-    // as the entry kernel has laid it out: for the rows there are, not for those there was room for
+    // the rows there are, not those there was room for (whose tiles keep their places: own_tiles)
     HdtSchedule &s = c->s;
     s.n_pos = s.n_own = n_c;
     s.tr = s.tr_own = (n_c + s.bm - 1) / s.bm;

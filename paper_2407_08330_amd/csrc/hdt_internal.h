@@ -51,9 +51,9 @@ struct HdtSchedule {
     // A schedule over the visible positions of a cross-attention layout (hdt_cross.hip; dK/dV pass only): row r of
     // sample b stands for row own_index[b * own_stride + r] of row-side tensors with own_stride rows per sample, r <
     // own_count[b] (the tiles behind hold nothing), and the rows with own_rank < 0 are the ones no tile writes (zeros).
-    // NULL: rows are rows.
+    // NULL: rows are rows.  q_range has room for own_tiles row tiles per sample, of which tr are in use.
     const int32_t *own_index, *own_count, *own_rank;
-    int32_t own_stride;
+    int32_t own_stride, own_tiles;
 };
 
 // whether row r of list entry t may attend to the key in slot c (plain indexing of bits_rm)

@@ -78,6 +78,37 @@ def test_cross_schedules_bit_exact(oracle, bm, bn, level_mask):
     assert hdt.load_library().hdt_status_string(status) == b"HDT_ERR_UNSUPPORTED"
 
 
+@pytest.mark.parametrize("B,n_enc,n_dec,share", [
+    (1, 63, 1, 0.5), (2, 64, 33, 1.0),           # one group of 64 positions, ragged and whole
+    (1, 4097, 65, 0.9), (2, 4160, 40, 0.02),     # 65 groups: the search for a key's group takes two steps
+    (3, 9001, 130, 0.3),                         # keys of an entry in more than four groups, and in up to four
+    (300, 70, 65, 0.4),                          # a workgroup per sample
+    (1, 340001, 20, 0.004),                      # more LDS than a launch gets by default, groups without a key
+])
+def test_cross_build_of_one_launch_at_its_edges(oracle, B, n_enc, n_dec, share):
+    import paper_2407_08330_amd as hdt
+    level = np.where(np.random.default_rng(n_enc).random((B, n_enc)) < share, 1, 3).astype(np.int32)
+    level[0, -1] = 1                              # the last position is visible
+    lay = hdt.hdt_build_cross_layout(to_dev_i32(level), n_dec, SEC)
+    for b in sorted({0, B // 2, B - 1}):
+        f_ref, t_ref = oracle.cross_schedule(level[b], n_dec, SEC, 128, 64)
+        _compare_schedule(lay, f_ref, b, "forward")
+        _compare_schedule(lay.transposed(), t_ref, b, "transposed")
+
+
+@pytest.mark.parametrize("tile", [(128, 64), (64, 32)])
+def test_cross_backward_of_samples_with_different_counts(oracle, tile):
+    """The schedule over the visible positions has room for a quarter of the encoder's rows per sample; its tiles keep their
+    places whatever the largest sample takes: none, two and up to the quarter visible, and beyond it in one sample.  (Not one: P is
+    1 then and dK zero in the oracle, where run_cross_case takes a row for a hidden one.)"""
+    level = np.full((4, 2000), 3, np.int32)
+    for b, visible in enumerate((0, 2, 129, 300)):
+        level[b, np.random.default_rng(b).choice(2000, visible, replace=False)] = 1
+    run_cross_case(oracle, level, 70, SEC, 2, 64, "bf16", 61, tile=tile, poison_invisible=True)
+    level[3, :501] = 1
+    run_cross_case(oracle, level, 70, SEC, 2, 64, "bf16", 62, tile=tile)
+
+
 def _tensors(B, H, n_dec, n_enc, D, seed, dtype):
     import torch
     rng = np.random.default_rng(seed)
