@@ -594,6 +594,7 @@ struct KeyListArgs {
     unsigned long long *report_dev;  // the layout's own copy of the report
     uint32_t ticket;
     int self_reset;  // the counters are a slot that must be zero again when the build has reported
+    int host_waits;  // the host is waiting for the report
 };
 
 struct KeyListLaunch {
@@ -797,9 +798,29 @@ __device__ __forceinline__ void key_lists(const KeyListArgs &a)
     for (int u = 0; u < kBatch; u++) asm volatile("" : "+v"(klv[u]), "+v"(kp[u]));
     lds_barrier();
     // These tiles' slice of the per-entry arrays: reserved by wave 1 as soon as the length of the lists is known,
-    // used once the lists have been packed.  The last workgroup to reserve knows the final count and tells the
-    // host, which is waiting for exactly this word, while the lists and the bitmaps are still being written (no
-    // device-scope fence: it would write back the whole L2 of this XCD).
+    // used once the lists have been packed.  The last workgroup to reserve knows the final count and reports it
+    // (no device-scope fence: it would write back the whole L2 of this XCD).  Where the host is waiting for exactly this
+    // word, wave 1 looks at its reservation on the spot, and the lists and the bitmaps are made while the host goes on:
+    // the others wait for it at the next barrier, 0.4 us of the kernel, and the host has its word some 2 us earlier.  Otherwise
+    // it is looked at once the lists are sorted.  Us for a build that is waited for and a forward, later - on the spot: 1000
+    // positions x 12 heads 27.2 - 25.9, 4 samples of them 27.7 - 26.4, 8192 x 12 32.7 - 31.7, 32768 x 4 43.1 - 42.1, with 256
+    // workgroups, whose reservations queue, 8192 x 4 x 12 60.2 - 60.0; a build that is not waited for and a forward,
+    // 8192 x 4 x 12, 50.3 - 51.5.
+    auto look_at_reservation = [&](unsigned long long reserved, int n_all) {
+        s_base = reserved_first(reserved);
+        if (is_last(reserved)) {
+            const int err = __hip_atomic_load(&a.counters[CNT_ERR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (a.self_reset) {  // nobody touches the counters after the last reservation: clear them for the next build
+                __hip_atomic_store(&a.counters[CNT_ERR], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(reinterpret_cast<unsigned long long *>(a.counters + CNT_CAND), 0ull, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            }
+            const unsigned long long word = report_word(a.ticket, err, (uint32_t)(s_base + n_all));
+            *a.report_dev = word;
+            __hip_atomic_store(a.report, word, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    };
+    const bool early = a.host_waits != 0;
     unsigned long long reserved;  // (of thread 64; no value elsewhere, so that nothing waits for it before it is looked at)
     if (wave == 1) {
         int entries = 0;
@@ -809,7 +830,13 @@ __device__ __forceinline__ void key_lists(const KeyListArgs &a)
             entries += (t + bn - 1) / bn;
             if (lane == 0) s_total[h] = t;
         }
-        if (lane == 0) reserved = reserve_entries(a.counters, entries);
+        if (lane == 0) {
+            const unsigned long long mine = reserve_entries(a.counters, entries);
+            if (early)
+                look_at_reservation(mine, entries);
+            else
+                reserved = mine;
+        }
     }
     if (wave >= 4 && wave < 4 + T) {  // the needed keys of a tile in front of every group of 64 positions
         const int h = wave - 4;
@@ -927,20 +954,7 @@ __device__ __forceinline__ void key_lists(const KeyListArgs &a)
             }
         }
     }
-    if (tid == 64) {
-        s_base = reserved_first(reserved);
-        if (is_last(reserved)) {
-            const int err = __hip_atomic_load(&a.counters[CNT_ERR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (a.self_reset) {  // nobody touches the counters after the last reservation: clear them for the next build
-                __hip_atomic_store(&a.counters[CNT_ERR], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(reinterpret_cast<unsigned long long *>(a.counters + CNT_CAND), 0ull, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            }
-            const unsigned long long word = report_word(a.ticket, err, (uint32_t)(s_base + n_all));
-            *a.report_dev = word;
-            __hip_atomic_store(a.report, word, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-        }
-    }
+    if (tid == 64 && !early) look_at_reservation(reserved, n_all);
     lds_barrier();
     if (have_row) {  // (not earlier: a store takes 2-3 us to be acknowledged, and a wait for a later load waits for it)
         a.level_copy[(size_t)b * n + my_row] = my_level;
@@ -2067,7 +2081,7 @@ static hdt_status_t build_one(const int32_t *d_level, const int32_t *d_parent, i
                 KeyListArgs ka{d_level, d_parent, n, bm, bn, tr, no_sort, edges, cap, p.q_range, q.c_row, q.q_keys, q.q_kpar,
                                q.c_cnt, p.level_copy, p.parent_copy, q.q_sub, q.bits_rm,
                                slot_counters ? slot_counters : p.counters, report, p.report_copy, ticket,
-                               slot_counters != nullptr};
+                               slot_counters != nullptr, !deferred};
                 L->entries_like = entries_of_one_like(ticket, {batch, n, bm, bn, edges});
                 if (both) {
                     both->args[both->n++] = ka;
