@@ -27,7 +27,7 @@ constexpr int kOrdWaves = kOrdThreads / 64;
 // has to know about the positions in front of its share it finds by reading them, all waves together.  That reads up
 // to `shares` / 2 times the sample's ids (a few hundred KB, out of L2), and takes less time than carrying the state from
 // chunk to chunk in one workgroup per sample, whose chunks follow one another (8192 positions x 4 samples: parents
-// 31 -> 6.7 us, ordinals 20.8 -> 8.2; 32768 positions, 1 sample: 126 -> 11 and 78 -> 18), as long as the workgroups of all
+// 31 -> 6.7 us, ordinals 20.8 -> 8.2, now 6.3; 32768 positions, 1 sample: 126 -> 11 and 78 -> 18), as long as the workgroups of all
 // samples are on the chip at the same time, one per compute unit: further ones only wait, and read more.  8192 positions,
 // us for parents / index vectors, one workgroup per sample - a share per 1024 positions - at most 256 workgroups:
 // 64 samples 31 / 29 - 12 / 22 - 8.6 / 16; 256 samples 32 / 47 - 46 / 80 - 20 / 41; 512 samples 61 / 89 - 91 / 152 - 37 / 63.
@@ -153,7 +153,9 @@ __device__ __forceinline__ bool run_head(int grp, int lane, int *len)
     return head;
 }
 
-__global__ __launch_bounds__(kOrdThreads) void k_sibling_ordinals(const int32_t *__restrict__ level,
+// SPREAD: several shares per sample; otherwise nothing stands in front of a share.
+template <bool SPREAD>
+__global__ __launch_bounds__(kOrdThreads, SPREAD ? 4 : 8) void k_sibling_ordinals(const int32_t *__restrict__ level,
                                                                    const int32_t *__restrict__ parent, int n, int shares,
                                                                    int32_t *__restrict__ ord)  // [B][n]
 {
@@ -166,7 +168,25 @@ __global__ __launch_bounds__(kOrdThreads) void k_sibling_ordinals(const int32_t 
     const HpeShare share = hpe_share(blockIdx.x % shares, n, shares);
     if (share.empty()) return;
     const int window = min(n + 1, kOrdWindow);
+    // The first positions in front of the share, and its own first chunk, are on their way while the counters are cleared, and a
+    // chunk's while the one before it is worked on.  The kernel is bound by such round trips.  What they used to be were loads
+    // under a branch with the use beside them, each waited for before the next went out.  (Us: 8192 x 4 samples in a
+    // front end 8.4 -> 6.3 for this kernel; warm, 32768 x 1 17.9 -> 16.1, 70001 x 1 73 -> 60, 131072 x 16 190 -> 119, 8192 x 512
+    // 63.1 -> 61.7; 2000 x 4 8.70 -> 8.81.)
+    auto load = [&](int i, int &l, int &p) {
+        const int j = min(i, n - 1);
+        l = level[o + j];
+        p = parent[o + j];
+    };
+    auto group_of = [&](int i, int end, int l, int p) { return i < end ? ord_group(l, p, n) : -1; };
+    int front_l[kBack], front_p[kBack], first_l, first_p;
+    if (SPREAD && share.first > 0) {
+#pragma unroll
+        for (int u = 0; u < kBack; u++) load(u * kOrdThreads + tid, front_l[u], front_p[u]);
+    }
+    load(share.first + tid, first_l, first_p);
     if (tid == 0) s_windows = n + 1 > kOrdWindow ? 0u : 1u;
+    for (int t = tid; t < window; t += kOrdThreads) s_count[t] = 0;
     __syncthreads();
     if (n + 1 > kOrdWindow) {
         unsigned mine = 0u;
@@ -177,28 +197,37 @@ __global__ __launch_bounds__(kOrdThreads) void k_sibling_ordinals(const int32_t 
         if (mine) atomicOr(&s_windows, mine);
         __syncthreads();
     }
-    for (unsigned todo = s_windows; todo; todo &= todo - 1u) {
+    const unsigned windows = s_windows;
+    for (unsigned todo = windows; todo; todo &= todo - 1u) {
         const int w0 = (__ffs(todo) - 1) * window;
-        for (int t = tid; t < window; t += kOrdThreads) s_count[t] = 0;
-        __syncthreads();
-        for (int j0 = 0; j0 < share.first; j0 += kBack * kOrdThreads) {
-            int g[kBack];
+        if (todo != windows) {
+            for (int t = tid; t < window; t += kOrdThreads) s_count[t] = 0;
+            __syncthreads();
+        }
+        for (int j0 = 0; SPREAD && j0 < share.first; j0 += kBack * kOrdThreads) {
+            int l[kBack], p[kBack];
 #pragma unroll
             for (int u = 0; u < kBack; u++) {
-                const int j = j0 + u * kOrdThreads + tid;
-                g[u] = -1;
-                if (j < share.first) g[u] = ord_group(level[o + j], parent[o + j], n);
+                l[u] = front_l[u], p[u] = front_p[u];
+                asm volatile("" : "+v"(l[u]), "+v"(p[u]));  // (what is made of them is made here, not in front of the loops)
+            }
+            if (j0 > 0) {
+#pragma unroll
+                for (int u = 0; u < kBack; u++) load(j0 + u * kOrdThreads + tid, l[u], p[u]);
             }
 #pragma unroll
             for (int u = 0; u < kBack; u++) {
+                const int g = group_of(j0 + u * kOrdThreads + tid, share.first, l[u], p[u]);
                 int len;
-                const bool head = run_head(g[u], lane, &len);
-                if (head && g[u] >= w0 && g[u] < w0 + window) atomicAdd(&s_count[g[u] - w0], len);
+                const bool head = run_head(g, lane, &len);
+                if (head && g >= w0 && g < w0 + window) atomicAdd(&s_count[g - w0], len);
             }
         }
+        int next_l = first_l, next_p = first_p;
         for (int c0 = share.first; c0 < share.last; c0 += kOrdThreads) {
             const int i = c0 + tid;
-            const int grp = i < share.last ? ord_group(level[o + i], parent[o + i], n) : -1;
+            const int grp = group_of(i, share.last, next_l, next_p);
+            if (c0 + kOrdThreads < share.last) load(i + kOrdThreads, next_l, next_p);
             int len;
             const bool head = run_head(grp, lane, &len);
             const unsigned long long heads = __ballot(head);
@@ -546,10 +575,11 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_index_vectors
             hipLaunchKernelGGL(k_sibling_ordinals_chain, dim3((unsigned)batch), dim3(kOrdThreads), 0, st, d_level, d_parent, n_pos,
                                cnt, ord);
         } else {
+            const auto kernel = shares > 1 ? k_sibling_ordinals<true> : k_sibling_ordinals<false>;
             if (lds > 48 * 1024)  // with the static arrays: beyond the 64 KB a launch gets by default
-                HDT_HIP_TRY(hipFuncSetAttribute((const void *)k_sibling_ordinals, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-            hipLaunchKernelGGL(k_sibling_ordinals, dim3((unsigned)batch * shares), dim3(kOrdThreads), lds, st, d_level, d_parent,
-                               n_pos, shares, ord);
+                HDT_HIP_TRY(hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            hipLaunchKernelGGL(kernel, dim3((unsigned)batch * shares), dim3(kOrdThreads), lds, st, d_level, d_parent, n_pos, shares,
+                               ord);
         }
     }
     {
