@@ -1,5 +1,5 @@
 """Hierarchical document attention (HDT, arXiv 2407.08330) for AMD MI355X: hand-written HIP
-kernels behind a C ABI (``include/hdt.h``), with a thin ctypes binding.  PyTorch is only used for
+kernels behind a C ABI (``include/hdt.h``), with a thin binding.  PyTorch is only used for
 device memory and streams."""
 from .binding import (  # noqa: F401
     HDT_EDGE_ALL,

@@ -1,6 +1,7 @@
-"""ctypes binding of libhdt.so: argument marshalling only.  Every step of the method runs in the
+"""Binding of libhdt.so: argument marshalling only.  Every step of the method runs in the
 HIP kernels behind the C ABI declared in ``include/hdt.h``; there is no fallback path, and a
-missing library is an error."""
+missing library is an error.  The calls every layer makes (build, forward, backward) go through native code
+(``csrc/hdt_pycall.cpp``) where their arguments are plain tensors and numbers, and through ctypes otherwise."""
 from __future__ import annotations
 
 import ctypes
@@ -12,6 +13,7 @@ import numpy as np
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libhdt.so")
 _lib = None
+_calls = None  # csrc/hdt_pycall.cpp: the hot calls in native code, None where their arguments are not the plain case
 _DTYPES = {}  # torch dtype -> hdt_dtype_t, filled with the library
 
 HDT_BF16, HDT_F32 = 0, 1
@@ -53,7 +55,7 @@ def library_path() -> str:
 def load_library():
     """Load libhdt.so built in-tree (``python -m paper_2407_08330_amd.build`` or
     ``__graft_entry__.build()``).  Raises if it is missing: there is no other path."""
-    global _lib
+    global _lib, _calls
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -120,7 +122,10 @@ def load_library():
     lib.hdt_hpe_table.restype = ctypes.c_int
     lib.hdt_hpe_add.argtypes = [vp, i32, i32, i32, vp, i32, vp, i32, ctypes.c_int, vp]
     lib.hdt_hpe_add.restype = ctypes.c_int
-    _lib = lib
+    from . import _hdt_pycall
+    _hdt_pycall.bind(*(ctypes.cast(f, vp).value for f in (lib.hdt_build_layout, lib.hdt_attn_fwd, lib.hdt_attn_fwd_ws,
+                                                          lib.hdt_attn_bwd, lib.hdt_attn_bwd_workspace_bytes)))
+    _lib, _calls = lib, _hdt_pycall
     return lib
 
 
@@ -244,6 +249,14 @@ def hdt_build_layout(level, parent, tile_m: int = 0, tile_n: int = 0, force_dens
     """level, parent: int32 device tensors [batch][n_pos].  ``edges``: OR of HDT_EDGE_* (0 = all).
     ``deferred``: only enqueue the build (see hdt_build_layout in include/hdt.h); ``capacity``: list entries
     the layout has room for (0 = the library chooses)."""
+    if _calls is None:
+        load_library()
+    r = _calls.build_layout(level, parent, tile_m, tile_n, force_dense, no_sort, windowed, edges, deferred, capacity,
+                            None if stream is None else stream.cuda_stream)
+    if r.__class__ is tuple:
+        return Layout(*r)
+    if r is not None:
+        _check(r)
     import torch
     if level.dtype != torch.int32 or parent.dtype != torch.int32:
         raise TypeError("level and parent must be int32")
@@ -302,6 +315,15 @@ def hdt_attn_fwd(layout: Layout, q, k, v, softmax_scale: float, o=None, lse=None
     """q: [batch][heads][n_pos][head_dim], k, v: [batch][heads][n_kv][head_dim] device tensors (bf16 or fp32;
     n_kv = n_pos unless the layout is a cross-attention layout).  ``workspace``: a uint8 device tensor for
     hdt_attn_fwd_ws (long key lists of a cross-attention layout cut into pieces).  Returns (o, lse)."""
+    if _calls is None:
+        load_library()
+    handle = layout.handle
+    r = _calls.attn_fwd(handle.value if handle is not None else None, layout.batch, layout.n_pos, layout.n_kv, q, k, v, softmax_scale,
+                        o, lse, workspace, None if stream is None else stream.cuda_stream)
+    if r.__class__ is tuple:
+        return r
+    if r is not None:
+        _check(r)
     import torch
     B, H, N, D = q.shape
     _check_tensors((q,), q.shape)
@@ -329,6 +351,15 @@ def hdt_attn_bwd_workspace_bytes(layout: Layout, heads: int, head_dim: int, dtyp
 def hdt_attn_bwd(layout: Layout, q, k, v, o, lse, d_o, softmax_scale: float, dq=None, dk=None, dv=None,
                  workspace=None, stream=None):
     """Returns (dq, dk, dv); dq like q, dk and dv like k."""
+    if _calls is None:
+        load_library()
+    handle = layout.handle
+    r = _calls.attn_bwd(handle.value if handle is not None else None, layout.batch, layout.n_pos, layout.n_kv, q, k, v, softmax_scale,
+                        o, lse, d_o, dq, dk, dv, workspace, None if stream is None else stream.cuda_stream)
+    if r.__class__ is tuple:
+        return r
+    if r is not None:
+        _check(r)
     import torch
     B, H, N, D = q.shape
     _check_tensors((q, o, d_o), q.shape)

@@ -1,14 +1,16 @@
-"""Builds libhdt.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libhdt.so (HIP kernels + C ABI) for gfx950 with hipcc, and the Python module of its hot calls, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_PKG)
 CSRC = os.path.join(_PKG, "csrc")
 LIB = os.path.join(_PKG, "libhdt.so")
+PYCALL = os.path.join(_PKG, "_hdt_pycall.so")
 SOURCES = ["hdt_api.hip", "hdt_layout.hip", "hdt_f32.hip", "hdt_fwd.hip", "hdt_bwd.hip", "hdt_hpe.hip", "hdt_cross.hip", "hdt_probe.hip"]
 
 HIPCC_FLAGS = [
@@ -25,8 +27,21 @@ HIPCC_FLAGS = [
 ]
 
 
+def _pycall_command():
+    """The host compiler's line for the Python module (against torch's headers; no device code)."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include/torch/csrc/api/include"),
+            "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
+            "-I", os.path.join(_ROOT, "include"), os.path.join(CSRC, "hdt_pycall.cpp"), "-o", PYCALL,
+            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source and link the shared library.  Always recompiles."""
+    """Compile every source and link the shared library and the Python module.  Always recompiles."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs = []
     procs = []
@@ -38,6 +53,10 @@ def build(verbose: bool = False) -> str:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    cmd = _pycall_command()
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    procs.append(("hdt_pycall.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     failed = False
     for src, p in procs:
         log, _ = p.communicate()
@@ -48,7 +67,7 @@ def build(verbose: bool = False) -> str:
         elif verbose and log.strip():
             print(log)
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("a compiler failed")
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
     return LIB
