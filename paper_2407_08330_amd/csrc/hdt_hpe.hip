@@ -426,11 +426,17 @@ __global__ __launch_bounds__(256) void k_hpe_table(float *__restrict__ table, in
 // ---- x += sum over the levels of the table rows -------------------------------------------------------
 // A thread owns 8 consecutive channels (16 bytes of bf16) of kPerThread consecutive positions: the kernel is a stream
 // over x, and what it must keep away from that stream is the table, whose rows (fp32, out of L2) are three times
-// the bytes of x.  Consecutive positions mostly share their upper-level indices, so a thread keeps the table row of
-// every level in registers and reads another one only where the index changes.
-// Measured, bf16, 32768 positions of 768 / 1024 channels: 24.2 / 30.3 us; every row read for every position 25.9 / 32.7;
-// one position per thread 26.8 / 34.4, four 26.2 / 31.8.  x is requested in front of the table rows in bf16 and behind
-// them in fp32, where the other order costs 3 us of 22 (registers).
+// the bytes of x.  Consecutive positions mostly share their upper-level indices, so a position's row of a level is read only
+// where the index differs from that of the position before it.
+// What bounds a thread is its chain of round trips: x, then the indices, then all rows it needs, requested together.  (With
+// a branch per row for indices beyond the table, every row was waited for before the next was asked for, six in turn.)  So
+// one question for the whole wave, are all indices inside the table, and no branch behind it but the masks of rows that
+// repeat.  us, before - now, over six batches in turn: bf16 4 x 8192 x 768 26.2 - 25.9, 32768 x 512 17.6 - 14.9, 2 x 8192 x
+// 1024 17.3 - 14.6, 1024 x 768 4.15 - 3.6; fp32 4 x 8192 x 768 47.7 - 44.3, 8 x 2048 x 512 15.8 - 15.1; the first behind the
+// kernels that make its indices 23 - 19.5.  With repeated rows read again 27.3, 16.0 and 15.7 for the first three; one
+// position per thread 27.5, 15.3, 15.2, four 27.7, 17.2, 16.8; the indices in front of x 25.7, 15.9, 15.1 and, the first behind
+// its index kernels, a microsecond more; x behind the rows 26.7, 14.7, 14.6.  The first 128 rows in the LDS of workgroups
+// that take 64 channels each: 27.8, 16.5, 16.1.
 constexpr int kPerThread = 2, kMaxLevelsFast = 4;
 
 __device__ __noinline__ float hpe_direct(int v, int c, int d_model)
@@ -440,84 +446,117 @@ __device__ __noinline__ float hpe_direct(int v, int c, int d_model)
     return (float)((c & 1) ? cos(x) : sin(x));
 }
 
-template <bool BF16>
-__global__ __launch_bounds__(256) void k_hpe_add(const int32_t *__restrict__ p, unsigned positions, int L,
+// L levels at a time: all of them, or with MORE (beyond kMaxLevelsFast) group after group.
+template <bool BF16, int L, bool MORE>
+__global__ __launch_bounds__(256) void k_hpe_add(const int32_t *__restrict__ p, unsigned positions, int n_levels,
                                                  const float *__restrict__ table, int rows, void *__restrict__ x,
                                                  int d_model, unsigned groups)
 {
     typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+    constexpr int XV = BF16 ? 1 : 2;  // 16-byte pieces of x per thread and position
     const unsigned per_pos = (unsigned)d_model / 8u;
     const unsigned g = blockIdx.x * blockDim.x + threadIdx.x;  // (group of kPerThread positions, channel group)
     const unsigned pos0 = g / per_pos, c0 = (g - pos0 * per_pos) * 8u;
     if (pos0 >= groups) return;
-#define POS(u) (pos0 * kPerThread + (u))
+    unsigned pos[kPerThread];  // a position behind the last one stands for the last
+    float4 xv[kPerThread][XV];
     float acc[kPerThread][8];
-    bool live[kPerThread];
+    float4 *xs = reinterpret_cast<float4 *>(x);
 #pragma unroll
     for (int u = 0; u < kPerThread; u++) {
-        live[u] = POS(u) < positions;
+        pos[u] = min(pos0 * kPerThread + u, positions - 1u);
+#pragma unroll
+        for (int w = 0; w < XV; w++) xv[u][w] = xs[((size_t)pos[u] * per_pos + c0 / 8u) * XV + w];
 #pragma unroll
         for (int e = 0; e < 8; e++) acc[u][e] = 0.f;
     }
-    bf16x8 xb[kPerThread];
-#pragma unroll
-    for (int u = 0; u < kPerThread; u++) {
-        const size_t at = (size_t)(live[u] ? POS(u) : POS(0)) * per_pos + c0 / 8u;
-        if (BF16) {
-            xb[u] = reinterpret_cast<const bf16x8 *>(x)[at];
-        }
-    }
-    for (int l0 = 0; l0 < L; l0 += kMaxLevelsFast) {
-        int v[kPerThread][kMaxLevelsFast];
+    asm volatile("" ::: "memory");  // (x is asked for first)
+    auto add = [&](int u, const float4 &a, const float4 &b) {
+        acc[u][0] += a.x, acc[u][1] += a.y, acc[u][2] += a.z, acc[u][3] += a.w;
+        acc[u][4] += b.x, acc[u][5] += b.y, acc[u][6] += b.z, acc[u][7] += b.w;
+    };
+    auto row_of = [&](int v) { return reinterpret_cast<const float4 *>(table + (size_t)v * d_model + c0); };
+    const int stride = MORE ? n_levels : L;
+    for (int l0 = 0; l0 < (MORE ? n_levels : 1); l0 += L) {
+        int v[kPerThread][L];
+        bool inside = true;
 #pragma unroll
         for (int u = 0; u < kPerThread; u++)
 #pragma unroll
-            for (int l = 0; l < kMaxLevelsFast; l++)
-                v[u][l] = (live[u] && l0 + l < L) ? p[(size_t)POS(u) * L + l0 + l] : -1;
+            for (int l = 0; l < L; l++) v[u][l] = p[(size_t)pos[u] * stride + (MORE ? min(l0 + l, n_levels - 1) : l)];
 #pragma unroll
-        for (int l = 0; l < kMaxLevelsFast; l++) {
-            if (l0 + l >= L) break;
-            float4 t0[kPerThread], t1[kPerThread];
+        for (int u = 0; u < kPerThread; u++)
 #pragma unroll
-            for (int u = 0; u < kPerThread; u++) {
-                const int vv = v[u][l];
-                if (u > 0 && vv == v[u > 0 ? u - 1 : 0][l]) {
-                    t0[u] = t0[u > 0 ? u - 1 : 0], t1[u] = t1[u > 0 ? u - 1 : 0];
-                } else if (vv >= 0 && vv < rows) {
-                    t0[u] = *reinterpret_cast<const float4 *>(table + (size_t)vv * d_model + c0);
-                    t1[u] = *reinterpret_cast<const float4 *>(table + (size_t)vv * d_model + c0 + 4);
-                } else if (live[u]) {
-                    float d[8];
-                    for (int e = 0; e < 8; e++) d[e] = hpe_direct(vv, (int)c0 + e, d_model);
-                    t0[u] = make_float4(d[0], d[1], d[2], d[3]), t1[u] = make_float4(d[4], d[5], d[6], d[7]);
-                } else {
-                    t0[u] = t1[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int l = 0; l < L; l++) inside = inside && v[u][l] >= 0 && v[u][l] < rows;
+        if (!__any(!inside)) {
+            float4 t[kPerThread][L][2];
+#pragma unroll
+            for (int l = 0; l < L; l++)
+#pragma unroll
+                for (int u = 0; u < kPerThread; u++) {
+                    const float4 *row = row_of(v[u][l]);
+                    if (u > 0) t[u][l][0] = t[u][l][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (u == 0 || v[u][l] != v[u > 0 ? u - 1 : 0][l]) {
+                        t[u][l][0] = row[0];
+                        t[u][l][1] = row[1];
+                    }
                 }
-            }
 #pragma unroll
-            for (int u = 0; u < kPerThread; u++) {
-                acc[u][0] += t0[u].x, acc[u][1] += t0[u].y, acc[u][2] += t0[u].z, acc[u][3] += t0[u].w;
-                acc[u][4] += t1[u].x, acc[u][5] += t1[u].y, acc[u][6] += t1[u].z, acc[u][7] += t1[u].w;
-            }
+            for (int u = 0; u < kPerThread; u++)
+#pragma unroll
+                for (int l = 0; l < L; l++) {
+                    if (u > 0 && v[u][l] == v[u > 0 ? u - 1 : 0][l]) {
+                        t[u][l][0] = t[u > 0 ? u - 1 : 0][l][0];
+                        t[u][l][1] = t[u > 0 ? u - 1 : 0][l][1];
+                    }
+                    if (!MORE || l0 + l < n_levels) add(u, t[u][l][0], t[u][l][1]);
+                }
+        } else {  // some index has no row
+#pragma unroll
+            for (int u = 0; u < kPerThread; u++)
+#pragma unroll 1
+                for (int l = l0; l < (MORE ? min(l0 + L, n_levels) : L); l++) {
+                    const int vv = p[(size_t)pos[u] * stride + l];
+                    if (vv >= 0 && vv < rows) {
+                        const float4 *row = row_of(vv);
+                        add(u, row[0], row[1]);
+                    } else {
+                        float d[8];
+                        for (int e = 0; e < 8; e++) d[e] = hpe_direct(vv, (int)c0 + e, d_model);
+                        add(u, make_float4(d[0], d[1], d[2], d[3]), make_float4(d[4], d[5], d[6], d[7]));
+                    }
+                }
         }
     }
 #pragma unroll
     for (int u = 0; u < kPerThread; u++) {
-        if (!live[u]) continue;
-        const size_t at = (size_t)POS(u) * per_pos + c0 / 8u;
+        if (pos0 * kPerThread + u >= positions) continue;
+        const size_t at = ((size_t)pos[u] * per_pos + c0 / 8u) * XV;
         if (BF16) {
+            bf16x8 xb = __builtin_bit_cast(bf16x8, xv[u][0]);
 #pragma unroll
-            for (int e = 0; e < 8; e++) xb[u][e] = (__bf16)((float)xb[u][e] + acc[u][e]);
-            reinterpret_cast<bf16x8 *>(x)[at] = xb[u];
+            for (int e = 0; e < 8; e++) xb[e] = (__bf16)((float)xb[e] + acc[u][e]);
+            xs[at] = __builtin_bit_cast(float4, xb);
         } else {
-            float4 a = reinterpret_cast<const float4 *>(x)[2 * at], c = reinterpret_cast<const float4 *>(x)[2 * at + 1];
+            float4 a = xv[u][0], b = xv[u][XV - 1];
             a.x += acc[u][0], a.y += acc[u][1], a.z += acc[u][2], a.w += acc[u][3];
-            c.x += acc[u][4], c.y += acc[u][5], c.z += acc[u][6], c.w += acc[u][7];
-            reinterpret_cast<float4 *>(x)[2 * at] = a;
-            reinterpret_cast<float4 *>(x)[2 * at + 1] = c;
+            b.x += acc[u][4], b.y += acc[u][5], b.z += acc[u][6], b.w += acc[u][7];
+            xs[at] = a;
+            xs[at + 1] = b;
         }
     }
-#undef POS
+}
+
+template <bool BF16>
+auto hpe_add_kernel(int n_levels)
+{
+    switch (n_levels) {
+    case 1: return k_hpe_add<BF16, 1, false>;
+    case 2: return k_hpe_add<BF16, 2, false>;
+    case 3: return k_hpe_add<BF16, 3, false>;
+    case 4: return k_hpe_add<BF16, 4, false>;
+    default: return k_hpe_add<BF16, kMaxLevelsFast, true>;
+    }
 }
 
 }  // namespace
@@ -625,12 +664,9 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_hpe_add(const
     if (positions > 0x7fffffffLL || threads > 0x7fffffffLL) return hdt_fail(HDT_ERR_SHAPE, "hdt_hpe_add: too many elements");
     hipStream_t st = (hipStream_t)stream;
     HdtTimer t(dt == HDT_BF16 ? "hdt_hpe_add_bf16" : "hdt_hpe_add_f32", st);
-    if (dt == HDT_BF16)
-        hipLaunchKernelGGL(k_hpe_add<true>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, d_p,
-                           (unsigned)positions, n_levels, d_table, table_rows, x, d_model, (unsigned)pos_stride);
-    else
-        hipLaunchKernelGGL(k_hpe_add<false>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, d_p,
-                           (unsigned)positions, n_levels, d_table, table_rows, x, d_model, (unsigned)pos_stride);
+    const auto kernel = dt == HDT_BF16 ? hpe_add_kernel<true>(n_levels) : hpe_add_kernel<false>(n_levels);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, d_p, (unsigned)positions, n_levels,
+                       d_table, table_rows, x, d_model, (unsigned)pos_stride);
     HDT_HIP_TRY(hipGetLastError());
     return HDT_OK;
 }

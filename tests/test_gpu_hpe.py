@@ -132,6 +132,40 @@ def test_hpe_add(oracle, dtype, table_rows):
     assert worst <= tol
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("levels", [1, 2, 3, 4, 5, 9])
+@pytest.mark.parametrize("n,d", [(1, 8), (2, 24), (63, 520), (130, 64)])
+def test_hpe_add_levels_and_edges(oracle, dtype, levels, n, d):
+    """Odd numbers of positions, channels that end inside a wave, groups of levels.  Inside the table the result is one rounding
+    of fp32 sums in the order of the levels, the same bits in torch; with indices beyond it, the definition: up to 9 table values
+    of error 1e-6 and 10 additions below 16 (2^-21 each)."""
+    import torch
+    import paper_2407_08330_amd as hdt
+    rng = np.random.default_rng([levels, n, d])
+    rows = 40
+    table = hdt.hdt_hpe_table(rows, d)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    for beyond in (False, True):
+        p = rng.integers(0, rows, (3, n, levels))
+        p[:, 1::2][rng.random(p[:, 1::2].shape) < 0.5] = 7
+        p[:, ::3] = 7  # rows that repeat, and that do not
+        if beyond:
+            p[rng.random(p.shape) < 0.02] = 600
+            p[0, -1, -1] = 55
+        x = torch.from_numpy(rng.standard_normal((3, n, d), dtype=np.float32)).cuda().to(dt)
+        p_dev, got = to_dev_i32(p), x.clone()
+        hdt.hdt_hpe_add(p_dev, table, got)
+        if beyond:
+            ref = x.double().cpu().numpy() + np.stack([oracle.hpe(q, d) for q in p])
+            err = np.abs(got.double().cpu().numpy() - ref) - (np.abs(ref) * 2.0 ** -8 if dtype == "bf16" else 0)
+            assert err.max() <= 9e-6 + 10 * 2.0 ** -21
+        else:
+            acc = torch.zeros((3, n, d), device="cuda")
+            for l in range(levels):
+                acc += table[p_dev[:, :, l].long()]
+            assert torch.equal(got, (x.float() + acc).to(dt))
+
+
 def test_hpe_argument_errors():
     import torch
     import paper_2407_08330_amd as hdt
