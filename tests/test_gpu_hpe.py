@@ -132,6 +132,19 @@ def test_hpe_add(oracle, dtype, table_rows):
     assert worst <= tol
 
 
+@pytest.mark.parametrize("levels", [1, 2, 3, 4, 5])
+def test_index_vectors_of_few_levels(oracle, levels):
+    """The first columns of the vectors of a deep forest, for every number of levels with a kernel of its own."""
+    import paper_2407_08330_amd as hdt
+    n = 517
+    level, parent = map(np.stack, zip(*(inputs.listops_like_tree(np.random.default_rng(b), n) for b in range(3))))
+    level[1, 400:], parent[1, 400:] = -1, -1
+    parent[1][parent[1] >= 400] = -1
+    got = hdt.hdt_index_vectors(to_dev_i32(level), to_dev_i32(parent), levels).cpu().numpy()
+    for b in range(3):
+        np.testing.assert_array_equal(got[b], oracle.index_vectors(level[b], parent[b], 25)[:, :levels])
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("levels", [1, 2, 3, 4, 5, 9])
 @pytest.mark.parametrize("n,d", [(1, 8), (2, 24), (63, 520), (130, 64)])
