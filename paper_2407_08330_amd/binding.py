@@ -125,7 +125,8 @@ def load_library():
     from . import _hdt_pycall
     _hdt_pycall.bind(*(ctypes.cast(f, vp).value for f in (lib.hdt_build_layout, lib.hdt_attn_fwd, lib.hdt_attn_fwd_ws,
                                                           lib.hdt_attn_bwd, lib.hdt_attn_bwd_workspace_bytes)))
-    _lib, _calls = lib, _hdt_pycall
+    _calls = _hdt_pycall
+    _lib = lib  # the last step: whoever sees it, in another thread too, uses _calls
     return lib
 
 
@@ -249,7 +250,7 @@ def hdt_build_layout(level, parent, tile_m: int = 0, tile_n: int = 0, force_dens
     """level, parent: int32 device tensors [batch][n_pos].  ``edges``: OR of HDT_EDGE_* (0 = all).
     ``deferred``: only enqueue the build (see hdt_build_layout in include/hdt.h); ``capacity``: list entries
     the layout has room for (0 = the library chooses)."""
-    if _calls is None:
+    if _lib is None:
         load_library()
     r = _calls.build_layout(level, parent, tile_m, tile_n, force_dense, no_sort, windowed, edges, deferred, capacity,
                             None if stream is None else stream.cuda_stream)
@@ -315,7 +316,7 @@ def hdt_attn_fwd(layout: Layout, q, k, v, softmax_scale: float, o=None, lse=None
     """q: [batch][heads][n_pos][head_dim], k, v: [batch][heads][n_kv][head_dim] device tensors (bf16 or fp32;
     n_kv = n_pos unless the layout is a cross-attention layout).  ``workspace``: a uint8 device tensor for
     hdt_attn_fwd_ws (long key lists of a cross-attention layout cut into pieces).  Returns (o, lse)."""
-    if _calls is None:
+    if _lib is None:
         load_library()
     handle = layout.handle
     r = _calls.attn_fwd(handle.value if handle is not None else None, layout.batch, layout.n_pos, layout.n_kv, q, k, v, softmax_scale,
@@ -351,7 +352,7 @@ def hdt_attn_bwd_workspace_bytes(layout: Layout, heads: int, head_dim: int, dtyp
 def hdt_attn_bwd(layout: Layout, q, k, v, o, lse, d_o, softmax_scale: float, dq=None, dk=None, dv=None,
                  workspace=None, stream=None):
     """Returns (dq, dk, dv); dq like q, dk and dv like k."""
-    if _calls is None:
+    if _lib is None:
         load_library()
     handle = layout.handle
     r = _calls.attn_bwd(handle.value if handle is not None else None, layout.batch, layout.n_pos, layout.n_kv, q, k, v, softmax_scale,
