@@ -1,11 +1,13 @@
 """Binding of libhdt.so: argument marshalling only.  Every step of the method runs in the
 HIP kernels behind the C ABI declared in ``include/hdt.h``; there is no fallback path, and a
 missing library is an error.  The calls every layer makes (build, forward, backward) go through native code
-(``csrc/hdt_pycall.cpp``) where their arguments are plain tensors and numbers, and through ctypes otherwise."""
+(``csrc/hdt_pycall.cpp``) where their arguments are plain tensors and numbers, and through ctypes otherwise; that module is
+compiled for one Python and one torch, and under others, or without it, ctypes takes all calls."""
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional
 
 import numpy as np
@@ -50,6 +52,27 @@ class _Info(ctypes.Structure):
 
 def library_path() -> str:
     return _LIB_PATH
+
+
+class _NoCalls:
+    """In the place of csrc/hdt_pycall.cpp: takes no call."""
+    build_layout = attn_fwd = attn_bwd = staticmethod(lambda *a: None)
+
+
+def _native_calls(lib, torch_version: str):
+    try:
+        from . import _hdt_pycall as calls
+        found = getattr(calls, "torch_version", "of an earlier build")
+        why = None if found == torch_version else f"compiled for torch {found}"
+    except ImportError as e:
+        why = str(e)
+    if why is not None:
+        warnings.warn(f"_hdt_pycall, the native form of the hot calls, is not used ({why}): build, forward and backward take a few "
+                      "microseconds more of host time each.  Run __graft_entry__.build()", RuntimeWarning, stacklevel=3)
+        return _NoCalls
+    calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.hdt_build_layout, lib.hdt_attn_fwd, lib.hdt_attn_fwd_ws,
+                                                                 lib.hdt_attn_bwd, lib.hdt_attn_bwd_workspace_bytes)))
+    return calls
 
 
 def load_library():
@@ -122,10 +145,7 @@ def load_library():
     lib.hdt_hpe_table.restype = ctypes.c_int
     lib.hdt_hpe_add.argtypes = [vp, i32, i32, i32, vp, i32, vp, i32, ctypes.c_int, vp]
     lib.hdt_hpe_add.restype = ctypes.c_int
-    from . import _hdt_pycall
-    _hdt_pycall.bind(*(ctypes.cast(f, vp).value for f in (lib.hdt_build_layout, lib.hdt_attn_fwd, lib.hdt_attn_fwd_ws,
-                                                          lib.hdt_attn_bwd, lib.hdt_attn_bwd_workspace_bytes)))
-    _calls = _hdt_pycall
+    _calls = _native_calls(lib, str(torch.__version__))
     _lib = lib  # the last step: whoever sees it, in another thread too, uses _calls
     return lib
 

@@ -1,6 +1,7 @@
 """Builds libhdt.so (HIP kernels + C ABI) for gfx950 with hipcc, and the Python module of its hot calls, in-tree."""
 from __future__ import annotations
 
+import glob
 import os
 import subprocess
 import sys
@@ -10,7 +11,8 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_PKG)
 CSRC = os.path.join(_PKG, "csrc")
 LIB = os.path.join(_PKG, "libhdt.so")
-PYCALL = os.path.join(_PKG, "_hdt_pycall.so")
+# compiled for one Python (the suffix says which) and one torch; libhdt.so takes any of both
+PYCALL = os.path.join(_PKG, "_hdt_pycall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 SOURCES = ["hdt_api.hip", "hdt_layout.hip", "hdt_f32.hip", "hdt_fwd.hip", "hdt_bwd.hip", "hdt_hpe.hip", "hdt_cross.hip", "hdt_probe.hip"]
 
 HIPCC_FLAGS = [
@@ -33,7 +35,7 @@ def _pycall_command():
     root = os.path.dirname(torch.__file__)
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DHDT_TORCH_VERSION="{torch.__version__}"',
             "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include/torch/csrc/api/include"),
             "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
             "-I", os.path.join(_ROOT, "include"), os.path.join(CSRC, "hdt_pycall.cpp"), "-o", PYCALL,
@@ -41,7 +43,8 @@ def _pycall_command():
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every source and link the shared library and the Python module.  Always recompiles."""
+    """Compile every source and link the shared library and the Python module.  Always recompiles.  The module needs g++ and the
+    headers of torch and Python; where it cannot be made the library is linked all the same, and this raises behind that."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs = []
     procs = []
@@ -53,23 +56,32 @@ def build(verbose: bool = False) -> str:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
-    cmd = _pycall_command()
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    procs.append(("hdt_pycall.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-    failed = False
+    failed = []
+    for old in glob.glob(os.path.join(os.path.dirname(PYCALL), "_hdt_pycall*.so")):
+        os.remove(old)  # made for the library of an earlier build
+    module = "hdt_pycall.cpp"
+    try:
+        cmd = _pycall_command()
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        procs.append((module, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    except (ImportError, OSError) as e:  # no torch, no compiler
+        failed.append(module)
+        print(f"[build] {module} FAILED\n{e}", file=sys.stderr)
     for src, p in procs:
         log, _ = p.communicate()
         log = "\n".join(l for l in log.splitlines() if "packed-fp32-ops" not in l)
         if p.returncode != 0:
-            failed = True
+            failed.append(src)
             print(f"[build] {src} FAILED\n{log}", file=sys.stderr)
         elif verbose and log.strip():
             print(log)
-    if failed:
-        raise RuntimeError("a compiler failed")
+    if any(src != module for src in failed):
+        raise RuntimeError("hipcc failed")
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
+    if failed:
+        raise RuntimeError(f"{LIB} is built, the Python module of its hot calls (_hdt_pycall) is not")
     return LIB
 
 

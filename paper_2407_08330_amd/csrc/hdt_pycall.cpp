@@ -264,4 +264,13 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_hdt_pycall", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__hdt_pycall() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__hdt_pycall()
+{
+    PyObject *m = PyModule_Create(&module);
+    // (binding.py uses the module under this torch alone: nothing else says that its tensors are laid out as in these headers)
+    if (m && PyModule_AddStringConstant(m, "torch_version", HDT_TORCH_VERSION) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}
