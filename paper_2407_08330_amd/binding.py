@@ -289,8 +289,8 @@ def hdt_build_layout(level, parent, tile_m: int = 0, tile_n: int = 0, force_dens
                  int(capacity))
     h = ctypes.c_void_p(0)
     B, N = level.shape
-    _check(load_library().hdt_build_layout(_ptr(level) if B * N else None, _ptr(parent) if B * N else None, B, N,
-                                           ctypes.byref(opts), _stream_ptr(stream), ctypes.byref(h)))
+    _check(_lib.hdt_build_layout(_ptr(level) if B * N else None, _ptr(parent) if B * N else None, B, N,
+                                 ctypes.byref(opts), _stream_ptr(stream), ctypes.byref(h)))
     return Layout(h.value, B, N)
 
 
@@ -356,12 +356,12 @@ def hdt_attn_fwd(layout: Layout, q, k, v, softmax_scale: float, o=None, lse=None
     if lse is None:
         lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
     if workspace is not None:
-        _check(load_library().hdt_attn_fwd_ws(layout.handle, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), H, D,
-                                              _dtype_code(q), float(softmax_scale), _ptr(workspace),
-                                              workspace.numel() * workspace.element_size(), _stream_ptr(stream)))
+        _check(_lib.hdt_attn_fwd_ws(layout.handle, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), H, D,
+                                    _dtype_code(q), float(softmax_scale), _ptr(workspace),
+                                    workspace.numel() * workspace.element_size(), _stream_ptr(stream)))
         return o, lse
-    _check(load_library().hdt_attn_fwd(layout.handle, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), H, D,
-                                       _dtype_code(q), float(softmax_scale), _stream_ptr(stream)))
+    _check(_lib.hdt_attn_fwd(layout.handle, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), H, D,
+                             _dtype_code(q), float(softmax_scale), _stream_ptr(stream)))
     return o, lse
 
 
@@ -393,10 +393,10 @@ def hdt_attn_bwd(layout: Layout, q, k, v, o, lse, d_o, softmax_scale: float, dq=
     need = hdt_attn_bwd_workspace_bytes(layout, H, D, _dtype_code(q))
     if workspace is None:
         workspace = _scratch(need, q.device, stream)
-    _check(load_library().hdt_attn_bwd(layout.handle, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(d_o),
-                                       _ptr(dq), _ptr(dk), _ptr(dv), H, D, _dtype_code(q), float(softmax_scale),
-                                       _ptr(workspace), workspace.numel() * workspace.element_size(),
-                                       _stream_ptr(stream)))
+    _check(_lib.hdt_attn_bwd(layout.handle, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(d_o),
+                             _ptr(dq), _ptr(dk), _ptr(dv), H, D, _dtype_code(q), float(softmax_scale),
+                             _ptr(workspace), workspace.numel() * workspace.element_size(),
+                             _stream_ptr(stream)))
     return dq, dk, dv
 
 
