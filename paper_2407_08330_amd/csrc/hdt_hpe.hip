@@ -538,21 +538,34 @@ __global__ __launch_bounds__(256) void k_hpe_add(const int32_t *__restrict__ p, 
                     }
                     if (!MORE || l0 + l < n_levels) add(u, t[u][l][0], t[u][l][1]);
                 }
-        } else {  // some index has no row
-#pragma unroll
-            for (int u = 0; u < kPerThread; u++)
+        } else {
+            // Some index has no row.  What an index adds goes to both positions at once where it repeats: its values take longer
+            // than everything else here.  (us, every position its own - one evaluation: 4 x 8192 x 768, three levels, no table
+            // 507 - 341, the top level alone beyond the table 178 - 94.)
+            static_assert(kPerThread == 2, "one repeat to look for");
 #pragma unroll 1
-                for (int l = l0; l < (MORE ? min(l0 + L, n_levels) : L); l++) {
-                    const int vv = p[(size_t)pos[u] * stride + l];
+            for (int l = l0; l < (MORE ? min(l0 + L, n_levels) : L); l++) {
+                const int first = p[(size_t)pos[0] * stride + l], second = p[(size_t)pos[1] * stride + l];
+#pragma unroll
+                for (int u = 0; u < kPerThread; u++) {
+                    const int vv = u ? second : first;
+                    if (u > 0 && second == first) continue;
+                    const bool both = u == 0 && second == first;
                     if (vv >= 0 && vv < rows) {
                         const float4 *row = row_of(vv);
-                        add(u, row[0], row[1]);
+                        const float4 r0 = row[0], r1 = row[1];
+                        add(u, r0, r1);
+                        if (both) add(1, r0, r1);
                     } else {
-                        float d[8];
-                        for (int e = 0; e < 8; e++) d[e] = hpe_direct(vv, (int)c0 + e, d_model);
-                        add(u, make_float4(d[0], d[1], d[2], d[3]), make_float4(d[4], d[5], d[6], d[7]));
+#pragma unroll
+                        for (int e = 0; e < 8; e++) {
+                            const float value = hpe_direct(vv, (int)c0 + e, d_model);
+                            acc[u][e] += value;
+                            if (both) acc[1][e] += value;
+                        }
                     }
                 }
+            }
         }
     }
 #pragma unroll

@@ -179,6 +179,33 @@ def test_hpe_add_levels_and_edges(oracle, dtype, levels, n, d):
             assert torch.equal(got, (x.float() + acc).to(dt))
 
 
+@pytest.mark.parametrize("rows", [0, 40])
+def test_hpe_add_evaluates_a_repeated_index_once(rows):
+    """Beyond the table a position's values take longer than everything else of the add, and positions come in pairs: with the
+    indices of the first of a pair also in the second there is half as much to evaluate (four fifths of the time allowed)."""
+    import torch
+    import paper_2407_08330_amd as hdt
+    n, d = 4096, 512
+    x = torch.zeros((1, n, d), device="cuda")
+    table = hdt.hdt_hpe_table(rows, d) if rows else None
+    i = torch.arange(n, device="cuda", dtype=torch.int32)
+
+    def us(p):
+        p = (p + 50).view(1, n, 1).expand(1, n, 3).contiguous()
+        begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        times = []
+        for _ in range(6):
+            begin.record()
+            for _ in range(10):
+                hdt.hdt_hpe_add(p, table, x)
+            end.record()
+            end.synchronize()
+            times.append(begin.elapsed_time(end) * 100)
+        return min(times)
+
+    assert us(i // 2) < 0.8 * us(i)
+
+
 def test_hpe_argument_errors():
     import torch
     import paper_2407_08330_amd as hdt
