@@ -464,8 +464,11 @@ __global__ __launch_bounds__(256) void k_hpe_table(float *__restrict__ table, in
 // position per thread 27.5, 15.3, 15.2, four 27.7, 17.2, 16.8; the indices in front of x 25.7, 15.9, 15.1 and, the first behind
 // its index kernels, a microsecond more; x behind the rows 26.7, 14.7, 14.6.  The first 128 rows in the LDS of workgroups
 // that take 64 channels each: 27.8, 16.5, 16.1.
-constexpr int kPerThread = 2, kMaxLevelsFast = 4;
+constexpr int kPerThread = 2, kMoreLevels = 2;
 
+__device__ __noinline__ double hpe_frequency(int c, int d_model) { return pow(10000.0, -2.0 * (double)(c / 2) / (double)d_model); }
+__device__ __noinline__ float hpe_value(double x, int c) { return (float)((c & 1) ? cos(x) : sin(x)); }
+// (both in one call)
 __device__ __noinline__ float hpe_direct(int v, int c, int d_model)
 {
     const double w = pow(10000.0, -2.0 * (double)(c / 2) / (double)d_model);
@@ -473,13 +476,72 @@ __device__ __noinline__ float hpe_direct(int v, int c, int d_model)
     return (float)((c & 1) ? cos(x) : sin(x));
 }
 
-// L levels at a time: all of them, or with MORE (beyond kMaxLevelsFast) group after group.
+// The whole add of one thread of a wave in which an index has no row, for more than four levels: around calls the form below would
+// hold what it keeps from group to group in registers of two waves per SIMD, so this starts again and nothing is kept.  Two channels at
+// a time, which have their frequency in common (4 x 8192 x 768, five levels, no table, us: 865, 563 with what repeats evaluated once,
+// 196 with the frequency found once).
+template <bool BF16>
+__device__ __forceinline__ void hpe_add_beyond(const int32_t *p, unsigned pos0, unsigned pos1, int n_levels, const float *table, int rows,
+                                               void *x, int d_model, int c0)
+{
+#pragma unroll 1
+    for (int c = c0; c < c0 + 8; c += 2) {
+        const double w = hpe_frequency(c, d_model);
+        float acc[2][2] = {};
+#pragma unroll 1
+        for (int l = 0; l < n_levels; l++) {
+            const int first = p[(size_t)pos0 * n_levels + l], second = p[(size_t)pos1 * n_levels + l];
+#pragma unroll
+            for (int u = 0; u < 2; u++) {
+                const int v = u ? second : first;
+                if (u > 0 && second == first) continue;
+                const bool both = u == 0 && second == first;
+                if (v >= 0 && v < rows) {
+                    const float *row = table + (size_t)v * d_model + c;
+#pragma unroll
+                    for (int e = 0; e < 2; e++) {
+                        acc[u][e] += row[e];
+                        if (both) acc[1][e] += row[e];
+                    }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 2; e++) {
+                        const float value = hpe_value(w * (double)v, c + e);
+                        acc[u][e] += value;
+                        if (both) acc[1][e] += value;
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (unsigned u = 0; u < 2; u++) {
+            if (u && pos1 == pos0) break;
+            const size_t at = (size_t)(u ? pos1 : pos0) * d_model + c;
+#pragma unroll
+            for (int e = 0; e < 2; e++) {
+                if (BF16) {
+                    __bf16 *to = reinterpret_cast<__bf16 *>(x) + at;
+                    to[e] = (__bf16)((float)to[e] + acc[u][e]);
+                } else {
+                    reinterpret_cast<float *>(x)[at + e] += acc[u][e];
+                }
+            }
+        }
+    }
+}
+
+// L levels at a time: all of them, or with MORE (five levels and more) group after group, the next group's indices requested in
+// front of this one's rows.  Groups of two, and fp32 asks for x last: five waves per SIMD.  us, bf16 and fp32, of 4 x 8192 x 768 with
+// five levels / nine / 25: groups of four 35.1, 42.3 / 48.3, 55.3 / 95.6, 102 (133 and 141 registers); of two 24.1, 33.5 / 34.2, 42.8 / 81.7,
+// 90.5; of three, without the next indices, 24.2, 34.2 / 35.6, 43.7 / 84.7, 93.6; one level after the other, each row waited for, 25.7,
+// 35.7 / 37.3, 47.3 / 86, 96.  At 1001 x 512 the groups of four are ahead, by a tenth from 12 levels on (25: 8.4, of two 9.5).
 template <bool BF16, int L, bool MORE>
 __global__ __launch_bounds__(256) void k_hpe_add(const int32_t *__restrict__ p, unsigned positions, int n_levels,
                                                  const float *__restrict__ table, int rows, void *__restrict__ x,
                                                  int d_model, unsigned groups)
 {
     typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+    constexpr bool X_LAST = MORE && !BF16;
     constexpr int XV = BF16 ? 1 : 2;  // 16-byte pieces of x per thread and position
     const unsigned per_pos = (unsigned)d_model / 8u;
     const unsigned g = blockIdx.x * blockDim.x + threadIdx.x;  // (group of kPerThread positions, channel group)
@@ -493,7 +555,7 @@ __global__ __launch_bounds__(256) void k_hpe_add(const int32_t *__restrict__ p, 
     for (int u = 0; u < kPerThread; u++) {
         pos[u] = min(pos0 * kPerThread + u, positions - 1u);
 #pragma unroll
-        for (int w = 0; w < XV; w++) xv[u][w] = xs[((size_t)pos[u] * per_pos + c0 / 8u) * XV + w];
+        for (int w = 0; w < (X_LAST ? 0 : XV); w++) xv[u][w] = xs[((size_t)pos[u] * per_pos + c0 / 8u) * XV + w];
 #pragma unroll
         for (int e = 0; e < 8; e++) acc[u][e] = 0.f;
     }
@@ -504,25 +566,41 @@ __global__ __launch_bounds__(256) void k_hpe_add(const int32_t *__restrict__ p, 
     };
     auto row_of = [&](int v) { return reinterpret_cast<const float4 *>(table + (size_t)v * d_model + c0); };
     const int stride = MORE ? n_levels : L;
-    for (int l0 = 0; l0 < (MORE ? n_levels : 1); l0 += L) {
-        int v[kPerThread][L];
-        bool inside = true;
+    int v[kPerThread][L], next[kPerThread][L];
+    auto indices = [&](int l0, int (&to)[kPerThread][L]) {
 #pragma unroll
         for (int u = 0; u < kPerThread; u++)
 #pragma unroll
-            for (int l = 0; l < L; l++) v[u][l] = p[(size_t)pos[u] * stride + (MORE ? min(l0 + l, n_levels - 1) : l)];
+            for (int l = 0; l < L; l++) to[u][l] = p[(size_t)pos[u] * stride + (MORE ? min(l0 + l, n_levels - 1) : l)];
+    };
+    indices(0, v);
+    for (int l0 = 0; l0 < (MORE ? n_levels : 1); l0 += L) {
+        bool inside = true;
+        if (MORE && l0 > 0) {
+#pragma unroll
+            for (int u = 0; u < kPerThread; u++)
+#pragma unroll
+                for (int l = 0; l < L; l++) v[u][l] = next[u][l];
+        }
+        if (MORE) indices(l0 + L, next);
 #pragma unroll
         for (int u = 0; u < kPerThread; u++)
 #pragma unroll
             for (int l = 0; l < L; l++) inside = inside && v[u][l] >= 0 && v[u][l] < rows;
-        if (!__any(!inside)) {
+        const bool beyond = __any(!inside);
+        if (MORE && beyond) {
+            hpe_add_beyond<BF16>(p, pos[0], pos[1], n_levels, table, rows, x, d_model, (int)c0);
+            return;
+        }
+        if (!beyond) {
             float4 t[kPerThread][L][2];
 #pragma unroll
             for (int l = 0; l < L; l++)
 #pragma unroll
                 for (int u = 0; u < kPerThread; u++) {
                     const float4 *row = row_of(v[u][l]);
-                    if (u > 0) t[u][l][0] = t[u][l][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (u > 0 || (MORE && l > 0)) t[u][l][0] = t[u][l][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (MORE && l > 0 && l0 + l >= n_levels) continue;
                     if (u == 0 || v[u][l] != v[u > 0 ? u - 1 : 0][l]) {
                         t[u][l][0] = row[0];
                         t[u][l][1] = row[1];
@@ -544,7 +622,7 @@ __global__ __launch_bounds__(256) void k_hpe_add(const int32_t *__restrict__ p, 
             // 507 - 341, the top level alone beyond the table 178 - 94.)
             static_assert(kPerThread == 2, "one repeat to look for");
 #pragma unroll 1
-            for (int l = l0; l < (MORE ? min(l0 + L, n_levels) : L); l++) {
+            for (int l = 0; l < L; l++) {
                 const int first = p[(size_t)pos[0] * stride + l], second = p[(size_t)pos[1] * stride + l];
 #pragma unroll
                 for (int u = 0; u < kPerThread; u++) {
@@ -567,6 +645,12 @@ __global__ __launch_bounds__(256) void k_hpe_add(const int32_t *__restrict__ p, 
                 }
             }
         }
+    }
+    if (X_LAST) {
+#pragma unroll
+        for (int u = 0; u < kPerThread; u++)
+#pragma unroll
+            for (int w = 0; w < XV; w++) xv[u][w] = xs[((size_t)pos[u] * per_pos + c0 / 8u) * XV + w];
     }
 #pragma unroll
     for (int u = 0; u < kPerThread; u++) {
@@ -595,7 +679,7 @@ auto hpe_add_kernel(int n_levels)
     case 2: return k_hpe_add<BF16, 2, false>;
     case 3: return k_hpe_add<BF16, 3, false>;
     case 4: return k_hpe_add<BF16, 4, false>;
-    default: return k_hpe_add<BF16, kMaxLevelsFast, true>;
+    default: return k_hpe_add<BF16, kMoreLevels, true>;
     }
 }
 

@@ -179,6 +179,21 @@ def test_hpe_add_levels_and_edges(oracle, dtype, levels, n, d):
             assert torch.equal(got, (x.float() + acc).to(dt))
 
 
+def add_us(p, table, x):
+    import torch
+    import paper_2407_08330_amd as hdt
+    begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    times = []
+    for _ in range(8):
+        begin.record()
+        for _ in range(10):
+            hdt.hdt_hpe_add(p, table, x)
+        end.record()
+        end.synchronize()
+        times.append(begin.elapsed_time(end) * 100)
+    return min(times)
+
+
 @pytest.mark.parametrize("rows", [0, 40])
 def test_hpe_add_evaluates_a_repeated_index_once(rows):
     """Beyond the table a position's values take longer than everything else of the add, and positions come in pairs: with the
@@ -192,18 +207,27 @@ def test_hpe_add_evaluates_a_repeated_index_once(rows):
 
     def us(p):
         p = (p + 50).view(1, n, 1).expand(1, n, 3).contiguous()
-        begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
-        times = []
-        for _ in range(6):
-            begin.record()
-            for _ in range(10):
-                hdt.hdt_hpe_add(p, table, x)
-            end.record()
-            end.synchronize()
-            times.append(begin.elapsed_time(end) * 100)
-        return min(times)
+        return add_us(p, table, x)
 
     assert us(i // 2) < 0.8 * us(i)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_hpe_add_of_a_fifth_level_costs_a_level(dtype):
+    """Five levels go through a form of their own; 1.3 (bf16) and 1.1 times as long as four, 1.9 and 1.35 where a form takes eight
+    rows and half of the waves for them."""
+    import torch
+    import paper_2407_08330_amd as hdt
+    n, d = 8192, 768
+    x = torch.zeros((4, n, d), device="cuda", dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+    table = hdt.hdt_hpe_table(64, d)
+    i = torch.arange(n, device="cuda", dtype=torch.int32)
+
+    def us(levels):
+        runs = [max(1, 400 // 5 ** l) for l in range(levels - 1)] + [1]
+        return add_us(torch.stack([(i // r) % 60 for r in runs], dim=1).expand(4, n, levels).contiguous(), table, x)
+
+    assert us(5) < (1.6 if dtype == "bf16" else 1.22) * us(4)
 
 
 def test_hpe_argument_errors():
