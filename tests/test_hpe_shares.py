@@ -57,3 +57,45 @@ def test_every_position_a_workgroup_reads_is_inside_its_sample(tmp_path):
                     "-o", str(exe)], check=True)
     run = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True)
     assert run.returncode == 0, run.stdout[-2000:]
+
+
+PROGRAM_BUILD = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "hdt_share.h"
+
+// entries that a wave of the busiest compute unit takes, in all rounds
+static double busiest(int batch, long long entries, int shares)
+{
+    const long long rounds = ((long long)batch * shares + kOnChip - 1) / kOnChip;
+    return (double)rounds * (double)((entries + 16ll * shares - 1) / (16ll * shares));
+}
+
+int main()
+{
+    int bad = 0;
+    for (int batch = 1; batch <= 2000; batch += batch < 700 ? 1 : 37)
+        for (long long entries : {1, 13, 40, 72, 208, 288, 1152, 5000, 70000, 300000000}) {
+            const int shares = cross_build_shares(batch, entries);
+            const double fair = (double)batch * (double)entries / (16. * kOnChip);
+            // a scan is worth 2.5 entries: up to a handful of entries nothing can be divided, beyond them little is idle
+            if (shares < 1 || (shares - 1) * 16ll >= entries || (fair > 20. && busiest(batch, entries, shares) > 1.4 * fair + 4.)) {
+                bad++;
+                std::printf("batch %d, %lld entries: %d shares, busiest %g, fair %g\n", batch, entries, shares, busiest(batch, entries, shares), fair);
+            }
+        }
+    for (int batch : {1 << 20, 2147483647})
+        for (long long entries : {1ll, 1152ll, 600000000ll}) bad += cross_build_shares(batch, entries) < 1;
+    return bad != 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
+def test_the_cross_attention_build_leaves_no_half_of_the_chip_idle(tmp_path):
+    src, exe = tmp_path / "shares.cpp", tmp_path / "shares"
+    src.write_text(PROGRAM_BUILD)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__host__=", "-D__device__=", "-D__forceinline__=inline", "-I", CSRC, str(src),
+                    "-o", str(exe)], check=True)
+    run = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True)
+    assert run.returncode == 0, run.stdout[-2000:]
