@@ -216,7 +216,7 @@ struct CrossEntries {
 // 1024 samples 71 / 76 - 43 / 46; 8192 x 64, 256 samples 44 / 48 - 28 / 39.  512 x 8192 x 4 x 12 heads, anchors visible, build, forward
 // and backward: 42.9 -> 39.2 us.  Workgroups for half of the compute units' LDS instead of one each (512): 8.5 -> 12.3 at 8192 x
 // 4 samples.  One loop over all sides instead of one per side: 9.1 at 8192 x 4, 60.8 at 8192 x 256, tokens visible.
-constexpr int kBuildThreads = kCrossBuildThreads, kBuildBatch = 8;
+constexpr int kBuildThreads = kCrossBuildThreads, kBuildBatch = kCrossBuildBatch;
 __global__ __launch_bounds__(kBuildThreads) void k_cross_build(CrossArgs a)
 {
     constexpr int W = kBuildThreads / 64;
@@ -606,7 +606,7 @@ extern "C" __attribute__((visibility("default"))) hdt_status_t hdt_build_cross_l
             }
             if (e_fwd >= kSplitEntries)
                 for (int k = 0; k < 3; k++) L->cross_split_range[k] = args.split_range[k] = f.split_range[k];
-            args.shares = cross_build_shares(batch, per_sample);
+            args.shares = cross_build_shares(batch, n_enc, per_sample);
             const size_t lds = (size_t)((n_enc + 63) / 64) * (sizeof(unsigned long long) + sizeof(int));
             if (lds > 60 * 1024)  // with the static array: beyond the 64 KB a launch gets by default
                 CROSS_TRY(hipFuncSetAttribute((const void *)k_cross_build, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));

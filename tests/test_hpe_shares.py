@@ -76,7 +76,7 @@ int main()
     int bad = 0;
     for (int batch = 1; batch <= 2000; batch += batch < 700 ? 1 : 37)
         for (long long entries : {1, 13, 40, 72, 208, 288, 1152, 5000, 70000, 300000000}) {
-            const int shares = cross_build_shares(batch, entries);
+            const int shares = cross_build_shares(batch, 8192, entries);
             const double fair = (double)batch * (double)entries / (16. * kOnChip);
             // a scan is worth 2.5 entries: up to a handful of entries nothing can be divided, beyond them little is idle
             if (shares < 1 || (shares - 1) * 16ll >= entries || (fair > 20. && busiest(batch, entries, shares) > 1.4 * fair + 4.)) {
@@ -85,7 +85,9 @@ int main()
             }
         }
     for (int batch : {1 << 20, 2147483647})
-        for (long long entries : {1ll, 1152ll, 600000000ll}) bad += cross_build_shares(batch, entries) < 1;
+        for (long long entries : {1ll, 1152ll, 600000000ll}) bad += cross_build_shares(batch, 1 << 19, entries) < 1;
+    // a long scan is not repeated for entries that take less time: one round where there can be one
+    for (int batch : {1, 3, 10, 24, 40}) bad += batch * cross_build_shares(batch, 1 << 19, 13312) > kOnChip;
     return bad != 0;
 }
 """
