@@ -655,11 +655,11 @@ void hdt_cross_record(const hdt_layout_t *l, int c_max)
     const int n_c = compact_rows(c_max, l->s.n_kv);
     hdt_layout_t *c = l->compact_built;
     if (n_c == 0 || !c) return;
-    // the rows there are, not those there was room for (whose tiles keep their places: own_tiles)
+    // The rows there are, not those there was room for.  The tiles keep their places: q_range and c_row go by own_tiles per sample, not
+    // by tr, and the list entries stay the reserved ones, spread over all of them.
     HdtSchedule &s = c->s;
     s.n_pos = s.n_own = n_c;
     s.tr = s.tr_own = (n_c + s.bm - 1) / s.bm;
-    c->n_entries = c->capacity = (int64_t)s.batch * s.tr * ((s.n_kv + s.bn - 1) / s.bn);
     l->n_compact = n_c;
     l->compact = c;
 }
