@@ -17,23 +17,28 @@ class General:
 
 
 class Counting:
-    """The native calls, and how many of them were taken."""
+    """The native calls, and which of them were taken."""
 
     def __init__(self, calls):
-        self.calls, self.taken = calls, 0
+        self.calls, self.taken = calls, set()
 
     def __getattr__(self, name):
         f = getattr(self.calls, name)
 
         def call(*a):
             r = f(*a)
-            self.taken += r is not None
+            if r is not None:
+                self.taken.add(name)
             return r
         return call
 
 
-def both(monkeypatch, f, native=True):
-    """f() on the general path, then with the native calls, which must have taken it (or not)."""
+BUILD, FWD, BWD = "build_layout", "attn_fwd", "attn_bwd"
+
+
+def both(monkeypatch, f, taken, raises=False):
+    """f() on the general path, then with the native calls, which must have taken exactly those of `taken`.  ``raises``: what
+    the library and the binding raise is the result; a failed assertion is one in any case."""
     from paper_2407_08330_amd import binding
     binding.load_library()
     calls = Counting(binding._calls)
@@ -41,11 +46,14 @@ def both(monkeypatch, f, native=True):
     for c in (General, calls):
         with monkeypatch.context() as m:
             m.setattr(binding, "_calls", c)
-            try:
+            if not raises:
                 out.append(f())
-            except Exception as e:  # noqa: BLE001 (compared below)
-                out.append((type(e), str(e)))
-    assert (calls.taken > 0) == native
+                continue
+            with pytest.raises(Exception) as caught:
+                f()
+            assert not issubclass(caught.type, AssertionError)
+            out.append((caught.type, str(caught.value)))
+    assert calls.taken == set(taken)
     return out
 
 
@@ -102,7 +110,8 @@ def test_same_results(monkeypatch, dtype, d, tile, form):
         lay.destroy()
         return [t.detach() if form == "grad" else t for t in (o, lse, *g)]
 
-    equal(*both(monkeypatch, run))
+    # (on another stream a temporary workspace is the general path's business)
+    equal(*both(monkeypatch, run, {"stream": {BUILD, FWD}, "subclass": {BUILD}}.get(form, {BUILD, FWD, BWD})))
 
 
 def test_cross_attention_with_a_workspace(monkeypatch):
@@ -119,27 +128,27 @@ def test_cross_attention_with_a_workspace(monkeypatch):
         o, lse = hdt.hdt_attn_fwd(lay, q, k, v, 0.125, workspace=ws)
         return [o, lse, *hdt.hdt_attn_bwd(lay, q, k, v, o, lse, d_o, 0.125)]
 
-    equal(*both(monkeypatch, run))
+    equal(*both(monkeypatch, run, {FWD, BWD}))
 
 
 ERRORS = {
-    "shape": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q[:, :, :-1].contiguous(), s.k, s.v, 0.125), False),
-    "kv shape": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q, s.k[:, :, :-1].contiguous(), s.v, 0.125), False),
-    "three dimensions": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q[0], s.k, s.v, 0.125), False),
-    "dtypes differ": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q, s.k.float(), s.v, 0.125), False),
-    "float64": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q.double(), s.k.double(), s.v.double(), 0.125), False),
-    "strided": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q.transpose(2, 3), s.k, s.v, 0.125), False),
-    "on the host": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q.cpu(), s.k, s.v, 0.125), False),
-    "scale": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q, s.k, s.v, -1.0), True),
-    "aliased": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q, s.k, s.v, 0.125, o=s.q), True),
-    "d_o shape": (lambda h, s: h.hdt_attn_bwd(s.lay, s.q, s.k, s.v, s.q, s.lse, s.d_o[:, :1].contiguous(), 0.125), False),
-    "small workspace": (lambda h, s: h.hdt_attn_bwd(s.lay, s.q, s.k, s.v, s.d_o, s.lse, s.d_o, 0.125, workspace=s.lse[:0]), True),
-    "ids on the host": (lambda h, s: h.hdt_build_layout(s.level.cpu(), s.parent), False),
-    "int64 ids": (lambda h, s: h.hdt_build_layout(s.level.long(), s.parent), False),
-    "ids' shapes": (lambda h, s: h.hdt_build_layout(s.level, s.parent[:, :-1].contiguous()), False),
-    "tile": (lambda h, s: h.hdt_build_layout(s.level, s.parent, 48, 64), True),
-    "hierarchy": (lambda h, s: h.hdt_build_layout(s.level, s.level + 400), True),
-    "destroyed": (lambda h, s: h.hdt_attn_fwd(s.dead, s.q, s.k, s.v, 0.125), True),
+    "shape": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q[:, :, :-1].contiguous(), s.k, s.v, 0.125), ()),
+    "kv shape": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q, s.k[:, :, :-1].contiguous(), s.v, 0.125), ()),
+    "three dimensions": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q[0], s.k, s.v, 0.125), ()),
+    "dtypes differ": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q, s.k.float(), s.v, 0.125), ()),
+    "float64": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q.double(), s.k.double(), s.v.double(), 0.125), ()),
+    "strided": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q.transpose(2, 3), s.k, s.v, 0.125), ()),
+    "on the host": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q.cpu(), s.k, s.v, 0.125), ()),
+    "scale": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q, s.k, s.v, -1.0), {FWD}),
+    "aliased": (lambda h, s: h.hdt_attn_fwd(s.lay, s.q, s.k, s.v, 0.125, o=s.q), {FWD}),
+    "d_o shape": (lambda h, s: h.hdt_attn_bwd(s.lay, s.q, s.k, s.v, s.q, s.lse, s.d_o[:, :1].contiguous(), 0.125), ()),
+    "small workspace": (lambda h, s: h.hdt_attn_bwd(s.lay, s.q, s.k, s.v, s.d_o, s.lse, s.d_o, 0.125, workspace=s.lse[:0]), {BWD}),
+    "ids on the host": (lambda h, s: h.hdt_build_layout(s.level.cpu(), s.parent), ()),
+    "int64 ids": (lambda h, s: h.hdt_build_layout(s.level.long(), s.parent), ()),
+    "ids' shapes": (lambda h, s: h.hdt_build_layout(s.level, s.parent[:, :-1].contiguous()), ()),
+    "tile": (lambda h, s: h.hdt_build_layout(s.level, s.parent, 48, 64), {BUILD}),
+    "hierarchy": (lambda h, s: h.hdt_build_layout(s.level, s.level + 400), {BUILD}),
+    "destroyed": (lambda h, s: h.hdt_attn_fwd(s.dead, s.q, s.k, s.v, 0.125), {FWD}),
 }
 
 
@@ -152,9 +161,9 @@ def test_same_errors(monkeypatch, name):
     s = types.SimpleNamespace(level=level, parent=parent, q=q, k=k, v=v, d_o=d_o, lse=torch.zeros(q.shape[:3], device="cuda"),
                               lay=hdt.hdt_build_layout(level, parent), dead=hdt.hdt_build_layout(level, parent))
     s.dead.destroy()
-    call, native = ERRORS[name]
-    general, here = both(monkeypatch, lambda: call(hdt, s), native)
-    assert isinstance(general, tuple) and issubclass(general[0], Exception) and general == here
+    call, taken = ERRORS[name]
+    general, here = both(monkeypatch, lambda: call(hdt, s), taken, raises=True)
+    assert general == here
 
 
 @pytest.mark.parametrize("scale", [1, np.float64(0.125), "tensor"])
@@ -164,4 +173,4 @@ def test_other_numbers_take_the_general_path(monkeypatch, scale):
     level, parent, (q, k, v, _) = state()
     lay = hdt.hdt_build_layout(level, parent)
     scale = torch.tensor(0.25) if scale == "tensor" else scale
-    equal(*both(monkeypatch, lambda: hdt.hdt_attn_fwd(lay, q, k, v, scale), native=False))
+    equal(*both(monkeypatch, lambda: hdt.hdt_attn_fwd(lay, q, k, v, scale), ()))
