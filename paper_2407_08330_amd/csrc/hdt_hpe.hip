@@ -170,9 +170,9 @@ __global__ __launch_bounds__(kOrdThreads, SPREAD ? 4 : 8) void k_sibling_ordinal
     const int window = min(n + 1, kOrdWindow);
     // The first positions in front of the share, and its own first chunk, are on their way while the counters are cleared, and a
     // chunk's while the one before it is worked on.  The kernel is bound by such round trips.  What they used to be were loads
-    // under a branch with the use beside them, each waited for before the next went out.  (Us: 8192 x 4 samples in a
-    // front end 8.4 -> 6.3 for this kernel; warm, 32768 x 1 17.9 -> 16.1, 70001 x 1 73 -> 60, 131072 x 16 190 -> 119, 8192 x 512
-    // 63.1 -> 61.7; 2000 x 4 8.70 -> 8.81.)
+    // under a branch with the use beside them, each waited for before the next went out.  (Us for this kernel, documents: 32768 x 1
+    // 16.4 -> 14.5, 70001 x 1 72 -> 58, 131072 x 16 178 -> 99, 8192 x 512 25.6 -> 23.3, 2000 x 4 7.8 -> 7.3; 8192 x 4 in a front end
+    // 8.4 -> 6.3.)
     auto load = [&](int i, int &l, int &p) {
         const int j = min(i, n - 1);
         l = level[o + j];
@@ -249,9 +249,10 @@ __global__ __launch_bounds__(kOrdThreads, SPREAD ? 4 : 8) void k_sibling_ordinal
                 const int g = s_run_grp[r];
                 if (g < w0 || g >= w0 + window) continue;  // a pad's, or of another window
                 int k = 0;
-                // (no branch on the group: with one, and a wait for each look, the loop's place in the program decided 5 % of the
-                // kernel.  ListOps-shaped trees, us for this kernel: 130 x 8192 110 to 116 - 81, 4 x 1000 17.1 to 18.0 - 14.0.)
-#pragma unroll 4
+                // (No branch on the group: with one, and a wait for each look, the loop's place in the program decided 5 % of the
+                // kernel.  ListOps-shaped trees, us for this kernel: 130 x 8192 110 to 116 - 83, 4 x 1000 17.1 to 18.0 - 14.2.  Unrolled
+                // four times it takes more than 64 registers where a sample has several shares: 16 x 131072 99 -> 109.)
+#pragma unroll 1
                 for (int e = tid % kOrdSplit; e < r; e += kOrdSplit) {
                     const int length = s_run_len[e];
                     k += s_run_grp[e] == g ? length : 0;
