@@ -182,10 +182,10 @@ hdt_status_t hdt_build_layout(const int32_t *d_level, const int32_t *d_parent, i
  * hdt_attn_bwd tiles the visible rows instead of all encoder rows.  (hdt_attn_bwd_workspace_bytes asks for four tensors
  * of that many rows more on such a layout.)  Results and arguments are the same either way.
  *
- * Kernels are enqueued on `stream`; the call does not wait for them.  The number of visible positions, which the first of
- * them reports, is looked at by the calls that depend on it: the workspace queries, hdt_attn_fwd_ws with a workspace,
+ * One kernel is enqueued on `stream`; the call does not wait for it.  The number of visible positions, which it reports
+ * midway, is looked at by the calls that depend on it: the workspace queries, hdt_attn_fwd_ws with a workspace,
  * hdt_attn_bwd and hdt_attn_bwd_no_alloc, hdt_layout_status, hdt_layout_info, hdt_layout_sample_info, hdt_layout_export.  The
- * first of them on a layout waits for that kernel, and for what was enqueued on `stream` before it, should the report not be
+ * first of them on a layout waits for that report, and for what was enqueued on `stream` before the kernel, should it not be
  * in.  The wait itself asks nothing of the device: these calls (but not the last three, which synchronise the device) may be
  * made while a stream is being captured, on a layout that was built outside the capture.  Any number of such builds may be in
  * flight.  Device memory as for hdt_build_layout, sized for the case that every position is visible, and from four encoder

@@ -638,7 +638,7 @@ constexpr int kLdsKeys = 2048;  // key lists up to this length stay in LDS betwe
 // Then the workgroup evaluates its own entries by key columns (entry_columns: lane masks, pair counts, summaries), one
 // wave per 64 key slots, the entries of both tiles in one sequence.  It also validates its own rows.
 // The lists are in LDS by the time the reservation of their entries (a returning device-scope atomic, about 2 us) is
-// back.  Lists beyond kLdsKeys keys in all are packed straight into global memory instead, with a contiguous share of
+// back, unless the host waits for the build: then it is waited for first (see there).  Lists beyond kLdsKeys keys in all are packed straight into global memory instead, with a contiguous share of
 // the document per wave, and read again from there.
 // 512 threads for documents whose scan is a single batch of their 8 waves, 4096 positions: a barrier is shorter, and two or
 // three workgroups share a compute unit where one of 1024 fills it.  Event-bracketed us, 1024 - 512 threads: sections,
@@ -860,7 +860,7 @@ __device__ __forceinline__ void key_lists(const KeyListArgs &a)
     }
     const bool in_lds = n_all * bn <= kLdsKeys;
     auto bucket = [&](int l) { return a.no_sort ? 0 : bucket_of(l); };
-    if (in_lds) {  // while the reservation is in flight
+    if (in_lds) {  // (while the reservation is in flight, unless the host waits)
         // document order: key and level in one word (positions take 19 bits), the parents beside it
         auto put = [&](uint32_t lo, uint32_t hi, int first, int g, int l, int p) {
             const unsigned long long m = (unsigned long long)lo | ((unsigned long long)hi << 32);
