@@ -17,7 +17,7 @@ SOURCES = ["hdt_api.hip", "hdt_layout.hip", "hdt_f32.hip", "hdt_fwd.hip", "hdt_b
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
-    # packed fp32 instructions are kept off on the test machines
+    # no packed fp32 instructions: some of their forms have given wrong results on this hardware
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # no NaN-quieting v_max(x, x) in front of every fmaxf: wherever a NaN can stand (rows of pad positions may
     # hold anything) it is removed by a select before any arithmetic looks at it, and the kernels produce none
